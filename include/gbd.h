@@ -102,7 +102,17 @@ typedef struct {
                                setup finds every beamlet's log2-amplitude curvature below
                                0.1 per row^2 (well-sampled spots).  Auto: separable, else
                                rotor, else direct; a request that does not apply falls
-                               back to auto's choice among the others. */
+                               back to auto's choice among the others.
+                               Separable by rows: where at least 64 beamlets come in runs
+                               (four or more on average) that share one ABCD and differ
+                               along x only, as on a pupil grid stored row by row, and the
+                               setup finds each run's y factors V equal, forms 0 and 4 (not
+                               5) sum each run's U first, E = sum_runs V(y) sum_j U_j(x):
+                               factors and terms as above, FP32 sums of at most 1,024 U
+                               and FP32 MFMA products of at most N / 32 runs in the mixed
+                               form, FP64 in the FP64 one.  It has no segments: a count
+                               given is that of the products by beamlet, which other
+                               decompositions take */
 } gbd_eval_opts;
 
 /* --- context ------------------------------------------------------------ */
@@ -295,7 +305,9 @@ void gbd_plan_free(gbd_plan_t plan);
  * before any launch: an explicit opts->segments whose partials do not fit,
  * or a workload whose fewest allowed segments do not (partials take
  * 8 bytes per pixel and segment in the mixed separable form, 16 otherwise;
- * one segment without truncated beamlets takes none).  All calls on one GPU
+ * one segment without truncated beamlets takes none; the separable form by
+ * rows instead takes 8 bytes, FP64 16, per pixel column and run, and where
+ * those do not fit the beamlets are taken as if in no rows).  All calls on one GPU
  * share its buffer, which keeps the last call's contents (every partial is
  * written before it is read): calls that overlap in time on one GPU, from two
  * streams, threads or contexts, race; calls ordered on one stream do not. */

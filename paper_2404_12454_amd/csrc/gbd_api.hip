@@ -40,7 +40,7 @@ struct DevBuf {
 };
 
 struct BatchWork {
-    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point;
+    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, row_v;
     uint32_t *host_flags = nullptr;  // pinned: the point evaluation's status
     void *stage = nullptr;           // pinned staging of the batch tables
     size_t stage_bytes = 0;
@@ -161,6 +161,10 @@ struct gbd_plan_s {
     RecCut64 *c64;  // truncation factors, allocated at the first setup of truncated beamlets
     RecCut32 *c32;
     int64_t n_cut;  // truncated beamlets of the last setup (the last n_cut records)
+    int32_t rows;   // row chunks of the last setup's beamlets (0: no table)
+    int32_t *row_start;  // the last setup's chunk table, and the chunks' y factors (RowV32 / RowV64)
+    void *row_v;
+    int64_t row_cap;     // chunks both hold, allocated at the first setup of beamlets with a table
     uint32_t *status_dev;   // two (flags, peak) word pairs used by alternate setups; each setup clears the other
     int status_parity;      // the pair the next setup uses
     bool status_zeroed;     // both words cleared (once, before the first setup)
@@ -177,6 +181,9 @@ struct gbd_plan_s {
 // plan_eval_impl under a guard: the configuration writes the output without
 // the guarded reduction (no partials), so it cannot run before the status
 constexpr int kNoSpeculation = 1;
+
+// the setup flags that select how an evaluation runs
+constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS;
 
 struct gbd_mlp_s {
     gbd_ctx_s *ctx;
@@ -264,6 +271,47 @@ bool symplectic_balanced(const double *m, double tol) {
             if (!(fabs(v - J[r][c]) <= tol * big * big)) return false;
         }
     return true;
+}
+
+// The row chunks (BeamletsDev::row_start) of n whole beamlets in stored order
+// (perm[i] the caller's index of the i-th): consecutive beamlets whose inputs
+// can give the same y factor, i.e. equal y, y slope and waist under one
+// shared matrix, kRowLen at most; whether they do is checked on the device.
+// Higher orders: a row's beamlets are first put in order of their y order
+// (stable), which the y factor depends on.  Empty if the rows are too short
+// to gain: the product over the chunks replaces one over the beamlets, at
+// least kRowGain times as many.
+constexpr int64_t kRowMinBeamlets = 64, kRowGain = 4;
+std::vector<int32_t> row_chunks(int64_t n, std::vector<int64_t> &perm, const double *r1, const double *th1,
+                                const double *w0, int64_t n_w0, const int32_t *order) {
+    std::vector<int32_t> start;
+    if (n < kRowMinBeamlets || n > 0x7fffffff) return start;
+    auto same = [&](int64_t a, int64_t b) {
+        return r1[2 * a + 1] == r1[2 * b + 1] && (!th1 || th1[2 * a + 1] == th1[2 * b + 1]) &&
+               (n_w0 == 1 || w0[a] == w0[b]);
+    };
+    const size_t most = (size_t)(n / kRowGain);
+    for (int64_t i = 0; i < n;) {
+        int64_t e = i + 1;
+        while (e < n && same(perm[e - 1], perm[e])) e++;
+        if (order) {  // a counting sort by the y order
+            int64_t at[4] = {0, 0, 0, 0};
+            for (int64_t k = i; k < e; k++) at[order[2 * perm[k] + 1] + 1]++;
+            for (int o = 1; o < 4; o++) at[o] += at[o - 1];
+            const std::vector<int64_t> run(perm.begin() + i, perm.begin() + e);
+            for (int64_t j : run) perm[i + at[order[2 * j + 1]]++] = j;
+        }
+        int64_t first = i;
+        for (int64_t k = i; k < e; k++)
+            if (k == i || k - first == kRowLen || (order && order[2 * perm[k] + 1] != order[2 * perm[k - 1] + 1])) {
+                if (start.size() >= most) return std::vector<int32_t>();
+                start.push_back((int32_t)k);
+                first = k;
+            }
+        i = e;
+    }
+    start.push_back((int32_t)n);
+    return start;
 }
 
 bool finite_all(const double *p, int64_t count) {
@@ -564,15 +612,39 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     const bool compact = n_main > 0 && s.form == 3 && precision == GBD_MIXED;
     EvalGeom g{}, gc{};
     int32_t nseg_main = 0, nseg_cut = 0;
-    if (n_main > 0) {
-        g = make_geom(plan->pl, n_main, s);
-        nseg_main = g.nseg;
-    }
     if (plan->n_cut > 0) {
         gc = cut_geom(ctx, precision, plan->pl, plan->n_cut);
         nseg_cut = gc.nseg;
     }
-    if (fixed) {
+    // The separable form by rows wherever the beamlets come in row chunks
+    // (row_chunks; the setup found their y factors equal) and FP32 MFMA in
+    // Gauss's form is not asked for: one segment, written by the product (with
+    // truncated beamlets into the first partial).  Segment counts do not apply.
+    // The fixed buffer has to hold the row sums beside any partials.
+    bool by_rows = s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
+                   (precision == GBD_FP64 || s.half);
+    const size_t row_bytes = by_rows ? (size_t)plan->rows * (size_t)plan->pl.nx * (size_t)elem : 0;
+    auto row_offset = [&](int64_t nc) -> size_t {  // where the row sums start, with nc truncated segments
+        const size_t part = nc == 0 ? 0 : reduce_wide_offset(compact ? 1 : 0, M) + (size_t)(nc + (compact ? 0 : 1)) * M * 16;
+        return (part + 255) & ~(size_t)255;
+    };
+    if (fixed && by_rows) {
+        while (nseg_cut > 1 && row_offset(nseg_cut) + row_bytes > fixed_bytes) {
+            gc = cut_geom(ctx, precision, plan->pl, plan->n_cut, nseg_cut - 1);
+            nseg_cut = gc.nseg;
+        }
+        by_rows = row_offset(nseg_cut) + row_bytes <= fixed_bytes;
+        if (!by_rows && plan->n_cut > 0) {
+            gc = cut_geom(ctx, precision, plan->pl, plan->n_cut);
+            nseg_cut = gc.nseg;
+        }
+    }
+    if (by_rows) s.nseg = 1;
+    if (n_main > 0) {
+        g = make_geom(plan->pl, n_main, s);
+        nseg_main = g.nseg;
+    }
+    if (fixed && !by_rows) {
         // partial bytes of nm main and nc truncated segments (none when one
         // segment writes the output directly)
         const size_t per_main = (size_t)M * (compact ? 8 : 16), per_cut = (size_t)M * 16;
@@ -621,7 +693,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         return fail(GBD_ERANGE, "grid too large");
     const int32_t total = nseg_main + nseg_cut;
     const bool reduce = total > 1 || nseg_cut > 0;
-    if (guard && !reduce) return kNoSpeculation;
+    if (guard && !reduce && !by_rows) return kNoSpeculation;
     StatusPost sp;  // the post handed to the separable form's kernel
     if (post_req && post_req->post) {
         if (n_main > 0 && s.form == 3) {
@@ -633,8 +705,9 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     }
     const int32_t nseg2 = compact ? nseg_main : 0;
     void *partial = fixed ? fixed : plan->scratch;
-    if (reduce && !fixed) {
-        const size_t need = (size_t)total * (size_t)M * 16;  // bounds the compact layout too
+    if ((reduce || by_rows) && !fixed) {
+        const size_t need = by_rows ? row_offset(nseg_cut) + row_bytes
+                                    : (size_t)total * (size_t)M * 16;  // bounds the compact layout too
         if (need > plan->scratch_bytes) {
             if (plan->scratch) (void)hipFree(plan->scratch);
             plan->scratch = nullptr;
@@ -649,7 +722,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         const bool hg = (plan->flags & FLAG_HG) != 0;
         const void *hrec = !hg ? nullptr : precision == GBD_FP64 ? (const void *)plan->h64 : (const void *)plan->h32;
         EvalGeom gl = g;
-        if (reduce) gl.nseg = std::max<int32_t>(total, 2);  // segment partials, never the output
+        if (reduce && !by_rows) gl.nseg = std::max<int32_t>(total, 2);  // segment partials, never the output
         if (s.form == 2)
             HIP_TRY(launch_sigma(gl, plan->r64, precision == GBD_FP64 ? plan->q64 : nullptr,
                                  precision == GBD_FP64 ? nullptr : plan->r32, ctx->stream),
@@ -675,7 +748,27 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
             // others are bracketed by event records
             if (s.form != 3) HIP_TRY(hipEventRecord(tev.first, ctx->stream), "hipEventRecord");
         }
-        if (s.form == 3 && precision == GBD_FP64)
+        if (by_rows) {
+            const RowGeom rg{plan->pl.nx, plan->pl.ny, g.dx, g.dy, g.a0, g.b0, plan->rows};
+            void *sums = static_cast<char *>(partial) + row_offset(nseg_cut);
+            void *dst = reduce ? partial : out;
+            // with a reduction behind it the product writes a partial, which needs no guard
+            EvalGuard gd;
+            if (guard && !reduce) {
+                guard->check_key = 0;  // the scale is read on the device
+                gd = *guard;
+            }
+            if (precision == GBD_FP64)
+                HIP_TRY(launch_rows64(rg, plan->row_start, plan->r64, static_cast<const RecHG64 *>(hrec),
+                                      static_cast<double2 *>(sums), static_cast<RowV64 *>(plan->row_v),
+                                      static_cast<double2 *>(dst), gd, ctx->stream, tev.first, tev.second, sp),
+                        "row kernels launch");
+            else
+                HIP_TRY(launch_rows32(rg, plan->row_start, plan->r32, static_cast<const RecHG32 *>(hrec),
+                                      plan->status_cur, static_cast<float2 *>(sums), static_cast<RowV32 *>(plan->row_v),
+                                      static_cast<float2 *>(dst), gd, ctx->stream, tev.first, tev.second, sp),
+                        "row kernels launch");
+        } else if (s.form == 3 && precision == GBD_FP64)
             HIP_TRY(launch_eval_sep64(gl, plan->r64, static_cast<const RecHG64 *>(hrec),
                                       static_cast<double2 *>(partial), static_cast<double2 *>(out), ctx->stream,
                                       tev.first, tev.second, sp),
@@ -709,7 +802,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         gr.nseg = total;
         EvalGuard gd;
         if (guard) {
-            guard->check_key = s.form == 3 && s.half;  // the FP16 form's scale came from the key
+            guard->check_key = s.form == 3 && s.half && !by_rows;  // the FP16 form's scale came from the key
             gd = *guard;
         }
         HIP_TRY(launch_reduce(precision, gr, nseg2, partial, out, ctx->stream, gd), "reduce kernel launch");
@@ -751,6 +844,19 @@ int plan_setup_launch(gbd_ctx_s *ctx, gbd_plan_s *plan, gbd_beamlets_s *b, gbd_p
         if (!plan->h64) HIP_TRY(hipMalloc(&plan->h64, cap * sizeof(RecHG64)), "hipMalloc(Hermite-Gaussian records)");
         if (!plan->h32) HIP_TRY(hipMalloc(&plan->h32, cap * sizeof(RecHG32)), "hipMalloc(Hermite-Gaussian records)");
     }
+    plan->rows = b->dev.rows;
+    if (plan->rows > plan->row_cap) {
+        // for any beamlets the plan takes (at most one chunk per kRowGain beamlets)
+        const int64_t cap = std::max<int64_t>(plan->rows, plan->capacity / kRowGain);
+        if (plan->row_start) (void)hipFree(plan->row_start);
+        if (plan->row_v) (void)hipFree(plan->row_v);
+        plan->row_start = nullptr;
+        plan->row_v = nullptr;
+        plan->row_cap = 0;
+        HIP_TRY(hipMalloc(&plan->row_start, (size_t)(cap + 1) * sizeof(int32_t)), "hipMalloc(row chunks)");
+        HIP_TRY(hipMalloc(&plan->row_v, (size_t)cap * sizeof(RowV64)), "hipMalloc(row chunks)");
+        plan->row_cap = cap;
+    }
     if (b->dev.n > 0) {
         // the axial term l0 / lambda is common to every beamlet: reduce it once
         const double g0 = b->dev.l0 / b->dev.lam;
@@ -765,7 +871,7 @@ int plan_setup_launch(gbd_ctx_s *ctx, gbd_plan_s *plan, gbd_beamlets_s *b, gbd_p
         uint32_t *status_next = plan->status_dev + 2 * (plan->status_parity ^ 1);
         HIP_TRY(launch_setup(b->dev, p->g, gturns, plan->r64, plan->r32, hg ? plan->h64 : nullptr,
                              hg ? plan->h32 : nullptr, cut ? plan->c64 : nullptr, cut ? plan->c32 : nullptr,
-                             status, status_next, ctx->stream),
+                             status, status_next, plan->row_start, ctx->stream),
                 "setup kernel launch");
         plan->status_parity ^= 1;
         plan->status_seq++;
@@ -807,7 +913,7 @@ int plan_setup_finish(gbd_ctx_s *ctx, gbd_plan_s *plan) {
         if (st & FLAG_NONFINITE) return fail(GBD_EINVAL, "non-finite beamlet parameters after propagation");
         if (st & FLAG_HG_TILT)
             return fail(GBD_EINVAL, "higher-order and truncated beamlets need a detector plane normal to the axis");
-        plan->flags = st & (FLAG_STEEP | FLAG_CROSS | FLAG_HG);
+        plan->flags = st & kFormFlags;
     }
     plan->ready = true;
     plan->spec_ok = plan->status_cur != nullptr;
@@ -828,6 +934,8 @@ void plan_destroy(gbd_plan_s *plan) {
     if (plan->h32) (void)hipFree(plan->h32);
     if (plan->c64) (void)hipFree(plan->c64);
     if (plan->c32) (void)hipFree(plan->c32);
+    if (plan->row_start) (void)hipFree(plan->row_start);
+    if (plan->row_v) (void)hipFree(plan->row_v);
     if (plan->status_dev) (void)hipFree(plan->status_dev);
     if (plan->scratch) (void)hipFree(plan->scratch);
     if (plan->status_post) {
@@ -872,7 +980,7 @@ int grow(DevBuf &b, size_t bytes, const char *what) {
 
 void batch_free(BatchWork &w) {
     DevBuf *all[] = {&w.rec,    &w.l5,   &w.e0t,     &w.tab1,  &w.tab2, &w.e0,
-                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point};
+                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.row_v};
     if (w.stage_ev) {
         (void)hipEventSynchronize(w.stage_ev);
         (void)hipEventDestroy(w.stage_ev);
@@ -1032,18 +1140,23 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
                 n_cut++;
             }
     }
+    std::vector<int32_t> chunks;
+    if (n_abcd == 1 && !base) chunks = row_chunks(n - n_cut, perm, r1, th1, w0, n_w0, order);
+    const int64_t n_rows = chunks.empty() ? 0 : (int64_t)chunks.size() - 1;
     bool higher = false;
     if (order)
         for (int64_t i = 0; i < 2 * n && !higher; i++) higher = order[i] != 0;
     int rc = ensure_device(ctx);
     if (rc) return rc;
     // one device block: r1, th1, amp [n][2]; w0 [n_w0]; path [n]; abcd [n_abcd][16]; base [n][5];
-    // edge [n][3]; orders [n][2] int32 packed into the trailing n doubles
+    // edge [n][3]; orders [n][2] int32; the row chunks' starts int32 and their bits
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     const size_t off_r1 = 0, off_th1 = off_r1 + 2 * nn, off_amp = off_th1 + 2 * nn, off_w0 = off_amp + 2 * nn,
                  off_path = off_w0 + (size_t)n_w0, off_abcd = off_path + nn, off_base = off_abcd + 16 * (size_t)n_abcd,
                  off_edge = off_base + (base ? 5 * nn : 0), off_order = off_edge + (edge ? 3 * nn : 0),
-                 total = off_order + (order ? nn : 0);
+                 off_rows = off_order + (order ? nn : 0),
+                 off_bits = off_rows + (n_rows ? ((size_t)n_rows + 2) / 2 : 0),
+                 total = off_bits + (n_rows ? ((size_t)(n - n_cut) + 63) / 64 : 0);
     const size_t bytes = total * sizeof(double);
     if (!ctx->up_ev) HIP_TRY(hipEventCreateWithFlags(&ctx->up_ev, hipEventDisableTiming), "hipEventCreate");
     if (ctx->up_pending) HIP_TRY(hipEventSynchronize(ctx->up_ev), "hipEventSynchronize");
@@ -1081,6 +1194,11 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
                 ord[2 * i] = order[2 * j];
                 ord[2 * i + 1] = order[2 * j + 1];
             }
+        }
+        if (n_rows) {
+            memcpy(&host[off_rows], chunks.data(), chunks.size() * sizeof(int32_t));
+            uint32_t *bits = reinterpret_cast<uint32_t *>(&host[off_bits]);
+            for (int64_t c = 0; c < n_rows; c++) bits[chunks[c] >> 5] |= 1u << (chunks[c] & 31);
         }
     } else {
         host[off_w0] = 1.0;
@@ -1122,6 +1240,9 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
     b->dev.order = order ? reinterpret_cast<const int32_t *>(d + off_order) : nullptr;
     b->dev.edge = edge ? d + off_edge : nullptr;
     b->dev.n_cut = n_cut;
+    b->dev.row_start = n_rows ? reinterpret_cast<const int32_t *>(d + off_rows) : nullptr;
+    b->dev.row_bits = n_rows ? reinterpret_cast<const uint32_t *>(d + off_bits) : nullptr;
+    b->dev.rows = (int32_t)n_rows;
     b->higher_order = higher;
     *out = b;
     return GBD_OK;
@@ -1349,7 +1470,6 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
     // The reduction writes the output only if the status has no error and
     // the same flags and key (EvalGuard); otherwise it writes nothing and,
     // for a mere change of form or scale, the evaluation runs again below.
-    const uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG;
     const uint32_t pflags = plan->flags;
     const uint32_t pkey = plan->sep_key;
     const int pscale = plan->sep_scale;
@@ -1580,7 +1700,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     auto tiles_of = [&](const PlaneGeom &g, int r) -> int64_t {
         return (int64_t)((g.nx + 63) / 64) * ((g.ny + waves * r - 1) / (waves * r));
     };
-    int64_t total = 0, field_elems = 0, n_items = 0;
+    int64_t total = 0, field_elems = 0, n_items = 0, row_tiles = 0, setup_blocks = 0, row_blocks = 0;
     for (int32_t i = 0; i < n_inst; i++) {
         const PlaneGeom &g = ps[i]->g;
         if (airy) {
@@ -1591,20 +1711,23 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         total += bs[i]->dev.n;
         field_elems += (int64_t)g.nx * g.ny;
         n_items += tiles_of(g, std::min(rows, 16));
+        row_tiles += (int64_t)((g.nx + kRowTilePx - 1) / kRowTilePx) * ((g.ny + kRowTilePx - 1) / kRowTilePx);
+        setup_blocks += batch_setup_blocks(bs[i]->dev);
+        row_blocks += (int64_t)bs[i]->dev.rows * ((g.nx + 63) / 64);
     }
     if (fields_out && fields_bytes < field_elems * 8)
         return fail(GBD_ERANGE, "fields_out holds %lld bytes, %lld needed", (long long)fields_bytes,
                     (long long)(field_elems * 8));
-    if (n_items > 0x3fffffff) return fail(GBD_ERANGE, "too many work items");
+    if (n_items > 0x3fffffff || row_tiles > 0x0fffffff || setup_blocks > 0x3fffffff || row_blocks > 0x3fffffff) return fail(GBD_ERANGE, "too many work items");
     if (total / kE0Chunk + n_inst > 0x3fffffff) return fail(GBD_ERANGE, "too many beamlets in the batch");
     int rc = ensure_device(ctx);
     if (rc) return rc;
 
     // per-beamlet setup of every instance; the status decides the mixed form.
     // The host tables pass through one pinned staging buffer:
-    //   [BatchInst x n | offs x (n + 1)]   uploaded before the setup (tab1)
-    //   [status x 4 | peaks x n]           read back after it
-    //   [BatchEval x n | items | e0map]    uploaded before the evaluation (tab2)
+    //   [BatchInst x n | offs x (n + 1) | blks x (n + 1)]   uploaded before the setup (tab1)
+    //   [status x 4 | peaks x n | row flags x n]            read back after it
+    //   [BatchEval x n | items | e0map | row lists]         uploaded before the evaluation (tab2)
     // each table part in one copy to a device buffer of the same layout.  The
     // host rewrites the buffer only once the stream has passed the previous
     // call's copies from it (stage_ev).
@@ -1613,18 +1736,21 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     const int64_t max_chunks = total / kE0Chunk + n_inst;  // normalisation chunks, at most
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t t1_offs = al(n_inst * sizeof(BatchInst));
-    const size_t t1_bytes = t1_offs + al((n_inst + 1) * sizeof(int64_t));
-    const size_t rb_bytes = al((4 + (size_t)n_inst) * sizeof(uint32_t));
+    const size_t t1_blks = t1_offs + al((n_inst + 1) * sizeof(int64_t));
+    const size_t t1_bytes = t1_blks + al((n_inst + 1) * sizeof(int32_t));
+    const size_t n_words = 4 + 2 * (size_t)n_inst;
+    const size_t rb_bytes = al(n_words * sizeof(uint32_t));
     const size_t t2_items = al(n_inst * sizeof(BatchEval));
     const size_t t2_e0map = t2_items + al((size_t)std::max<int64_t>(2 * n_items, 2) * sizeof(int32_t));
-    const size_t t2_bytes = t2_e0map + al((size_t)max_chunks * sizeof(int32_t));
+    const size_t t2_rows = t2_e0map + al((size_t)max_chunks * sizeof(int32_t));
+    const size_t t2_bytes = t2_rows + al((4 * (size_t)n_inst + 1) * sizeof(int32_t));
     if ((rc = grow(w.rec, (size_t)std::max<int64_t>(total, 1) * sizeof(Rec32), "batch records")) ||
         (rc = grow(w.l5, (size_t)std::max<int64_t>(total, 1) * sizeof(double), "batch records")) ||
         (airy && (rc = grow(w.e0t, (size_t)std::max<int64_t>(total, 1) * sizeof(double2), "batch normalisation"))) ||
         (airy && (rc = grow(w.e0part, (size_t)max_chunks * sizeof(double2), "batch normalisation"))) ||
         (rc = grow(w.tab1, t1_bytes, "batch table")) || (rc = grow(w.tab2, t2_bytes, "batch table")) ||
         (rc = grow(w.e0, n_inst * sizeof(double2), "batch normalisation")) ||
-        (rc = grow(w.part, (size_t)std::max<int64_t>(n_items, 1) * PS * sizeof(double), "batch partials")) ||
+        (rc = grow(w.part, (size_t)std::max<int64_t>(n_items + row_tiles, 1) * PS * sizeof(double), "batch partials")) ||
         (rc = grow(w.metrics, (size_t)n_inst * (2 + n_zones) * sizeof(double), "batch metrics")) ||
         (rc = grow(w.flags, rb_bytes, "batch flags")))
         return rc;
@@ -1644,10 +1770,13 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     char *d1 = static_cast<char *>(w.tab1.p), *d2 = static_cast<char *>(w.tab2.p);
     BatchInst *inst = reinterpret_cast<BatchInst *>(h1);
     int64_t *offs = reinterpret_cast<int64_t *>(h1 + t1_offs);
+    int32_t *blks = reinterpret_cast<int32_t *>(h1 + t1_blks);
     offs[0] = 0;
+    blks[0] = 0;
     for (int32_t i = 0; i < n_inst; i++) {
         const BeamletsDev &b = bs[i]->dev;
         offs[i + 1] = offs[i] + b.n;
+        blks[i + 1] = blks[i] + (int32_t)batch_setup_blocks(b);
         const double g0 = b.l0 / b.lam;
         inst[i].b = b;
         inst[i].pl = ps[i]->g;
@@ -1659,18 +1788,18 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     HIP_TRY(hipMemcpyAsync(d1, h1, t1_bytes, hipMemcpyHostToDevice, st), "table upload");
     HIP_TRY(hipEventRecord(w.stage_ev, st), "hipEventRecord");
     w.stage_pending = true;
-    // [0] status, [1] first bad instance, [2] queue head, [4 ...] per-instance peaks
+    // [0] status, [1] first bad instance, [2] queue head, [4 ...] per-instance peaks, then row flags
     uint32_t *flags = static_cast<uint32_t *>(w.flags.p);
     HIP_TRY(launch_batch_clear(flags, n_inst, st), "batch clear launch");
-    HIP_TRY(launch_batch_setup(dinst, doffs, n_inst, total, static_cast<Rec32 *>(w.rec.p),
-                               static_cast<double *>(w.l5.p), airy ? static_cast<double2 *>(w.e0t.p) : nullptr,
-                               flags, reinterpret_cast<int32_t *>(flags + 1), flags + 4, st),
+    HIP_TRY(launch_batch_setup(dinst, doffs, reinterpret_cast<const int32_t *>(d1 + t1_blks), n_inst, blks[n_inst],
+                               static_cast<Rec32 *>(w.rec.p), static_cast<double *>(w.l5.p),
+                               airy ? static_cast<double2 *>(w.e0t.p) : nullptr, flags,
+                               reinterpret_cast<int32_t *>(flags + 1), flags + 4, flags + 4 + n_inst, st),
             "batch setup launch");
-    HIP_TRY(hipMemcpyAsync(hrb, flags, (4 + (size_t)n_inst) * sizeof(uint32_t), hipMemcpyDeviceToHost, st),
-            "status copy");
+    HIP_TRY(hipMemcpyAsync(hrb, flags, n_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st), "status copy");
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
     w.stage_pending = false;
-    const uint32_t *hflags = reinterpret_cast<const uint32_t *>(hrb), *peaks = hflags + 4;
+    const uint32_t *hflags = reinterpret_cast<const uint32_t *>(hrb), *peaks = hflags + 4, *rowbad = peaks + n_inst;
     const uint32_t stat = hflags[0];
     const int32_t bad = (int32_t)hflags[1];
     if (stat & FLAG_PARALLEL) return fail(GBD_EPARALLEL, "instance %d: a base ray is parallel to the plane", bad);
@@ -1694,6 +1823,12 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     BatchEval *ev = reinterpret_cast<BatchEval *>(h2);
     int32_t *items = reinterpret_cast<int32_t *>(h2 + t2_items);
     int32_t *e0map = reinterpret_cast<int32_t *>(h2 + t2_e0map);  // normalisation chunk -> instance
+    // each instance whose beamlets come in row chunks goes by rows, as a single evaluation of it does
+    int32_t *sum_inst = reinterpret_cast<int32_t *>(h2 + t2_rows), *sum_first = sum_inst + n_inst,
+            *prod_inst = sum_first + n_inst + 1, *prod_first = prod_inst + n_inst;
+    BatchRows br{};
+    int32_t sum_blocks = 0, v_off = 0;
+    int64_t sum_off = 0;
     int64_t foff = 0;
     int32_t n_chunks = 0;
     for (int32_t i = 0; i < n_inst; i++) {
@@ -1704,7 +1839,21 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         e.n = bs[i]->dev.n;
         e.nx = g.nx;
         e.ny = g.ny;
-        if (form == 3) {  // separable form: the single evaluation's workgroup tiles
+        const BeamletsDev &b = bs[i]->dev;
+        if (half && b.rows > 0 && !rowbad[i] && (int64_t)g.nx * g.ny > 0) {
+            e.rows = b.rows;
+            e.row_start = b.row_start;
+            e.sum_off = sum_off;
+            e.v_off = v_off;
+            sum_off += (int64_t)b.rows * g.nx;
+            v_off += b.rows;
+            sum_inst[br.n] = i;
+            sum_first[br.n++] = sum_blocks;
+            const int cols = g.nx > 64 ? 128 : 64;
+            sum_blocks += b.rows * ((g.nx + cols - 1) / cols);
+            e.tiles_x = (g.nx + kRowTilePx - 1) / kRowTilePx;
+            e.tiles_y = (g.ny + kRowTilePx - 1) / kRowTilePx;
+        } else if (form == 3) {  // separable form: the single evaluation's workgroup tiles
             Shape sh;
             sh.form = 3;
             sh.half = half;
@@ -1729,14 +1878,36 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         e.e0_chunks = (int32_t)((e.n + kE0Chunk - 1) / kE0Chunk);
         for (int32_t c = 0; c < e.e0_chunks; c++) e0map[n_chunks++] = i;
     }
+    sum_first[br.n] = sum_blocks;
     std::vector<int32_t> order(n_inst);
     for (int32_t i = 0; i < n_inst; i++) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        return ev[x].n * ((int64_t)ev[x].nx * ev[x].ny) > ev[y].n * ((int64_t)ev[y].nx * ev[y].ny);
-    });
-    int64_t n_it = 0;
+    // an instance's cost: its pairs, by rows its (chunk, pixel) products
+    auto cost = [&](int32_t i) { return (ev[i].rows ? ev[i].rows : ev[i].n) * ((int64_t)ev[i].nx * ev[i].ny); };
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost(x) > cost(y); });
+    // by rows: the k-th largest to XCD 0 ... 7, 7 ... 0, 0 ...
+    {
+        std::vector<int32_t> list[kXcds];
+        int32_t k = 0;
+        for (int32_t i : order)
+            if (ev[i].rows) {
+                const int32_t r = k++ % (2 * kXcds);
+                list[r < kXcds ? r : 2 * kXcds - 1 - r].push_back(i);
+            }
+        int32_t at = 0;
+        for (int x = 0; x < kXcds; x++) {
+            br.prod_list[x] = at;
+            for (int32_t i : list[x]) {
+                prod_inst[at] = i;
+                prod_first[at++] = br.prod_tiles[x];
+                br.prod_tiles[x] += ev[i].tiles_x * ev[i].tiles_y;
+            }
+        }
+        br.prod_list[kXcds] = at;
+    }
+    int64_t n_it = 0, n_part = 0;
     for (int32_t k = 0; k < n_inst; k++) {
         const int32_t i = order[k];
+        if (ev[i].rows) continue;
         ev[i].item_off = n_it;
         const int32_t tiles = ev[i].tiles_x * ev[i].tiles_y;
         for (int32_t t = 0; t < tiles; t++) {
@@ -1746,8 +1917,18 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         }
     }
     n_items = n_it;
-    HIP_TRY(hipMemcpyAsync(d2, h2, t2_e0map + (size_t)n_chunks * sizeof(int32_t), hipMemcpyHostToDevice, st),
-            "table upload");
+    n_part = n_it;  // the partials of instances by rows follow those of the work list
+    for (int32_t i = 0; i < n_inst; i++)
+        if (ev[i].rows) {
+            ev[i].item_off = n_part;
+            n_part += (int64_t)ev[i].tiles_x * ev[i].tiles_y;
+        }
+    if ((rc = grow(w.row_sums, (size_t)std::max<int64_t>(sum_off, 1) * sizeof(float2), "batch row sums")) ||
+        (rc = grow(w.row_v, (size_t)std::max<int32_t>(v_off, 1) * sizeof(RowV32), "batch row factors")))
+        return rc;
+    // the tables up to the last part in use (the work list is empty when every instance goes by rows)
+    const size_t t2_used = br.n ? t2_bytes : t2_e0map + (size_t)n_chunks * sizeof(int32_t);
+    HIP_TRY(hipMemcpyAsync(d2, h2, t2_used, hipMemcpyHostToDevice, st), "table upload");
     HIP_TRY(hipEventRecord(w.stage_ev, st), "hipEventRecord");
     w.stage_pending = true;
 
@@ -1770,6 +1951,16 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
                                 static_cast<const double2 *>(w.e0t.p), static_cast<double2 *>(w.e0part.p),
                                 static_cast<double2 *>(w.e0.p), st),
                 "normalisation launch");
+    if (br.n > 0) {
+        const int32_t *lists = reinterpret_cast<const int32_t *>(d2 + t2_rows);
+        br.sum_inst = lists;
+        br.sum_first = lists + n_inst;
+        br.prod_inst = lists + 2 * n_inst + 1;
+        br.prod_first = lists + 3 * n_inst + 1;
+        br.peaks = flags + 4;
+        br.sums = static_cast<float2 *>(w.row_sums.p);
+        HIP_TRY(launch_batch_rows(a, br, sum_blocks, static_cast<RowV32 *>(w.row_v.p), st), "batch row launch");
+    }
     HIP_TRY(launch_batch_eval(rows, waves, form, half, ctx->cus, a, st), "batch eval launch");
     if (airy) {
         HIP_TRY(launch_batch_finalize(a.inst, n_inst, a.part, n_zones, static_cast<double *>(w.metrics.p), st),

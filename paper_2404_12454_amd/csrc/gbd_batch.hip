@@ -18,10 +18,12 @@
 //                      halves, 128 x 128 on FP32 MFMA when requested), each
 //                      an MFMA accumulation over all of the instance's
 //                      beamlets
+//  batch_row_*_kernel  the instances on pupil grids stored row by row in the
+//                      row-factored form (gbd_rows.hip): row sums, then a
+//                      product per 32 x 32 tile with the same epilogue
 //  batch_finalize      per instance, fixed-order sum of its items' partials
 //  airy_kernel         reference irradiance (2 J1(v)/v)^2 in FP64
-#include "gbd_device.h"
-#include "gbd_sep_core.h"
+#include "gbd_row_core.h"
 
 namespace gbd {
 
@@ -30,9 +32,10 @@ namespace {
 using namespace dev;
 
 // The batch's flag words before its setup: [0] status 0, [1] first bad
-// instance 0x7f7f7f7f, [2] queue head 0, [3] 0, [4 ...] the n_inst peaks 0.
+// instance 0x7f7f7f7f, [2] queue head 0, [3] 0, [4 ...] the n_inst peaks and
+// then the n_inst row flags 0.
 __global__ void __launch_bounds__(256) batch_clear_kernel(uint32_t *__restrict__ flags, int32_t n_inst) {
-    const int64_t n = 4 + (int64_t)n_inst;
+    const int64_t n = 4 + 2 * (int64_t)n_inst;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         flags[i] = i == 1 ? 0x7f7f7f7fu : 0u;
 }
@@ -44,6 +47,19 @@ __device__ inline int instance_of(const int64_t *__restrict__ offs, int32_t n_in
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (offs[mid] <= j)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+// the same over int32 starts: the last of n entries with first[e] <= k
+__device__ inline int list_entry(const int32_t *__restrict__ first, int32_t n, int32_t k) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= k)
             lo = mid;
         else
             hi = mid - 1;
@@ -65,42 +81,48 @@ __device__ inline double2 e0_term(const Rec32 &r) {
 
 // The records' first 112 bytes (the rotor tables are left to
 // batch_sigma_kernel, run only before a rotor-form evaluation), with each
-// beamlet's FP64 l5 for that pass and, when e0t is given, its E(0) term.
-__global__ void __launch_bounds__(256) batch_setup_kernel(const BatchInst *__restrict__ inst,
-                                                          const int64_t *__restrict__ offs, int32_t n_inst,
-                                                          int64_t total, Rec32 *__restrict__ rec,
-                                                          double *__restrict__ l5, double2 *__restrict__ e0t,
-                                                          uint32_t *__restrict__ status, int32_t *__restrict__ bad,
-                                                          uint32_t *__restrict__ peak) {
-    const int64_t j0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = j0 < total;
-    const int64_t j = live ? j0 : total - 1;  // a lane past the end repeats the last beamlet, writing nothing
-    const int lo = instance_of(offs, n_inst, j);
-    const BatchInst &I = inst[lo];
+// beamlet's FP64 l5 for that pass and, when e0t is given, its E(0) term.  A
+// workgroup holds beamlets of one instance (with a row table, thread 0 the
+// one before them: row_check).
+__global__ void __launch_bounds__(kRowBlock) batch_setup_kernel(const BatchInst *__restrict__ inst,
+                                                                const int64_t *__restrict__ offs,
+                                                                const int32_t *__restrict__ blks, int32_t n_inst,
+                                                                Rec32 *__restrict__ rec, double *__restrict__ l5,
+                                                                double2 *__restrict__ e0t,
+                                                                uint32_t *__restrict__ status,
+                                                                int32_t *__restrict__ bad,
+                                                                uint32_t *__restrict__ peak,
+                                                                uint32_t *__restrict__ rowbad) {
+    const int i = list_entry(blks, n_inst, (int32_t)blockIdx.x);
+    const BatchInst &I = inst[i];
+    const int halo = I.b.rows ? 1 : 0;
+    const int64_t k = (int64_t)(blockIdx.x - blks[i]) * (kRowBlock - halo) + threadIdx.x - halo;
+    const bool live = k >= 0 && k < I.b.n, own = live && (int)threadIdx.x >= halo;
     float pk = -INFINITY;
     uint32_t flag = 0;
+    double ykey[kYKey] = {};
     if (live) {
         double l5v;
         Rec32 o;
-        flag = setup_one(I.b, I.pl, I.gturns, j - offs[lo], nullptr, rec + I.rec_off, nullptr, nullptr, nullptr,
-                         nullptr, false, &pk, &l5v, &o);
-        l5[j] = l5v;
-        if (e0t) e0t[j] = e0_term(o);
+        flag = setup_one(I.b, I.pl, I.gturns, k, nullptr, rec + I.rec_off, nullptr, nullptr, nullptr, nullptr, false,
+                         &pk, &l5v, &o, ykey, own);
+        if (own) {
+            l5[offs[i] + k] = l5v;
+            if (e0t) e0t[offs[i] + k] = e0_term(o);
+        }
+    }
+    if (I.b.rows) {  // uniform
+        __shared__ double wkey[kRowBlock / 64][kYKey];
+        if (row_check<false>(ykey, live, k, I.b.n, I.b.row_bits, wkey)) rowbad[i] = FLAG_ROWS;
     }
     if (flag) atomicOr(status, flag);
-    if (flag & FLAG_ERRORS) atomicMin(bad, lo);
-    // the instance's largest term over its grid (the FP16 halves form's
-    // range): one atomic per wavefront when all its lanes hold one instance
-    // (instances are hundreds of beamlets long), else one per lane
+    if (flag & FLAG_ERRORS) atomicMin(bad, i);
+    // the instance's largest term over its grid (the FP32 and FP16 sums'
+    // range): one atomic per wavefront
     uint32_t key = (live && isfinite(pk)) ? (uint32_t)fminf(fmaxf(ceilf(pk) + 2048.0f, 1.0f), 4095.0f) : 0u;
-    const int lo0 = __shfl(lo, 0);
-    if (__all(lo == lo0)) {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) key = max(key, (uint32_t)__shfl_xor((int)key, o));
-        if ((threadIdx.x & 63) == 0 && key) atomicMax(peak + lo0, key);
-    } else if (key) {
-        atomicMax(peak + lo, key);
-    }
+    for (int o = 32; o > 0; o >>= 1) key = max(key, (uint32_t)__shfl_xor((int)key, o));
+    if ((threadIdx.x & 63) == 0 && key) atomicMax(peak + i, key);
 }
 
 // Rotor tables sigma^(k^2), k = 1..16, rows dy apart (each instance's dy),
@@ -368,17 +390,97 @@ __global__ void __launch_bounds__(64 * BatchTile<HALF>::WX * BatchTile<HALF>::WY
     }
 }
 
+// Row sums of the instances taken by rows, then their products with the
+// figure of merit's partials: the single evaluation's arithmetic (so a field
+// equals gbd_eval's bit for bit), see gbd_rows.hip.
+__global__ void __launch_bounds__(64 * rows::kRowSumWaves) batch_row_sum_kernel(BatchArgs A, BatchRows B,
+                                                                               RowV32 *__restrict__ v) {
+    const int k = list_entry(B.sum_first, B.n, (int32_t)blockIdx.x);
+    const int i = B.sum_inst[k];
+    const BatchEval &I = A.inst[i];
+    const RowGeom g{I.nx, I.ny, I.dx, I.dy, I.a0, I.b0, I.rows};
+    if (I.nx > 64)
+        rows::row_sum_block32<false, 2>(g, blockIdx.x - B.sum_first[k], I.row_start, A.rec + I.rec_off, nullptr,
+                                        B.peaks[i], B.sums + I.sum_off, v + I.v_off);
+    else
+        rows::row_sum_block32<false, 1>(g, blockIdx.x - B.sum_first[k], I.row_start, A.rec + I.rec_off, nullptr,
+                                        B.peaks[i], B.sums + I.sum_off, v + I.v_off);
+}
+
+__global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel(BatchArgs A, BatchRows B,
+                                                                               const RowV32 *__restrict__ v) {
+    constexpr int NQ = 2 + 2 * kMaxZones, WAVES = rows::kRowWaves;
+    __shared__ float2 part[WAVES][256];
+    __shared__ double red[WAVES][NQ];
+    const int x = blockIdx.x % kXcds, r = blockIdx.x / kXcds;
+    if (r >= B.prod_tiles[x]) return;
+    const int e0 = B.prod_list[x];
+    const int e = e0 + list_entry(B.prod_first + e0, B.prod_list[x + 1] - e0, r);
+    const int i = B.prod_inst[e], t = r - B.prod_first[e];
+    const BatchEval &I = A.inst[i];
+    const int x0 = (t / I.tiles_y) * rows::kRowTile, y0 = (t % I.tiles_y) * rows::kRowTile;
+    sep::f4 re[2][2], im[2][2];
+    rows::row_product<false>(v + I.v_off, B.sums + I.sum_off, I.rows, I.nx, I.a0, I.b0, I.dy, x0, y0, re, im);
+    const int P = (int)rows::row_exponent(B.peaks[i]);
+    double q[NQ];
+#pragma unroll
+    for (int z = 0; z < NQ; z++) q[z] = 0.0;
+    double inv0 = 0.0;
+    if (A.airy) {
+        const double2 f0 = A.e0[i];
+        const double n0 = f0.x * f0.x + f0.y * f0.y;
+        inv0 = n0 > 0.0 ? 1.0 / n0 : 0.0;
+    }
+    rows::row_fold<RowV32>(re, im, part, [&](int p, int c, int k, double sr, double si) {
+        const int ix = x0 + 16 * c + (k & 15), iy = y0 + 16 * p + (k >> 4);
+        if (ix >= I.nx || iy >= I.ny) return;
+        const int64_t px = (int64_t)iy * I.nx + ix;
+        const float2 f = rows::row_value(sr, si, P);
+        if (A.fields) A.fields[I.field_off + px] = f;
+        if (A.airy) {
+            const double d = ((double)f.x * f.x + (double)f.y * f.y) * inv0 - (double)A.airy[px];
+            q[0] += d * d;
+            q[1] = fmax(q[1], fabs(d));
+            const double a = I.a0 + ix * I.dx, b = I.b0 + iy * I.dy;
+            const double r2 = a * a + b * b;
+#pragma unroll
+            for (int z = 0; z < kMaxZones; z++)
+                if (z < A.n_zones && r2 >= A.zone_r2[z] && r2 < A.zone_r2[z + 1]) {
+                    q[2 + 2 * z] += d * d;
+                    q[3 + 2 * z] += 1.0;
+                }
+        }
+    });
+    if (!A.airy) return;
+    // the pixels lie with the first 256 threads
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, PS = 2 + 2 * A.n_zones;
+#pragma unroll
+    for (int z = 0; z < NQ; z++)
+        if (z < PS) q[z] = (z == 1) ? wave_max<64>(q[z]) : wave_sum<64>(q[z]);
+    if (lane == 0)
+#pragma unroll
+        for (int z = 0; z < NQ; z++) red[wv][z] = q[z];
+    __syncthreads();
+    if ((int)threadIdx.x < PS) {
+        const int z = threadIdx.x;
+        double s = red[0][z];
+        for (int w = 1; w < 4; w++) s = (z == 1) ? fmax(s, red[w][z]) : s + red[w][z];
+        A.part[(I.item_off + t) * PS + z] = s;
+    }
+}
+
+// one wavefront per instance: lane l adds the partials of items l, l + 64,
+// ..., then a shuffle tree
 __global__ void __launch_bounds__(64) batch_finalize_kernel(const BatchEval *__restrict__ inst, int32_t n_inst,
                                                             const double *__restrict__ part, int32_t n_zones,
                                                             double *__restrict__ metrics) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_inst) return;
-    const BatchEval I = inst[i];
+    const int i = blockIdx.x, lane = threadIdx.x;
+    const BatchEval &I = inst[i];
     const int PS = 2 + 2 * n_zones;
     const int tiles = I.tiles_x * I.tiles_y;
     double s = 0.0, mx = 0.0, zs[kMaxZones], zc[kMaxZones];
     for (int z = 0; z < kMaxZones; z++) zs[z] = zc[z] = 0.0;
-    for (int t = 0; t < tiles; t++) {
+    for (int t = lane; t < tiles; t += 64) {
         const double *q = part + (I.item_off + t) * PS;
         s += q[0];
         mx = fmax(mx, q[1]);
@@ -387,6 +489,13 @@ __global__ void __launch_bounds__(64) batch_finalize_kernel(const BatchEval *__r
             zc[z] += q[3 + 2 * z];
         }
     }
+    s = wave_sum<64>(s);
+    mx = wave_max<64>(mx);
+    for (int z = 0; z < n_zones; z++) {
+        zs[z] = wave_sum<64>(zs[z]);
+        zc[z] = wave_sum<64>(zc[z]);
+    }
+    if (lane) return;
     double *o = metrics + (int64_t)i * (2 + n_zones);
     const double M = (double)I.nx * I.ny;
     o[0] = M > 0 ? sqrt(s / M) : 0.0;
@@ -423,17 +532,28 @@ hipError_t launch_batch_eval_t(int cus, const BatchArgs &a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_batch_clear(uint32_t *flags, int32_t n_inst, hipStream_t s) {
-    const int64_t blocks = min((4 + (int64_t)n_inst + 255) / 256, (int64_t)1024);
+    const int64_t blocks = min((4 + 2 * (int64_t)n_inst + 255) / 256, (int64_t)1024);
     batch_clear_kernel<<<(unsigned)blocks, 256, 0, s>>>(flags, n_inst);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, int32_t n_inst, int64_t total, Rec32 *rec,
-                              double *l5, double2 *e0t, uint32_t *status, int32_t *bad, uint32_t *peak,
-                              hipStream_t s) {
-    if (total == 0) return hipSuccess;
-    batch_setup_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(inst, offs, n_inst, total, rec, l5, e0t,
-                                                                       status, bad, peak);
+hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, const int32_t *blks, int32_t n_inst,
+                              int32_t n_blocks, Rec32 *rec, double *l5, double2 *e0t, uint32_t *status, int32_t *bad,
+                              uint32_t *peak, uint32_t *rowbad, hipStream_t s) {
+    if (n_blocks == 0) return hipSuccess;
+    batch_setup_kernel<<<(unsigned)n_blocks, kRowBlock, 0, s>>>(inst, offs, blks, n_inst, rec, l5, e0t, status, bad,
+                                                                peak, rowbad);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, RowV32 *v, hipStream_t s) {
+    if (r.n == 0 || sum_blocks == 0) return hipSuccess;
+    batch_row_sum_kernel<<<(unsigned)sum_blocks, 64 * rows::kRowSumWaves, 0, s>>>(a, r, v);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    int32_t most = 0;
+    for (int x = 0; x < kXcds; x++) most = max(most, r.prod_tiles[x]);
+    batch_row_product_kernel<<<(unsigned)(kXcds * most), 64 * rows::kRowWaves, 0, s>>>(a, r, v);
     return hipGetLastError();
 }
 
@@ -494,7 +614,7 @@ hipError_t launch_batch_eval(int rows, int waves, int form, bool half, int cus, 
 hipError_t launch_batch_finalize(const BatchEval *inst, int32_t n_inst, const double *part, int32_t n_zones,
                                  double *metrics, hipStream_t s) {
     if (n_inst == 0) return hipSuccess;
-    batch_finalize_kernel<<<(n_inst + 63) / 64, 64, 0, s>>>(inst, n_inst, part, n_zones, metrics);
+    batch_finalize_kernel<<<n_inst, 64, 0, s>>>(inst, n_inst, part, n_zones, metrics);
     return hipGetLastError();
 }
 

@@ -125,11 +125,14 @@ __device__ inline double log2_hg_envelope_max(double c1, double c2, double d0, d
 // l5_out and r32_copy (optional): the FP64 ln-amplitude curvature l5 (with
 // p5 of the record, the source of the rotor tables when a later pass fills
 // them) and a copy of the finished Rec32 record.
+// ykey (optional): everything the beamlet's y factor is made of.  store
+// false: no record is written (the record pointers still say what is formed).
+constexpr int kYKey = 11;
 __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, double gturns, int64_t j,
                                      Rec64 *r64, Rec32 *r32, RecHG64 *h64 = nullptr, RecHG32 *h32 = nullptr,
                                      RecCut64 *c64 = nullptr, RecCut32 *c32 = nullptr, bool sigma32 = true,
                                      float *sep_peak = nullptr, double *l5_out = nullptr,
-                                     Rec32 *r32_copy = nullptr) {
+                                     Rec32 *r32_copy = nullptr, double *ykey = nullptr, bool store = true) {
     const double *M = b.abcd + (b.n_abcd == 1 ? 0 : 16 * j);
     double A[2][2], B[2][2], C[2][2], D[2][2];
 #pragma unroll
@@ -454,6 +457,13 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
     }
     if (l5_out) *l5_out = o64.l[5];
     if (r32_copy) *r32_copy = o32;
+    if (ykey) {
+        const double v[kYKey] = {o64.brho,       o64.p[2],  o64.p[5],  o64.l[2], o64.l[5], oh.g[1][1][0],
+                                 oh.g[1][1][1], oh.cy0[0], oh.cy0[1], oh.cy1,   oh.cy2};
+#pragma unroll
+        for (int k = 0; k < kYKey; k++) ykey[k] = v[k];
+    }
+    if (!store) return flag;
     if (r64) r64[j] = o64;
     if (r32) {
         if (sigma32) {
@@ -490,6 +500,33 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         h32[j] = o;
     }
     return flag;
+}
+
+// Setups of beamlets with a row table run kRowBlock - 1 beamlets to a
+// workgroup of kRowBlock threads, thread 0 repeating the beamlet before them,
+// so that each beamlet can be compared with its predecessor.  row_check:
+// FLAG_ROWS if thread t > 0's beamlet (local index j < n) continues a row
+// chunk (no chunk starts there, `bits`) but its y factor differs from its
+// predecessor's; 0 otherwise.  The whole workgroup calls it (it
+// synchronises), wkey its LDS; HG: compares the higher-order words too.
+template <bool HG>
+__device__ inline uint32_t row_check(const double (&key)[kYKey], bool live, int64_t j, int64_t n,
+                                     const uint32_t *__restrict__ bits, double (*wkey)[kYKey]) {
+    constexpr int K = HG ? kYKey : 5;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 63)
+#pragma unroll
+        for (int k = 0; k < K; k++) wkey[w][k] = key[k];
+    __syncthreads();
+    bool diff = false;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        double prev = __shfl_up(key[k], 1);
+        if (lane == 0 && w > 0) prev = wkey[w - 1][k];
+        diff = diff || !(prev == key[k]);
+    }
+    if (!live || threadIdx.x == 0 || j >= n || ((bits[j >> 5] >> (j & 31)) & 1u)) return 0u;
+    return diff ? FLAG_ROWS : 0u;
 }
 
 // Hermite-Gaussian factor P (the polynomial of RecHG64) at the pixel offset
@@ -946,6 +983,13 @@ __device__ inline void mixed_accumulate_rotor(Rec32 *tile, const Rec32 *__restri
             acc_re[k] = acc_im[k] = 0.0f;
         }
     }
+}
+
+// the guard's condition (EvalGuard), the same for every thread
+__device__ inline bool guard_holds(const EvalGuard &gd) {
+    if (!gd.status) return true;
+    const uint32_t st = gd.status[0], key = gd.status[1];
+    return !(st & FLAG_ERRORS) && (st & gd.mask) == gd.flags && (!gd.check_key || key == gd.key);
 }
 
 // XCD-aware work mapping: workgroup b runs on XCD (b mod 8); give each XCD a

@@ -35,7 +35,16 @@ struct BeamletsDev {
     const int32_t *order;  // [n][2] elegant Hermite-Gaussian orders (m, n) in 0..2, or null
     const double *edge;    // [n][3] truncating edges (e_x, e_y, t): keep e . r <= t, or null
     int64_t n_cut;         // truncated beamlets; they are stored last, [n - n_cut, n)
+    // row chunks (see launch_rows32): consecutive whole beamlets whose inputs
+    // differ along x only, at most kRowLen; chunk c is [row_start[c],
+    // row_start[c + 1]); row_bits marks the first beamlet of each.  rows == 0:
+    // no table.
+    const int32_t *row_start;   // [rows + 1]
+    const uint32_t *row_bits;   // [(n - n_cut + 31) / 32]
+    int32_t rows;
 };
+constexpr int kRowBlock = 256;  // the setups' workgroup (see row_check)
+constexpr int kRowLen = 1024;   // beamlets of a row chunk at most (an FP32 sum takes a quarter of them)
 
 // Per-beamlet phasor on the plane, about the base-ray hit point (a_rho, b_rho):
 //   log E_j(d) = ln|.| + 2 pi i Theta(d),  d = (a - a_rho, b - b_rho)
@@ -147,6 +156,9 @@ enum : uint32_t {
     // not an error: some beamlet is of higher order, so the evaluation
     // multiplies its Hermite-Gaussian factor in (direct and separable forms)
     FLAG_HG = 64u,
+    // not an error: a row chunk's beamlets do not share their y factor, so
+    // the row-factored sum (launch_rows) does not apply
+    FLAG_ROWS = 128u,
 };
 
 // largest |d^2 log2(amplitude) / d row^2| / 2 for which the mixed kernel may
@@ -189,6 +201,12 @@ struct BatchEval {
     int64_t field_off;  // element offset of this instance in the optional field output
     int32_t scale;      // FP16 halves form: its accumulators hold the field times 2^scale
     int32_t e0_off, e0_chunks;  // its normalisation chunks (kE0Chunk beamlets each), contiguous
+    // an instance taken by rows (launch_batch_rows): its chunk table, and where
+    // its row sums [rows][nx] and y factors [rows] start; its tiles are the row
+    // product's
+    const int32_t *row_start;
+    int64_t sum_off;
+    int32_t rows, v_off;
 };
 
 // beamlets per workgroup of the normalisation sum
@@ -209,16 +227,38 @@ struct BatchArgs {
     double zone_r2[kMaxZones + 1];  // squared radii bounding the annular zones
 };
 
+// The instances of a batch taken by rows.  Row sums: list position k's
+// workgroups are [sum_first[k], sum_first[k + 1]).  Products: workgroup b
+// runs on XCD b % 8, which takes the instances prod_inst[prod_list[x] ...
+// prod_list[x + 1] - 1] whole, one after the other (their row sums stay in
+// that XCD's L2); prod_first[e] tiles of its precede list entry e.
+constexpr int kXcds = 8;
+struct BatchRows {
+    int32_t n;               // instances taken by rows
+    const int32_t *sum_inst, *sum_first;    // [n], [n + 1]
+    const int32_t *prod_inst, *prod_first;  // [n], [n]
+    int32_t prod_list[kXcds + 1], prod_tiles[kXcds];
+    const uint32_t *peaks;   // per instance, the setup's key
+    float2 *sums;
+};
+
 // peak: per instance, the largest beamlet term modulus over the grid as
 // ceil(log2) + 2048 (0: none), the setup kernel's atomic maximum; zero on entry.
-// flags[0 .. 3] and the n_inst peaks after them set for a batch setup (the
-// first bad instance to 0x7f7f7f7f, the rest to 0)
+// flags[0 .. 3], the n_inst peaks and the n_inst row flags after them set for
+// a batch setup (the first bad instance to 0x7f7f7f7f, the rest to 0)
 hipError_t launch_batch_clear(uint32_t *flags, int32_t n_inst, hipStream_t s);
 // The records' first 112 bytes; l5[j] receives beamlet j's FP64 l5 (the rotor
 // tables' source) and, unless e0t is null, e0t[j] its term at the plane origin.
-hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, int32_t n_inst, int64_t total,
-                              Rec32 *rec, double *l5, double2 *e0t, uint32_t *status, int32_t *bad, uint32_t *peak,
-                              hipStream_t s);
+// Instance i's workgroups are [blks[i], blks[i + 1]) (batch_setup_blocks of
+// its beamlets each), n_blocks in all; rowbad[i] receives FLAG_ROWS if its
+// row chunks do not share their y factors.
+inline int64_t batch_setup_blocks(const BeamletsDev &b) {
+    const int64_t per = kRowBlock - (b.rows ? 1 : 0);
+    return (b.n + per - 1) / per;
+}
+hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, const int32_t *blks, int32_t n_inst,
+                              int32_t n_blocks, Rec32 *rec, double *l5, double2 *e0t, uint32_t *status, int32_t *bad,
+                              uint32_t *peak, uint32_t *rowbad, hipStream_t s);
 // the rotor tables of every record (before a rotor-form evaluation)
 hipError_t launch_batch_sigma(const BatchInst *inst, const int64_t *offs, int32_t n_inst, int64_t total,
                               const double *l5, Rec32 *rec, hipStream_t s);
@@ -230,6 +270,11 @@ hipError_t launch_batch_e0(const BatchEval *inst, int32_t n_inst, const int32_t 
 // form 3: the separable form (rows and waves do not apply), in FP16 halves
 // when half (scales from BatchEval::scale), else on FP32 MFMA
 hipError_t launch_batch_eval(int rows, int waves, int form, bool half, int cus, const BatchArgs &a, hipStream_t s);
+// The instances of r in the row-factored form (a.inst, a.rec, a.e0, a.airy,
+// a.fields, a.part and the zones as for launch_batch_eval); v: RowV32 scratch
+// for all their chunks.
+struct RowV32;
+hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, RowV32 *v, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchEval *inst, int32_t n_inst, const double *part, int32_t n_zones,
                                  double *metrics, hipStream_t s);
 hipError_t launch_airy(int32_t nx, int32_t ny, double dx, double dy, double vscale, float *out, hipStream_t s);
@@ -319,9 +364,12 @@ __device__ inline void post_status(const StatusPost &sp) {
     __hip_atomic_store(sp.post, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 hipError_t launch_status_post(const StatusPost &sp, hipStream_t s);
+// row_out (with b.rows > 0): receives the handle's chunk table (rows + 1
+// entries), so that the plan outlives the handle; the setup checks that each
+// chunk's beamlets have bit-equal y factors (FLAG_ROWS if not).
 hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, Rec64 *r64,
                         Rec32 *r32, RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32,
-                        uint32_t *status, uint32_t *status_next, hipStream_t s);
+                        uint32_t *status, uint32_t *status_next, int32_t *row_out, hipStream_t s);
 
 // The rotor forms' sigma^(k^2) tables (k = 1..16) of the g.n beamlets, from
 // their FP64 records on rows g.dy apart: into q64 (FP64 rotor form) or the
@@ -427,6 +475,44 @@ hipError_t launch_eval_sep64(const EvalGeom &g, const Rec64 *rec, const RecHG64 
 hipError_t launch_eval_sep(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, float2 *partial, float2 *out,
                            hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
                            const StatusPost &sp = StatusPost());
+
+// Row-factored separable sum (gbd_rows.hip).  On a pupil grid stored row by
+// row the beamlets of a grid row share their y factor V bit for bit, so with
+// the beamlets cut into chunks c of such rows
+//   sum_j U_j(x) V_j(y) = sum_c V_c(y) T_c(x),   T_c(x) = sum_{j in c} U_j(x):
+// N nx factors and a matrix product over the chunks instead of one over the
+// beamlets.
+constexpr int kRowTilePx = 32;  // the product's workgroup tile
+struct RowGeom {
+    int32_t nx, ny;
+    double dx, dy, a0, b0;
+    int32_t chunks;
+};
+// A chunk's y factor, gathered by the row sums for the product (lv0: log2 of
+// its scale, minus the bound of its modulus over the grid rows).
+struct alignas(16) RowV32 {
+    double brho, p2, p5;
+    float m2, m5, brho_f, lv0;
+    float gyr, gyi, cy0r, cy0i, cy1, cy2;
+};
+static_assert(sizeof(RowV32) == 64, "RowV32 layout");
+struct alignas(16) RowV64 {
+    double brho, p2, p5, l2, l5;
+    double gyr, gyi, cy0r, cy0i, cy1, cy2, pad;
+};
+static_assert(sizeof(RowV64) == 96, "RowV64 layout");
+// Row chunks of beamlets [0, start[chunks]) from the records: sums [chunks][nx]
+// and V factors [chunks] are scratch.  Mixed: status[1] is the setup's key
+// (the largest term's log2, the FP32 sums' common scale).  Writes out, or
+// partial when out is null (complex64 / complex128), unless the guard's
+// condition fails.  t0 / t1 time the two kernels from the first one's start
+// to the second one's end; sp: a setup status to post at the start.
+hipError_t launch_rows32(const RowGeom &g, const int32_t *start, const Rec32 *rec, const RecHG32 *hg,
+                         const uint32_t *status, float2 *sums, RowV32 *v, float2 *out, const EvalGuard &guard,
+                         hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp);
+hipError_t launch_rows64(const RowGeom &g, const int32_t *start, const Rec64 *rec, const RecHG64 *hg, double2 *sums,
+                         RowV64 *v, double2 *out, const EvalGuard &guard, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
+                         const StatusPost &sp);
 
 // The same form for fundamental beamlets on FP16 MFMA (v_mfma_f32_16x16x32_f16)
 // with every factor split into FP16 hi and lo halves (products hi hi, hi lo,

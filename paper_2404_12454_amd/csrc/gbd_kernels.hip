@@ -20,20 +20,32 @@ namespace {
 
 using namespace dev;
 
-__global__ void __launch_bounds__(256) setup_kernel(BeamletsDev b, PlaneGeom pl, double gturns,
+__global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGeom pl, double gturns,
                                                     Rec64 *__restrict__ r64, Rec32 *__restrict__ r32,
                                                     RecHG64 *__restrict__ h64, RecHG32 *__restrict__ h32,
                                                     RecCut64 *__restrict__ c64, RecCut32 *__restrict__ c32,
                                                     uint32_t *__restrict__ status,
-                                                    uint32_t *__restrict__ status_next) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j == 0) {  // the next setup's flag and peak words (not used by this one)
+                                                    uint32_t *__restrict__ status_next,
+                                                    int32_t *__restrict__ row_out) {
+    const int halo = b.rows ? 1 : 0;  // thread 0 repeats the previous workgroup's last beamlet (row_check)
+    const int64_t j = (int64_t)blockIdx.x * (kRowBlock - halo) + threadIdx.x - halo;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // the next setup's flag and peak words (not used by this one)
         status_next[0] = 0u;
         status_next[1] = 0u;
     }
     float peak = -INFINITY;
     uint32_t flag = 0;
-    if (j < b.n) flag = setup_one(b, pl, gturns, j, r64, r32, h64, h32, c64, c32, false, &peak);
+    double ykey[kYKey] = {};
+    const bool live = j >= 0 && j < b.n;
+    if (live)
+        flag = setup_one(b, pl, gturns, j, r64, r32, h64, h32, c64, c32, false, &peak, nullptr, nullptr, ykey,
+                         (int)threadIdx.x >= halo);
+    if (b.rows) {  // uniform
+        __shared__ double wkey[kRowBlock / 64][kYKey];
+        flag |= h64 ? row_check<true>(ykey, live, j, b.n - b.n_cut, b.row_bits, wkey)
+                    : row_check<false>(ykey, live, j, b.n - b.n_cut, b.row_bits, wkey);
+        if (live && j <= b.rows) row_out[j] = b.row_start[j];
+    }
     // status[0]: the flags OR-ed; status[1]: the largest term modulus of any
     // beamlet over the grid, as ceil(log2) + 2048 clamped to [1, 4095] (0:
     // none).  One atomic of each per workgroup: the words are shared by the
@@ -379,13 +391,6 @@ __global__ void __launch_bounds__(64 * WAVES) eval_fp64_rotor_kernel(EvalGeom g,
     }
 }
 
-// the guard's condition (EvalGuard), the same for every thread
-__device__ inline bool guard_holds(const EvalGuard &gd) {
-    if (!gd.status) return true;
-    const uint32_t st = gd.status[0], key = gd.status[1];
-    return !(st & FLAG_ERRORS) && (st & gd.mask) == gd.flags && (!gd.check_key || key == gd.key);
-}
-
 __global__ void __launch_bounds__(256) reduce_mixed_kernel(int64_t M, int32_t nseg2, const float2 *__restrict__ part2,
                                                            int32_t nseg4, const float4 *__restrict__ part4,
                                                            float2 *__restrict__ out, EvalGuard gd) {
@@ -521,11 +526,13 @@ hipError_t launch_status_post(const StatusPost &sp, hipStream_t s) {
 
 hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, Rec64 *r64, Rec32 *r32,
                         RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32, uint32_t *status,
-                        uint32_t *status_next, hipStream_t s) {
+                        uint32_t *status_next, int32_t *row_out, hipStream_t s) {
     if (b.n == 0) return hipSuccess;
-    const int64_t blocks = (b.n + 255) / 256;
-    setup_kernel<<<(unsigned)blocks, 256, 0, s>>>(b, pl, global_turns, r64, r32, h64, h32, c64, c32, status,
-                                                  status_next);
+    if (b.rows >= b.n || (b.rows && !row_out)) return hipErrorInvalidValue;  // the threads copy rows + 1 entries
+    const int per = kRowBlock - (b.rows ? 1 : 0);
+    const int64_t blocks = (b.n + per - 1) / per;
+    setup_kernel<<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, r64, r32, h64, h32, c64, c32, status,
+                                                        status_next, row_out);
     return hipGetLastError();
 }
 

@@ -27,15 +27,13 @@
 // rows l / 16 + 4 e, e = 0..3, column l % 16 of each result block (found by a
 // lane-layout probe and fixed by the parity tests).  Segments are summed in
 // FP64 by the reduction; the host sizes them so that every one is non-empty.
-#include "gbd_device.h"
+#include "gbd_sep_core.h"
 
 namespace gbd {
 
 namespace {
 
-using namespace dev;
-
-typedef double d4 __attribute__((ext_vector_type(4)));
+using namespace sep;
 
 constexpr int kBX = 4, kBY = 2;  // 16-pixel blocks per wavefront along x and y
 constexpr int kWX = 2, kWY = 4;  // wavefronts per workgroup along x and y
@@ -84,23 +82,6 @@ __device__ inline Fields64 load_fields64(const Rec64 *__restrict__ rec, const Re
     f.l5 = rp->l[5];
     f.lbias = j < je ? 0.0 : -INFINITY;
     return f;
-}
-
-// The factor times a higher-order beamlet's axis polynomial c0 + g (c1 + c2 g),
-// g = G d (no cross terms: G diagonal), FP64.
-__device__ inline double2 hg_axis64(double2 u, double d, double gr0, double gi0, double c0r, double c0i, double c1,
-                                   double c2) {
-    const double gr = gr0 * d, gi = gi0 * d;
-    const double tr = fma(c2, gr, c1), ti = c2 * gi;
-    const double pr = c0r + (gr * tr - gi * ti), pi = c0i + (gr * ti + gi * tr);
-    return make_double2(u.x * pr - u.y * pi, u.x * pi + u.y * pr);
-}
-
-// e^(g0 + d (g1 + g2 d)) e^(2 pi i (c0 + d (c1 + c2 d))), FP64
-__device__ inline double2 factor64(double d, double c0, double c1, double c2, double g0, double g1, double g2) {
-    double T = c0 + d * (c1 + c2 * d);
-    T -= rint(T);
-    return cexp_turns64(g0 + d * (g1 + g2 * d), T);
 }
 
 struct Lds64 {

@@ -14,6 +14,7 @@ namespace sep {
 using namespace dev;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 // One factor: 2^(L) e^(2 pi i T), T = c0 + d (c1 + c2 d) in FP64 (turns),
 // L = l0 + df (l1 + l2 df) in FP32 from the pixel's own offset.
@@ -36,6 +37,23 @@ __device__ inline void hg_axis(float df, float gr0, float gi0, float c0r, float 
     const float r = re * pr - im * pi;
     im = re * pi + im * pr;
     re = r;
+}
+
+// The factor times a higher-order beamlet's axis polynomial c0 + g (c1 + c2 g),
+// g = G d (no cross terms: G diagonal), FP64.
+__device__ inline double2 hg_axis64(double2 u, double d, double gr0, double gi0, double c0r, double c0i, double c1,
+                                   double c2) {
+    const double gr = gr0 * d, gi = gi0 * d;
+    const double tr = fma(c2, gr, c1), ti = c2 * gi;
+    const double pr = c0r + (gr * tr - gi * ti), pi = c0i + (gr * ti + gi * tr);
+    return make_double2(u.x * pr - u.y * pi, u.x * pi + u.y * pr);
+}
+
+// e^(g0 + d (g1 + g2 d)) e^(2 pi i (c0 + d (c1 + c2 d))), FP64
+__device__ inline double2 factor64(double d, double c0, double c1, double c2, double g0, double g1, double g2) {
+    double T = c0 + d * (c1 + c2 * d);
+    T -= rint(T);
+    return cexp_turns64(g0 + d * (g1 + g2 * d), T);
 }
 
 // The record fields one lane's factors need; a beamlet index past the

@@ -1,0 +1,121 @@
+"""The row-factored separable sum (pupil grids stored row by row) against the
+FP64 oracle, at the edges of its tiles, chunks and column blocks, and the
+decompositions that it must leave to the dense form: beamlets in no order, a
+detector turned about the axis, rows too short.  Tolerances as everywhere
+(relative L2 1e-12 FP64, 1e-5 mixed)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2404_12454_amd as gbd
+from paper_2404_12454_amd import scenes
+from gbd_testutil import ensure_library, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+TOL = {gbd.GBD_FP64: 1e-12, gbd.GBD_MIXED: 1e-5}
+BOTH = [gbd.GBD_FP64, gbd.GBD_MIXED]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    ensure_library()
+    return gbd.Context(0)
+
+
+def field(ctx, sc, precision):
+    return gbd.gbd_eval(ctx, gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc), precision).cpu().numpy()
+
+
+def permuted(sc, seed):
+    """The same beamlets in no order: no two neighbours share a row."""
+    p = np.random.default_rng(seed).permutation(sc.n)
+    out = scenes.Scene(sc.lam, sc.l0, sc.r1[p], sc.th1[p], sc.w0[p], sc.amp[p], sc.path[p], sc.abcd, sc.plane)
+    if sc.order is not None:
+        out.order = sc.order[p]
+    return out
+
+
+@pytest.mark.parametrize("precision", BOTH)
+@pytest.mark.parametrize("across,nx,ny", [(10, 1, 1), (11, 31, 33), (16, 64, 32), (21, 65, 97), (24, 128, 31),
+                                          (33, 129, 64), (17, 192, 5), (17, 193, 40), (40, 513, 2)])
+def test_rows_ragged_defocused_off_axis(ctx, precision, across, nx, ny):
+    sc = scenes.airy_scene(across, npix=nx, npix_y=ny, half_span_lamF=6.0, field_angle=(1e-3, -5e-4), z0=30e-6)
+    ref = oracle.eval_field(sc)
+    assert rel_l2(field(ctx, sc, precision), ref) <= TOL[precision]
+    assert rel_l2(field(ctx, permuted(sc, nx), precision), ref) <= TOL[precision]  # the dense form
+
+
+@pytest.mark.parametrize("precision", BOTH)
+def test_rows_higher_orders(ctx, precision):
+    sc = scenes.hermite_scene(20, npix=201, npix_y=70, half_span_lamF=8.0, z0=40e-6)
+    ref = oracle.eval_field(sc)
+    assert rel_l2(field(ctx, sc, precision), ref) <= TOL[precision]
+    assert rel_l2(field(ctx, permuted(sc, 3), precision), ref) <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", BOTH)
+def test_rows_longer_than_a_chunk(ctx, precision):
+    """Rows of 1, 1,024, 1,025 and 2,500 beamlets, amplitudes over 1e12 with some zero."""
+    rng = np.random.default_rng(5)
+    a = scenes.airy_scene(12, npix=70, npix_y=45, half_span_lamF=5.0)
+    r1 = np.concatenate([np.stack([np.linspace(-4e-3, 4e-3, k), np.full(k, y)], axis=1)
+                         for k, y in ((1, -1e-3), (1024, 0.0), (1025, 5e-4), (2500, 1.2e-3))])
+    n = len(r1)
+    amp = (10.0 ** rng.uniform(-12, 0, n))[:, None] * rng.normal(size=(n, 2))
+    amp[::7] = 0.0
+    sc = scenes.Scene(a.lam, a.l0, r1, np.zeros((n, 2)), np.full(n, 3e-4), amp, np.zeros(n), a.abcd, a.plane)
+    assert rel_l2(field(ctx, sc, precision), oracle.eval_field(sc)) <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", BOTH)
+def test_rows_refused_on_a_turned_detector(ctx, precision):
+    """Turned about the axis the rows' hit points leave the detector's rows; turned by a quarter the columns are
+    the pupil's rows.  The setup finds both, and a plan goes from one detector to the other."""
+    sc = scenes.airy_scene(24, npix=80, npix_y=66, half_span_lamF=6.0, field_angle=(1e-3, 0.0), z0=200e-6)
+    plan = gbd.Plan(ctx, sc.n)
+    b = gbd.beamlets_from_scene(ctx, sc)
+    for angle in (0.0, 0.3, 0.0, np.pi / 2, 0.0):
+        sc.plane.xhint = np.array([np.cos(angle), np.sin(angle), 0.0])
+        E = plan.setup(b, gbd.plane_from_scene(ctx, sc)).eval(precision).cpu().numpy()
+        assert rel_l2(E, oracle.eval_field(sc)) <= TOL[precision], angle
+        E = gbd.gbd_eval(ctx, b, gbd.plane_from_scene(ctx, sc), precision).cpu().numpy()
+        assert rel_l2(E, oracle.eval_field(sc)) <= TOL[precision], angle
+
+
+def test_rows_of_a_steep_grid_fp64(ctx):
+    """A column pitch of several spot radii: FP64 row sums form every column's factor by itself."""
+    sc = scenes.airy_scene(10, OF=1.7, npix=260, npix_y=12, half_span_lamF=250.0)
+    sc.plane.dy = 1e-6
+    assert rel_l2(field(ctx, sc, gbd.GBD_FP64), oracle.eval_field(sc)) <= 1e-12
+
+
+def test_a_plan_outlives_its_rows_handle(ctx):
+    import torch
+    sc = scenes.airy_scene(30, npix=64, half_span_lamF=6.0)
+    other = scenes.airy_scene(30, OF=1.2, npix=64, half_span_lamF=6.0)
+    b = gbd.beamlets_from_scene(ctx, sc)
+    plan = gbd.Plan(ctx, sc.n).setup(b, gbd.plane_from_scene(ctx, sc))
+    want = plan.eval(gbd.GBD_MIXED).cpu()
+    del b  # its block serves the next handles
+    keep = [gbd.beamlets_from_scene(ctx, permuted(other, k)) for k in range(3)]
+    got = plan.eval(gbd.GBD_MIXED).cpu()
+    assert torch.equal(got.view(torch.float32), want.view(torch.float32)) and keep
+
+
+def test_batch_mixes_rows_and_dense_instances(ctx):
+    """A batch of instances by rows, one in no order and one of too few beamlets: every field equals gbd_eval's
+    (one segment) bit for bit, and the metrics a batch of each alone."""
+    import torch
+    ss = [scenes.airy_scene(k, npix=97, npix_y=66, half_span_lamF=6.0) for k in (24, 7, 40, 16)]
+    ss[2] = permuted(ss[2], 1)
+    bs, ps = [gbd.beamlets_from_scene(ctx, s) for s in ss], [gbd.plane_from_scene(ctx, s) for s in ss]
+    m = scenes.airy_scene(7).meta
+    airy = gbd.gbd_airy(ctx, ps[0], m["D"], m["f"], ss[0].lam)
+    metrics, fields = gbd.gbd_eval_batch(ctx, bs, ps, airy=airy, zone_edges=[0.0, 3e-5, 6e-5], fields=True)
+    for k, (b, p) in enumerate(zip(bs, ps)):
+        E = gbd.gbd_eval(ctx, b, p, gbd.GBD_MIXED, opts=dict(segments=1, variant=4)).cpu()
+        assert torch.equal(E.view(torch.float32), fields[k].cpu().view(torch.float32)), k
+        alone, _ = gbd.gbd_eval_batch(ctx, [b], [p], airy=airy, zone_edges=[0.0, 3e-5, 6e-5])
+        assert np.array_equal(alone[0], metrics[k]), k
+        assert rel_l2(E.numpy(), oracle.eval_field(ss[k])) <= 1e-5
