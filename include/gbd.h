@@ -103,6 +103,12 @@ typedef struct {
                                0.1 per row^2 (well-sampled spots).  Auto: separable, else
                                rotor, else direct; a request that does not apply falls
                                back to auto's choice among the others.
+                               Weak cross terms: at the rotor form's 32 rows x 4 wavefronts
+                               (0 or so requested) and two or more segments, a plane whose
+                               cross terms the setup finds weak over 128 x 128 pixel tiles
+                               takes forms 0 and 3 as matrix products, e^(x u v) by its
+                               series (within 1e-7 of a term) about each tile's centre, on
+                               FP16 MFMA in halves; shape and options stay the rotor's.
                                Separable by rows: where at least 64 beamlets come in runs
                                (four or more on average) that share one ABCD and differ
                                along x only, as on a pupil grid stored row by row, and the

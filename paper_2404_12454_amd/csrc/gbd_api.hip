@@ -183,7 +183,7 @@ struct gbd_plan_s {
 constexpr int kNoSpeculation = 1;
 
 // the setup flags that select how an evaluation runs
-constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS;
+constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS | FLAG_CROSS1 | FLAG_CROSS2;
 
 struct gbd_mlp_s {
     gbd_ctx_s *ctx;
@@ -328,6 +328,7 @@ int ensure_device(gbd_ctx_s *ctx) {
 struct Shape {
     int rows, waves, nseg, form;
     bool half;  // mixed separable form in FP16 hi/lo halves (else FP32 MFMA)
+    bool cross = false;  // the rotor's sum by the cross form (launch_eval_cross)
 };
 
 // mixed kernel form (0 direct, 1 stepped, 2 rotor, 3 separable): requested
@@ -382,6 +383,38 @@ TuneKey tune_key(int kind, int precision, int64_t n, int64_t m) { return TuneKey
 // plain FP32 on the matrix cores, at most kSepMaxSegLen beamlets per sum.
 int64_t min_segments(int precision, int form, int64_t n) {
     return (form == 3 && precision == GBD_MIXED) ? (n + kSepMaxSegLen - 1) / kSepMaxSegLen : 1;
+}
+
+// The cross form takes over the rotor form's sums where every cross term is
+// weak (the setup's flags), at the rotor's default shape (32 rows, 4
+// wavefronts) and at two segments or more: one segment asked for is the
+// batched sweep's arithmetic, the rotor recurrence.  Below kCrossMinPairs
+// the rotor form is as fast (448 beamlets on 64 x 90 pixels 18 us against 24;
+// 1,264 on 64 x 90 31 against 27, 12,892 on 1024^2 2,640 against 560).
+constexpr int64_t kCrossMinPairs = 3000000;
+bool cross_applies(int precision, int form, uint32_t flags, int64_t n, int64_t m) {
+    return precision == GBD_MIXED && form == 2 && (flags & FLAG_CROSS) && !(flags & (FLAG_HG | FLAG_CROSS2)) &&
+           n * m >= kCrossMinPairs;
+}
+
+// Its automatic segment count: one workgroup per CU at a time, each pass of 16
+// beamlets about 2.4 us and three passes' worth of start-up, 16 bytes per
+// pixel and segment through memory for the partials; segments of 64 ... 768
+// beamlets (an FP32 sum's error grows with its length: 64 across on 256^2
+// pixels 2.0e-7 at 403 per sum, 2.7e-7 at 807, 4.3e-7 at 1,614).
+int64_t cross_segments(int cus, int64_t tiles, int64_t n, int64_t m) {
+    int64_t best = 1;
+    double best_t = 1e300;
+    for (int64_t seg = std::max<int64_t>(2, (n + 767) / 768); seg <= std::max<int64_t>(2, n / 64); seg++) {
+        const double rounds = (double)((tiles * seg + cus - 1) / cus);
+        const double t = rounds * (double)((n / seg + 15) / 16 + 3) * 2.4e-6 + (double)seg * (double)m * 16.0 / 5e12;
+        if (t < best_t) {
+            best_t = t;
+            best = seg;
+        }
+        if (seg > 1024) break;
+    }
+    return best;
 }
 
 // Workgroup tile of a separable shape in pixels.
@@ -443,7 +476,8 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
         return s;
     }
     // rotor form: 32 rows per lane where the grid fills a 4-wave tile
-    s.rows = (s.form == 2 && pl.ny >= 128) ? 32 : (precision != GBD_MIXED && s.form == 0) ? 4 : 16;
+    const bool cross = cross_applies(precision, s.form, flags, n, (int64_t)pl.nx * pl.ny);
+    s.rows = (s.form == 2 && (pl.ny >= 128 || cross)) ? 32 : (precision != GBD_MIXED && s.form == 0) ? 4 : 16;
     s.waves = 4;
     s.nseg = 0;
     int seg_pct = 100;
@@ -465,6 +499,20 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
     if (precision != GBD_MIXED && s.form == 0 && s.rows > 8) s.rows = 8;  // FP64 direct form: up to 8 rows
     // FP64 rotor form with higher-order factors: up to 16 rows (registers)
     if (precision != GBD_MIXED && s.form == 2 && (flags & FLAG_HG) && s.rows > 16) s.rows = 16;
+    if (cross && s.rows == 32 && s.waves == 4) {
+        int64_t seg = s.nseg;
+        if (seg <= 0) {
+            const int64_t tiles = std::max<int64_t>(1, (int64_t)((pl.nx + kCrossTile - 1) / kCrossTile) *
+                                                           ((pl.ny + kCrossTile - 1) / kCrossTile));
+            seg = cross_segments(ctx->cus, tiles, n, (int64_t)pl.nx * pl.ny) * seg_pct / 100;
+            seg = std::max<int64_t>(2, std::min<int64_t>(seg, 1024));
+        }
+        seg = std::max<int64_t>(seg, seg > 1 ? (n + kSepMaxSegLen - 1) / kSepMaxSegLen : 1);
+        if (seg >= 2 && n >= 4) {
+            s.cross = true;
+            s.nseg = (int)std::min<int64_t>(seg, 0x7fffffff);
+        }
+    }
     if (s.nseg <= 0) {
         // enough workgroups to keep every SIMD of every CU busy ~6 waves deep,
         // while each segment keeps at least two LDS tiles of beamlets
@@ -494,7 +542,10 @@ EvalGeom make_geom(const PlaneGeom &pl, int64_t n, const Shape &s) {
     g.dy = pl.dy;
     g.a0 = -0.5 * (pl.nx - 1) * pl.dx;
     g.b0 = -0.5 * (pl.ny - 1) * pl.dy;
-    if (s.form == 3) {
+    if (s.cross) {
+        g.tiles_x = (pl.nx + kCrossTile - 1) / kCrossTile;
+        g.tiles_y = (pl.ny + kCrossTile - 1) / kCrossTile;
+    } else if (s.form == 3) {
         int wgx, wgy;
         sep_wg_tile(s, wgx, wgy);
         g.tiles_x = (pl.nx + wgx - 1) / wgx;
@@ -609,7 +660,8 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     // [n_main, n) by their own kernel into the following segments
     const int64_t n_main = plan->n - plan->n_cut;
     // the mixed separable form's partials are compact (float2) and come first
-    const bool compact = n_main > 0 && s.form == 3 && precision == GBD_MIXED;
+    // (of the cross form too)
+    bool compact = n_main > 0 && (s.form == 3 || s.cross) && precision == GBD_MIXED;
     EvalGeom g{}, gc{};
     int32_t nseg_main = 0, nseg_cut = 0;
     if (plan->n_cut > 0) {
@@ -647,10 +699,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     if (fixed && !by_rows) {
         // partial bytes of nm main and nc truncated segments (none when one
         // segment writes the output directly)
-        const size_t per_main = (size_t)M * (compact ? 8 : 16), per_cut = (size_t)M * 16;
+        // (the cross form's count as the rotor form's, whose shape it reports)
+        const bool small = compact && !s.cross;
+        const size_t per_main = (size_t)M * (small ? 8 : 16), per_cut = (size_t)M * 16;
         auto need_of = [&](int64_t nm, int64_t nc) -> size_t {
             if (nm + nc <= 1 && nc == 0) return 0;
-            return compact ? reduce_wide_offset((int32_t)nm, M) + (size_t)nc * per_cut : (size_t)(nm + nc) * per_cut;
+            return small ? reduce_wide_offset((int32_t)nm, M) + (size_t)nc * per_cut : (size_t)(nm + nc) * per_cut;
         };
         if (need_of(nseg_main, nseg_cut) > fixed_bytes) {
             if (opts && opts->segments > 0)
@@ -668,7 +722,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                 }
             }
             if (n_main > 0) {
-                const size_t used = (size_t)nseg_cut * per_cut + (compact ? 16 : 0);
+                const size_t used = (size_t)nseg_cut * per_cut + (small ? 16 : 0);
                 int64_t max_main = used < fixed_bytes ? (int64_t)((fixed_bytes - used) / per_main) : 0;
                 if (nseg_cut == 0 && max_main < 2) max_main = 1;  // one segment: no partials
                 const int64_t floor_seg = min_segments(precision, s.form, n_main);
@@ -687,6 +741,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                             need_of(nseg_main, nseg_cut), fixed_bytes);
         }
     }
+    if (s.cross && nseg_main < 2) {  // lowered to one segment: the rotor form's
+        s.cross = false;
+        compact = false;
+        g = make_geom(plan->pl, n_main, s);
+        nseg_main = g.nseg;
+    }
     if (n_main > 0 && (int64_t)g.tiles_x * g.tiles_y * g.nseg > (int64_t)0x7fffffff - 8)
         return fail(GBD_ERANGE, "grid too large");
     if (nseg_cut > 0 && (int64_t)gc.tiles_x * gc.tiles_y * gc.nseg > (int64_t)0x7fffffff - 8)
@@ -696,7 +756,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     if (guard && !reduce && !by_rows) return kNoSpeculation;
     StatusPost sp;  // the post handed to the separable form's kernel
     if (post_req && post_req->post) {
-        if (n_main > 0 && s.form == 3) {
+        if (n_main > 0 && (s.form == 3 || s.cross)) {
             sp = *post_req;
         } else {
             HIP_TRY(launch_status_post(*post_req, ctx->stream), "status post launch");
@@ -723,7 +783,8 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         const void *hrec = !hg ? nullptr : precision == GBD_FP64 ? (const void *)plan->h64 : (const void *)plan->h32;
         EvalGeom gl = g;
         if (reduce && !by_rows) gl.nseg = std::max<int32_t>(total, 2);  // segment partials, never the output
-        if (s.form == 2)
+        const bool stamped = s.form == 3 || s.cross;  // the launch's events take the kernel's own times
+        if (s.form == 2 && !s.cross)
             HIP_TRY(launch_sigma(gl, plan->r64, precision == GBD_FP64 ? plan->q64 : nullptr,
                                  precision == GBD_FP64 ? nullptr : plan->r32, ctx->stream),
                     "sigma table kernel launch");
@@ -744,9 +805,9 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                 }
             }
             ctx->timed.push_back(tev);
-            // the separable forms' launches take the kernel's own times; the
+            // the matrix forms' launches take the kernel's own times; the
             // others are bracketed by event records
-            if (s.form != 3) HIP_TRY(hipEventRecord(tev.first, ctx->stream), "hipEventRecord");
+            if (!stamped) HIP_TRY(hipEventRecord(tev.first, ctx->stream), "hipEventRecord");
         }
         if (by_rows) {
             const RowGeom rg{plan->pl.nx, plan->pl.ny, g.dx, g.dy, g.a0, g.b0, plan->rows};
@@ -768,7 +829,11 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                                       plan->status_cur, static_cast<float2 *>(sums), static_cast<RowV32 *>(plan->row_v),
                                       static_cast<float2 *>(dst), gd, ctx->stream, tev.first, tev.second, sp),
                         "row kernels launch");
-        } else if (s.form == 3 && precision == GBD_FP64)
+        } else if (s.cross)
+            HIP_TRY(launch_eval_cross((plan->flags & FLAG_CROSS1) ? 2 : 1, gl, plan->r32, plan->status_cur,
+                                      static_cast<float2 *>(partial), ctx->stream, tev.first, tev.second, sp),
+                    "eval kernel launch");
+        else if (s.form == 3 && precision == GBD_FP64)
             HIP_TRY(launch_eval_sep64(gl, plan->r64, static_cast<const RecHG64 *>(hrec),
                                       static_cast<double2 *>(partial), static_cast<double2 *>(out), ctx->stream,
                                       tev.first, tev.second, sp),
@@ -787,7 +852,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
             HIP_TRY(launch_eval(precision, s.rows, s.waves, s.form, gl, rec, hrec, plan->q64, partial, out,
                                 ctx->stream),
                     "eval kernel launch");
-        if (tev.second && s.form != 3) HIP_TRY(hipEventRecord(tev.second, ctx->stream), "hipEventRecord");
+        if (tev.second && !stamped) HIP_TRY(hipEventRecord(tev.second, ctx->stream), "hipEventRecord");
         if (post_req) post_req->post = nullptr;  // posted by the kernel just launched (form 3), or above
     }
     if (nseg_cut > 0) {
@@ -902,9 +967,9 @@ int plan_setup_finish(gbd_ctx_s *ctx, gbd_plan_s *plan) {
             }
             if (dt > std::chrono::microseconds(200)) std::this_thread::yield();
         }
-        const uint32_t st = (uint32_t)w & 0xffu;
+        const uint32_t st = (uint32_t)w & 0xfffu;
         // FP16 separable form: largest term 2^P over the grid -> scale 2^(2 kSepHalfExp - P)
-        const uint32_t key = ((uint32_t)w >> 8) & 0xfffu;
+        const uint32_t key = ((uint32_t)w >> 12) & 0xfffu;
         plan->sep_key = key;
         plan->sep_scale = key ? 2 * kSepHalfExp - ((int)key - 2048) : 0;
         if (st & FLAG_PARALLEL) return fail(GBD_EPARALLEL, "a base ray is parallel to the detector plane");

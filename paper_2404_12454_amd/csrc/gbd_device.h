@@ -402,7 +402,21 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         }
         if (!fin) flag |= FLAG_NONFINITE;
         if (!is_cut && fabs(l[5]) * il2_dev() * pl.dy * pl.dy > kStepCurvature) flag |= FLAG_STEEP;
-        if (!is_cut && (p[4] != 0.0 || l[4] != 0.0)) flag |= FLAG_CROSS;
+        if (!is_cut && (p[4] != 0.0 || l[4] != 0.0)) {
+            flag |= FLAG_CROSS;
+            // the cross form: |x| in a tile's corner, and the cross terms'
+            // share in the factors' moduli over the grid's tiles
+            const double h = 0.5 * kCrossTile;
+            const double X = hypot(2.0 * kPi * p[4], l[4]) * (h * pl.dx) * (h * pl.dy);
+            auto reach = [](int n, double d, double at) {  // largest offset from `at` over the tiles of one axis
+                const double c0 = -0.5 * (n - 1) * d;
+                const int full = (n + kCrossTile - 1) / kCrossTile * kCrossTile;
+                return fmax(fabs(c0 - at), fabs(c0 + (full - 1) * d - at));
+            };
+            const double share = fabs(l[4]) * il2_dev() * reach(pl.nx, pl.dx, arho) * reach(pl.ny, pl.dy, brho);
+            if (!(X <= kCrossLimit1)) flag |= FLAG_CROSS1;
+            if (!(X <= kCrossLimit2 && share <= 1.0)) flag |= FLAG_CROSS2;
+        }
         o64.arho = arho;
         o64.brho = brho;
         o32.arho = arho;

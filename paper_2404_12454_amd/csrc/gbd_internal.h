@@ -159,7 +159,15 @@ enum : uint32_t {
     // not an error: a row chunk's beamlets do not share their y factor, so
     // the row-factored sum (launch_rows) does not apply
     FLAG_ROWS = 128u,
+    // not an error: some beamlet's cross term in the corner of a tile of the
+    // cross form (launch_eval_cross) exceeds its first level's limit; its
+    // second level's, or the cross terms' share in the factors' bounds over
+    // the grid exceeds a factor 2
+    FLAG_CROSS1 = 256u,
+    FLAG_CROSS2 = 512u,
 };
+constexpr int kCrossTile = 128;  // the cross form's workgroup tile in pixels
+constexpr double kCrossLimit1 = 1.0 / 1024.0, kCrossLimit2 = 1.0 / 64.0;
 
 // largest |d^2 log2(amplitude) / d row^2| / 2 for which the mixed kernel may
 // step the amplitude along a column by multiplication: over 16 rows no term
@@ -345,8 +353,8 @@ hipError_t launch_mlp_adamw(float *p, const float *g, float *m, float *v, int64_
 // as ceil(log2) + 2048 (0: none; the FP16 separable form's range); and
 // status_next: the next setup's two words, set to zero (the host alternates
 // the pairs, so no separate clear is needed).
-// A finished setup's status[0] (flags, < 256) and status[1] (key, < 4096)
-// posted to the host: (seq << 32) | flags | key << 8 in one system-scope
+// A finished setup's status[0] (flags, < 4096) and status[1] (key, < 4096)
+// posted to the host: (seq << 32) | flags | key << 12 in one system-scope
 // store into *post (coherent host memory), which the host polls for seq (an
 // event after a copy would end with a system-scope release that stalls the
 // stream for the cache writeback).  Any kernel that runs after the setup in
@@ -360,7 +368,7 @@ struct StatusPost {
 };
 __device__ inline void post_status(const StatusPost &sp) {
     const uint32_t f = sp.status[0], k = sp.status[1];
-    const uint64_t w = ((uint64_t)sp.seq << 32) | (uint64_t)(f & 0xffu) | ((uint64_t)(k & 0xfffu) << 8);
+    const uint64_t w = ((uint64_t)sp.seq << 32) | (uint64_t)(f & 0xfffu) | ((uint64_t)(k & 0xfffu) << 12);
     __hip_atomic_store(sp.post, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 hipError_t launch_status_post(const StatusPost &sp, hipStream_t s);
@@ -476,6 +484,12 @@ hipError_t launch_eval_sep(const EvalGeom &g, const Rec32 *rec, const RecHG32 *h
                            hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
                            const StatusPost &sp = StatusPost());
 
+// Matrix form for fundamental beamlets with weak cross terms (gbd_cross.hip),
+// level 1 or 2 of its series (no FLAG_CROSS1, no FLAG_CROSS2): compact
+// partials always.  status[1]: the setup's key.
+hipError_t launch_eval_cross(int level, const EvalGeom &g, const Rec32 *rec, const uint32_t *status, float2 *partial,
+                             hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp);
+
 // Row-factored separable sum (gbd_rows.hip).  On a pupil grid stored row by
 // row the beamlets of a grid row share their y factor V bit for bit, so with
 // the beamlets cut into chunks c of such rows
@@ -492,8 +506,8 @@ struct RowGeom {
 // its scale, minus the bound of its modulus over the grid rows).
 struct alignas(16) RowV32 {
     double brho, p2, p5;
-    float m2, m5, brho_f, lv0;
-    float gyr, gyi, cy0r, cy0i, cy1, cy2;
+    float m2, m5, lv0;
+    float gyr, gyi, cy0r, cy0i, cy1, cy2, pad;
 };
 static_assert(sizeof(RowV32) == 64, "RowV32 layout");
 struct alignas(16) RowV64 {

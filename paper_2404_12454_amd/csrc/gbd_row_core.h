@@ -35,7 +35,7 @@ __device__ inline RowWords row_words(const Rec *__restrict__ r) {
     w.b = *(reinterpret_cast<const u8w *>(r) + 2);
     return w;
 }
-static_assert(offsetof(Rec32, p) == 16 && offsetof(Rec32, m) == 64 && offsetof(Rec32, arho_f) == 88, "RowWords, Rec32");
+static_assert(offsetof(Rec32, p) == 16 && offsetof(Rec32, m) == 64, "RowWords, Rec32");
 static_assert(offsetof(Rec64, p) == 16 && offsetof(Rec64, l) == 64, "RowWords, Rec64");
 
 // T(x) of one chunk at the lane's columns: the x factors of beamlets j0,
@@ -44,12 +44,8 @@ static_assert(offsetof(Rec64, p) == 16 && offsetof(Rec64, l) == 64, "RowWords, R
 template <bool HG, int C>
 __device__ inline void row_sum32(const Rec32 *__restrict__ rec, const RecHG32 *__restrict__ hg, int j0, int j1,
                                  int step, const double (&ax)[C], float ls, float2 (&t)[C]) {
-    float axf[C];
 #pragma unroll
-    for (int k = 0; k < C; k++) {
-        axf[k] = (float)ax[k];
-        t[k] = make_float2(0.0f, 0.0f);
-    }
+    for (int k = 0; k < C; k++) t[k] = make_float2(0.0f, 0.0f);
     if (j0 >= j1) return;
     RowWords w = row_words(rec + j0);
     for (int j = j0; j < j1; j += step) {
@@ -57,12 +53,13 @@ __device__ inline void row_sum32(const Rec32 *__restrict__ rec, const RecHG32 *_
         w = row_words(rec + min(j + step, j1 - 1));  // the next one's, in flight during this one's factors
         __builtin_amdgcn_sched_barrier(0);
         const double arho = r.f64(0), p0 = r.f64(4), p1 = r.f64(6), p3 = r.f64(10);
-        const float m0 = r.f32(16) + ls, m1 = r.f32(17), m3 = r.f32(19), arf = r.f32(22);
+        const float m0 = r.f32(16) + ls, m1 = r.f32(17), m3 = r.f32(19);
 #pragma unroll
         for (int k = 0; k < C; k++) {
             float ur, ui;
-            const float df = axf[k] - arf;
-            factor(ax[k] - arho, df, p0, p1, p3, m0, m1, m3, ur, ui);
+            const double d = ax[k] - arho;
+            const float df = (float)d;  // rounded once: a pixel and a hit point each in FP32 would lose their difference
+            factor(d, df, p0, p1, p3, m0, m1, m3, ur, ui);
             if constexpr (HG) {
                 const RecHG32 *h = hg + j;
                 hg_axis(df, h->g[0][0][0], h->g[0][0][1], h->cx0[0], h->cx0[1], h->cx1, h->cx2, ur, ui);
@@ -142,7 +139,6 @@ __device__ inline RowV32 row_v32(const Rec32 &r, const RecHG32 *h, double b0, do
     v.p5 = r.p[5];
     v.m2 = r.m[2];
     v.m5 = r.m[5];
-    v.brho_f = r.brho_f;
     double b;
     if constexpr (HG) {
         v.gyr = h->g[1][1][0];
@@ -181,15 +177,16 @@ __device__ inline RowV64 row_v64(const Rec64 &r, const RecHG64 *h) {
 }
 
 template <bool HG>
-__device__ inline float2 row_factor(const RowV32 &v, double by, float byf) {
+__device__ inline float2 row_factor(const RowV32 &v, double by) {
     float vr, vi;
-    const float df = byf - v.brho_f;
-    factor(by - v.brho, df, 0.0, v.p2, v.p5, v.lv0, v.m2, v.m5, vr, vi);
+    const double d = by - v.brho;
+    const float df = (float)d;
+    factor(d, df, 0.0, v.p2, v.p5, v.lv0, v.m2, v.m5, vr, vi);
     if constexpr (HG) hg_axis(df, v.gyr, v.gyi, v.cy0r, v.cy0i, v.cy1, v.cy2, vr, vi);
     return make_float2(vr, vi);
 }
 template <bool HG>
-__device__ inline double2 row_factor(const RowV64 &v, double by, float) {
+__device__ inline double2 row_factor(const RowV64 &v, double by) {
     const double d = by - v.brho;
     double2 f = factor64(d, 0.0, v.p2, v.p5, 0.0, v.l2, v.l5);
     if constexpr (HG) f = hg_axis64(f, d, v.gyr, v.gyi, v.cy0r, v.cy0i, v.cy1, v.cy2);
@@ -273,12 +270,10 @@ __device__ inline void row_product(const V *__restrict__ v, const typename RowTy
     using R2 = typename RowType<V>::R2;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
     double by[2];
-    float byf[2];
     int xc[2];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
         by[p] = b0 + (y0 + 16 * p + li) * dy;
-        byf[p] = (float)by[p];
         xc[p] = min(x0 + 16 * p + li, nx - 1);
     }
 #pragma unroll
@@ -305,7 +300,7 @@ __device__ inline void row_product(const V *__restrict__ v, const typename RowTy
         load(min(s + kRowWaves, steps - 1), vn, tn);  // the next step's, used after this one's products
 #pragma unroll
         for (int p = 0; p < 2; p++) {
-            const R2 f = row_factor<HG>(vv, by[p], byf[p]);
+            const R2 f = row_factor<HG>(vv, by[p]);
             const R fn = -f.y;
 #pragma unroll
             for (int q = 0; q < 2; q++) {

@@ -1,0 +1,88 @@
+"""The matrix form for weak cross terms (tilted, aberrated planes) against the
+FP64 oracle at 1e-6 relative L2, twice the rotor form's error: both levels of
+its series, grids at the edges of its 128 x 128 tiles and 16 x 16 blocks,
+beamlet counts at the edges of its passes, and what it leaves to the rotor
+form (one segment, other launch shapes, stronger cross terms)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2404_12454_amd as gbd
+from paper_2404_12454_amd import scenes
+from gbd_testutil import ensure_library, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    ensure_library()
+    return gbd.Context(0)
+
+
+def scene(across, nx, ny, pitch, seed=11):
+    s = scenes.zernike_scene(seed, n_across=across, npix=nx, half_span=0.5 * nx * pitch)
+    s.plane.ny = ny
+    return s
+
+
+def plan_of(ctx, sc):
+    return gbd.Plan(ctx, sc.n).setup(gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc))
+
+
+# pitches 0.05 and 0.2 um: 1.0e-3 and 1.6e-2 bound the corner's cross term at
+# these beamlet counts, one level each
+@pytest.mark.parametrize("pitch", [0.05e-6, 0.15e-6])
+@pytest.mark.parametrize("across,nx,ny,seg", [(40, 127, 65, 0), (40, 128, 128, 2), (48, 129, 17, 3), (40, 300, 140, 5),
+                                              (64, 16, 129, 40), (40, 257, 255, 0)])
+def test_cross_form_ragged(ctx, pitch, across, nx, ny, seg):
+    import torch
+    sc = scene(across, nx, ny, pitch)
+    plan = plan_of(ctx, sc)
+    o = dict(segments=seg) if seg else None
+    shape = plan.shape(gbd.GBD_MIXED, o)
+    assert shape["variant"] == 3 and (shape["rows_per_lane"], shape["waves"]) == (32, 4) and shape["segments"] >= 2
+    E = plan.eval(gbd.GBD_MIXED, opts=o).cpu()
+    assert rel_l2(E.numpy(), oracle.eval_field(sc)) <= 1e-6
+    back = plan.eval(gbd.GBD_MIXED, opts=shape).cpu()  # the reported shape gives the same field
+    assert torch.equal(back.view(torch.float32), E.view(torch.float32))
+
+
+@pytest.mark.parametrize("n,seg", [(130, 2), (131, 9), (255, 4), (256, 8), (257, 16), (1000, 7)])
+def test_cross_form_short_and_ragged_segments(ctx, n, seg):
+    full = scene(40, 200, 180, 0.1e-6)
+    keep = np.zeros(full.n, bool)
+    keep[np.random.default_rng(n).choice(full.n, n, replace=False)] = True
+    sc = oracle._subset(full, keep)
+    sc.amp = sc.amp * (10.0 ** np.random.default_rng(1).uniform(-9, 3, n))[:, None]
+    E = plan_of(ctx, sc).eval(gbd.GBD_MIXED, opts=dict(segments=seg)).cpu().numpy()
+    assert rel_l2(E, oracle.eval_field(sc)) <= 1e-6
+
+
+def test_cross_form_leaves_one_segment_and_other_shapes_to_the_rotor_form(ctx):
+    """One segment is the batched sweep's arithmetic (bit for bit); other rows and wavefronts the rotor's."""
+    import torch
+    sc = scene(40, 160, 144, 0.1e-6)
+    ref = oracle.eval_field(sc)
+    b, p = gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc)
+    plan = gbd.Plan(ctx, sc.n).setup(b, p)
+    for o in (dict(segments=1), dict(rows_per_lane=16, waves=4), dict(rows_per_lane=32, waves=2), dict(variant=1)):
+        assert rel_l2(plan.eval(gbd.GBD_MIXED, opts=o).cpu().numpy(), ref) <= 1e-6
+    _, fields = gbd.gbd_eval_batch(ctx, [b], [p], fields=True)
+    E = plan.eval(gbd.GBD_MIXED, opts=dict(segments=1, variant=3, rows_per_lane=32, waves=4)).cpu()
+    assert torch.equal(fields[0].cpu().view(torch.float32), E.view(torch.float32))
+
+
+def test_cross_form_from_call_to_call(ctx):
+    """gbd_eval's launch ahead over planes of level 1, level 2, none, and no cross terms at all."""
+    import torch
+    ss = [scene(40, 160, 144, h) for h in (0.05e-6, 0.15e-6, 1.0e-6)] + [scenes.airy_scene(24, npix=100)]
+    hs = [(gbd.beamlets_from_scene(ctx, s), gbd.plane_from_scene(ctx, s)) for s in ss]
+    want = []
+    for s in ss:
+        fresh = gbd.Context(0)
+        want.append(gbd.gbd_eval(fresh, gbd.beamlets_from_scene(fresh, s), gbd.plane_from_scene(fresh, s)).cpu())
+        assert rel_l2(want[-1].numpy(), oracle.eval_field(s)) <= 1e-6
+    for i in (0, 0, 1, 1, 2, 2, 0, 2, 1, 0, 3, 3, 0, 1, 3, 2):
+        E = gbd.gbd_eval(ctx, *hs[i]).cpu()
+        assert torch.equal(E.view(torch.float32), want[i].view(torch.float32)), i
