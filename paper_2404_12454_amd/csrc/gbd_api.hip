@@ -428,6 +428,18 @@ void sep_wg_tile(const Shape &s, int &px, int &py) {
     }
 }
 
+// Most segments an automatic count takes: at least 256 beamlets each, or
+// down to `shortest` while the partial sums (elem bytes per pixel and
+// segment) stay within 64 MiB, where their traffic is small against a chip
+// left idle (rotor form, 4 wavefronts: 448 beamlets on 64 x 90 pixels 174 us
+// in one segment, 14 in 32; 1,264 on 300^2 202 us in 4, 62 in 46; FP64, 3,228
+// on 512^2 505 us in 12, 398 in 16) and the allocation-free evaluation's
+// buffer holds them.
+int64_t most_segments(int64_t n, int64_t shortest, const PlaneGeom &pl, int64_t elem) {
+    const int64_t fit = GBD_NOALLOC_SCRATCH_BYTES / std::max<int64_t>(1, (int64_t)pl.nx * pl.ny * elem);
+    return std::max<int64_t>(1, std::max<int64_t>(n / 256, std::min<int64_t>(n / shortest, fit)));
+}
+
 // Launch shape and mixed form.  32 rows per lane is a rotor-form shape: where
 // the form resolves to direct or stepped it runs 16.
 Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGeom &pl, uint32_t flags,
@@ -468,7 +480,7 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
             int64_t seg = ((int64_t)ctx->cus * per_cu + tiles - 1) / tiles;
             auto it = ctx->tuned.find(tune_key(kTuneSep, precision, n, (int64_t)pl.nx * pl.ny));
             if (it != ctx->tuned.end()) seg = std::max<int64_t>(1, seg * it->second.seg_scale_pct / 100);
-            seg = std::min<int64_t>(seg, std::max<int64_t>(1, n / 256));
+            seg = std::min<int64_t>(seg, most_segments(n, 64, pl, mixed ? 8 : 16));
             s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, 1024));
         }
         // the cap wins over the 1024-segment limit (above 16.7 M beamlets)
@@ -514,15 +526,14 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
         }
     }
     if (s.nseg <= 0) {
-        // enough workgroups to keep every SIMD of every CU busy ~6 waves deep,
-        // while each segment keeps at least two LDS tiles of beamlets
+        // enough workgroups to keep every SIMD of every CU busy ~6 waves deep
         const int64_t tx = (pl.nx + 63) / 64;
         const int64_t ty = (pl.ny + s.waves * s.rows - 1) / (s.waves * s.rows);
         const int64_t tiles = std::max<int64_t>(1, tx * ty);
         const int64_t target_blocks = (int64_t)ctx->cus * 4 * 6 / s.waves;
         int64_t seg = (target_blocks + tiles - 1) / tiles;
         seg = std::max<int64_t>(1, seg * seg_pct / 100);
-        seg = std::min<int64_t>(seg, std::max<int64_t>(1, n / 256));
+        seg = std::min<int64_t>(seg, most_segments(n, 8, pl, 16));
         s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, 1024));
     }
     return s;
