@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgbd.so")
-SOURCES = ["gbd_api.hip", "gbd_kernels.hip", "gbd_sep.hip", "gbd_batch.hip", "gbd_mlp.hip", "gbd_point.hip",
+SOURCES = ["gbd_api.hip", "gbd_kernels.hip", "gbd_sep.hip", "gbd_batch.hip", "gbd_mlp.hip", "gbd_mlp_fused.hip", "gbd_point.hip",
            "gbd_trace.hip", "gbd_cut.hip", "gbd_rows.hip", "gbd_cross.hip", "gbd_sep64.hip", "gbd_probe.hip"]
 ARCH = os.environ.get("GBD_OFFLOAD_ARCH", "gfx950")
 

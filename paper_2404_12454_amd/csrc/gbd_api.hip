@@ -195,6 +195,7 @@ struct gbd_mlp_s {
     float *Z, *H;                     // [depth][max_batch][width]
     float *dz0, *dz1;                 // [max_batch][width]
     float *xb, *yb, *yhat, *g, *loss;
+    uint16_t *xt;                     // BF16 inputs, transposed (the two-kernel path)
     int64_t step;
 };
 
@@ -2110,26 +2111,30 @@ int gbd_mlp_create(gbd_ctx_t ctx, gbd_mlp_t *out, int32_t n_in, int32_t width, i
         prev = width;
     }
     m->P = k;
-    const int64_t act = (int64_t)depth * max_batch * width, bw = (int64_t)max_batch * width;
-    const int64_t total = 4 * m->P + 2 * act + 2 * bw + (int64_t)max_batch * (n_in + 3) + 1;
+    // activations in rows of a batch rounded up to 16, on 16-byte boundaries
+    // (the two-kernel path keeps BF16 transposes in H's place)
+    const int64_t mb = ((int64_t)max_batch + 15) / 16 * 16, P4 = (m->P + 3) / 4 * 4;
+    const int64_t act = (int64_t)depth * mb * width, bw = mb * width;
+    const int64_t total = 4 * P4 + 2 * act + 2 * bw + mb * (n_in + 3 + (n_in + 1) / 2) + 1;
     hipError_t e = hipMalloc(&m->mem, (size_t)total * sizeof(float));
     if (e != hipSuccess) {
         delete m;
         return hip_fail(e, "hipMalloc(mlp)");
     }
     float *q = m->mem;
-    m->params = q; q += m->P;
-    m->grads = q; q += m->P;
-    m->m = q; q += m->P;
-    m->v = q; q += m->P;
+    m->params = q; q += P4;
+    m->grads = q; q += P4;
+    m->m = q; q += P4;
+    m->v = q; q += P4;
     m->Z = q; q += act;
     m->H = q; q += act;
     m->dz0 = q; q += bw;
     m->dz1 = q; q += bw;
-    m->xb = q; q += (int64_t)max_batch * n_in;
-    m->yb = q; q += max_batch;
-    m->yhat = q; q += max_batch;
-    m->g = q; q += max_batch;
+    m->xb = q; q += mb * n_in;
+    m->yb = q; q += mb;
+    m->yhat = q; q += mb;
+    m->g = q; q += mb;
+    m->xt = reinterpret_cast<uint16_t *>(q); q += mb * ((n_in + 1) / 2);
     m->loss = q;
     e = hipMemsetAsync(m->mem, 0, (size_t)total * sizeof(float), ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -2159,7 +2164,8 @@ int gbd_mlp_set_params(gbd_mlp_t m, const float *params, int64_t n) {
     if (rc) return rc;
     hipStream_t st = m->ctx->stream;
     HIP_TRY(hipMemcpyAsync(m->params, params, n * sizeof(float), hipMemcpyHostToDevice, st), "parameter upload");
-    HIP_TRY(hipMemsetAsync(m->m, 0, 2 * n * sizeof(float), st), "optimiser reset");  // m and v are adjacent
+    HIP_TRY(hipMemsetAsync(m->m, 0, n * sizeof(float), st), "optimiser reset");
+    HIP_TRY(hipMemsetAsync(m->v, 0, n * sizeof(float), st), "optimiser reset");
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
     m->step = 0;
     return GBD_OK;
@@ -2208,6 +2214,42 @@ static int mlp_forward_impl(gbd_mlp_t m, int B) {
     return GBD_OK;
 }
 
+// The two-kernel path's view of a batch (mlp_fused)
+static MlpNet mlp_net(gbd_mlp_t m, const float *x, const float *target, const int32_t *rows, int B, float *yhat) {
+    MlpNet n{};
+    n.n_in = m->n_in;
+    n.W = m->width;
+    n.D = m->depth;
+    n.B = B;
+    n.bt = (B + 15) / 16 * 16;
+    n.params = m->params;
+    for (int l = 0; l <= m->depth; l++) {
+        n.woff[l] = m->woff[l];
+        n.boff[l] = m->boff[l];
+    }
+    n.x = x;
+    n.y = target;
+    n.rows = rows;
+    n.yhat = yhat;
+    n.dz = m->Z;
+    n.hlast = m->dz0;
+    n.g = m->g;
+    n.yb = m->yb;
+    n.dzt = reinterpret_cast<uint16_t *>(m->H);
+    n.ht = n.dzt + (int64_t)m->depth * m->width * n.bt;
+    n.xt = m->xt;
+    return n;
+}
+
+// Gradients of one batch (and, with adam.on, the step) by the two-kernel path
+static int mlp_fused_backward(gbd_mlp_t m, const float *x, const float *target, const int32_t *rows, int B,
+                              float *loss, float *loss_sum, const MlpAdam &adam) {
+    const MlpNet n = mlp_net(m, x, target, rows, B, m->yhat);
+    HIP_TRY(launch_mlp_rows(n, true, m->ctx->stream), "mlp rows launch");
+    HIP_TRY(launch_mlp_grads(n, m->grads, loss, loss_sum, adam, m->ctx->stream), "mlp gradient launch");
+    return GBD_OK;
+}
+
 int gbd_mlp_forward(gbd_mlp_t m, const float *x, const int32_t *rows, int32_t batch, float *y) {
     if (!m || !x || !y) return fail(GBD_EINVAL, "NULL argument");
     if (batch < 0 || batch > m->max_batch) return fail(GBD_ERANGE, "batch %d outside [0, %d]", batch, m->max_batch);
@@ -2215,6 +2257,10 @@ int gbd_mlp_forward(gbd_mlp_t m, const float *x, const int32_t *rows, int32_t ba
     int rc = ensure_device(m->ctx);
     if (rc) return rc;
     hipStream_t st = m->ctx->stream;
+    if (mlp_fused(m->mode == GBD_MLP_BF16, m->width, m->depth)) {
+        HIP_TRY(launch_mlp_rows(mlp_net(m, x, nullptr, rows, batch, y), false, st), "mlp rows launch");
+        return GBD_OK;
+    }
     HIP_TRY(launch_mlp_gather(x, nullptr, rows, batch, m->n_in, m->xb, nullptr, st), "mlp gather launch");
     rc = mlp_forward_impl(m, batch);
     if (rc) return rc;
@@ -2230,6 +2276,8 @@ int gbd_mlp_backward(gbd_mlp_t m, const float *x, const float *target, const int
     if (rc) return rc;
     hipStream_t st = m->ctx->stream;
     const int W = m->width, B = batch, D = m->depth;
+    if (mlp_fused(m->mode == GBD_MLP_BF16, W, D))
+        return mlp_fused_backward(m, x, target, rows, B, loss_dev ? loss_dev : m->loss, nullptr, MlpAdam{});
     HIP_TRY(launch_mlp_gather(x, target, rows, B, m->n_in, m->xb, m->yb, st), "mlp gather launch");
     rc = mlp_forward_impl(m, B);
     if (rc) return rc;
@@ -2309,7 +2357,19 @@ int gbd_mlp_train(gbd_mlp_t m, const float *x, const float *target, const int32_
     for (int32_t s = 0; s < steps; s++)
         if (!adamw_args_ok(lr_host[s], beta1, beta2, eps, weight_decay))
             return fail(GBD_EINVAL, "invalid AdamW hyper-parameters (step %d)", s);
-    for (int32_t s = 0; s < steps; s++) {
+    const bool fused = mlp_fused(m->mode == GBD_MLP_BF16, m->width, m->depth);
+    if (fused && steps > 0) {
+        const int rc = ensure_device(m->ctx);
+        if (rc) return rc;
+    }
+    for (int32_t s = 0; s < steps && fused; s++) {
+        m->step++;
+        const float c1 = 1.0f - powf(beta1, (float)m->step), c2 = 1.0f - powf(beta2, (float)m->step);
+        const MlpAdam adam{1, m->m, m->v, lr_host[s], beta1, beta2, eps, weight_decay, c1, c2};
+        const int rc = mlp_fused_backward(m, x, target, rows + (int64_t)s * batch, batch, m->loss, loss_sum_dev, adam);
+        if (rc) return rc;
+    }
+    for (int32_t s = 0; s < steps && !fused; s++) {
         int rc = gbd_mlp_backward(m, x, target, rows + (int64_t)s * batch, batch, nullptr);
         if (rc) return rc;
         if (loss_sum_dev) HIP_TRY(launch_mlp_accum(loss_sum_dev, m->loss, m->ctx->stream), "loss sum launch");

@@ -337,6 +337,40 @@ struct MlpGemm {
 };
 
 hipError_t launch_mlp_gemm(int bf16, const MlpGemm &g, hipStream_t s);
+
+// The whole network in BF16 mode by two kernels (gbd_mlp_fused.hip), for
+// widths 16 ... kMlpFusedWidth and depths up to kMlpFusedDepth: one for the
+// forward pass and the back-propagated activations of 16 rows a workgroup,
+// one for all gradients with, optionally, the AdamW step.  The products'
+// partial sums and every other sum run in the order of the kernel-per-
+// operation path, so both give the same bits.
+constexpr int kMlpFusedWidth = 256, kMlpFusedDepth = 4;
+inline bool mlp_fused(int bf16, int width, int depth) {
+    return bf16 && width >= 16 && width <= kMlpFusedWidth && depth <= kMlpFusedDepth;
+}
+struct MlpNet {
+    int n_in, W, D, B;
+    int bt;                                // rows of a transposed activation: B rounded up to 16
+    float *params;
+    int64_t woff[kMlpFusedDepth + 1], boff[kMlpFusedDepth + 1];
+    const float *x, *y;                    // inputs [*][n_in], targets [*]
+    const int32_t *rows;                   // row indices, or null
+    float *yhat;                           // [B]
+    // backward: FP32 dZ of every layer [D][B][W], its BF16 transpose [D][W][bt],
+    // H's [D - 1][W][bt], the inputs' [n_in][bt], the last H [B][W], g and
+    // the targets [B]
+    float *dz, *hlast, *g, *yb;
+    uint16_t *dzt, *ht, *xt;
+};
+struct MlpAdam {
+    int on;
+    float *m, *v;
+    float lr, b1, b2, eps, wd, c1, c2;
+};
+hipError_t launch_mlp_rows(const MlpNet &n, bool backward, hipStream_t s);
+// grads [params], loss: one float; loss_sum (or null) has the loss added
+hipError_t launch_mlp_grads(const MlpNet &n, float *grads, float *loss, float *loss_sum, const MlpAdam &adam,
+                            hipStream_t s);
 hipError_t launch_mlp_accum(float *acc, const float *v, hipStream_t s);
 hipError_t launch_mlp_gather(const float *X, const float *y, const int32_t *idx, int B, int n_in, float *Xb, float *yb,
                              hipStream_t s);

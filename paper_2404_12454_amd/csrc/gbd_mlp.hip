@@ -7,23 +7,13 @@
 // accumulate); the FP32 mode runs the same products with FP32 FMAs (used to
 // check gradients tightly).  The 1-wide head, the loss, the bias gradients and
 // the optimiser are FP32 elementwise / fixed-order reductions.
-#include "gbd_internal.h"
-
-#include <math.h>
+#include "gbd_mlp_core.h"
 
 namespace gbd {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-__device__ inline float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
-__device__ inline float silu(float z) { return z * sigmoid(z); }
-__device__ inline float dsilu(float z) {
-    const float s = sigmoid(z);
-    return s * (1.0f + z * (1.0f - s));
-}
+using namespace mlp;
 
 __device__ inline void epilogue(const MlpGemm &g, int m, int n, float acc) {
     const int64_t o = (int64_t)m * g.N + n;
@@ -134,38 +124,11 @@ __global__ void __launch_bounds__(256) loss_kernel(const float *__restrict__ yha
     if (threadIdx.x == 0 && loss) loss[0] = part[0] / (float)B;
 }
 
-// Column sums over a batch, in parallel and in a fixed order: a block of
-// 256 threads takes 32 columns, thread (c, r) sums rows r, r + 8, ... of
-// column c (coalesced across c), and the 8 partial sums of a column are
-// added in order r = 0 ... 7.  out[i] = sum_b wgt[b] X[b][i] for i < W (wgt
-// null: weight 1), and with bias_col also out[W] = sum_b wgt[b].
-constexpr int kSumCols = 32, kSumRows = 8;
-__device__ inline void column_sums(const float *__restrict__ X, const float *__restrict__ wgt, int B, int W,
-                                   bool bias_col, float *__restrict__ out) {
-    __shared__ float part[kSumRows][kSumCols];
-    const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols;
-    const int i = blockIdx.x * kSumCols + c;
-    float acc = 0.0f;
-    if (i < W) {
-        for (int b = r; b < B; b += kSumRows) acc = fmaf(wgt ? wgt[b] : 1.0f, X[(int64_t)b * W + i], acc);
-    } else if (bias_col && i == W) {
-        for (int b = r; b < B; b += kSumRows) acc += wgt ? wgt[b] : 1.0f;
-    }
-    part[r][c] = acc;
-    __syncthreads();
-    if (r == 0 && (i < W || (bias_col && i == W))) {
-        float s = part[0][c];
-#pragma unroll
-        for (int k = 1; k < kSumRows; k++) s += part[k][c];
-        out[i] = s;
-    }
-}
-
 // head gradients: dw[i] = sum_b g[b] H[b][i] (i < W), dw0 = sum_b g[b] (i == W)
 __global__ void __launch_bounds__(kSumCols * kSumRows) head_grad_kernel(const float *__restrict__ g,
                                                                         const float *__restrict__ H, int B, int W,
                                                                         float *__restrict__ dw) {
-    column_sums(H, g, B, W, true, dw);
+    column_sums(H, g, B, W, true, (int)blockIdx.x, [&](int i, float s) { dw[i] = s; });
 }
 
 // dZ[b][i] = g[b] w[i] SiLU'(Z[b][i]) for the last hidden layer
@@ -181,7 +144,7 @@ __global__ void __launch_bounds__(256) head_back_kernel(const float *__restrict_
 // db[o] = sum_b dZ[b][o]
 __global__ void __launch_bounds__(kSumCols * kSumRows) colsum_kernel(const float *__restrict__ dZ, int B, int W,
                                                                      float *__restrict__ db) {
-    column_sums(dZ, nullptr, B, W, false, db);
+    column_sums(dZ, nullptr, B, W, false, (int)blockIdx.x, [&](int i, float s) { db[i] = s; });
 }
 
 __global__ void __launch_bounds__(256) adamw_kernel(float *__restrict__ p, const float *__restrict__ g,
@@ -189,13 +152,7 @@ __global__ void __launch_bounds__(256) adamw_kernel(float *__restrict__ p, const
                                                     float b1, float b2, float eps, float wd, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float mh = mi / c1, vh = vi / c2;
-    p[i] = p[i] - lr * (mh / (sqrtf(vh) + eps) + wd * p[i]);
+    adamw_step(p[i], g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
 }
 
 // acc[0] += v[0] (one running loss sum in step order)

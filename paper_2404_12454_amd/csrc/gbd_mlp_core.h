@@ -1,0 +1,61 @@
+// Device functions shared by the surrogate network's kernels.
+#pragma once
+
+#include "gbd_internal.h"
+
+#include <math.h>
+
+namespace gbd {
+namespace mlp {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ inline float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
+__device__ inline float silu(float z) { return z * sigmoid(z); }
+__device__ inline float dsilu(float z) {
+    const float s = sigmoid(z);
+    return s * (1.0f + z * (1.0f - s));
+}
+
+__device__ inline void adamw_step(float &p, float g, float &m, float &v, float lr, float b1, float b2, float eps, float wd,
+                                  float c1, float c2) {
+    const float mi = b1 * m + (1.0f - b1) * g;
+    const float vi = b2 * v + (1.0f - b2) * g * g;
+    m = mi;
+    v = vi;
+    const float mh = mi / c1, vh = vi / c2;
+    p = p - lr * (mh / (sqrtf(vh) + eps) + wd * p);
+}
+
+// Column sums over a batch, in parallel and in a fixed order: a block of
+// 256 threads takes 32 columns, thread (c, r) sums rows r, r + 8, ... of
+// column c (coalesced across c), and the 8 partial sums of a column are
+// added in order r = 0 ... 7.  out(i, sum_b wgt[b] X[b][i]) for i < W (wgt
+// null: weight 1), and with bias_col also out(W, sum_b wgt[b]).
+constexpr int kSumCols = 32, kSumRows = 8;
+template <class F>
+__device__ inline void column_sums(const float *__restrict__ X, const float *__restrict__ wgt, int B, int W,
+                                   bool bias_col, int block, F out) {
+    __shared__ float part[kSumRows][kSumCols];
+    const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols;
+    const int i = block * kSumCols + c;
+    float acc = 0.0f;
+    if (i < W) {
+#pragma unroll 16
+        for (int b = r; b < B; b += kSumRows) acc = fmaf(wgt ? wgt[b] : 1.0f, X[(int64_t)b * W + i], acc);
+    } else if (bias_col && i == W) {
+        for (int b = r; b < B; b += kSumRows) acc += wgt ? wgt[b] : 1.0f;
+    }
+    part[r][c] = acc;
+    __syncthreads();
+    if (r == 0 && (i < W || (bias_col && i == W))) {
+        float s = part[0][c];
+#pragma unroll
+        for (int k = 1; k < kSumRows; k++) s += part[k][c];
+        out(i, s);
+    }
+}
+
+}  // namespace mlp
+}  // namespace gbd
