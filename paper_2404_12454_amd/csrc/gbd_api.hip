@@ -443,8 +443,10 @@ int64_t most_segments(int64_t n, int64_t shortest, const PlaneGeom &pl, int64_t 
 
 // Launch shape and mixed form.  32 rows per lane is a rotor-form shape: where
 // the form resolves to direct or stepped it runs 16.
+// general: the forms that hold for any records with these form flags only (no
+// cross form).
 Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGeom &pl, uint32_t flags,
-                   const gbd_eval_opts *o) {
+                   const gbd_eval_opts *o, bool general = false) {
     Shape s;
     s.form = pick_form(precision, flags, o);
     // the mixed separable form runs on FP16 MFMA in hi/lo halves unless the
@@ -489,7 +491,7 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
         return s;
     }
     // rotor form: 32 rows per lane where the grid fills a 4-wave tile
-    const bool cross = cross_applies(precision, s.form, flags, n, (int64_t)pl.nx * pl.ny);
+    const bool cross = !general && cross_applies(precision, s.form, flags, n, (int64_t)pl.nx * pl.ny);
     s.rows = (s.form == 2 && (pl.ny >= 128 || cross)) ? 32 : (precision != GBD_MIXED && s.form == 0) ? 4 : 16;
     s.waves = 4;
     s.nseg = 0;
@@ -626,6 +628,25 @@ EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, const PlaneGeom &pl, int6
     return make_geom(pl, n_cut, s);
 }
 
+// Whether launches on the context's stream are being captured into a graph.
+bool captures(const gbd_ctx_s *ctx) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();  // the null stream, while another one is captured
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Bytes of partial sums of an evaluation in the general forms.
+size_t general_scratch(const gbd_ctx_s *ctx, const gbd_plan_s *plan, int precision, const gbd_eval_opts *opts) {
+    const int64_t n = plan->n - plan->n_cut;
+    const Shape s = choose_shape(ctx, precision, n, plan->pl, plan->flags, opts, true);
+    const int64_t seg = (n > 0 ? make_geom(plan->pl, n, s).nseg : 0) +
+                        (plan->n_cut > 0 ? cut_geom(ctx, precision, plan->pl, plan->n_cut).nseg : 0);
+    return (size_t)seg * (size_t)plan->pl.nx * (size_t)plan->pl.ny * 16;
+}
+
 // fixed: a caller-provided partial-sum buffer of fixed_bytes (the static
 // buffer of gbd_plan_eval_noalloc), used instead of the plan's grow-only one;
 // then nothing is allocated and an automatic segment count is lowered to fit.
@@ -655,7 +676,11 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     if (opts && opts->rows_per_lane && !sep_form &&
         !valid_shape(opts->rows_per_lane, opts->waves ? opts->waves : 4, precision))
         return fail(GBD_EINVAL, "unsupported rows_per_lane %d / waves %d", opts->rows_per_lane, opts->waves);
-    Shape s = choose_shape(ctx, precision, plan->n - plan->n_cut, plan->pl, plan->flags, opts);
+    // A captured evaluation is replayed over whatever records later setups
+    // leave in the plan: it takes the general forms, not those that rest on
+    // this setup's row chunks or small cross terms.
+    const bool general = !guard && captures(ctx);
+    Shape s = choose_shape(ctx, precision, plan->n - plan->n_cut, plan->pl, plan->flags, opts, general);
     if (s.form != 3 && !valid_shape(s.rows, s.waves, precision))
         return fail(GBD_EINVAL, "unsupported rows_per_lane %d / waves %d", s.rows, s.waves);
     int rc = ensure_device(ctx);
@@ -685,7 +710,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     // Gauss's form is not asked for: one segment, written by the product (with
     // truncated beamlets into the first partial).  Segment counts do not apply.
     // The fixed buffer has to hold the row sums beside any partials.
-    bool by_rows = s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
+    bool by_rows = !general && s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
                    (precision == GBD_FP64 || s.half);
     const size_t row_bytes = by_rows ? (size_t)plan->rows * (size_t)plan->pl.nx * (size_t)elem : 0;
     auto row_offset = [&](int64_t nc) -> size_t {  // where the row sums start, with nc truncated segments
@@ -778,8 +803,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     const int32_t nseg2 = compact ? nseg_main : 0;
     void *partial = fixed ? fixed : plan->scratch;
     if ((reduce || by_rows) && !fixed) {
-        const size_t need = by_rows ? row_offset(nseg_cut) + row_bytes
-                                    : (size_t)total * (size_t)M * 16;  // bounds the compact layout too
+        size_t need = by_rows ? row_offset(nseg_cut) + row_bytes
+                              : (size_t)total * (size_t)M * 16;  // bounds the compact layout too
+        // a caller's plan has its evaluation captured after a first one that
+        // allocates: enough for the general forms too
+        if ((by_rows || s.cross) && plan != ctx->own_plan)
+            need = std::max(need, general_scratch(ctx, plan, precision, opts));
         if (need > plan->scratch_bytes) {
             if (plan->scratch) (void)hipFree(plan->scratch);
             plan->scratch = nullptr;
@@ -852,8 +881,8 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                     "eval kernel launch");
         else if (s.form == 3 && s.half)
             HIP_TRY(launch_eval_seph(gl, plan->r32, static_cast<const RecHG32 *>(hrec), plan->sep_scale,
-                                     static_cast<float2 *>(partial), static_cast<float2 *>(out), ctx->stream,
-                                     tev.first, tev.second, sp),
+                                     general ? plan->status_dev : nullptr, static_cast<float2 *>(partial),
+                                     static_cast<float2 *>(out), ctx->stream, tev.first, tev.second, sp),
                     "eval kernel launch");
         else if (s.form == 3)
             HIP_TRY(launch_eval_sep(gl, plan->r32, static_cast<const RecHG32 *>(hrec),
@@ -983,7 +1012,7 @@ int plan_setup_finish(gbd_ctx_s *ctx, gbd_plan_s *plan) {
         // FP16 separable form: largest term 2^P over the grid -> scale 2^(2 kSepHalfExp - P)
         const uint32_t key = ((uint32_t)w >> 12) & 0xfffu;
         plan->sep_key = key;
-        plan->sep_scale = key ? 2 * kSepHalfExp - ((int)key - 2048) : 0;
+        plan->sep_scale = seph_scale(key);
         if (st & FLAG_PARALLEL) return fail(GBD_EPARALLEL, "a base ray is parallel to the detector plane");
         if (st & FLAG_BRANCH)
             return fail(GBD_EBRANCH, "an eigenvalue of A + B Q1^-1 lies off the principal branch (inverting system)");

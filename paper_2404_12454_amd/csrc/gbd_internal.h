@@ -571,8 +571,11 @@ hipError_t launch_rows64(const RowGeom &g, const int32_t *start, const Rec64 *re
 // 2^scale (scale = 2 kSepHalfExp - P, 2^P the largest term over the grid,
 // from the setup); partials and output are written descaled.
 constexpr int kSepHalfExp = 14;
-hipError_t launch_eval_seph(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, int scale, float2 *partial,
-                            float2 *out, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
+__host__ __device__ inline int seph_scale(uint32_t key) { return key ? 2 * kSepHalfExp - ((int)key - 2048) : 0; }
+// pairs (null: scale is the host's): a captured launch's, the plan's two
+// status pairs, one the last setup's and the other cleared by it.
+hipError_t launch_eval_seph(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, int scale, const uint32_t *pairs,
+                            float2 *partial, float2 *out, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
                             const StatusPost &sp = StatusPost());
 
 }  // namespace gbd

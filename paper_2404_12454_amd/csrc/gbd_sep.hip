@@ -90,6 +90,7 @@ __global__ void __launch_bounds__(64 * k3WX * k3WY) eval_sep_kernel(EvalGeom g, 
 template <class T, bool HG>
 __global__ void __launch_bounds__(64 * T::WX * T::WY) eval_seph_kernel(EvalGeom g, const Rec32 *__restrict__ rec,
                                                                         const RecHG32 *__restrict__ hg, int scale,
+                                                                        const uint32_t *__restrict__ pairs,
                                                                         float2 *__restrict__ partial,
                                                                         float2 *__restrict__ out, StatusPost sp) {
     __shared__ SepHLdsT<T> L;
@@ -107,6 +108,7 @@ __global__ void __launch_bounds__(64 * T::WX * T::WY) eval_seph_kernel(EvalGeom 
     const SepGeom sg{g.nx, g.ny, g.a0, g.b0, g.dx, g.dy};
     const int64_t jb = (int64_t)seg * g.seg_len;
     const int64_t je = min(g.n, jb + g.seg_len);
+    if (pairs) scale = seph_scale(pairs[1] | pairs[3]);
     f4 accR[T::BY][T::BX], accI[T::BY][T::BX];
     sep_accumulate_h<T, HG>(sg, rec, hg, jb, je, tx, ty, scale, L, accR, accI);
 
@@ -133,15 +135,15 @@ __global__ void __launch_bounds__(64 * T::WX * T::WY) eval_seph_kernel(EvalGeom 
 
 }  // namespace
 
-hipError_t launch_eval_seph(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, int scale, float2 *partial,
-                            float2 *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp) {
+hipError_t launch_eval_seph(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, int scale, const uint32_t *pairs,
+                            float2 *partial, float2 *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp) {
     using T = HTileLarge;
     static_assert(T::WX == kSepHWavesX && T::WY == kSepHWavesY && 16 * T::BX == kSepHTile && 16 * T::BY == kSepHTile,
                   "FP16 halves tiles: host and kernel disagree");
     const dim3 grid((g.work + 7) / 8 * 8), block(64 * T::WX * T::WY);
     if (hg)
-        return launch_timed(eval_seph_kernel<T, true>, grid, block, s, t0, t1, g, rec, hg, scale, partial, out, sp);
-    return launch_timed(eval_seph_kernel<T, false>, grid, block, s, t0, t1, g, rec, hg, scale, partial, out, sp);
+        return launch_timed(eval_seph_kernel<T, true>, grid, block, s, t0, t1, g, rec, hg, scale, pairs, partial, out, sp);
+    return launch_timed(eval_seph_kernel<T, false>, grid, block, s, t0, t1, g, rec, hg, scale, pairs, partial, out, sp);
 }
 
 hipError_t launch_eval_sep(const EvalGeom &g, const Rec32 *rec, const RecHG32 *hg, float2 *partial, float2 *out,

@@ -1,0 +1,86 @@
+"""Captured plan evaluations replayed over the plan's later setups.
+
+A graph of a plan evaluation reads the plan's records at each replay, so a
+setup between replays changes its field.  The second setup's beamlets keep the
+count and the form but not what a specialised form would rest on: rows of
+equal y factors, or weak cross terms.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2404_12454_amd as gbd
+from paper_2404_12454_amd import scenes
+from gbd_testutil import ensure_library, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+TOL = {gbd.GBD_FP64: 1e-12, gbd.GBD_MIXED: 1e-5}
+
+
+def scattered():
+    """airy_scene's beamlets with their rows broken up."""
+    sc = scenes.airy_scene(24, npix=96, npix_y=80)
+    sc.r1 = sc.r1 + np.random.default_rng(2).uniform(-1, 1, sc.r1.shape) * 1e-5
+    return sc
+
+
+def weak():
+    return scenes.zernike_scene(7, n_across=70, npix=130, half_span=30e-6)
+
+
+def strong():
+    """The same behind a crossed pair of cylinders: cross terms beyond the series."""
+    sc = weak()
+    lens = np.eye(4)
+    lens[2, 1] = lens[3, 0] = 5.0
+    sc.abcd = np.ascontiguousarray((sc.abcd.reshape(-1, 4, 4) @ lens).reshape(-1, 16))
+    return sc
+
+
+def rim():
+    return scenes.truncated_airy_scene(40, npix=96, half_span_lamF=3.0)
+
+
+def wide_rim():
+    """Wider waists: the edge terms vary 12 times as fast over the plane."""
+    sc = rim()
+    sc.w0 = 12.0 * sc.w0
+    return sc
+
+
+PAIRS = {
+    "rows": (lambda: scenes.airy_scene(24, npix=96, npix_y=80), scattered),
+    "cross": (weak, strong),
+    "truncated": (rim, wide_rim),
+}
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("precision", [gbd.GBD_FP64, gbd.GBD_MIXED])
+@pytest.mark.parametrize("kind", list(PAIRS))
+def test_replay_follows_the_plans_setup(kind, precision, noalloc):
+    import torch
+    ensure_library()
+    first, second = (f() for f in PAIRS[kind])
+    assert first.n == second.n
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = gbd.Context(0, stream)
+        handles = [(gbd.beamlets_from_scene(ctx, s), gbd.plane_from_scene(ctx, s)) for s in (first, second)]
+        plan = gbd.Plan(ctx, first.n).setup(*handles[0])
+        call = plan.eval_noalloc if noalloc else plan.eval
+        out = call(precision)  # allocates
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            call(precision, out=out)
+        refs = [oracle.eval_field(s) for s in (first, second)]
+        for i in (0, 1, 0, 1):
+            plan.setup(*handles[i])
+            out.zero_()
+            graph.replay()
+            stream.synchronize()
+            err = rel_l2(out.cpu().numpy().astype(np.complex128), refs[i])
+            print(f"{kind} precision {precision} noalloc {noalloc} setup {i}: rel_l2 {err:.2e}", flush=True)
+            assert err < TOL[precision]
