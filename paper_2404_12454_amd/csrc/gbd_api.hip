@@ -183,7 +183,8 @@ struct gbd_plan_s {
 constexpr int kNoSpeculation = 1;
 
 // the setup flags that select how an evaluation runs
-constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS | FLAG_CROSS1 | FLAG_CROSS2;
+constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS | FLAG_CROSS1 | FLAG_CROSS2 |
+                               FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
 
 struct gbd_mlp_s {
     gbd_ctx_s *ctx;
@@ -610,20 +611,31 @@ const FaddeevaCoef &faddeeva_coef() {
     return fc;
 }
 
+constexpr int kCutWaves = 2;  // workgroups a CU holds of the column form (240 registers a lane): one round of them
+
+// The truncated-beamlet kernel's column form (launch_eval_cut's level) where
+// its polynomials reach; pixel by pixel where the direct form is asked for.
+int cut_level(uint32_t flags, const gbd_eval_opts *o) {
+    if (o && o->variant == 1) return 0;
+    return !(flags & FLAG_CUT1) ? 3 : !(flags & FLAG_CUT2) ? 2 : !(flags & FLAG_CUT3) ? 1 : 0;
+}
+
 // Launch geometry of the truncated-beamlet kernel: 64-column tiles of
-// 4 wavefronts x kCutRows rows, segments for ~6 wavefronts per SIMD, each
-// segment at least 32 beamlets.
-EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, const PlaneGeom &pl, int64_t n_cut, int64_t max_seg = 1024) {
+// 4 wavefronts x the level's rows, segments for 2 wavefronts per SIMD (pixel
+// by pixel ~6), each of at least 8 beamlets while the partials are small
+// (most_segments), else 32.
+EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, int level, const PlaneGeom &pl, int64_t n_cut,
+                  int64_t max_seg = 1024) {
     Shape s;
     s.form = 0;
     s.half = false;
     s.waves = 4;
-    s.rows = precision == GBD_MIXED ? kCutRows32 : kCutRows64;
+    s.rows = level > 1 ? kCutRows : level == 1 ? kCutRows / 2 : precision == GBD_MIXED ? kCutRows32 : kCutRows64;
     const int64_t tx = (pl.nx + 63) / 64;
     const int64_t ty = (pl.ny + s.waves * s.rows - 1) / (s.waves * s.rows);
     const int64_t tiles = std::max<int64_t>(1, tx * ty);
-    int64_t seg = ((int64_t)ctx->cus * 6 + tiles - 1) / tiles;
-    seg = std::min<int64_t>(seg, std::max<int64_t>(1, n_cut / 32));
+    int64_t seg = ((int64_t)ctx->cus * (level ? kCutWaves : 6) + tiles - 1) / tiles;
+    seg = std::min<int64_t>(seg, std::max<int64_t>(n_cut / 32, most_segments(n_cut, 8, pl, 16)));
     s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, max_seg));
     return make_geom(pl, n_cut, s);
 }
@@ -643,7 +655,7 @@ size_t general_scratch(const gbd_ctx_s *ctx, const gbd_plan_s *plan, int precisi
     const int64_t n = plan->n - plan->n_cut;
     const Shape s = choose_shape(ctx, precision, n, plan->pl, plan->flags, opts, true);
     const int64_t seg = (n > 0 ? make_geom(plan->pl, n, s).nseg : 0) +
-                        (plan->n_cut > 0 ? cut_geom(ctx, precision, plan->pl, plan->n_cut).nseg : 0);
+                        (plan->n_cut > 0 ? cut_geom(ctx, precision, 0, plan->pl, plan->n_cut).nseg : 0);
     return (size_t)seg * (size_t)plan->pl.nx * (size_t)plan->pl.ny * 16;
 }
 
@@ -678,7 +690,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         return fail(GBD_EINVAL, "unsupported rows_per_lane %d / waves %d", opts->rows_per_lane, opts->waves);
     // A captured evaluation is replayed over whatever records later setups
     // leave in the plan: it takes the general forms, not those that rest on
-    // this setup's row chunks or small cross terms.
+    // this setup's row chunks, small cross terms or slow edge terms.
     const bool general = !guard && captures(ctx);
     Shape s = choose_shape(ctx, precision, plan->n - plan->n_cut, plan->pl, plan->flags, opts, general);
     if (s.form != 3 && !valid_shape(s.rows, s.waves, precision))
@@ -701,8 +713,9 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     bool compact = n_main > 0 && (s.form == 3 || s.cross) && precision == GBD_MIXED;
     EvalGeom g{}, gc{};
     int32_t nseg_main = 0, nseg_cut = 0;
+    const int level = general ? 0 : cut_level(plan->flags, opts);
     if (plan->n_cut > 0) {
-        gc = cut_geom(ctx, precision, plan->pl, plan->n_cut);
+        gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut);
         nseg_cut = gc.nseg;
     }
     // The separable form by rows wherever the beamlets come in row chunks
@@ -719,12 +732,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     };
     if (fixed && by_rows) {
         while (nseg_cut > 1 && row_offset(nseg_cut) + row_bytes > fixed_bytes) {
-            gc = cut_geom(ctx, precision, plan->pl, plan->n_cut, nseg_cut - 1);
+            gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut, nseg_cut - 1);
             nseg_cut = gc.nseg;
         }
         by_rows = row_offset(nseg_cut) + row_bytes <= fixed_bytes;
         if (!by_rows && plan->n_cut > 0) {
-            gc = cut_geom(ctx, precision, plan->pl, plan->n_cut);
+            gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut);
             nseg_cut = gc.nseg;
         }
     }
@@ -754,7 +767,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                     return fail(GBD_ERANGE, "%lld pixels: one segment of partial sums (%zu bytes) exceeds half the "
                                 "static buffer (%zu bytes)", (long long)M, per_cut, fixed_bytes);
                 if (nseg_cut > max_cut) {
-                    gc = cut_geom(ctx, precision, plan->pl, plan->n_cut, max_cut);
+                    gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut, max_cut);
                     nseg_cut = gc.nseg;
                 }
             }
@@ -807,7 +820,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                               : (size_t)total * (size_t)M * 16;  // bounds the compact layout too
         // a caller's plan has its evaluation captured after a first one that
         // allocates: enough for the general forms too
-        if ((by_rows || s.cross) && plan != ctx->own_plan)
+        if ((by_rows || s.cross || (nseg_cut > 0 && level)) && plan != ctx->own_plan)
             need = std::max(need, general_scratch(ctx, plan, precision, opts));
         if (need > plan->scratch_bytes) {
             if (plan->scratch) (void)hipFree(plan->scratch);
@@ -900,7 +913,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         const void *rec = precision == GBD_FP64 ? (const void *)(plan->r64 + n_main) : (const void *)(plan->r32 + n_main);
         const void *crec = precision == GBD_FP64 ? (const void *)plan->c64 : (const void *)plan->c32;
         void *wide = static_cast<char *>(partial) + reduce_wide_offset(nseg2, M);
-        HIP_TRY(launch_eval_cut(precision, gc, rec, crec, faddeeva_coef(), nseg_main - nseg2, wide, ctx->stream),
+        HIP_TRY(launch_eval_cut(precision, level, gc, rec, crec, faddeeva_coef(), nseg_main - nseg2, wide, ctx->stream),
                 "truncated-beamlet kernel launch");
     }
     if (reduce) {
@@ -1008,9 +1021,9 @@ int plan_setup_finish(gbd_ctx_s *ctx, gbd_plan_s *plan) {
             }
             if (dt > std::chrono::microseconds(200)) std::this_thread::yield();
         }
-        const uint32_t st = (uint32_t)w & 0xfffu;
+        const uint32_t st = (uint32_t)w & 0xffffu;
         // FP16 separable form: largest term 2^P over the grid -> scale 2^(2 kSepHalfExp - P)
-        const uint32_t key = ((uint32_t)w >> 12) & 0xfffu;
+        const uint32_t key = ((uint32_t)w >> 16) & 0xfffu;
         plan->sep_key = key;
         plan->sep_scale = seph_scale(key);
         if (st & FLAG_PARALLEL) return fail(GBD_EPARALLEL, "a base ray is parallel to the detector plane");

@@ -399,6 +399,19 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
             oc.zb[1] = zb.im;
             for (int i = 0; i < 6; i++) fin = fin && isfinite((&oc.z0[0])[i]);
             if (ez[0] != 0.0 || ez[1] != 0.0) flag |= FLAG_HG_TILT;
+            // the column form: the reach of its Taylor polynomials
+            double zmax = 0.0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const double da = 0.5 * (i & 1 ? 1 - pl.nx : pl.nx - 1) * pl.dx - arho;
+                const double db = 0.5 * (i & 2 ? 1 - pl.ny : pl.ny - 1) * pl.dy - brho;
+                zmax = fmax(zmax, hypot(z0.re + za.re * da + zb.re * db, z0.im + za.im * da + zb.im * db));
+            }
+            const double step = hypot(zb.re, zb.im) * pl.dy * (2.0 * zmax + sqrt(32.0));
+            const bool slow = fabs(l[5]) * il2_dev() * pl.dy * pl.dy <= kStepCurvature;
+            if (!(slow && kCutRows / 2 * step <= kCutReachLow)) flag |= FLAG_CUT1;
+            if (!(slow && kCutRows / 2 * step <= kCutReachHigh)) flag |= FLAG_CUT2;
+            if (!(slow && kCutRows / 4 * step <= kCutReachHigh)) flag |= FLAG_CUT3;
         }
         if (!fin) flag |= FLAG_NONFINITE;
         if (!is_cut && fabs(l[5]) * il2_dev() * pl.dy * pl.dy > kStepCurvature) flag |= FLAG_STEEP;

@@ -134,6 +134,7 @@ static_assert(sizeof(RecCut32) == 32, "RecCut32 layout");
 // the mixed form (4e-7 in exact arithmetic, 5e-7 with FP32 rounding).
 constexpr int kFaddeevaN64 = 40, kFaddeevaN32 = 16;
 constexpr int kCutRows32 = 2, kCutRows64 = 4;  // rows per lane of the truncated-beamlet kernels (4 wavefronts)
+constexpr int kCutRows = 16;  // of their column form (half as many at its lowest level)
 struct FaddeevaCoef {
     double L64, a64[kFaddeevaN64];
     float L32, a32[kFaddeevaN32];
@@ -165,7 +166,18 @@ enum : uint32_t {
     // the grid exceeds a factor 2
     FLAG_CROSS1 = 256u,
     FLAG_CROSS2 = 512u,
+    // not an error: some truncated beamlet's erfc argument varies too fast
+    // along a column for the column form's low degree; for its high degree;
+    // for that on half the rows, or the amplitude does
+    FLAG_CUT1 = 1024u,
+    FLAG_CUT2 = 2048u,
+    FLAG_CUT3 = 4096u,
 };
+// largest t = |k zb dy| (2 |zeta| + sqrt(2 p)) over the rows k of a column
+// of the truncated beamlets' column form (gbd_cut.hip): (e t / p)^p is 2^-26
+// at t = 0.115 for p = 6 and 2^-50 for p = 10, 2^-25 at t = 0.67 for p = 10
+// and 2^-50 for p = 16
+constexpr double kCutReachLow = 0.115, kCutReachHigh = 0.67;
 constexpr int kCrossTile = 128;  // the cross form's workgroup tile in pixels
 constexpr double kCrossLimit1 = 1.0 / 1024.0, kCrossLimit2 = 1.0 / 64.0;
 
@@ -388,7 +400,7 @@ hipError_t launch_mlp_adamw(float *p, const float *g, float *m, float *v, int64_
 // status_next: the next setup's two words, set to zero (the host alternates
 // the pairs, so no separate clear is needed).
 // A finished setup's status[0] (flags, < 4096) and status[1] (key, < 4096)
-// posted to the host: (seq << 32) | flags | key << 12 in one system-scope
+// posted to the host: (seq << 32) | flags | key << 16 in one system-scope
 // store into *post (coherent host memory), which the host polls for seq (an
 // event after a copy would end with a system-scope release that stalls the
 // stream for the cache writeback).  Any kernel that runs after the setup in
@@ -402,7 +414,7 @@ struct StatusPost {
 };
 __device__ inline void post_status(const StatusPost &sp) {
     const uint32_t f = sp.status[0], k = sp.status[1];
-    const uint64_t w = ((uint64_t)sp.seq << 32) | (uint64_t)(f & 0xfffu) | ((uint64_t)(k & 0xfffu) << 12);
+    const uint64_t w = ((uint64_t)sp.seq << 32) | (uint64_t)(f & 0xffffu) | ((uint64_t)(k & 0xfffu) << 16);
     __hip_atomic_store(sp.post, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 hipError_t launch_status_post(const StatusPost &sp, hipStream_t s);
@@ -422,8 +434,9 @@ hipError_t launch_sigma(const EvalGeom &g, const Rec64 *r64, RecSq64 *q64, Rec32
 // Truncated beamlets (direct form with the complex error function): the n
 // beamlets of g (records rec / cut, both starting at the first truncated
 // beamlet) summed per segment into partial segments seg_base + s; precision
-// 0 FP64 (double2 partials), 1 mixed (float4 (sum, compensation)).
-hipError_t launch_eval_cut(int precision, const EvalGeom &g, const void *rec, const void *cut,
+// 0 FP64 (double2 partials), 1 mixed (float4 (sum, compensation)); level 3,
+// 2, 1: the column form (no FLAG_CUT1; no FLAG_CUT2; no FLAG_CUT3), 0: pixel by pixel.
+hipError_t launch_eval_cut(int precision, int level, const EvalGeom &g, const void *rec, const void *cut,
                            const FaddeevaCoef &fc, int32_t seg_base, void *partial, hipStream_t s);
 
 // Mixed precision only, form = 0 direct: per-pixel FP64 phase and exp2;
