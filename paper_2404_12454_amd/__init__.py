@@ -456,11 +456,15 @@ def gbd_eval_batch(ctx: Context, beamlets, planes, airy=None, zone_edges=None, f
         None if o is None else ctypes.byref(o)))
     out_fields = None
     if fbuf is not None:
-        out_fields, off = [], 0
-        for p in planes:
-            m = p.nx * p.ny
-            out_fields.append(fbuf[off:off + m].view(p.ny, p.nx))
-            off += m
+        nx, ny = (planes[0].nx, planes[0].ny) if n else (0, 0)
+        if n and nx * ny > 0 and all(p.nx == nx and p.ny == ny for p in planes):
+            out_fields = list(fbuf.view(n, ny, nx).unbind(0))
+        else:
+            out_fields, off = [], 0
+            for p in planes:
+                m = p.nx * p.ny
+                out_fields.append(fbuf[off:off + m].view(p.ny, p.nx))
+                off += m
     return metrics, out_fields
 
 
