@@ -197,25 +197,28 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
         h8 a[NV], w[NV], a2, w2;
 #pragma unroll
         for (int k = 0; k < 4; k++) {
+            // operands first: a load cannot pass the factors' stores to LDS
+            static_assert(kBX % 2 == 0, "two blocks of one row at a time");
+            if (2 * k % kBX == 0) {
+                const int p = 2 * k / kBX;
+#pragma unroll
+                for (int t = 0; t < NV; t++) a[t] = operand(&lv[buf][wy][p][t][li][rd]);
+                if constexpr (LEVEL == 1) {
+                    w[0] = a[2];
+                    w[1] = a[3];
+                    a2 = pk_scale(a[0], vr_[p]);
+                    w2 = pk_scale(w[0], vr_[p]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < NV; t++) w[t] = rot8(a[t]);
+                    a2 = pk_scale(a[2], vr_[p]);
+                    w2 = pk_scale(w[2], vr_[p]);
+                }
+            }
             publish(buf ^ 1, buf ^ 1, k);
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 const int m = 2 * k + i, p = m / kBX, q = m % kBX;
-                if (q == 0) {
-#pragma unroll
-                    for (int t = 0; t < NV; t++) a[t] = operand(&lv[buf][wy][p][t][li][rd]);
-                    if constexpr (LEVEL == 1) {
-                        w[0] = a[2];
-                        w[1] = a[3];
-                        a2 = pk_scale(a[0], vr_[p]);
-                        w2 = pk_scale(w[0], vr_[p]);
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < NV; t++) w[t] = rot8(a[t]);
-                        a2 = pk_scale(a[2], vr_[p]);
-                        w2 = pk_scale(w[2], vr_[p]);
-                    }
-                }
                 auto mac = [&](const h8 &x, const h8 &y, f4 &c) {
                     c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, y, c, 0, 0, 0);
                 };
@@ -239,6 +242,17 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
                     mac(a2, b[q][4], R);
                     mac(w2, b[q][4], I);
                 }
+            }
+            if constexpr (LEVEL == 1) {
+                // four VALU instructions behind each MFMA, section by section:
+                // left to itself the scheduler forms half of the factors
+                // before any product (LEVEL 2 has no registers left for it)
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         rs[buf][sr][sc] = wnext;
