@@ -40,7 +40,7 @@ struct DevBuf {
 };
 
 struct BatchWork {
-    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, row_v;
+    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, row_v, terms;
     uint32_t *host_flags = nullptr;  // pinned: the point evaluation's status
     void *stage = nullptr;           // pinned staging of the batch tables
     size_t stage_bytes = 0;
@@ -140,6 +140,8 @@ struct gbd_beamlets_s {
     size_t mem_class;               // mem's size class in pool
     std::shared_ptr<DevPool> pool;  // where mem returns (kept alive past the context)
     bool higher_order;  // some beamlet has a nonzero Hermite-Gaussian order
+    bool one_matrix;    // one matrix and one waist for all: abcd0, w00
+    double abcd0[16], w00;
 };
 
 struct gbd_plane_s {
@@ -945,6 +947,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     return GBD_OK;
 }
 
+// Whether the beamlets meet the plane at one distance with one curvature: the
+// setup then takes these from the host (gbd_terms.h).
+bool shares_terms(const gbd_beamlets_s *b, const gbd_plane_s *p) {
+    return b->one_matrix && p->g.n[0] == 0.0 && p->g.n[1] == 0.0;
+}
+
 // The post of the last launched setup's status.
 StatusPost pending_post(const gbd_plan_s *plan) {
     StatusPost sp;
@@ -1004,7 +1012,11 @@ int plan_setup_launch(gbd_ctx_s *ctx, gbd_plan_s *plan, gbd_beamlets_s *b, gbd_p
         const bool cut = b->dev.n_cut > 0;
         uint32_t *status = plan->status_dev + 2 * plan->status_parity;
         uint32_t *status_next = plan->status_dev + 2 * (plan->status_parity ^ 1);
-        HIP_TRY(launch_setup(b->dev, p->g, gturns, plan->r64, plan->r32, hg ? plan->h64 : nullptr,
+        MatrixTerms mt;
+        const bool shared = shares_terms(b, p);
+        if (shared)
+            mt = matrix_terms(b->abcd0, (p->g.n[2] * p->g.O[2]) / p->g.n[2], b->dev.lam, b->w00);
+        HIP_TRY(launch_setup(b->dev, p->g, gturns, shared ? &mt : nullptr, plan->r64, plan->r32, hg ? plan->h64 : nullptr,
                              hg ? plan->h32 : nullptr, cut ? plan->c64 : nullptr, cut ? plan->c32 : nullptr,
                              status, status_next, plan->row_start, ctx->stream),
                 "setup kernel launch");
@@ -1115,7 +1127,7 @@ int grow(DevBuf &b, size_t bytes, const char *what) {
 
 void batch_free(BatchWork &w) {
     DevBuf *all[] = {&w.rec,    &w.l5,   &w.e0t,     &w.tab1,  &w.tab2, &w.e0,
-                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.row_v};
+                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.row_v, &w.terms};
     if (w.stage_ev) {
         (void)hipEventSynchronize(w.stage_ev);
         (void)hipEventDestroy(w.stage_ev);
@@ -1404,6 +1416,12 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
     b->dev.row_bits = n_rows ? reinterpret_cast<const uint32_t *>(d + off_bits) : nullptr;
     b->dev.rows = (int32_t)n_rows;
     b->higher_order = higher;
+    b->one_matrix = n > 0 && n_abcd == 1 && !base;
+    for (int64_t i = 1; i < n_w0; i++) b->one_matrix &= w0[i] == w0[0];
+    if (b->one_matrix) {
+        memcpy(b->abcd0, abcd, sizeof b->abcd0);
+        b->w00 = w0[0];
+    }
     *out = b;
     return GBD_OK;
 }
@@ -1912,6 +1930,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         (airy && (rc = grow(w.e0part, (size_t)max_chunks * sizeof(double2), "batch normalisation"))) ||
         (rc = grow(w.tab1, t1_bytes, "batch table")) || (rc = grow(w.tab2, t2_bytes, "batch table")) ||
         (rc = grow(w.e0, n_inst * sizeof(double2), "batch normalisation")) ||
+        (rc = grow(w.terms, n_inst * sizeof(MatrixTerms), "batch matrix terms")) ||
         (rc = grow(w.part, (size_t)std::max<int64_t>(n_items + row_tiles, 1) * PS * sizeof(double), "batch partials")) ||
         (rc = grow(w.metrics, (size_t)n_inst * (2 + n_zones) * sizeof(double), "batch metrics")) ||
         (rc = grow(w.flags, rb_bytes, "batch flags")))
@@ -1944,6 +1963,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         inst[i].pl = ps[i]->g;
         inst[i].rec_off = offs[i];
         inst[i].gturns = g0 - nearbyint(g0);
+        inst[i].shared = shares_terms(bs[i], ps[i]) ? 1 : 0;
     }
     const BatchInst *dinst = reinterpret_cast<const BatchInst *>(d1);
     const int64_t *doffs = reinterpret_cast<const int64_t *>(d1 + t1_offs);
@@ -1952,11 +1972,12 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     w.stage_pending = true;
     // [0] status, [1] first bad instance, [2] queue head, [4 ...] per-instance peaks, then row flags
     uint32_t *flags = static_cast<uint32_t *>(w.flags.p);
-    HIP_TRY(launch_batch_clear(flags, n_inst, st), "batch clear launch");
+    HIP_TRY(launch_batch_clear(flags, dinst, static_cast<MatrixTerms *>(w.terms.p), n_inst, st), "batch clear launch");
     HIP_TRY(launch_batch_setup(dinst, doffs, reinterpret_cast<const int32_t *>(d1 + t1_blks), n_inst, blks[n_inst],
                                static_cast<Rec32 *>(w.rec.p), static_cast<double *>(w.l5.p),
                                airy ? static_cast<double2 *>(w.e0t.p) : nullptr, flags,
-                               reinterpret_cast<int32_t *>(flags + 1), flags + 4, flags + 4 + n_inst, st),
+                               reinterpret_cast<int32_t *>(flags + 1), flags + 4, flags + 4 + n_inst,
+                               static_cast<const MatrixTerms *>(w.terms.p), st),
             "batch setup launch");
     HIP_TRY(hipMemcpyAsync(hrb, flags, n_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st), "status copy");
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");

@@ -33,9 +33,18 @@ using namespace dev;
 
 // The batch's flag words before its setup: [0] status 0, [1] first bad
 // instance 0x7f7f7f7f, [2] queue head 0, [3] 0, [4 ...] the n_inst peaks and
-// then the n_inst row flags 0.
-__global__ void __launch_bounds__(256) batch_clear_kernel(uint32_t *__restrict__ flags, int32_t n_inst) {
+// then the n_inst row flags 0.  Beside them the matrix terms of each instance
+// whose beamlets share them, bit for bit as the host's (gbd_terms.h).
+__global__ void __launch_bounds__(256) batch_clear_kernel(uint32_t *__restrict__ flags,
+                                                          const BatchInst *__restrict__ inst,
+                                                          MatrixTerms *__restrict__ terms, int32_t n_inst) {
     const int64_t n = 4 + 2 * (int64_t)n_inst;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_inst; i += (int64_t)gridDim.x * blockDim.x) {
+        const BatchInst &I = inst[i];
+        if (!I.shared) continue;
+        const double z = (I.pl.n[2] * I.pl.O[2]) / I.pl.n[2];
+        terms[i] = matrix_terms(I.b.abcd, z, I.b.lam, I.b.w0[0]);
+    }
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         flags[i] = i == 1 ? 0x7f7f7f7fu : 0u;
 }
@@ -92,7 +101,8 @@ __global__ void __launch_bounds__(kRowBlock) batch_setup_kernel(const BatchInst 
                                                                 uint32_t *__restrict__ status,
                                                                 int32_t *__restrict__ bad,
                                                                 uint32_t *__restrict__ peak,
-                                                                uint32_t *__restrict__ rowbad) {
+                                                                uint32_t *__restrict__ rowbad,
+                                                                const MatrixTerms *__restrict__ terms) {
     const int i = list_entry(blks, n_inst, (int32_t)blockIdx.x);
     const BatchInst &I = inst[i];
     const int halo = I.b.rows ? 1 : 0;
@@ -105,7 +115,7 @@ __global__ void __launch_bounds__(kRowBlock) batch_setup_kernel(const BatchInst 
         double l5v;
         Rec32 o;
         flag = setup_one(I.b, I.pl, I.gturns, k, nullptr, rec + I.rec_off, nullptr, nullptr, nullptr, nullptr, false,
-                         &pk, &l5v, &o, ykey, own);
+                         &pk, &l5v, &o, ykey, own, I.shared ? terms + i : nullptr);
         if (own) {
             l5[offs[i] + k] = l5v;
             if (e0t) e0t[offs[i] + k] = e0_term(o);
@@ -531,18 +541,19 @@ hipError_t launch_batch_eval_t(int cus, const BatchArgs &a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_batch_clear(uint32_t *flags, int32_t n_inst, hipStream_t s) {
+hipError_t launch_batch_clear(uint32_t *flags, const BatchInst *inst, MatrixTerms *terms, int32_t n_inst,
+                              hipStream_t s) {
     const int64_t blocks = min((4 + 2 * (int64_t)n_inst + 255) / 256, (int64_t)1024);
-    batch_clear_kernel<<<(unsigned)blocks, 256, 0, s>>>(flags, n_inst);
+    batch_clear_kernel<<<(unsigned)blocks, 256, 0, s>>>(flags, inst, terms, n_inst);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, const int32_t *blks, int32_t n_inst,
                               int32_t n_blocks, Rec32 *rec, double *l5, double2 *e0t, uint32_t *status, int32_t *bad,
-                              uint32_t *peak, uint32_t *rowbad, hipStream_t s) {
+                              uint32_t *peak, uint32_t *rowbad, const MatrixTerms *terms, hipStream_t s) {
     if (n_blocks == 0) return hipSuccess;
     batch_setup_kernel<<<(unsigned)n_blocks, kRowBlock, 0, s>>>(inst, offs, blks, n_inst, rec, l5, e0t, status, bad,
-                                                                peak, rowbad);
+                                                                peak, rowbad, terms);
     return hipGetLastError();
 }
 

@@ -127,12 +127,14 @@ __device__ inline double log2_hg_envelope_max(double c1, double c2, double d0, d
 // them) and a copy of the finished Rec32 record.
 // ykey (optional): everything the beamlet's y factor is made of.  store
 // false: no record is written (the record pointers still say what is formed).
+// shared (optional): the matrix terms, where all beamlets have the same.
 constexpr int kYKey = 11;
 __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, double gturns, int64_t j,
                                      Rec64 *r64, Rec32 *r32, RecHG64 *h64 = nullptr, RecHG32 *h32 = nullptr,
                                      RecCut64 *c64 = nullptr, RecCut32 *c32 = nullptr, bool sigma32 = true,
                                      float *sep_peak = nullptr, double *l5_out = nullptr,
-                                     Rec32 *r32_copy = nullptr, double *ykey = nullptr, bool store = true) {
+                                     Rec32 *r32_copy = nullptr, double *ykey = nullptr, bool store = true,
+                                     const MatrixTerms *shared = nullptr) {
     const double *M = b.abcd + (b.n_abcd == 1 ? 0 : 16 * j);
     double A[2][2], B[2][2], C[2][2], D[2][2];
 #pragma unroll
@@ -183,37 +185,18 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         const double arho = pl.e1[0] * X[0] + pl.e1[1] * X[1] + pl.e1[2] * X[2];
         const double brho = pl.e2[0] * X[0] + pl.e2[1] * X[1] + pl.e2[2] * X[2];
 
-        // system extended by free space z; Q1^-1 = -i kappa I
-        const double kappa = lam / (kPi * w0 * w0);
-        cd Mm[2][2], Nm[2][2];
-#pragma unroll
-        for (int r = 0; r < 2; r++)
-#pragma unroll
-            for (int c = 0; c < 2; c++) {
-                Mm[r][c] = mk(A[r][c] + z * C[r][c], -kappa * (B[r][c] + z * D[r][c]));
-                Nm[r][c] = mk(C[r][c], -kappa * D[r][c]);
-            }
-        // complex-curvature law Q^-1 = Nm Mm^-1 (closed-form 2x2 inverse), symmetrised
-        const cd det = sub(mul(Mm[0][0], Mm[1][1]), mul(Mm[0][1], Mm[1][0]));
-        cd Mi[2][2];
-        Mi[0][0] = cdiv(Mm[1][1], det);
-        Mi[1][1] = cdiv(Mm[0][0], det);
-        Mi[0][1] = cdiv(scl(Mm[0][1], -1.0), det);
-        Mi[1][0] = cdiv(scl(Mm[1][0], -1.0), det);
+        // complex curvature and amplitude on the plane
+        MatrixTerms mt;
+        if (shared)
+            mt = *shared;
+        else
+            mt = matrix_terms(M, z, lam, w0);
         cd Q[2][2];
-#pragma unroll
-        for (int r = 0; r < 2; r++)
-#pragma unroll
-            for (int c = 0; c < 2; c++) Q[r][c] = add(mul(Nm[r][0], Mi[0][c]), mul(Nm[r][1], Mi[1][c]));
-        const cd qo = scl(add(Q[0][1], Q[1][0]), 0.5);
-        Q[0][1] = qo;
-        Q[1][0] = qo;
-        // amplitude det(Mm)^(-1/2) from the eigenvalues' principal roots
-        const cd tr = add(Mm[0][0], Mm[1][1]);
-        const cd disc = csqrt_p(sub(mul(tr, tr), scl(det, 4.0)));
-        const cd mu1 = scl(add(tr, disc), 0.5), mu2 = scl(sub(tr, disc), 0.5);
-        if (!on_branch(mu1) || !on_branch(mu2)) flag |= FLAG_BRANCH;
-        const cd gamma = cdiv(mk(1.0, 0.0), mul(csqrt_p(mu1), csqrt_p(mu2)));
+        Q[0][0] = mk(mt.q00.re, mt.q00.im);
+        Q[1][1] = mk(mt.q11.re, mt.q11.im);
+        Q[0][1] = Q[1][0] = mk(mt.q01.re, mt.q01.im);
+        if (!mt.on_branch) flag |= FLAG_BRANCH;
+        const cd gamma = mk(mt.gamma.re, mt.gamma.im);
 
         // misalignment phase at the hit point, in turns (l0 handled by the
         // host): Euler's relation for the eikonal, or the traced optical path

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gbd_terms.h"
+
 #include <tuple>
 #include <utility>
 
@@ -210,6 +212,7 @@ struct BatchInst {
     PlaneGeom pl;
     int64_t rec_off;
     double gturns;
+    int32_t shared;  // all beamlets have the same matrix terms
 };
 
 // per instance, for the batched evaluation
@@ -266,7 +269,9 @@ struct BatchRows {
 // ceil(log2) + 2048 (0: none), the setup kernel's atomic maximum; zero on entry.
 // flags[0 .. 3], the n_inst peaks and the n_inst row flags after them set for
 // a batch setup (the first bad instance to 0x7f7f7f7f, the rest to 0)
-hipError_t launch_batch_clear(uint32_t *flags, int32_t n_inst, hipStream_t s);
+// and the matrix terms of the instances that share them (BatchInst::shared)
+hipError_t launch_batch_clear(uint32_t *flags, const BatchInst *inst, MatrixTerms *terms, int32_t n_inst,
+                              hipStream_t s);
 // The records' first 112 bytes; l5[j] receives beamlet j's FP64 l5 (the rotor
 // tables' source) and, unless e0t is null, e0t[j] its term at the plane origin.
 // Instance i's workgroups are [blks[i], blks[i + 1]) (batch_setup_blocks of
@@ -278,7 +283,7 @@ inline int64_t batch_setup_blocks(const BeamletsDev &b) {
 }
 hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, const int32_t *blks, int32_t n_inst,
                               int32_t n_blocks, Rec32 *rec, double *l5, double2 *e0t, uint32_t *status, int32_t *bad,
-                              uint32_t *peak, uint32_t *rowbad, hipStream_t s);
+                              uint32_t *peak, uint32_t *rowbad, const MatrixTerms *terms, hipStream_t s);
 // the rotor tables of every record (before a rotor-form evaluation)
 hipError_t launch_batch_sigma(const BatchInst *inst, const int64_t *offs, int32_t n_inst, int64_t total,
                               const double *l5, Rec32 *rec, hipStream_t s);
@@ -421,8 +426,9 @@ hipError_t launch_status_post(const StatusPost &sp, hipStream_t s);
 // row_out (with b.rows > 0): receives the handle's chunk table (rows + 1
 // entries), so that the plan outlives the handle; the setup checks that each
 // chunk's beamlets have bit-equal y factors (FLAG_ROWS if not).
-hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, Rec64 *r64,
-                        Rec32 *r32, RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32,
+// shared (null: none): the matrix terms where all beamlets have the same.
+hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, const MatrixTerms *shared,
+                        Rec64 *r64, Rec32 *r32, RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32,
                         uint32_t *status, uint32_t *status_next, int32_t *row_out, hipStream_t s);
 
 // The rotor forms' sigma^(k^2) tables (k = 1..16) of the g.n beamlets, from

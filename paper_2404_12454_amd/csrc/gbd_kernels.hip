@@ -20,7 +20,8 @@ namespace {
 
 using namespace dev;
 
-__global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGeom pl, double gturns,
+__global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGeom pl, double gturns, MatrixTerms mt,
+                                                    int have_mt,
                                                     Rec64 *__restrict__ r64, Rec32 *__restrict__ r32,
                                                     RecHG64 *__restrict__ h64, RecHG32 *__restrict__ h32,
                                                     RecCut64 *__restrict__ c64, RecCut32 *__restrict__ c32,
@@ -39,7 +40,7 @@ __global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGe
     const bool live = j >= 0 && j < b.n;
     if (live)
         flag = setup_one(b, pl, gturns, j, r64, r32, h64, h32, c64, c32, false, &peak, nullptr, nullptr, ykey,
-                         (int)threadIdx.x >= halo);
+                         (int)threadIdx.x >= halo, have_mt ? &mt : nullptr);
     if (b.rows) {  // uniform
         __shared__ double wkey[kRowBlock / 64][kYKey];
         flag |= h64 ? row_check<true>(ykey, live, j, b.n - b.n_cut, b.row_bits, wkey)
@@ -524,15 +525,15 @@ hipError_t launch_status_post(const StatusPost &sp, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, Rec64 *r64, Rec32 *r32,
-                        RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32, uint32_t *status,
+hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global_turns, const MatrixTerms *shared,
+                        Rec64 *r64, Rec32 *r32, RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32, uint32_t *status,
                         uint32_t *status_next, int32_t *row_out, hipStream_t s) {
     if (b.n == 0) return hipSuccess;
     if (b.rows >= b.n || (b.rows && !row_out)) return hipErrorInvalidValue;  // the threads copy rows + 1 entries
     const int per = kRowBlock - (b.rows ? 1 : 0);
     const int64_t blocks = (b.n + per - 1) / per;
-    setup_kernel<<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, r64, r32, h64, h32, c64, c32, status,
-                                                        status_next, row_out);
+    setup_kernel<<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, shared ? *shared : MatrixTerms{}, shared != nullptr,
+                                                        r64, r32, h64, h32, c64, c32, status, status_next, row_out);
     return hipGetLastError();
 }
 
