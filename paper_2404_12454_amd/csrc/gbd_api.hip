@@ -199,6 +199,7 @@ struct gbd_mlp_s {
     float *dz0, *dz1;                 // [max_batch][width]
     float *xb, *yb, *yhat, *g, *loss;
     uint16_t *xt;                     // BF16 inputs, transposed (the two-kernel path)
+    uint16_t *wf, *wb;                // its BF16 operands of the weights (MlpNet), or null
     int64_t step;
 };
 
@@ -2221,7 +2222,9 @@ int gbd_mlp_create(gbd_ctx_t ctx, gbd_mlp_t *out, int32_t n_in, int32_t width, i
     // (the two-kernel path keeps BF16 transposes in H's place)
     const int64_t mb = ((int64_t)max_batch + 15) / 16 * 16, P4 = (m->P + 3) / 4 * 4;
     const int64_t act = (int64_t)depth * mb * width, bw = mb * width;
-    const int64_t total = 4 * P4 + 2 * act + 2 * bw + mb * (n_in + 3 + (n_in + 1) / 2) + 1;
+    const bool fused = mlp_fused(mode == GBD_MLP_BF16, width, depth);
+    const int64_t pack = fused ? depth * mlp_pack_layer(width) : 0;  // BF16 values, forward and transposed
+    const int64_t total = 4 * P4 + 2 * act + 2 * bw + mb * (n_in + 3 + (n_in + 1) / 2) + pack + 1;
     hipError_t e = hipMalloc(&m->mem, (size_t)total * sizeof(float));
     if (e != hipSuccess) {
         delete m;
@@ -2232,6 +2235,10 @@ int gbd_mlp_create(gbd_ctx_t ctx, gbd_mlp_t *out, int32_t n_in, int32_t width, i
     m->grads = q; q += P4;
     m->m = q; q += P4;
     m->v = q; q += P4;
+    if (fused) {
+        m->wf = reinterpret_cast<uint16_t *>(q); q += pack / 2;
+        m->wb = reinterpret_cast<uint16_t *>(q); q += pack / 2;
+    }
     m->Z = q; q += act;
     m->H = q; q += act;
     m->dz0 = q; q += bw;
@@ -2261,6 +2268,35 @@ void gbd_mlp_free(gbd_mlp_t m) {
 
 int64_t gbd_mlp_num_params(gbd_mlp_t m) { return m ? m->P : (int64_t)fail(GBD_EINVAL, "NULL argument"); }
 
+// The two-kernel path's view of a batch (mlp_fused)
+static MlpNet mlp_net(gbd_mlp_t m, const float *x, const float *target, const int32_t *rows, int B, float *yhat) {
+    MlpNet n{};
+    n.n_in = m->n_in;
+    n.W = m->width;
+    n.D = m->depth;
+    n.B = B;
+    n.bt = (B + 15) / 16 * 16;
+    n.params = m->params;
+    for (int l = 0; l <= m->depth && l <= kMlpFusedDepth; l++) {
+        n.woff[l] = m->woff[l];
+        n.boff[l] = m->boff[l];
+    }
+    n.x = x;
+    n.y = target;
+    n.rows = rows;
+    n.yhat = yhat;
+    n.dz = m->Z;
+    n.hlast = m->dz0;
+    n.g = m->g;
+    n.yb = m->yb;
+    n.dzt = reinterpret_cast<uint16_t *>(m->H);
+    n.ht = n.dzt + (int64_t)m->depth * m->width * n.bt;
+    n.xt = m->xt;
+    n.wf = m->wf;
+    n.wb = m->wb;
+    return n;
+}
+
 int gbd_mlp_set_params(gbd_mlp_t m, const float *params, int64_t n) {
     if (!m || !params) return fail(GBD_EINVAL, "NULL argument");
     if (n != m->P) return fail(GBD_EINVAL, "expected %lld parameters, got %lld", (long long)m->P, (long long)n);
@@ -2272,6 +2308,7 @@ int gbd_mlp_set_params(gbd_mlp_t m, const float *params, int64_t n) {
     HIP_TRY(hipMemcpyAsync(m->params, params, n * sizeof(float), hipMemcpyHostToDevice, st), "parameter upload");
     HIP_TRY(hipMemsetAsync(m->m, 0, n * sizeof(float), st), "optimiser reset");
     HIP_TRY(hipMemsetAsync(m->v, 0, n * sizeof(float), st), "optimiser reset");
+    HIP_TRY(launch_mlp_pack(mlp_net(m, nullptr, nullptr, nullptr, 0, nullptr), st), "weight packing launch");
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
     m->step = 0;
     return GBD_OK;
@@ -2318,33 +2355,6 @@ static int mlp_forward_impl(gbd_mlp_t m, int B) {
     HIP_TRY(launch_mlp_head_forward(in, m->params + m->woff[m->depth], m->params + m->boff[m->depth], B, W, m->yhat, st),
             "mlp head launch");
     return GBD_OK;
-}
-
-// The two-kernel path's view of a batch (mlp_fused)
-static MlpNet mlp_net(gbd_mlp_t m, const float *x, const float *target, const int32_t *rows, int B, float *yhat) {
-    MlpNet n{};
-    n.n_in = m->n_in;
-    n.W = m->width;
-    n.D = m->depth;
-    n.B = B;
-    n.bt = (B + 15) / 16 * 16;
-    n.params = m->params;
-    for (int l = 0; l <= m->depth; l++) {
-        n.woff[l] = m->woff[l];
-        n.boff[l] = m->boff[l];
-    }
-    n.x = x;
-    n.y = target;
-    n.rows = rows;
-    n.yhat = yhat;
-    n.dz = m->Z;
-    n.hlast = m->dz0;
-    n.g = m->g;
-    n.yb = m->yb;
-    n.dzt = reinterpret_cast<uint16_t *>(m->H);
-    n.ht = n.dzt + (int64_t)m->depth * m->width * n.bt;
-    n.xt = m->xt;
-    return n;
 }
 
 // Gradients of one batch (and, with adam.on, the step) by the two-kernel path
@@ -2448,8 +2458,8 @@ int gbd_mlp_adamw(gbd_mlp_t m, float lr, float beta1, float beta2, float eps, fl
     if (rc) return rc;
     m->step++;
     const float c1 = 1.0f - powf(beta1, (float)m->step), c2 = 1.0f - powf(beta2, (float)m->step);
-    HIP_TRY(launch_mlp_adamw(m->params, m->grads, m->m, m->v, m->P, lr, beta1, beta2, eps, weight_decay, c1, c2,
-                             m->ctx->stream),
+    HIP_TRY(launch_mlp_adamw(mlp_net(m, nullptr, nullptr, nullptr, 0, nullptr), m->grads, m->m, m->v, m->P, lr, beta1,
+                             beta2, eps, weight_decay, c1, c2, m->ctx->stream),
             "adamw launch");
     return GBD_OK;
 }

@@ -378,7 +378,16 @@ struct MlpNet {
     // the targets [B]
     float *dz, *hlast, *g, *yb;
     uint16_t *dzt, *ht, *xt;
+    // the hidden layers' weights in BF16 as MFMA operands (null: kept by no
+    // one), forward and transposed, kept equal to params by all that write those
+    uint16_t *wf, *wb;
 };
+// One layer's operands: column tiles of 16 (8, or 16 where W > 128), each half
+// as many K steps of 32, 64 lanes of 8 values, zero past the matrix.
+__host__ __device__ inline int mlp_pack_tiles(int W) { return W > 128 ? 16 : 8; }
+__host__ __device__ inline int64_t mlp_pack_layer(int W) { return (int64_t)mlp_pack_tiles(W) * (mlp_pack_tiles(W) / 2) * 512; }
+// packs all weights from params
+hipError_t launch_mlp_pack(const MlpNet &n, hipStream_t s);
 struct MlpAdam {
     int on;
     float *m, *v;
@@ -396,8 +405,9 @@ hipError_t launch_mlp_head_forward(const float *H, const float *w, const float *
 hipError_t launch_mlp_head_backward(const float *yhat, const float *y, const float *H, const float *w, const float *Z,
                                     int B, int W, float *g, float *loss, float *dw, float *dZ, hipStream_t s);
 hipError_t launch_mlp_colsum(const float *dZ, int B, int W, float *db, hipStream_t s);
-hipError_t launch_mlp_adamw(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
-                            float eps, float wd, float c1, float c2, hipStream_t s);
+// n.wf: the packed weights follow
+hipError_t launch_mlp_adamw(const MlpNet &n, const float *g, float *m, float *v, int64_t count, float lr, float b1,
+                            float b2, float eps, float wd, float c1, float c2, hipStream_t s);
 
 // status: two device words, zero on entry: [0] receives the OR of the
 // beamlets' FLAG_* bits, [1] the largest beamlet term modulus over the grid

@@ -147,12 +147,18 @@ __global__ void __launch_bounds__(kSumCols * kSumRows) colsum_kernel(const float
     column_sums(dZ, nullptr, B, W, false, (int)blockIdx.x, [&](int i, float s) { db[i] = s; });
 }
 
-__global__ void __launch_bounds__(256) adamw_kernel(float *__restrict__ p, const float *__restrict__ g,
+__global__ void __launch_bounds__(256) adamw_kernel(MlpNet net, const float *__restrict__ g,
                                                     float *__restrict__ m, float *__restrict__ v, int64_t n, float lr,
                                                     float b1, float b2, float eps, float wd, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    adamw_step(p[i], g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
+    adamw_step(net.params[i], g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
+    if (net.wf) pack_param(net, i, net.params[i]);
+}
+
+__global__ void __launch_bounds__(256) pack_kernel(MlpNet net, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) pack_param(net, i, net.params[i]);
 }
 
 // acc[0] += v[0] (one running loss sum in step order)
@@ -207,10 +213,17 @@ hipError_t launch_mlp_colsum(const float *dZ, int B, int W, float *db, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_adamw(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
-                            float eps, float wd, float c1, float c2, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    adamw_kernel<<<blocks_for(n, 256), 256, 0, s>>>(p, g, m, v, n, lr, b1, b2, eps, wd, c1, c2);
+hipError_t launch_mlp_adamw(const MlpNet &n, const float *g, float *m, float *v, int64_t count, float lr, float b1,
+                            float b2, float eps, float wd, float c1, float c2, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    adamw_kernel<<<blocks_for(count, 256), 256, 0, s>>>(n, g, m, v, count, lr, b1, b2, eps, wd, c1, c2);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_pack(const MlpNet &n, hipStream_t s) {
+    if (!n.wf) return hipSuccess;
+    const int64_t count = n.woff[n.D];  // up to the head
+    pack_kernel<<<blocks_for(count, 256), 256, 0, s>>>(n, count);
     return hipGetLastError();
 }
 

@@ -18,6 +18,25 @@ __device__ inline float dsilu(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
+// Layer l's weight W[o][k] in BF16 to its places as an operand of the forward
+// product (column o, K index k) and of the back-propagated one (column k, K index o)
+__device__ inline void pack_weight(const MlpNet &n, int l, int o, int k, float v) {
+    const int steps = mlp_pack_tiles(n.W) / 2;
+    const int64_t at = l * mlp_pack_layer(n.W);
+    const uint16_t b = __builtin_bit_cast(uint16_t, (__bf16)v);
+    auto place = [&](int c, int q) { return ((c >> 4) * steps + (q >> 5)) * 512 + ((c & 15) + 16 * (q >> 3 & 3)) * 8 + (q & 7); };
+    n.wf[at + place(o, k)] = b;
+    if (l > 0) n.wb[at + place(k, o)] = b;
+}
+// the same for flat parameter i, if it is a hidden layer's weight
+__device__ inline void pack_param(const MlpNet &n, int64_t i, float v) {
+    for (int l = 0; l < n.D; l++)
+        if (i >= n.woff[l] && i < n.boff[l]) {
+            const int fan = l == 0 ? n.n_in : n.W, j = (int)(i - n.woff[l]);
+            pack_weight(n, l, j / fan, j % fan, v);
+        }
+}
+
 __device__ inline void adamw_step(float &p, float g, float &m, float &v, float lr, float b1, float b2, float eps, float wd,
                                   float c1, float c2) {
     const float mi = b1 * m + (1.0f - b1) * g;

@@ -1,11 +1,12 @@
 // The surrogate network in BF16 mode by two kernels instead of one per
 // operation: a training step of the 5-128-128-128-1 network on 256 rows was
 // about 20 launches of 2 ... 10 us each, bound by launch and load latency and
-// not by its 50 MFLOP (102 us a step; the two kernels 22 us, of 25 us a step).  A row's activations, forward and back-propagated, need
-// no other row, so mlp_rows_kernel keeps 16 rows (one MFMA tile) per
-// workgroup in LDS and registers through all layers and back; the gradients,
-// which sum over the rows, then take one kernel for all layers, with the
-// optimiser's step behind each one.
+// not by its 50 MFLOP (101 us a step; now 17.8, the two kernels 16.5 of them).
+// A row's activations, forward and back-propagated, need no other row, so
+// mlp_rows_kernel keeps 16 rows (one MFMA tile) per workgroup in LDS and
+// registers through all layers and back; the gradients, which sum over the
+// rows, then take one kernel for all layers, with the optimiser's step behind
+// each one.
 #include "gbd_mlp_core.h"
 
 namespace gbd {
@@ -22,53 +23,23 @@ constexpr int kRowWaves = 8;            // wavefront w takes the column tiles w,
 
 __device__ inline uint16_t bf(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 
-// The operands of one wavefront's 16 x 16 tiles, as loaded (FP32): element i
-// of step s is W[column][k] (forward) or W[k][column] (back) at k = 32 s +
-// 8 kg + i.  Every load is issued, from a clamped place, none waits on a
-// branch; what lies past the matrix is zeroed on conversion.
+// The operands of one wavefront's column tile, K steps of 32, as packed: one
+// kilobyte a load, half the bytes of the FP32 weights, which 16 workgroups
+// each fetch whole, and nothing to convert or mask.
 template <int S>
 struct Weights {
-    float v[S][8];
-    __device__ void forward(const float *__restrict__ w, int K, int W, int c, int kg) {
-        const float *row = w + (int64_t)min(c, W - 1) * K;
-        if constexpr (S > 4) asm volatile("" : "+v"(kg));  // offsets formed here: held over the layers they spill
+    uint4 v[S];
+    __device__ void load(const uint16_t *__restrict__ layer, int tile, int lane, int K) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(layer) + (int64_t)tile * S * 64 + lane;
 #pragma unroll
-        for (int s = 0; s < S; s++) {
-            const int k = 32 * s + 8 * kg;
-            if (K % 8 == 0) {  // uniform
-                const float *p = row + min(k, K - 8);
-                const floatx4 x = *reinterpret_cast<const floatx4u *>(p), y = *reinterpret_cast<const floatx4u *>(p + 4);
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    v[s][i] = x[i];
-                    v[s][4 + i] = y[i];
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; i++) v[s][i] = 32 * s < K ? row[min(k + i, K - 1)] : 0.0f;
-            }
-        }
-    }
-    __device__ void back(const float *__restrict__ w, int W, int c, int kg) {
-        const float *col = w + min(c, W - 1);
-        if constexpr (S > 4) asm volatile("" : "+v"(kg));
-#pragma unroll
-        for (int s = 0; s < S; s++)
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[s][i] = col[(unsigned)(min(32 * s + 8 * kg + i, W - 1) * W)];
-    }
-    __device__ bf16x8 operand(int s, int K, bool in, int kg) const {
-        bf16x8 o;
-#pragma unroll
-        for (int i = 0; i < 8; i++) o[i] = (__bf16)(in && 32 * s + 8 * kg + i < K ? v[s][i] : 0.0f);
-        return o;
+        for (int s = 0; s < S; s++) v[s] = 32 * s < K ? p[64 * s] : make_uint4(0u, 0u, 0u, 0u);  // uniform
     }
 };
 
 // Four K ranges' partial products, added in their order: with K <= 128 one
 // step of 32 each, else two (K <= 256); a step past K adds zeros.
 template <int S>
-__device__ inline floatx4 product(const Weights<S> &b, const uint16_t *__restrict__ a, int K, bool in, int kg) {
+__device__ inline floatx4 product(const Weights<S> &b, const uint16_t *__restrict__ a, int K, int kg) {
     const int ks = S > 4 && K > 128 ? 2 : 1;
     floatx4 p[4];
 #pragma unroll
@@ -76,7 +47,7 @@ __device__ inline floatx4 product(const Weights<S> &b, const uint16_t *__restric
 #pragma unroll
     for (int s = 0; s < S; s++) {
         const bf16x8 x = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(a + 32 * s + 8 * kg));
-        const bf16x8 y = b.operand(s, K, in, kg);
+        const bf16x8 y = __builtin_bit_cast(bf16x8, b.v[s]);
         if (ks == 2)  // steps 0, 1 | 2, 3 | ...
             p[s / 2 & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, p[s / 2 & 3], 0, 0, 0);
         else if (s < 4)
@@ -89,10 +60,11 @@ __device__ inline floatx4 product(const Weights<S> &b, const uint16_t *__restric
 // 16 blockIdx ... + 15: T column tiles of 16 per wavefront (W <= 128 T).  Lane
 // l of a product's result holds rows 4 (l / 16) + e and column l % 16 of its
 // tile, forward and backward alike.  The kernel is a chain of short products
-// on a handful of CUs, so what it costs is latency: with T = 1 the next
-// product's weights are requested before this one's.  128-128-128 on 256
-// rows: 15.9 us, forward alone 9.7; with the layers as loops of one body,
-// whose waits cover every load and store of a pass, 18.9 and 11.6.
+// on a handful of CUs, so what it costs is latency: with T = 1 all products'
+// weights are requested at the start.  128-128-128 on 256 rows: 10.4 us,
+// forward alone 5.7 (from the FP32 weights 15.9 and 9.7: a layer's 64 KiB came
+// no faster than a CU's loads in flight allow, about 1.7 us, however early
+// they were issued; the layers as loops of one body 18.9 and 11.6).
 template <int D, int T, bool BWD>
 __global__ void __launch_bounds__(64 * kRowWaves) mlp_rows_kernel(MlpNet n) {
     constexpr int S = 4 * T, C = 128 * T;
@@ -102,9 +74,16 @@ __global__ void __launch_bounds__(64 * kRowWaves) mlp_rows_kernel(MlpNet n) {
     __shared__ float gs[kRows];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, kg = lane >> 4;
     const int b0 = blockIdx.x * kRows, W = n.W;
-    constexpr bool ahead = T == 1;
-    Weights<S> wt;
-    if (ahead) wt.forward(n.params + n.woff[0], n.n_in, W, 16 * w + r, kg);
+    constexpr bool all = T == 1;
+    const int64_t layer = mlp_pack_layer(W);
+    Weights<S> wf[all ? D : 1], wb[all ? D : 1];  // wb[l]: layer l's, transposed
+    if constexpr (all) {
+#pragma unroll
+        for (int l = 0; l < D; l++) wf[l].load(n.wf + l * layer, w, lane, l == 0 ? n.n_in : W);
+        if constexpr (BWD)
+#pragma unroll
+            for (int l = D - 1; l > 0; l--) wb[l].load(n.wb + l * layer, w, lane, W);
+    }
     const float *__restrict__ wh = n.params + n.woff[D];
     float whc[T], whl[2 * T];
 #pragma unroll
@@ -146,15 +125,9 @@ __global__ void __launch_bounds__(64 * kRowWaves) mlp_rows_kernel(MlpNet n) {
         for (int t = 0; t < T; t++) {
             const int c = 16 * (w + kRowWaves * t) + r;
             const bool in = c < W;
-            if (!ahead) wt.forward(n.params + n.woff[l], K, W, c, kg);
-            const Weights<S> now = wt;
-            if (ahead) {
-                if (l + 1 < D)
-                    wt.forward(n.params + n.woff[l + 1], W, W, c, kg);
-                else if (BWD && D > 1)
-                    wt.back(n.params + n.woff[D - 1], W, c, kg);
-            }
-            const floatx4 acc = product(now, &act[cur][r][0], K, in, kg);
+            Weights<S> &now = wf[all ? l : 0];
+            if (!all) now.load(n.wf + l * layer, w + kRowWaves * t, lane, K);
+            const floatx4 acc = product(now, &act[cur][r][0], K, kg);
             shortx4 ht;
 #pragma unroll
             for (int e = 0; e < 4; e++) {
@@ -219,10 +192,9 @@ __global__ void __launch_bounds__(64 * kRowWaves) mlp_rows_kernel(MlpNet n) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = gs[4 * kg + e] * whc[t];
             } else {
-                if (!ahead) wt.back(n.params + n.woff[l + 1], W, c, kg);
-                const Weights<S> now = wt;
-                if (ahead && l > 0) wt.back(n.params + n.woff[l], W, c, kg);
-                d = product(now, &act[cur][r][0], W, in, kg);
+                Weights<S> &now = wb[all ? l + 1 : 0];
+                if (!all) now.load(n.wb + (l + 1) * layer, w + kRowWaves * t, lane, W);
+                d = product(now, &act[cur][r][0], W, kg);
             }
             shortx4 dt;
 #pragma unroll
@@ -255,7 +227,8 @@ __global__ void __launch_bounds__(256) mlp_grads_kernel(MlpNet n, GradBlocks G, 
     const int blk = blockIdx.x, W = n.W, D = n.D;
     auto emit = [&](int64_t i, float g) {
         grads[i] = g;
-        if (A.on) adamw_step(n.params[i], g, A.m[i], A.v[i], A.lr, A.b1, A.b2, A.eps, A.wd, A.c1, A.c2);
+        if (!A.on) return;
+        adamw_step(n.params[i], g, A.m[i], A.v[i], A.lr, A.b1, A.b2, A.eps, A.wd, A.c1, A.c2);
     };
     if (blk < G.bias) {
         __shared__ floatx4 part[4][64];
@@ -285,7 +258,11 @@ __global__ void __launch_bounds__(256) mlp_grads_kernel(MlpNet n, GradBlocks G, 
         // thread t: element t / 64 of lane t % 64, so all wavefronts take the optimiser's step
         const float s = ((part[0][lane][w] + part[1][lane][w]) + part[2][lane][w]) + part[3][lane][w];
         const int m = tm + 4 * kg + w, c = tn + r;
-        if (m < W && c < fan) emit(n.woff[l] + (int64_t)m * fan + c, s);
+        if (m < W && c < fan) {
+            const int64_t i = n.woff[l] + (int64_t)m * fan + c;
+            emit(i, s);
+            if (A.on) pack_weight(n, l, m, c, n.params[i]);
+        }
     } else if (blk < G.head) {
         const int per = (W + kSumCols - 1) / kSumCols, l = (blk - G.bias) / per;
         column_sums(n.dz + (int64_t)l * n.B * W, nullptr, n.B, W, false, (blk - G.bias) % per,
@@ -328,7 +305,7 @@ void launch_rows_d(const MlpNet &n, bool backward, hipStream_t s) {
 
 hipError_t launch_mlp_rows(const MlpNet &n, bool backward, hipStream_t s) {
     if (n.B <= 0) return hipSuccess;
-    if (!mlp_fused(1, n.W, n.D) || n.n_in > 64 || n.bt % kRows != 0 || n.bt < n.B) return hipErrorInvalidValue;
+    if (!mlp_fused(1, n.W, n.D) || n.n_in > 64 || n.bt % kRows != 0 || n.bt < n.B || !n.wf) return hipErrorInvalidValue;
     switch (n.D) {
         case 1: launch_rows_d<1>(n, backward, s); break;
         case 2: launch_rows_d<2>(n, backward, s); break;
