@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(64 * rows::kRowSumWaves) batch_row_sum_kernel(
 __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel(BatchArgs A, BatchRows B,
                                                                                const RowV32 *__restrict__ v) {
     constexpr int NQ = 2 + 2 * kMaxZones, WAVES = rows::kRowWaves;
-    __shared__ float2 part[WAVES][256];
+    __shared__ float2 part[WAVES][256 * rows::kFoldBlocks<RowV32>];
     __shared__ double red[WAVES][NQ];
     const int x = blockIdx.x % kXcds, r = blockIdx.x / kXcds;
     if (r >= B.prod_tiles[x]) return;
@@ -429,6 +429,14 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
     const int i = B.prod_inst[e], t = r - B.prod_first[e];
     const BatchEval &I = A.inst[i];
     const int x0 = (t / I.tiles_y) * rows::kRowTile, y0 = (t % I.tiles_y) * rows::kRowTile;
+    // the reference at this thread's pixels, ahead of the product
+    float ref[2] = {0.0f, 0.0f};
+    if (A.airy)
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const int ix = x0 + 16 * (int)(threadIdx.x >> 8) + (threadIdx.x & 15), iy = y0 + 16 * p + (threadIdx.x >> 4 & 15);
+            if (ix < I.nx && iy < I.ny) ref[p] = A.airy[(int64_t)iy * I.nx + ix];
+        }
     sep::f4 re[2][2], im[2][2];
     rows::row_product<false>(v + I.v_off, B.sums + I.sum_off, I.rows, I.nx, I.a0, I.b0, I.dy, x0, y0, re, im);
     const int P = (int)rows::row_exponent(B.peaks[i]);
@@ -448,7 +456,7 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
         const float2 f = rows::row_value(sr, si, P);
         if (A.fields) A.fields[I.field_off + px] = f;
         if (A.airy) {
-            const double d = ((double)f.x * f.x + (double)f.y * f.y) * inv0 - (double)A.airy[px];
+            const double d = ((double)f.x * f.x + (double)f.y * f.y) * inv0 - (double)ref[p];
             q[0] += d * d;
             q[1] = fmax(q[1], fabs(d));
             const double a = I.a0 + ix * I.dx, b = I.b0 + iy * I.dy;
@@ -462,7 +470,6 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
         }
     });
     if (!A.airy) return;
-    // the pixels lie with the first 256 threads
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, PS = 2 + 2 * A.n_zones;
 #pragma unroll
     for (int z = 0; z < NQ; z++)
@@ -474,7 +481,7 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
     if ((int)threadIdx.x < PS) {
         const int z = threadIdx.x;
         double s = red[0][z];
-        for (int w = 1; w < 4; w++) s = (z == 1) ? fmax(s, red[w][z]) : s + red[w][z];
+        for (int w = 1; w < WAVES; w++) s = (z == 1) ? fmax(s, red[w][z]) : s + red[w][z];
         A.part[(I.item_off + t) * PS + z] = s;
     }
 }

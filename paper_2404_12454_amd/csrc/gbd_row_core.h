@@ -313,28 +313,35 @@ __device__ inline void row_product(const V *__restrict__ v, const typename RowTy
     }
 }
 
-// The workgroup's shares added in wavefront order in FP64, one 16 x 16 block
-// at a time through LDS; pixel(p, q, i, value) gets element i (row i / 16,
-// column i % 16) of block (p, q) from thread i.
+// The workgroup's shares added in wavefront order in FP64, a row of two
+// 16 x 16 blocks at a time through LDS in FP32 (FP64: one block, for 32 KiB of
+// LDS either way); pixel(p, q, i, value) gets element i (row i / 16, column
+// i % 16) of block (p, q) from one thread.
+template <typename V>
+constexpr int kFoldBlocks = sizeof(V) == sizeof(RowV32) ? 2 : 1;
 template <typename V, typename F>
 __device__ inline void row_fold(typename RowType<V>::A4 (&re)[2][2], typename RowType<V>::A4 (&im)[2][2],
-                                typename RowType<V>::R2 (*part)[256], F pixel) {
+                                typename RowType<V>::R2 (*part)[256 * kFoldBlocks<V>], F pixel) {
     using R2 = typename RowType<V>::R2;
+    constexpr int N = kFoldBlocks<V>;
+    static_assert(256 * N <= 64 * kRowWaves, "a thread per pixel");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
 #pragma unroll
     for (int p = 0; p < 2; p++)
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
+        for (int q0 = 0; q0 < 2; q0 += N) {
             __syncthreads();
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                R2 x;
-                x.x = re[p][q][e];
-                x.y = im[p][q][e];
-                part[w][16 * RowType<V>::row(lk, e) + li] = x;
-            }
+            for (int q = 0; q < N; q++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    R2 x;
+                    x.x = re[p][q0 + q][e];
+                    x.y = im[p][q0 + q][e];
+                    part[w][256 * q + 16 * RowType<V>::row(lk, e) + li] = x;
+                }
             __syncthreads();
-            if (threadIdx.x < 256) {
+            if (threadIdx.x < 256 * N) {
                 double sr = 0.0, si = 0.0;
 #pragma unroll
                 for (int k = 0; k < kRowWaves; k++) {
@@ -342,7 +349,7 @@ __device__ inline void row_fold(typename RowType<V>::A4 (&re)[2][2], typename Ro
                     sr += (double)x.x;
                     si += (double)x.y;
                 }
-                pixel(p, q, (int)threadIdx.x, sr, si);
+                pixel(p, q0 + (int)(threadIdx.x >> 8), (int)threadIdx.x & 255, sr, si);
             }
         }
 }

@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) row_product_kernel(RowGeom g, 
                                                                      typename RowType<V>::R2 *__restrict__ out,
                                                                      EvalGuard gd) {
     using R = typename RowType<V>::R;
-    __shared__ typename RowType<V>::R2 part[kRowWaves][256];
+    __shared__ typename RowType<V>::R2 part[kRowWaves][256 * kFoldBlocks<V>];
     if (!guard_holds(gd)) return;
     const int tx = (g.nx + kRowTile - 1) / kRowTile, ty = (g.ny + kRowTile - 1) / kRowTile;
     const int w = work_item(blockIdx.x, gridDim.x);
