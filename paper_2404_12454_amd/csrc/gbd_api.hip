@@ -186,7 +186,7 @@ constexpr int kNoSpeculation = 1;
 
 // the setup flags that select how an evaluation runs
 constexpr uint32_t kFormFlags = FLAG_STEEP | FLAG_CROSS | FLAG_HG | FLAG_ROWS | FLAG_CROSS1 | FLAG_CROSS2 |
-                               FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
+                               FLAG_CUT0 | FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
 
 struct gbd_mlp_s {
     gbd_ctx_s *ctx;
@@ -634,27 +634,33 @@ constexpr int kCutWaves = 2;  // workgroups a CU holds of the column form (240 r
 
 // The truncated-beamlet kernel's column form (launch_eval_cut's level) where
 // its polynomials reach; pixel by pixel where the direct form is asked for.
-int cut_level(uint32_t flags, const gbd_eval_opts *o) {
+int cut_level(int precision, uint32_t flags, const gbd_eval_opts *o) {
     if (o && o->variant == 1) return 0;
+    if (precision == GBD_MIXED && !(flags & FLAG_CUT0)) return 4;
     return !(flags & FLAG_CUT1) ? 3 : !(flags & FLAG_CUT2) ? 2 : !(flags & FLAG_CUT3) ? 1 : 0;
 }
 
 // Launch geometry of the truncated-beamlet kernel: 64-column tiles of
 // 4 wavefronts x the level's rows, segments for 2 wavefronts per SIMD (pixel
 // by pixel ~6), each of at least 8 beamlets while the partials are small
-// (most_segments), else 32.
-EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, int level, const PlaneGeom &pl, int64_t n_cut,
+// (most_segments), else 32.  Level 4 takes segments of one tile, with partials
+// of 64 MiB at most, or is lowered to 3 (2,028 on 512 x 512: the
+// kernel 300 us in 16 segments of 32 rows, 430 in 8 of 16).
+EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, int &level, const PlaneGeom &pl, int64_t n_cut,
                   int64_t max_seg = 1024) {
+    const int64_t one = (n_cut + kCutOneTile - 1) / kCutOneTile;
+    if (level == 4 && one > std::min<int64_t>(max_seg, most_segments(n_cut, kCutOneTile, pl, 16) + 1)) level = 3;
     Shape s;
     s.form = 0;
     s.half = false;
     s.waves = 4;
-    s.rows = level > 1 ? kCutRows : level == 1 ? kCutRows / 2 : precision == GBD_MIXED ? kCutRows32 : kCutRows64;
+    s.rows = level == 4 ? 2 * kCutRows : level > 1 ? kCutRows : level == 1 ? kCutRows / 2 : precision == GBD_MIXED ? kCutRows32 : kCutRows64;
     const int64_t tx = (pl.nx + 63) / 64;
     const int64_t ty = (pl.ny + s.waves * s.rows - 1) / (s.waves * s.rows);
     const int64_t tiles = std::max<int64_t>(1, tx * ty);
     int64_t seg = ((int64_t)ctx->cus * (level ? kCutWaves : 6) + tiles - 1) / tiles;
     seg = std::min<int64_t>(seg, std::max<int64_t>(n_cut / 32, most_segments(n_cut, 8, pl, 16)));
+    if (level == 4) seg = std::max<int64_t>(seg, one);
     s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, max_seg));
     return make_geom(pl, n_cut, s);
 }
@@ -673,8 +679,9 @@ bool captures(const gbd_ctx_s *ctx) {
 size_t general_scratch(const gbd_ctx_s *ctx, const gbd_plan_s *plan, int precision, const gbd_eval_opts *opts) {
     const int64_t n = plan->n - plan->n_cut;
     const Shape s = choose_shape(ctx, precision, n, plan->pl, plan->flags, opts, true);
+    int level = 0;
     const int64_t seg = (n > 0 ? make_geom(plan->pl, n, s).nseg : 0) +
-                        (plan->n_cut > 0 ? cut_geom(ctx, precision, 0, plan->pl, plan->n_cut).nseg : 0);
+                        (plan->n_cut > 0 ? cut_geom(ctx, precision, level, plan->pl, plan->n_cut).nseg : 0);
     return (size_t)seg * (size_t)plan->pl.nx * (size_t)plan->pl.ny * 16;
 }
 
@@ -732,7 +739,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     bool compact = n_main > 0 && (s.form == 3 || s.cross) && precision == GBD_MIXED;
     EvalGeom g{}, gc{};
     int32_t nseg_main = 0, nseg_cut = 0;
-    const int level = general ? 0 : cut_level(plan->flags, opts);
+    int level = general ? 0 : cut_level(precision, plan->flags, opts);
     if (plan->n_cut > 0) {
         gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut);
         nseg_cut = gc.nseg;

@@ -253,12 +253,14 @@ __global__ void __launch_bounds__(64 * WAVES) eval_cut_fp64_kernel(EvalGeom g, c
 // For all pixels |m_p k^p| falls at least as (e t / p)^p with
 // t = |k delta| (2 |zeta| + sqrt(2 p)); the setup bounds t over the cut
 // beamlets and the grid (kCutReachLow, kCutReachHigh), where degrees 5 and 9
-// leave 2^-25 of a term in FP32, 9 and 15 2^-50 in FP64: 16 rows at the low
-// degree, else at the high one, else 8 rows; beyond that the direct form.
-// Bound by VALU issue: 510 instructions a column of 16 pixels at the low
-// degree (32 a pixel), the direct form about 130 a pixel.  2,028 cut beamlets
-// on 512 x 512 pixels, mixed: 1,450 -> 370 us (the evaluation 1,762 -> 437 us,
-// error against FP64 7.7e-7 -> 1.8e-7); 512 on 256 x 256, FP64: 639 -> 142 us.
+// leave 2^-25 of a term in FP32, 9 and 15 2^-50 in FP64: 16 rows (mixed 32
+// where that reaches) at the low degree, else at the high one, else 8 rows;
+// beyond that the direct form.
+// Bound by VALU issue: at the low degree 510 instructions a column of 16
+// pixels (32 a pixel) or 820 of 32 (26), the direct form about 130 a pixel.
+// 2,028 cut beamlets on 512 x 512 pixels, mixed: the kernel 1,450 -> 430 us by
+// 16 rows, 300 by 32 (the evaluation 1,762 -> 437, 325 us, error against FP64
+// 7.7e-7 -> 1.8e-7, 1.4e-7); 512 on 256 x 256, FP64: 639 -> 142 us.
 // 512 on 400 x 400, which needs the high degree: 16 rows 155 us, 8 rows 197.
 // ---------------------------------------------------------------------------
 
@@ -339,7 +341,9 @@ __device__ inline void add_column(R ar, R ai, R ur, R ui, R vr, R vi, const R (&
     }
 }
 
-template <int ROWS, int DEG>
+// ONE: a segment is one tile of kMixedTile beamlets at most, so its FP32 sums
+// need no compensation (and 32 rows their registers).
+template <int ROWS, int DEG, bool ONE>
 __global__ void __launch_bounds__(256) cut_column_mixed_kernel(EvalGeom g, const Rec32 *__restrict__ rec,
                                                                const RecCut32 *__restrict__ cut, FaddeevaCoef fc,
                                                                int32_t seg_base, float4 *__restrict__ partial) {
@@ -361,9 +365,12 @@ __global__ void __launch_bounds__(256) cut_column_mixed_kernel(EvalGeom g, const
     const float dyf = (float)dy;
     constexpr float kLog2e = 1.4426950408889634f, kInv2Pi = 0.15915494309189535f;
 
-    float s_re[ROWS], s_im[ROWS], c_re[ROWS], c_im[ROWS], acc_re[ROWS], acc_im[ROWS];
+    constexpr int KS = ONE ? 1 : ROWS;
+    float s_re[KS], s_im[KS], c_re[KS], c_im[KS], acc_re[ROWS], acc_im[ROWS];
 #pragma unroll
-    for (int k = 0; k < ROWS; k++) s_re[k] = s_im[k] = c_re[k] = c_im[k] = acc_re[k] = acc_im[k] = 0.0f;
+    for (int k = 0; k < ROWS; k++) acc_re[k] = acc_im[k] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KS; k++) s_re[k] = s_im[k] = c_re[k] = c_im[k] = 0.0f;
     const int64_t jb = (int64_t)seg * g.seg_len;
     const int64_t je = min(g.n, jb + g.seg_len);
     for (int64_t j0 = jb; j0 < je; j0 += kMixedTile) {
@@ -417,12 +424,13 @@ __global__ void __launch_bounds__(256) cut_column_mixed_kernel(EvalGeom g, const
             add_column<ROWS, DEG>(ma * __builtin_amdgcn_cosf(pa), ma * __builtin_amdgcn_sinf(pa), mu * c1, mu * s1,
                                   md * c1, -(md * s1), m, sq[jj], acc_re, acc_im);
         }
+        if constexpr (!ONE)
 #pragma unroll
-        for (int k = 0; k < ROWS; k++) {
-            kahan(s_re[k], c_re[k], acc_re[k]);
-            kahan(s_im[k], c_im[k], acc_im[k]);
-            acc_re[k] = acc_im[k] = 0.0f;
-        }
+            for (int k = 0; k < ROWS; k++) {
+                kahan(s_re[k], c_re[k], acc_re[k]);
+                kahan(s_im[k], c_im[k], acc_im[k]);
+                acc_re[k] = acc_im[k] = 0.0f;
+            }
     }
     if (ix >= g.nx) return;
     const int64_t M = (int64_t)g.nx * g.ny;
@@ -431,7 +439,8 @@ __global__ void __launch_bounds__(256) cut_column_mixed_kernel(EvalGeom g, const
         const int iy = iy0 + k;
         if (iy < g.ny)
             partial[(int64_t)(seg_base + seg) * M + (int64_t)iy * g.nx + ix] =
-                make_float4(s_re[k], s_im[k], c_re[k], c_im[k]);
+                ONE ? make_float4(acc_re[k], acc_im[k], 0.0f, 0.0f)
+                    : make_float4(s_re[ONE ? 0 : k], s_im[ONE ? 0 : k], c_re[ONE ? 0 : k], c_im[ONE ? 0 : k]);
     }
 }
 
@@ -521,16 +530,19 @@ __global__ void __launch_bounds__(256) cut_column_fp64_kernel(EvalGeom g, const 
 hipError_t launch_eval_cut(int precision, int level, const EvalGeom &g, const void *rec, const void *cut,
                            const FaddeevaCoef &fc, int32_t seg_base, void *partial, hipStream_t s) {
     const int grid = (g.work + 7) / 8 * 8;
+    if (level == 4 && (precision != 1 || g.seg_len > kMixedTile)) return hipErrorInvalidValue;
     if (precision == 1) {
         auto *r = static_cast<const Rec32 *>(rec);
         auto *c = static_cast<const RecCut32 *>(cut);
         auto *p = static_cast<float4 *>(partial);
-        if (level == 3)
-            cut_column_mixed_kernel<kCutRows, 5><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
+        if (level == 4)
+            cut_column_mixed_kernel<2 * kCutRows, 5, true><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
+        else if (level == 3)
+            cut_column_mixed_kernel<kCutRows, 5, false><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
         else if (level == 2)
-            cut_column_mixed_kernel<kCutRows, 9><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
+            cut_column_mixed_kernel<kCutRows, 9, false><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
         else if (level == 1)
-            cut_column_mixed_kernel<kCutRows / 2, 9><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
+            cut_column_mixed_kernel<kCutRows / 2, 9, false><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
         else
             eval_cut_mixed_kernel<kCutRows32, 4><<<grid, 256, 0, s>>>(g, r, c, fc, seg_base, p);
     } else {

@@ -390,8 +390,9 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
                 const double db = 0.5 * (i & 2 ? 1 - pl.ny : pl.ny - 1) * pl.dy - brho;
                 zmax = fmax(zmax, hypot(z0.re + za.re * da + zb.re * db, z0.im + za.im * da + zb.im * db));
             }
-            const double step = hypot(zb.re, zb.im) * pl.dy * (2.0 * zmax + sqrt(32.0));
+            const double zstep = hypot(zb.re, zb.im) * pl.dy, step = zstep * (2.0 * zmax + sqrt(32.0));
             const bool slow = fabs(l[5]) * il2_dev() * pl.dy * pl.dy <= kStepCurvature;
+            if (!(slow && kCutRows * zstep * (2.0 * zmax + sqrt(12.0)) <= kCutReachLow)) flag |= FLAG_CUT0;
             if (!(slow && kCutRows / 2 * step <= kCutReachLow)) flag |= FLAG_CUT1;
             if (!(slow && kCutRows / 2 * step <= kCutReachHigh)) flag |= FLAG_CUT2;
             if (!(slow && kCutRows / 4 * step <= kCutReachHigh)) flag |= FLAG_CUT3;
@@ -715,6 +716,7 @@ __device__ inline void kahan(float &s, float &c, float x) {
 }
 
 constexpr int kMixedTile = 128;  // Rec32 records staged per LDS tile (30 KiB)
+static_assert(kCutOneTile == kMixedTile, "truncated beamlets: host and kernel tiles");
 
 // Mixed-precision sum over beamlets [jb, je) of the ROWS pixels a lane owns:
 // pixel k of the lane sits at plane coordinates (a, b0 + k dy).  The FP64

@@ -136,7 +136,8 @@ static_assert(sizeof(RecCut32) == 32, "RecCut32 layout");
 // the mixed form (4e-7 in exact arithmetic, 5e-7 with FP32 rounding).
 constexpr int kFaddeevaN64 = 40, kFaddeevaN32 = 16;
 constexpr int kCutRows32 = 2, kCutRows64 = 4;  // rows per lane of the truncated-beamlet kernels (4 wavefronts)
-constexpr int kCutRows = 16;  // of their column form (half as many at its lowest level)
+constexpr int kCutRows = 16;  // of their column form (half as many at its lowest level, twice at its highest)
+constexpr int kCutOneTile = 128;
 struct FaddeevaCoef {
     double L64, a64[kFaddeevaN64];
     float L32, a32[kFaddeevaN32];
@@ -174,6 +175,8 @@ enum : uint32_t {
     FLAG_CUT1 = 1024u,
     FLAG_CUT2 = 2048u,
     FLAG_CUT3 = 4096u,
+    // the same as FLAG_CUT1 for a column of twice the rows
+    FLAG_CUT0 = 8192u,
 };
 // largest t = |k zb dy| (2 |zeta| + sqrt(2 p)) over the rows k of a column
 // of the truncated beamlets' column form (gbd_cut.hip): (e t / p)^p is 2^-26
@@ -450,8 +453,9 @@ hipError_t launch_sigma(const EvalGeom &g, const Rec64 *r64, RecSq64 *q64, Rec32
 // Truncated beamlets (direct form with the complex error function): the n
 // beamlets of g (records rec / cut, both starting at the first truncated
 // beamlet) summed per segment into partial segments seg_base + s; precision
-// 0 FP64 (double2 partials), 1 mixed (float4 (sum, compensation)); level 3,
-// 2, 1: the column form (no FLAG_CUT1; no FLAG_CUT2; no FLAG_CUT3), 0: pixel by pixel.
+// 0 FP64 (double2 partials), 1 mixed (float4 (sum, compensation)); level 4
+// (mixed, segments of kCutOneTile beamlets at most), 3, 2, 1: the column form
+// (no FLAG_CUT0; no FLAG_CUT1; ...), 0: pixel by pixel.
 hipError_t launch_eval_cut(int precision, int level, const EvalGeom &g, const void *rec, const void *cut,
                            const FaddeevaCoef &fc, int32_t seg_base, void *partial, hipStream_t s);
 

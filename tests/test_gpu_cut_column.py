@@ -2,7 +2,7 @@
 
 Degrees and rows per column follow from how fast erfc's argument varies over
 the plane, so the planes below go from a fraction of a waist per column to
-several, ragged against its 64 x 64 and 64 x 32 pixel tiles, with deep cuts,
+several, ragged against its 64 x 128, 64 x 64 and 64 x 32 pixel tiles, with deep cuts,
 a dark beamlet and an asymmetric edge set; the pixel-by-pixel form (variant 1)
 is the reference beside the oracle.
 
@@ -36,7 +36,7 @@ def scene(across, nx, ny, span, deep):
 @pytest.mark.parametrize("precision", [gbd.GBD_FP64, gbd.GBD_MIXED])
 @pytest.mark.parametrize("across,nx,ny,span", [
     (60, 65, 33, 1.0), (40, 64, 64, 4.0), (24, 63, 65, 4.0), (24, 100, 31, 4.0), (16, 70, 24, 8.0), (10, 33, 17, 9.0),
-    (30, 1, 40, 3.0), (30, 130, 1, 3.0)])
+    (30, 1, 40, 3.0), (30, 130, 1, 3.0), (150, 66, 70, 0.8), (140, 65, 129, 1.5)])
 @pytest.mark.parametrize("deep", [0, 1])
 def test_column_form_matches_oracle_and_direct(across, nx, ny, span, precision, deep):
     ensure_library()
