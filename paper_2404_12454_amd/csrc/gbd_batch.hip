@@ -108,28 +108,34 @@ __global__ void __launch_bounds__(kRowBlock) batch_setup_kernel(const BatchInst 
     const int halo = I.b.rows ? 1 : 0;
     const int64_t k = (int64_t)(blockIdx.x - blks[i]) * (kRowBlock - halo) + threadIdx.x - halo;
     const bool live = k >= 0 && k < I.b.n, own = live && (int)threadIdx.x >= halo;
-    float pk = -INFINITY;
     uint32_t flag = 0;
-    double ykey[kYKey] = {};
+    const uint32_t bits = I.b.rows && live ? I.b.row_bits[k >> 5] : 0u;  // ahead of what waits for it
+    SetupOut so;
+    so.peak = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < kYKey; q++) so.ykey[q] = 0.0;
     if (live) {
-        double l5v;
-        Rec32 o;
-        flag = setup_one(I.b, I.pl, I.gturns, k, nullptr, rec + I.rec_off, nullptr, nullptr, nullptr, nullptr, false,
-                         &pk, &l5v, &o, ykey, own, I.shared ? terms + i : nullptr);
+        flag = setup_one<false>(I.b, I.pl, I.gturns, k, nullptr, nullptr, own, I.shared != 0,
+                                I.shared ? terms[i] : MatrixTerms(), so);
         if (own) {
-            l5[offs[i] + k] = l5v;
-            if (e0t) e0t[offs[i] + k] = e0_term(o);
+            l5[offs[i] + k] = so.l5;
+            if (e0t) e0t[offs[i] + k] = e0_term(so.rec);
         }
     }
+    __shared__ uint4 stage[7 * kRowBlock];
+    const int64_t first = (int64_t)(blockIdx.x - blks[i]) * (kRowBlock - halo);
+    store_records(stage, so.r32, own ? (int)threadIdx.x - halo : -1,
+                  (int)min((int64_t)(kRowBlock - halo), I.b.n - first),
+                  reinterpret_cast<uint4 *>(rec + I.rec_off + first), kRec32Vec4);
     if (I.b.rows) {  // uniform
         __shared__ double wkey[kRowBlock / 64][kYKey];
-        if (row_check<false>(ykey, live, k, I.b.n, I.b.row_bits, wkey)) rowbad[i] = FLAG_ROWS;
+        if (row_check<false>(so.ykey, live, k, I.b.n, bits, wkey)) rowbad[i] = FLAG_ROWS;
     }
     if (flag) atomicOr(status, flag);
     if (flag & FLAG_ERRORS) atomicMin(bad, i);
     // the instance's largest term over its grid (the FP32 and FP16 sums'
     // range): one atomic per wavefront
-    uint32_t key = (live && isfinite(pk)) ? (uint32_t)fminf(fmaxf(ceilf(pk) + 2048.0f, 1.0f), 4095.0f) : 0u;
+    uint32_t key = isfinite(so.peak) ? (uint32_t)fminf(fmaxf(ceilf(so.peak) + 2048.0f, 1.0f), 4095.0f) : 0u;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) key = max(key, (uint32_t)__shfl_xor((int)key, o));
     if ((threadIdx.x & 63) == 0 && key) atomicMax(peak + i, key);

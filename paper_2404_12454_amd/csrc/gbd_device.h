@@ -74,14 +74,15 @@ __device__ inline double2 rotor_sigma(double p5, double l5, double dy, int k) {
     return make_double2(g * cs, g * sn);
 }
 
-// One beamlet propagated onto the plane; writes its phasor records (either
-// pointer may be null) and returns FLAG_* bits (0 = fine).
-// Higher-order beamlets: h64 / h32 (either may be null) receive the
-// Hermite-Gaussian factor's coefficients of every beamlet (orders (0, 0)
-// give the factor 1).  Truncated beamlets (j >= n - n_cut): c64 / c32
-// receive the truncation factor's coefficients at j - (n - n_cut); their
-// FLAG_STEEP / FLAG_CROSS are not reported (they are evaluated by the
-// direct form of their own kernel).
+__device__ inline RecHG32 hg_to_32(const RecHG64 &h) {
+    RecHG32 o;
+    const double *src = &h.g[0][0][0];
+    float *dst = &o.g[0][0][0];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(RecHG32) / sizeof(float)); i++) dst[i] = (float)src[i];
+    return o;
+}
+
 // log2 of the largest modulus of a separable factor's envelope 2^(c1 d + c2 d^2)
 // over the pixel offsets d_k = d0 + k step, k = 0 .. n-1, of one grid axis:
 // the lattice points at both ends and, for a decaying envelope, the two next
@@ -119,22 +120,35 @@ __device__ inline double log2_hg_envelope_max(double c1, double c2, double d0, d
     return fmax(env + pm(R), env - 64.0 + pm(T));
 }
 
-// sep_peak (optional): log2 of the largest modulus of the beamlet's term over
-// the grid, U's part of it stored in the Rec32 record (pad) for the FP16
-// separable form's range balancing; -inf for a beamlet that contributes nothing.
-// l5_out and r32_copy (optional): the FP64 ln-amplitude curvature l5 (with
-// p5 of the record, the source of the rotor tables when a later pass fills
-// them) and a copy of the finished Rec32 record.
-// ykey (optional): everything the beamlet's y factor is made of.  store
-// false: no record is written (the record pointers still say what is formed).
-// shared (optional): the matrix terms, where all beamlets have the same.
+// One beamlet propagated onto the plane: what a setup kernel stores of it.
 constexpr int kYKey = 11;
-__device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, double gturns, int64_t j,
-                                     Rec64 *r64, Rec32 *r32, RecHG64 *h64 = nullptr, RecHG32 *h32 = nullptr,
-                                     RecCut64 *c64 = nullptr, RecCut32 *c32 = nullptr, bool sigma32 = true,
-                                     float *sep_peak = nullptr, double *l5_out = nullptr,
-                                     Rec32 *r32_copy = nullptr, double *ykey = nullptr, bool store = true,
-                                     const MatrixTerms *shared = nullptr) {
+template <int Q>
+struct Words {
+    uint4 v[Q];
+};
+struct SetupOut {
+    Rec32 rec;                                 // the record but for its rotor tables, and as words:
+    Words<sizeof(Rec64) / 16> r64;
+    Words<offsetof(Rec32, sq) / 16> r32;
+    // with HG the Hermite-Gaussian factor's coefficients (orders (0, 0): the factor 1)
+    Words<sizeof(RecHG64) / 16> h64;
+    Words<sizeof(RecHG32) / 16> h32;
+    // log2 of the largest modulus of the beamlet's term over the grid, U's
+    // part of it in the Rec32 record (pad) for the FP16 separable form's range
+    // balancing; -inf for a beamlet that contributes nothing
+    float peak;
+    double l5;                                 // ln-amplitude curvature, a source of the rotor tables
+    double ykey[kYKey];                        // everything the beamlet's y factor is made of
+};
+// Returns FLAG_* bits (0 = fine).  Truncated beamlets (j >= n - n_cut): c64 /
+// c32 receive the truncation factor's coefficients at j - (n - n_cut), with
+// store; their FLAG_STEEP / FLAG_CROSS are not reported (they are evaluated by
+// their own kernel).  shared: with have_mt the matrix terms, where all
+// beamlets have the same.  Inlined by force: `so` stays in registers.
+template <bool HG>
+__device__ __forceinline__ uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, double gturns, int64_t j,
+                                              RecCut64 *c64, RecCut32 *c32, bool store, bool have_mt,
+                                              const MatrixTerms &shared, SetupOut &so) {
     const double *M = b.abcd + (b.n_abcd == 1 ? 0 : 16 * j);
     double A[2][2], B[2][2], C[2][2], D[2][2];
 #pragma unroll
@@ -187,8 +201,8 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
 
         // complex curvature and amplitude on the plane
         MatrixTerms mt;
-        if (shared)
-            mt = *shared;
+        if (have_mt)
+            mt = shared;
         else
             mt = matrix_terms(M, z, lam, w0);
         cd Q[2][2];
@@ -253,10 +267,9 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         bool fin = isfinite(arho) && isfinite(brho) && isfinite(ag.re) && isfinite(ag.im);
         // higher-order factors' coefficient moduli (x: |cx0|, |cx1|, |cx2|, |g_xx|; y likewise)
         double hgb[8] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0};
-        bool has_hgb = false;
 #pragma unroll
         for (int i = 0; i < 6; i++) fin = fin && isfinite(p[i]) && (i == 0 || isfinite(l[i]));
-        if (h64 || h32) {
+        if constexpr (HG) {
             // elegant Hermite-Gaussian factor: with A' = A + z C, the
             // derivatives of the envelope's log E with respect to the input
             // centre are L w (L = -i k (C^T - A'^T Q)) and the constant
@@ -315,7 +328,6 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
             hgb[5] = fabs(oh.cy1);
             hgb[6] = fabs(oh.cy2);
             hgb[7] = hypot(Gh[1][1].re, Gh[1][1].im);
-            has_hgb = true;
             const cd k1 = scl(hxy, (double)(hm * hn));
             const cd k0 = (hm == 2 && hn == 2) ? scl(mul(hxy, hxy), 2.0) : mk(0.0, 0.0);
             oh.k1[0] = k1.re;
@@ -440,25 +452,15 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
             // (with a higher-order factor, times its axis polynomial's bound)
             const double umax =
                 (double)o32.m[0] +
-                (has_hgb ? log2_hg_envelope_max(o32.m[1], o32.m[3], a0 - arho, pl.dx, pl.nx, hgb[0], hgb[1], hgb[2],
+                (HG ? log2_hg_envelope_max(o32.m[1], o32.m[3], a0 - arho, pl.dx, pl.nx, hgb[0], hgb[1], hgb[2],
                                                 hgb[3])
                          : log2_envelope_max(o32.m[1], o32.m[3], a0 - arho, pl.dx, pl.nx));
-            const double vmax = has_hgb ? log2_hg_envelope_max(o32.m[2], o32.m[5], b0 - brho, pl.dy, pl.ny, hgb[4],
+            const double vmax = HG ? log2_hg_envelope_max(o32.m[2], o32.m[5], b0 - brho, pl.dy, pl.ny, hgb[4],
                                                                hgb[5], hgb[6], hgb[7])
                                         : log2_envelope_max(o32.m[2], o32.m[5], b0 - brho, pl.dy, pl.ny);
             const bool ok = isfinite(umax) && isfinite(vmax);
             o32.pad = ok ? (float)umax : 0.0f;
-            if (sep_peak) *sep_peak = ok ? (float)(umax + vmax) : -INFINITY;
-        }
-        // rotor form: sigma^(k^2), rounded from FP64 (else left to
-        // sigma32_kernel, run only before a rotor-form evaluation)
-        if (sigma32) {
-#pragma unroll
-            for (int k = 1; k <= kRotorRows; k++) {
-                const double2 sq = rotor_sigma(p[5], l[5], pl.dy, k);
-                o32.sq[k - 1][0] = (float)sq.x;
-                o32.sq[k - 1][1] = (float)sq.y;
-            }
+            so.peak = ok ? (float)(umax + vmax) : -INFINITY;
         }
     }
     if (flag & FLAG_ERRORS) {
@@ -466,29 +468,23 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         o64.l[0] = -INFINITY;
         o32.m[0] = -INFINITY;
     }
-    if (l5_out) *l5_out = o64.l[5];
-    if (r32_copy) *r32_copy = o32;
-    if (ykey) {
+    so.rec = o32;
+    so.l5 = o64.l[5];
+    {
         const double v[kYKey] = {o64.brho,       o64.p[2],  o64.p[5],  o64.l[2], o64.l[5], oh.g[1][1][0],
                                  oh.g[1][1][1], oh.cy0[0], oh.cy0[1], oh.cy1,   oh.cy2};
 #pragma unroll
-        for (int k = 0; k < kYKey; k++) ykey[k] = v[k];
+        for (int k = 0; k < kYKey; k++) so.ykey[k] = v[k];
+    }
+    so.r64 = __builtin_bit_cast(Words<sizeof(Rec64) / 16>, o64);
+    const auto w32 = __builtin_bit_cast(Words<sizeof(Rec32) / 16>, o32);
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(so.r32) / 16); k++) so.r32.v[k] = w32.v[k];
+    if constexpr (HG) {
+        so.h64 = __builtin_bit_cast(Words<sizeof(RecHG64) / 16>, oh);
+        so.h32 = __builtin_bit_cast(Words<sizeof(RecHG32) / 16>, hg_to_32(oh));
     }
     if (!store) return flag;
-    if (r64) r64[j] = o64;
-    if (r32) {
-        if (sigma32) {
-            r32[j] = o32;
-        } else {
-            // the rotor tables are left to launch_sigma, run before every
-            // rotor-form evaluation: the record's first 112 bytes only
-            static_assert(offsetof(Rec32, sq) == 112, "Rec32 layout");
-            const uint4 *src = reinterpret_cast<const uint4 *>(&o32);
-            uint4 *dst = reinterpret_cast<uint4 *>(r32 + j);
-#pragma unroll
-            for (int k = 0; k < 7; k++) dst[k] = src[k];
-        }
-    }
     if (is_cut && c64) c64[j - cut0] = oc;
     if (is_cut && c32) {
         RecCut32 o;
@@ -501,28 +497,42 @@ __device__ inline uint32_t setup_one(const BeamletsDev &b, const PlaneGeom &pl, 
         }
         c32[j - cut0] = o;
     }
-    if (h64) h64[j] = oh;
-    if (h32) {
-        RecHG32 o;
-        const double *src = &oh.g[0][0][0];
-        float *dst = &o.g[0][0][0];
-#pragma unroll
-        for (int i = 0; i < (int)(sizeof(RecHG32) / sizeof(float)); i++) dst[i] = (float)src[i];
-        h32[j] = o;
-    }
     return flag;
+}
+
+// Q words of 16 bytes of each of the workgroup's cnt records to dst (records
+// `stride` words apart), from the thread that holds slot `slot` (none: < 0)
+// through LDS: thread by thread a store touched one cache line per lane, 15 of
+// them 1.5 to 2.5 us of the setup and more of its end (812 beamlets 8.4 -> 7.5
+// us, 51,468 14.3 -> 11.8, of higher order 22.5 -> 17.7); in order they fill
+// whole lines.  Slots an odd number of words apart keep LDS free of conflicts.
+constexpr int kStageWords = 13 * kRowBlock;  // the largest record, 12 words
+template <int Q>
+__device__ __forceinline__ void store_records(uint4 *stage, const Words<Q> &w, int slot, int cnt, uint4 *__restrict__ dst,
+                                     int stride = Q) {
+    constexpr int P = Q | 1;
+    static_assert(P * kRowBlock <= kStageWords, "setup staging");
+    __syncthreads();
+    if (slot >= 0)
+#pragma unroll
+        for (int k = 0; k < Q; k++) stage[P * slot + k] = w.v[k];
+    __syncthreads();
+    for (int i = threadIdx.x; i < Q * cnt; i += kRowBlock) {
+        const int r = i / Q, k = i - r * Q;
+        dst[(int64_t)r * stride + k] = stage[P * r + k];
+    }
 }
 
 // Setups of beamlets with a row table run kRowBlock - 1 beamlets to a
 // workgroup of kRowBlock threads, thread 0 repeating the beamlet before them,
 // so that each beamlet can be compared with its predecessor.  row_check:
 // FLAG_ROWS if thread t > 0's beamlet (local index j < n) continues a row
-// chunk (no chunk starts there, `bits`) but its y factor differs from its
+// chunk (no chunk starts there: bits, the word of row_bits that holds j) but its y factor differs from its
 // predecessor's; 0 otherwise.  The whole workgroup calls it (it
 // synchronises), wkey its LDS; HG: compares the higher-order words too.
 template <bool HG>
 __device__ inline uint32_t row_check(const double (&key)[kYKey], bool live, int64_t j, int64_t n,
-                                     const uint32_t *__restrict__ bits, double (*wkey)[kYKey]) {
+                                     uint32_t bits, double (*wkey)[kYKey]) {
     constexpr int K = HG ? kYKey : 5;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 63)
@@ -536,7 +546,7 @@ __device__ inline uint32_t row_check(const double (&key)[kYKey], bool live, int6
         if (lane == 0 && w > 0) prev = wkey[w - 1][k];
         diff = diff || !(prev == key[k]);
     }
-    if (!live || threadIdx.x == 0 || j >= n || ((bits[j >> 5] >> (j & 31)) & 1u)) return 0u;
+    if (!live || threadIdx.x == 0 || j >= n || ((bits >> (j & 31)) & 1u)) return 0u;
     return diff ? FLAG_ROWS : 0u;
 }
 

@@ -20,6 +20,7 @@ namespace {
 
 using namespace dev;
 
+template <bool HG>
 __global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGeom pl, double gturns, MatrixTerms mt,
                                                     int have_mt,
                                                     Rec64 *__restrict__ r64, Rec32 *__restrict__ r32,
@@ -34,25 +35,28 @@ __global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGe
         status_next[0] = 0u;
         status_next[1] = 0u;
     }
-    float peak = -INFINITY;
     uint32_t flag = 0;
-    double ykey[kYKey] = {};
     const bool live = j >= 0 && j < b.n;
-    if (live)
-        flag = setup_one(b, pl, gturns, j, r64, r32, h64, h32, c64, c32, false, &peak, nullptr, nullptr, ykey,
-                         (int)threadIdx.x >= halo, have_mt ? &mt : nullptr);
+    // the row table's words, ahead of what they wait for
+    const bool in_rows = b.rows && live && j < b.n - b.n_cut, copies_row = b.rows && live && j <= b.rows;
+    const uint32_t bits = in_rows ? b.row_bits[j >> 5] : 0u;
+    const int32_t row = copies_row ? b.row_start[j] : 0;
+    SetupOut so;
+    so.peak = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < kYKey; q++) so.ykey[q] = 0.0;
+    if (live) flag = setup_one<HG>(b, pl, gturns, j, c64, c32, (int)threadIdx.x >= halo, have_mt != 0, mt, so);
     if (b.rows) {  // uniform
         __shared__ double wkey[kRowBlock / 64][kYKey];
-        flag |= h64 ? row_check<true>(ykey, live, j, b.n - b.n_cut, b.row_bits, wkey)
-                    : row_check<false>(ykey, live, j, b.n - b.n_cut, b.row_bits, wkey);
-        if (live && j <= b.rows) row_out[j] = b.row_start[j];
+        flag |= row_check<HG>(so.ykey, live, j, b.n - b.n_cut, bits, wkey);
+        if (copies_row) row_out[j] = row;
     }
     // status[0]: the flags OR-ed; status[1]: the largest term modulus of any
     // beamlet over the grid, as ceil(log2) + 2048 clamped to [1, 4095] (0:
     // none).  One atomic of each per workgroup: the words are shared by the
     // whole grid, so per-lane atomics serialise (an informational flag such as
     // FLAG_STEEP is set by most beamlets)
-    uint32_t key = isfinite(peak) ? (uint32_t)fminf(fmaxf(ceilf(peak) + 2048.0f, 1.0f), 4095.0f) : 0u;
+    uint32_t key = isfinite(so.peak) ? (uint32_t)fminf(fmaxf(ceilf(so.peak) + 2048.0f, 1.0f), 4095.0f) : 0u;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         key = max(key, (uint32_t)__shfl_xor((int)key, o));
@@ -72,6 +76,16 @@ __global__ void __launch_bounds__(kRowBlock) setup_kernel(BeamletsDev b, PlaneGe
         }
         if (f) atomicOr(status, f);
         if (k) atomicMax(status + 1, k);
+    }
+    __shared__ uint4 stage[HG ? kStageWords : 9 * kRowBlock];
+    const int slot = live ? (int)threadIdx.x - halo : -1;
+    const int64_t first = (int64_t)blockIdx.x * (kRowBlock - halo);
+    const int cnt = (int)min((int64_t)(kRowBlock - halo), b.n - first);
+    store_records(stage, so.r64, slot, cnt, reinterpret_cast<uint4 *>(r64 + first));
+    store_records(stage, so.r32, slot, cnt, reinterpret_cast<uint4 *>(r32 + first), kRec32Vec4);
+    if constexpr (HG) {
+        store_records(stage, so.h64, slot, cnt, reinterpret_cast<uint4 *>(h64 + first));
+        store_records(stage, so.h32, slot, cnt, reinterpret_cast<uint4 *>(h32 + first));
     }
 }
 
@@ -529,11 +543,17 @@ hipError_t launch_setup(const BeamletsDev &b, const PlaneGeom &pl, double global
                         Rec64 *r64, Rec32 *r32, RecHG64 *h64, RecHG32 *h32, RecCut64 *c64, RecCut32 *c32, uint32_t *status,
                         uint32_t *status_next, int32_t *row_out, hipStream_t s) {
     if (b.n == 0) return hipSuccess;
-    if (b.rows >= b.n || (b.rows && !row_out)) return hipErrorInvalidValue;  // the threads copy rows + 1 entries
+    if (!r64 || !r32 || !h64 != !h32 || (b.rows && !row_out)) return hipErrorInvalidValue;
+    if (b.rows >= b.n) return hipErrorInvalidValue;  // the threads copy rows + 1 entries
     const int per = kRowBlock - (b.rows ? 1 : 0);
     const int64_t blocks = (b.n + per - 1) / per;
-    setup_kernel<<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, shared ? *shared : MatrixTerms{}, shared != nullptr,
-                                                        r64, r32, h64, h32, c64, c32, status, status_next, row_out);
+    const MatrixTerms mt = shared ? *shared : MatrixTerms{};
+    if (h64)
+        setup_kernel<true><<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, mt, shared != nullptr, r64, r32,
+                                                                  h64, h32, c64, c32, status, status_next, row_out);
+    else
+        setup_kernel<false><<<(unsigned)blocks, kRowBlock, 0, s>>>(b, pl, global_turns, mt, shared != nullptr, r64, r32,
+                                                                   h64, h32, c64, c32, status, status_next, row_out);
     return hipGetLastError();
 }
 
