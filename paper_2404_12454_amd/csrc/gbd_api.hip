@@ -40,7 +40,7 @@ struct DevBuf {
 };
 
 struct BatchWork {
-    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, row_v, terms;
+    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, terms;
     uint32_t *host_flags = nullptr;  // pinned: the point evaluation's status
     void *stage = nullptr;           // pinned staging of the batch tables
     size_t stage_bytes = 0;
@@ -164,9 +164,8 @@ struct gbd_plan_s {
     RecCut32 *c32;
     int64_t n_cut;  // truncated beamlets of the last setup (the last n_cut records)
     int32_t rows;   // row chunks of the last setup's beamlets (0: no table)
-    int32_t *row_start;  // the last setup's chunk table, and the chunks' y factors (RowV32 / RowV64)
-    void *row_v;
-    int64_t row_cap;     // chunks both hold, allocated at the first setup of beamlets with a table
+    int32_t *row_start;  // the last setup's chunk table
+    int64_t row_cap;     // chunks it holds, allocated at the first setup of beamlets with a table
     uint32_t *status_dev;   // two (flags, peak) word pairs used by alternate setups; each setup clears the other
     int status_parity;      // the pair the next setup uses
     bool status_zeroed;     // both words cleared (once, before the first setup)
@@ -751,7 +750,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     // The fixed buffer has to hold the row sums beside any partials.
     bool by_rows = !general && s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
                    (precision == GBD_FP64 || s.half);
-    const size_t row_bytes = by_rows ? (size_t)plan->rows * (size_t)plan->pl.nx * (size_t)elem : 0;
+    const size_t row_bytes = by_rows ? (size_t)plan->rows * ((size_t)plan->pl.nx + plan->pl.ny) * (size_t)elem : 0;
     auto row_offset = [&](int64_t nc) -> size_t {  // where the row sums start, with nc truncated segments
         const size_t part = nc == 0 ? 0 : reduce_wide_offset(compact ? 1 : 0, M) + (size_t)(nc + (compact ? 0 : 1)) * M * 16;
         return (part + 255) & ~(size_t)255;
@@ -901,12 +900,12 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
             }
             if (precision == GBD_FP64)
                 HIP_TRY(launch_rows64(rg, plan->row_start, plan->r64, static_cast<const RecHG64 *>(hrec),
-                                      static_cast<double2 *>(sums), static_cast<RowV64 *>(plan->row_v),
+                                      static_cast<double2 *>(sums),
                                       static_cast<double2 *>(dst), gd, ctx->stream, tev.first, tev.second, sp),
                         "row kernels launch");
             else
                 HIP_TRY(launch_rows32(rg, plan->row_start, plan->r32, static_cast<const RecHG32 *>(hrec),
-                                      plan->status_cur, static_cast<float2 *>(sums), static_cast<RowV32 *>(plan->row_v),
+                                      plan->status_cur, static_cast<float2 *>(sums),
                                       static_cast<float2 *>(dst), gd, ctx->stream, tev.first, tev.second, sp),
                         "row kernels launch");
         } else if (s.cross)
@@ -1000,12 +999,9 @@ int plan_setup_launch(gbd_ctx_s *ctx, gbd_plan_s *plan, gbd_beamlets_s *b, gbd_p
         // for any beamlets the plan takes (at most one chunk per kRowGain beamlets)
         const int64_t cap = std::max<int64_t>(plan->rows, plan->capacity / kRowGain);
         if (plan->row_start) (void)hipFree(plan->row_start);
-        if (plan->row_v) (void)hipFree(plan->row_v);
         plan->row_start = nullptr;
-        plan->row_v = nullptr;
         plan->row_cap = 0;
         HIP_TRY(hipMalloc(&plan->row_start, (size_t)(cap + 1) * sizeof(int32_t)), "hipMalloc(row chunks)");
-        HIP_TRY(hipMalloc(&plan->row_v, (size_t)cap * sizeof(RowV64)), "hipMalloc(row chunks)");
         plan->row_cap = cap;
     }
     if (b->dev.n > 0) {
@@ -1090,7 +1086,6 @@ void plan_destroy(gbd_plan_s *plan) {
     if (plan->c64) (void)hipFree(plan->c64);
     if (plan->c32) (void)hipFree(plan->c32);
     if (plan->row_start) (void)hipFree(plan->row_start);
-    if (plan->row_v) (void)hipFree(plan->row_v);
     if (plan->status_dev) (void)hipFree(plan->status_dev);
     if (plan->scratch) (void)hipFree(plan->scratch);
     if (plan->status_post) {
@@ -1135,7 +1130,7 @@ int grow(DevBuf &b, size_t bytes, const char *what) {
 
 void batch_free(BatchWork &w) {
     DevBuf *all[] = {&w.rec,    &w.l5,   &w.e0t,     &w.tab1,  &w.tab2, &w.e0,
-                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.row_v, &w.terms};
+                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.terms};
     if (w.stage_ev) {
         (void)hipEventSynchronize(w.stage_ev);
         (void)hipEventDestroy(w.stage_ev);
@@ -2018,7 +2013,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     int32_t *sum_inst = reinterpret_cast<int32_t *>(h2 + t2_rows), *sum_first = sum_inst + n_inst,
             *prod_inst = sum_first + n_inst + 1, *prod_first = prod_inst + n_inst;
     BatchRows br{};
-    int32_t sum_blocks = 0, v_off = 0;
+    int32_t sum_blocks = 0;
     int64_t sum_off = 0;
     int64_t foff = 0;
     int32_t n_chunks = 0;
@@ -2035,9 +2030,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
             e.rows = b.rows;
             e.row_start = b.row_start;
             e.sum_off = sum_off;
-            e.v_off = v_off;
-            sum_off += (int64_t)b.rows * g.nx;
-            v_off += b.rows;
+            sum_off += (int64_t)b.rows * (g.nx + g.ny);
             sum_inst[br.n] = i;
             sum_first[br.n++] = sum_blocks;
             const int cols = g.nx > 64 ? 128 : 64;
@@ -2114,9 +2107,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
             ev[i].item_off = n_part;
             n_part += (int64_t)ev[i].tiles_x * ev[i].tiles_y;
         }
-    if ((rc = grow(w.row_sums, (size_t)std::max<int64_t>(sum_off, 1) * sizeof(float2), "batch row sums")) ||
-        (rc = grow(w.row_v, (size_t)std::max<int32_t>(v_off, 1) * sizeof(RowV32), "batch row factors")))
-        return rc;
+    if ((rc = grow(w.row_sums, (size_t)std::max<int64_t>(sum_off, 1) * sizeof(float2), "batch row sums"))) return rc;
     // the tables up to the last part in use (the work list is empty when every instance goes by rows)
     const size_t t2_used = br.n ? t2_bytes : t2_e0map + (size_t)n_chunks * sizeof(int32_t);
     HIP_TRY(hipMemcpyAsync(d2, h2, t2_used, hipMemcpyHostToDevice, st), "table upload");
@@ -2150,7 +2141,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         br.prod_first = lists + 3 * n_inst + 1;
         br.peaks = flags + 4;
         br.sums = static_cast<float2 *>(w.row_sums.p);
-        HIP_TRY(launch_batch_rows(a, br, sum_blocks, static_cast<RowV32 *>(w.row_v.p), st), "batch row launch");
+        HIP_TRY(launch_batch_rows(a, br, sum_blocks, st), "batch row launch");
     }
     HIP_TRY(launch_batch_eval(rows, waves, form, half, ctx->cus, a, st), "batch eval launch");
     if (airy) {

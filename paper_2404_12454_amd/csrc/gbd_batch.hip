@@ -409,24 +409,22 @@ __global__ void __launch_bounds__(64 * BatchTile<HALF>::WX * BatchTile<HALF>::WY
 // Row sums of the instances taken by rows, then their products with the
 // figure of merit's partials: the single evaluation's arithmetic (so a field
 // equals gbd_eval's bit for bit), see gbd_rows.hip.
-__global__ void __launch_bounds__(64 * rows::kRowSumWaves) batch_row_sum_kernel(BatchArgs A, BatchRows B,
-                                                                               RowV32 *__restrict__ v) {
+__global__ void __launch_bounds__(64 * rows::kRowSumWaves) batch_row_sum_kernel(BatchArgs A, BatchRows B) {
     const int k = list_entry(B.sum_first, B.n, (int32_t)blockIdx.x);
     const int i = B.sum_inst[k];
     const BatchEval &I = A.inst[i];
     const RowGeom g{I.nx, I.ny, I.dx, I.dy, I.a0, I.b0, I.rows};
     if (I.nx > 64)
         rows::row_sum_block32<false, 2>(g, blockIdx.x - B.sum_first[k], I.row_start, A.rec + I.rec_off, nullptr,
-                                        B.peaks[i], B.sums + I.sum_off, v + I.v_off);
+                                        B.peaks[i], B.sums + I.sum_off);
     else
         rows::row_sum_block32<false, 1>(g, blockIdx.x - B.sum_first[k], I.row_start, A.rec + I.rec_off, nullptr,
-                                        B.peaks[i], B.sums + I.sum_off, v + I.v_off);
+                                        B.peaks[i], B.sums + I.sum_off);
 }
 
-__global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel(BatchArgs A, BatchRows B,
-                                                                               const RowV32 *__restrict__ v) {
+__global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel(BatchArgs A, BatchRows B) {
     constexpr int NQ = 2 + 2 * kMaxZones, WAVES = rows::kRowWaves;
-    __shared__ float2 part[WAVES][256 * rows::kFoldBlocks<RowV32>];
+    __shared__ float2 part[WAVES][256 * rows::kFoldBlocks<float2>];
     __shared__ double red[WAVES][NQ];
     const int x = blockIdx.x % kXcds, r = blockIdx.x / kXcds;
     if (r >= B.prod_tiles[x]) return;
@@ -444,7 +442,8 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
             if (ix < I.nx && iy < I.ny) ref[p] = A.airy[(int64_t)iy * I.nx + ix];
         }
     sep::f4 re[2][2], im[2][2];
-    rows::row_product<false>(v + I.v_off, B.sums + I.sum_off, I.rows, I.nx, I.a0, I.b0, I.dy, x0, y0, re, im);
+    const float2 *sums = B.sums + I.sum_off;
+    rows::row_product(sums, sums + (int64_t)I.rows * I.nx, I.rows, I.nx, I.ny, x0, y0, re, im);
     const int P = (int)rows::row_exponent(B.peaks[i]);
     double q[NQ];
 #pragma unroll
@@ -455,7 +454,7 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
         const double n0 = f0.x * f0.x + f0.y * f0.y;
         inv0 = n0 > 0.0 ? 1.0 / n0 : 0.0;
     }
-    rows::row_fold<RowV32>(re, im, part, [&](int p, int c, int k, double sr, double si) {
+    rows::row_fold<float2>(re, im, part, [&](int p, int c, int k, double sr, double si) {
         const int ix = x0 + 16 * c + (k & 15), iy = y0 + 16 * p + (k >> 4);
         if (ix >= I.nx || iy >= I.ny) return;
         const int64_t px = (int64_t)iy * I.nx + ix;
@@ -570,14 +569,14 @@ hipError_t launch_batch_setup(const BatchInst *inst, const int64_t *offs, const 
     return hipGetLastError();
 }
 
-hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, RowV32 *v, hipStream_t s) {
+hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, hipStream_t s) {
     if (r.n == 0 || sum_blocks == 0) return hipSuccess;
-    batch_row_sum_kernel<<<(unsigned)sum_blocks, 64 * rows::kRowSumWaves, 0, s>>>(a, r, v);
+    batch_row_sum_kernel<<<(unsigned)sum_blocks, 64 * rows::kRowSumWaves, 0, s>>>(a, r);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int32_t most = 0;
     for (int x = 0; x < kXcds; x++) most = max(most, r.prod_tiles[x]);
-    batch_row_product_kernel<<<(unsigned)(kXcds * most), 64 * rows::kRowWaves, 0, s>>>(a, r, v);
+    batch_row_product_kernel<<<(unsigned)(kXcds * most), 64 * rows::kRowWaves, 0, s>>>(a, r);
     return hipGetLastError();
 }
 

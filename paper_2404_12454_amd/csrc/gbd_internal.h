@@ -228,11 +228,11 @@ struct BatchEval {
     int32_t scale;      // FP16 halves form: its accumulators hold the field times 2^scale
     int32_t e0_off, e0_chunks;  // its normalisation chunks (kE0Chunk beamlets each), contiguous
     // an instance taken by rows (launch_batch_rows): its chunk table, and where
-    // its row sums [rows][nx] and y factors [rows] start; its tiles are the row
-    // product's
+    // its row sums [rows][nx] and y factors [rows][ny] start; its tiles are the
+    // row product's
     const int32_t *row_start;
     int64_t sum_off;
-    int32_t rows, v_off;
+    int32_t rows;
 };
 
 // beamlets per workgroup of the normalisation sum
@@ -299,10 +299,8 @@ hipError_t launch_batch_e0(const BatchEval *inst, int32_t n_inst, const int32_t 
 // when half (scales from BatchEval::scale), else on FP32 MFMA
 hipError_t launch_batch_eval(int rows, int waves, int form, bool half, int cus, const BatchArgs &a, hipStream_t s);
 // The instances of r in the row-factored form (a.inst, a.rec, a.e0, a.airy,
-// a.fields, a.part and the zones as for launch_batch_eval); v: RowV32 scratch
-// for all their chunks.
-struct RowV32;
-hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, RowV32 *v, hipStream_t s);
+// a.fields, a.part and the zones as for launch_batch_eval).
+hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum_blocks, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchEval *inst, int32_t n_inst, const double *part, int32_t n_zones,
                                  double *metrics, hipStream_t s);
 hipError_t launch_airy(int32_t nx, int32_t ny, double dx, double dy, double vscale, float *out, hipStream_t s);
@@ -569,30 +567,17 @@ struct RowGeom {
     double dx, dy, a0, b0;
     int32_t chunks;
 };
-// A chunk's y factor, gathered by the row sums for the product (lv0: log2 of
-// its scale, minus the bound of its modulus over the grid rows).
-struct alignas(16) RowV32 {
-    double brho, p2, p5;
-    float m2, m5, lv0;
-    float gyr, gyi, cy0r, cy0i, cy1, cy2, pad;
-};
-static_assert(sizeof(RowV32) == 64, "RowV32 layout");
-struct alignas(16) RowV64 {
-    double brho, p2, p5, l2, l5;
-    double gyr, gyi, cy0r, cy0i, cy1, cy2, pad;
-};
-static_assert(sizeof(RowV64) == 96, "RowV64 layout");
-// Row chunks of beamlets [0, start[chunks]) from the records: sums [chunks][nx]
-// and V factors [chunks] are scratch.  Mixed: status[1] is the setup's key
+// Row chunks of beamlets [0, start[chunks]) from the records: sums is scratch
+// for the sums [chunks][nx] and behind them the y factors [chunks][ny].  Mixed: status[1] is the setup's key
 // (the largest term's log2, the FP32 sums' common scale).  Writes out, or
 // partial when out is null (complex64 / complex128), unless the guard's
 // condition fails.  t0 / t1 time the two kernels from the first one's start
 // to the second one's end; sp: a setup status to post at the start.
 hipError_t launch_rows32(const RowGeom &g, const int32_t *start, const Rec32 *rec, const RecHG32 *hg,
-                         const uint32_t *status, float2 *sums, RowV32 *v, float2 *out, const EvalGuard &guard,
+                         const uint32_t *status, float2 *sums, float2 *out, const EvalGuard &guard,
                          hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp);
 hipError_t launch_rows64(const RowGeom &g, const int32_t *start, const Rec64 *rec, const RecHG64 *hg, double2 *sums,
-                         RowV64 *v, double2 *out, const EvalGuard &guard, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
+                         double2 *out, const EvalGuard &guard, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
                          const StatusPost &sp);
 
 // The same form for fundamental beamlets on FP16 MFMA (v_mfma_f32_16x16x32_f16)

@@ -126,6 +126,17 @@ __device__ inline double2 row_step64(const Rec64 &r, double dx) {
     return cexp_turns64(2.0 * r.l[3] * dx * dx, T);
 }
 
+// A chunk's y factor (lv0: log2 of its scale, minus the bound of its modulus
+// over the grid rows).
+struct RowV32 {
+    double brho, p2, p5;
+    float m2, m5, lv0;
+    float gyr, gyi, cy0r, cy0i, cy1, cy2;
+};
+struct RowV64 {
+    double brho, p2, p5, l2, l5;
+    double gyr, gyi, cy0r, cy0i, cy1, cy2;
+};
 // The chunk's y factor from its first beamlet's record.  lv0 = minus the
 // bound of log2 |V| over the grid rows, so |V| 2^lv0 <= 1; the x factors
 // take the rest of the common scale, 2^(-lv0 - P), 2^P the largest term over
@@ -201,20 +212,34 @@ __device__ inline void row_item(int b, int nx, int &c, int &x0) {
     x0 = (b - c * nb) * 64 * C;
 }
 
+// The y factors [chunks][ny] lie behind the row sums [chunks][nx].
+template <typename R2>
+__host__ __device__ inline R2 *row_vtab(const RowGeom &g, R2 *sums) { return sums + (int64_t)g.chunks * g.nx; }
+
+// The chunk's y factors over the grid rows, shared out over the workgroups of
+// its column blocks (`cols` columns each): once each, where the tiles of the
+// product would form them nx / 32 times.
+template <bool HG, typename V, typename R2>
+__device__ inline void row_table(const RowGeom &g, const V &v, int c, int x0, int cols, R2 *__restrict__ vtab) {
+    const int nb = (g.nx + cols - 1) / cols, per = (g.ny + nb - 1) / nb, k = x0 / cols;
+    for (int y = k * per + threadIdx.x; y < min(g.ny, (k + 1) * per); y += 64 * kRowSumWaves)
+        vtab[(int64_t)c * g.ny + y] = row_factor<HG>(v, g.b0 + y * g.dy);
+}
+
 // Workgroup b of the FP32 row sums: its wavefronts take every fourth beamlet
 // of the chunk each, and their sums are added in order.  key: the setup's
 // (largest term).
 template <bool HG, int C>
 __device__ inline void row_sum_block32(const RowGeom &g, int b, const int32_t *__restrict__ start,
                                        const Rec32 *__restrict__ rec, const RecHG32 *__restrict__ hg, uint32_t key,
-                                       float2 *__restrict__ sums, RowV32 *__restrict__ v) {
+                                       float2 *__restrict__ sums) {
     __shared__ float2 part[kRowSumWaves][64 * C];
     int c, x0;
     row_item<C>(b, g.nx, c, x0);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j0 = start[c], j1 = start[c + 1];
     const RowV32 rv = row_v32<HG>(rec[j0], HG ? hg + j0 : nullptr, g.b0, g.dy, g.ny);
-    if (x0 == 0 && threadIdx.x == 0) v[c] = rv;
+    row_table<HG>(g, rv, c, x0, 64 * C, row_vtab(g, sums));
     double ax[C];
     float2 t[C];
 #pragma unroll
@@ -237,20 +262,18 @@ __device__ inline void row_sum_block32(const RowGeom &g, int b, const int32_t *_
 __device__ inline f4 row_mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 __device__ inline d4 row_mfma(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
-template <typename V>
+template <typename R2>
 struct RowType;
 template <>
-struct RowType<RowV32> {
+struct RowType<float2> {
     using R = float;
-    using R2 = float2;
     using A4 = f4;
     // row of element e of a result block
     __device__ static int row(int lk, int e) { return 4 * lk + e; }
 };
 template <>
-struct RowType<RowV64> {
+struct RowType<double2> {
     using R = double;
-    using R2 = double2;
     using A4 = d4;
     __device__ static int row(int lk, int e) { return lk + 4 * e; }
 };
@@ -260,56 +283,49 @@ struct RowType<RowV64> {
 // workgroup's wavefront w.  Lane l holds chunk 4 step + l / 16: its y factor
 // at rows 16 p + l % 16 as the A operand, its row sum at columns
 // 16 q + l % 16 as the B operand.  Four real products per complex one.
-// Chunks past the end and columns past the grid read a clamped element and
+// Chunks past the end and pixels past the grid read a clamped element and
 // count as zero / are not stored.
-template <bool HG, typename V>
-__device__ inline void row_product(const V *__restrict__ v, const typename RowType<V>::R2 *__restrict__ sums, int chunks,
-                                   int nx, double a0, double b0, double dy, int x0, int y0,
-                                   typename RowType<V>::A4 (&re)[2][2], typename RowType<V>::A4 (&im)[2][2]) {
-    using R = typename RowType<V>::R;
-    using R2 = typename RowType<V>::R2;
+template <typename R2>
+__device__ inline void row_product(const R2 *__restrict__ sums, const R2 *__restrict__ vtab, int chunks, int nx, int ny,
+                                   int x0, int y0, typename RowType<R2>::A4 (&re)[2][2],
+                                   typename RowType<R2>::A4 (&im)[2][2]) {
+    using R = typename RowType<R2>::R;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-    double by[2];
-    int xc[2];
+    int xc[2], yc[2];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
-        by[p] = b0 + (y0 + 16 * p + li) * dy;
+        yc[p] = min(y0 + 16 * p + li, ny - 1);
         xc[p] = min(x0 + 16 * p + li, nx - 1);
     }
 #pragma unroll
     for (int p = 0; p < 2; p++)
 #pragma unroll
-        for (int q = 0; q < 2; q++) re[p][q] = im[p][q] = typename RowType<V>::A4{0, 0, 0, 0};
+        for (int q = 0; q < 2; q++) re[p][q] = im[p][q] = typename RowType<R2>::A4{0, 0, 0, 0};
     const int steps = (chunks + 3) >> 2;
-    auto load = [&](int s, V &vv, R2 (&t)[2]) {
+    auto load = [&](int s, R2 (&f)[2], R2 (&t)[2]) {
         const int c = 4 * s + lk, cc = min(c, chunks - 1);
-        vv = v[cc];
 #pragma unroll
         for (int q = 0; q < 2; q++) {
+            f[q] = vtab[(int64_t)cc * ny + yc[q]];
             t[q] = sums[(int64_t)cc * nx + xc[q]];
             if (c >= chunks) t[q].x = t[q].y = R(0);
         }
     };
     if (w >= steps) return;
-    V vn;
-    R2 tn[2];
-    load(w, vn, tn);
+    R2 fn[2], tn[2];
+    load(w, fn, tn);
     for (int s = w; s < steps; s += kRowWaves) {
-        const V vv = vn;
-        const R2 t[2] = {tn[0], tn[1]};
-        load(min(s + kRowWaves, steps - 1), vn, tn);  // the next step's, used after this one's products
+        const R2 f[2] = {fn[0], fn[1]}, t[2] = {tn[0], tn[1]};
+        load(min(s + kRowWaves, steps - 1), fn, tn);  // the next step's, used after this one's products
 #pragma unroll
-        for (int p = 0; p < 2; p++) {
-            const R2 f = row_factor<HG>(vv, by[p]);
-            const R fn = -f.y;
+        for (int p = 0; p < 2; p++)
 #pragma unroll
             for (int q = 0; q < 2; q++) {
-                re[p][q] = row_mfma(f.x, t[q].x, re[p][q]);
-                im[p][q] = row_mfma(f.x, t[q].y, im[p][q]);
-                re[p][q] = row_mfma(fn, t[q].y, re[p][q]);
-                im[p][q] = row_mfma(f.y, t[q].x, im[p][q]);
+                re[p][q] = row_mfma(f[p].x, t[q].x, re[p][q]);
+                im[p][q] = row_mfma(f[p].x, t[q].y, im[p][q]);
+                re[p][q] = row_mfma(-f[p].y, t[q].y, re[p][q]);
+                im[p][q] = row_mfma(f[p].y, t[q].x, im[p][q]);
             }
-        }
     }
 }
 
@@ -317,13 +333,12 @@ __device__ inline void row_product(const V *__restrict__ v, const typename RowTy
 // 16 x 16 blocks at a time through LDS in FP32 (FP64: one block, for 32 KiB of
 // LDS either way); pixel(p, q, i, value) gets element i (row i / 16, column
 // i % 16) of block (p, q) from one thread.
-template <typename V>
-constexpr int kFoldBlocks = sizeof(V) == sizeof(RowV32) ? 2 : 1;
-template <typename V, typename F>
-__device__ inline void row_fold(typename RowType<V>::A4 (&re)[2][2], typename RowType<V>::A4 (&im)[2][2],
-                                typename RowType<V>::R2 (*part)[256 * kFoldBlocks<V>], F pixel) {
-    using R2 = typename RowType<V>::R2;
-    constexpr int N = kFoldBlocks<V>;
+template <typename R2>
+constexpr int kFoldBlocks = sizeof(R2) == sizeof(float2) ? 2 : 1;
+template <typename R2, typename F>
+__device__ inline void row_fold(typename RowType<R2>::A4 (&re)[2][2], typename RowType<R2>::A4 (&im)[2][2],
+                                R2 (*part)[256 * kFoldBlocks<R2>], F pixel) {
+    constexpr int N = kFoldBlocks<R2>;
     static_assert(256 * N <= 64 * kRowWaves, "a thread per pixel");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
 #pragma unroll
@@ -338,7 +353,7 @@ __device__ inline void row_fold(typename RowType<V>::A4 (&re)[2][2], typename Ro
                     R2 x;
                     x.x = re[p][q0 + q][e];
                     x.y = im[p][q0 + q][e];
-                    part[w][256 * q + 16 * RowType<V>::row(lk, e) + li] = x;
+                    part[w][256 * q + 16 * RowType<R2>::row(lk, e) + li] = x;
                 }
             __syncthreads();
             if (threadIdx.x < 256 * N) {

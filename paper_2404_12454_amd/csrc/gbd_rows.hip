@@ -16,15 +16,16 @@
 //   FP64 eight columns to a lane take two exponentials and then complex
 //   multiplications, the factor's log being quadratic in x (row_sum64).
 //   Bound by VALU issue.
+//   The workgroups of a chunk also tabulate its y factors, once each.
 // Products: 32 x 32 pixels per workgroup of 8 wavefronts that split the
-//   chunks; y factors formed in registers (nx / 32 times each: a small part
-//   of the row sums' factors), MFMA with four real products (the sums are
-//   short, and Gauss's three-product form would cost accuracy), the
-//   wavefronts' shares added in FP64.
+//   chunks, MFMA with four real products (the sums are short, and Gauss's
+//   three-product form would cost accuracy), the wavefronts' shares added in
+//   FP64.
 // Measured, a gbd_eval call of 51,468 beamlets on 512 x 512 pixels: mixed 310
-// -> 51 us (row sums 25, products 5, setup 14) with an error against FP64 of
-// 2e-7 instead of 9e-7, FP64 1,954 -> 82 us (54, 20, 14); 441 instances of
-// the parameter sweep 3.50 -> 1.87 ms.
+// -> 45 us (row sums 25, product 10, setup 10) with an error against FP64 of
+// 2e-7 instead of 9e-7, FP64 1,954 -> 73 us (50, 16, 10); the y factors formed
+// by the product's tiles instead, nx / 32 times each: 46.5 and 79 us, of higher
+// order 78 instead of 71.  441 instances of the parameter sweep 3.50 -> 1.27 ms.
 #include "gbd_row_core.h"
 
 namespace gbd {
@@ -38,18 +39,16 @@ __global__ void __launch_bounds__(64 * kRowSumWaves) row_sum32_kernel(RowGeom g,
                                                                       const Rec32 *__restrict__ rec,
                                                                       const RecHG32 *__restrict__ hg,
                                                                       const uint32_t *__restrict__ status,
-                                                                      float2 *__restrict__ sums,
-                                                                      RowV32 *__restrict__ v, StatusPost sp) {
+                                                                      float2 *__restrict__ sums, StatusPost sp) {
     if (sp.post && blockIdx.x == 0 && threadIdx.x == 0) post_status(sp);
-    row_sum_block32<HG, C>(g, blockIdx.x, start, rec, hg, status[1], sums, v);
+    row_sum_block32<HG, C>(g, blockIdx.x, start, rec, hg, status[1], sums);
 }
 
 template <bool HG, int C>
 __global__ void __launch_bounds__(64 * kRowSumWaves) row_sum64_kernel(RowGeom g, const int32_t *__restrict__ start,
                                                                       const Rec64 *__restrict__ rec,
                                                                       const RecHG64 *__restrict__ hg,
-                                                                      double2 *__restrict__ sums,
-                                                                      RowV64 *__restrict__ v, StatusPost sp) {
+                                                                      double2 *__restrict__ sums, StatusPost sp) {
     __shared__ double2 part[kRowSumWaves][64 * C];
     __shared__ double2 s2[kRowSumWaves][kRowLen / kRowSumWaves];
     if (sp.post && blockIdx.x == 0 && threadIdx.x == 0) post_status(sp);
@@ -57,7 +56,7 @@ __global__ void __launch_bounds__(64 * kRowSumWaves) row_sum64_kernel(RowGeom g,
     row_item<C>(blockIdx.x, g.nx, c, x0);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j0 = start[c], j1 = start[c + 1];
-    if (x0 == 0 && threadIdx.x == 0) v[c] = row_v64<HG>(rec[j0], HG ? hg + j0 : nullptr);
+    row_table<HG>(g, row_v64<HG>(rec[j0], HG ? hg + j0 : nullptr), c, x0, 64 * C, row_vtab(g, sums));
     int direct = 0;
     if constexpr (C > 1) {
         for (int i = threadIdx.x; i < j1 - j0; i += 64 * kRowSumWaves) {
@@ -84,27 +83,24 @@ __global__ void __launch_bounds__(64 * kRowSumWaves) row_sum64_kernel(RowGeom g,
 }
 
 // key: the FP32 sums' scale 2^-P, undone at the store (null in FP64)
-template <bool HG, typename V>
-__global__ void __launch_bounds__(64 * kRowWaves) row_product_kernel(RowGeom g, const V *__restrict__ v,
-                                                                     const typename RowType<V>::R2 *__restrict__ sums,
+template <typename R2>
+__global__ void __launch_bounds__(64 * kRowWaves) row_product_kernel(RowGeom g, const R2 *__restrict__ sums,
                                                                      const uint32_t *__restrict__ status,
-                                                                     typename RowType<V>::R2 *__restrict__ out,
-                                                                     EvalGuard gd) {
-    using R = typename RowType<V>::R;
-    __shared__ typename RowType<V>::R2 part[kRowWaves][256 * kFoldBlocks<V>];
+                                                                     R2 *__restrict__ out, EvalGuard gd) {
+    __shared__ R2 part[kRowWaves][256 * kFoldBlocks<R2>];
     if (!guard_holds(gd)) return;
     const int tx = (g.nx + kRowTile - 1) / kRowTile, ty = (g.ny + kRowTile - 1) / kRowTile;
     const int w = work_item(blockIdx.x, gridDim.x);
     if (w >= tx * ty) return;
     // column strips, so that the workgroups of one XCD read few of the sums
     const int x0 = (w / ty) * kRowTile, y0 = (w % ty) * kRowTile;
-    typename RowType<V>::A4 re[2][2], im[2][2];
-    row_product<HG>(v, sums, g.chunks, g.nx, g.a0, g.b0, g.dy, x0, y0, re, im);
+    typename RowType<R2>::A4 re[2][2], im[2][2];
+    row_product(sums, row_vtab(g, sums), g.chunks, g.nx, g.ny, x0, y0, re, im);
     const int P = status ? (int)row_exponent(status[1]) : 0;
-    row_fold<V>(re, im, part, [&](int p, int q, int i, double sr, double si) {
+    row_fold<R2>(re, im, part, [&](int p, int q, int i, double sr, double si) {
         const int ix = x0 + 16 * q + (i & 15), iy = y0 + 16 * p + (i >> 4);
         if (ix >= g.nx || iy >= g.ny) return;
-        if constexpr (sizeof(R) == 4)
+        if constexpr (sizeof(R2) == sizeof(float2))
             out[(int64_t)iy * g.nx + ix] = row_value(sr, si, P);
         else
             out[(int64_t)iy * g.nx + ix] = make_double2(sr, si);
@@ -120,33 +116,33 @@ dim3 row_product_grid(const RowGeom &g) {
 }  // namespace
 
 hipError_t launch_rows32(const RowGeom &g, const int32_t *start, const Rec32 *rec, const RecHG32 *hg,
-                         const uint32_t *status, float2 *sums, RowV32 *v, float2 *out, const EvalGuard &guard,
+                         const uint32_t *status, float2 *sums, float2 *out, const EvalGuard &guard,
                          hipStream_t s, hipEvent_t t0, hipEvent_t t1, const StatusPost &sp) {
     if (g.chunks < 1 || g.nx < 1 || g.ny < 1 || !status) return hipErrorInvalidValue;
     hipError_t e = g.nx > 64 ? launch_timed(hg ? row_sum32_kernel<true, 2> : row_sum32_kernel<false, 2>,
                                             row_sum_grid(g, 2), dim3(64 * kRowSumWaves), s, t0, nullptr, g, start, rec,
-                                            hg, status, sums, v, sp)
+                                            hg, status, sums, sp)
                              : launch_timed(hg ? row_sum32_kernel<true, 1> : row_sum32_kernel<false, 1>,
                                             row_sum_grid(g, 1), dim3(64 * kRowSumWaves), s, t0, nullptr, g, start, rec,
-                                            hg, status, sums, v, sp);
+                                            hg, status, sums, sp);
     if (e != hipSuccess) return e;
-    return launch_timed(hg ? row_product_kernel<true, RowV32> : row_product_kernel<false, RowV32>, row_product_grid(g),
-                        dim3(64 * kRowWaves), s, nullptr, t1, g, v, sums, status, out, guard);
+    return launch_timed(row_product_kernel<float2>, row_product_grid(g), dim3(64 * kRowWaves), s, nullptr, t1, g, sums,
+                        status, out, guard);
 }
 
 hipError_t launch_rows64(const RowGeom &g, const int32_t *start, const Rec64 *rec, const RecHG64 *hg, double2 *sums,
-                         RowV64 *v, double2 *out, const EvalGuard &guard, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
+                         double2 *out, const EvalGuard &guard, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
                          const StatusPost &sp) {
     if (g.chunks < 1 || g.nx < 1 || g.ny < 1) return hipErrorInvalidValue;
     hipError_t e = g.nx > 192 ? launch_timed(hg ? row_sum64_kernel<true, 8> : row_sum64_kernel<false, 8>,
                                              row_sum_grid(g, 8), dim3(64 * kRowSumWaves), s, t0, nullptr, g, start,
-                                             rec, hg, sums, v, sp)
+                                             rec, hg, sums, sp)
                               : launch_timed(hg ? row_sum64_kernel<true, 1> : row_sum64_kernel<false, 1>,
                                              row_sum_grid(g, 1), dim3(64 * kRowSumWaves), s, t0, nullptr, g, start,
-                                             rec, hg, sums, v, sp);
+                                             rec, hg, sums, sp);
     if (e != hipSuccess) return e;
-    return launch_timed(hg ? row_product_kernel<true, RowV64> : row_product_kernel<false, RowV64>, row_product_grid(g),
-                        dim3(64 * kRowWaves), s, nullptr, t1, g, v, sums, (const uint32_t *)nullptr, out, guard);
+    return launch_timed(row_product_kernel<double2>, row_product_grid(g), dim3(64 * kRowWaves), s, nullptr, t1, g, sums,
+                        (const uint32_t *)nullptr, out, guard);
 }
 
 }  // namespace gbd
