@@ -10,12 +10,14 @@ the coherent field, on inputs already resident in HBM.  Workload: 51,468 beamlet
 
 The mixed evaluation takes the library's automatic form: on this workload
 (a rotationally symmetric system on a plane normal to the axis, so no
-beamlet's phasor has a cross term) the separable matrix form on FP16 MFMA
-with every factor split into FP16 hi and lo halves, whose roofline is the
-FP16 MFMA peak; the same form on FP32 MFMA (separable_fp32) and the rotor
-form, which any plane with cross terms gets (general_form, with its
-instruction-mix roofline at nominal and at measured issue rates), are timed
-on the same workload beside it.
+beamlet's phasor has a cross term) the separable form, and since the pupil
+grid comes row by row, by rows: each beamlet's x factor once per column,
+summed over its row, and a matrix product over the rows, so the figure counts
+N * M pairs that are not multiplied out one by one (its roofline is the
+instruction mix of the N * nx factors plus the product's flops).  The dense
+separable form on FP32 MFMA (separable_fp32) and the rotor form (general_form,
+with its instruction-mix roofline at nominal and at measured issue rates) are
+timed on the same workload beside it.
 
 Also reported: the FP64 form on the same workload (and the mixed/FP64
 speed-up), the dominant kernel's live HIP-event duration, point evaluation,
@@ -158,6 +160,44 @@ def measured_rate(rates):
     return {"fp64": rates["fp64_fma"]["lanes_per_cu_clk"],
             "fp32": min(rates["fp32_fmac"]["lanes_per_cu_clk"], rates["fp32_mul"]["lanes_per_cu_clk"]),
             "trans": min(rates["sin_f32"]["lanes_per_cu_clk"], rates["exp_f32"]["lanes_per_cu_clk"])}
+
+
+# Row-factored separable form: VALU instructions per x factor (beamlet and
+# column), counted in the compiled loops (two columns to a lane; FP64 eight)
+ROWS_MIX = {"fp64": 12 / 2, "fp32": 11 / 2, "trans": 6 / 2}
+ROWS_MIX_HG = {"fp64": 12 / 2, "fp32": 44 / 2, "trans": 6 / 2}
+ROWS64_MIX = {"fp64": 160 / 8, "fp32": 69 / 8}
+# cross form (variant 3 of beamlets with weak cross terms): 8 FP16 MFMAs per
+# 16 beamlets and 16 x 16 pixels
+CROSS_FLOPS_PER_PAIR = 8 * 16384 / (16 * 256)
+
+
+def row_count(sc):
+    """Row chunks of a scene that the separable form takes by rows (beamlets
+    of equal y, higher orders of equal y order too, at least 4 to a chunk on
+    average, one matrix for all), else 0."""
+    import numpy as np
+    order = getattr(sc, "order", None)
+    if sc.n < 64 or sc.abcd.size != 16 or getattr(sc, "base", None) is not None:
+        return 0
+    whole = np.ones(sc.n, bool) if getattr(sc, "edge", None) is None else ~np.any(sc.edge[:, :2] != 0, axis=1)
+    key = np.column_stack([sc.r1[whole, 1], np.zeros(whole.sum()) if order is None else order[whole, 1]])
+    rows = len(np.unique(key, axis=0))
+    return rows if 4 * rows <= whole.sum() else 0
+
+
+def rows_roofline(sc, rows, kernel_ms, fp64=False):
+    """Time of the x factors at the nominal issue rates plus the product over
+    the rows at the MFMA peak, against the time the two kernels took."""
+    mix = ROWS64_MIX if fp64 else ROWS_MIX_HG if getattr(sc, "order", None) is not None else ROWS_MIX
+    nx, M = sc.plane.nx, sc.plane.npix
+    t_sum = sc.n * nx * sum(n / RATE[k] for k, n in mix.items()) / (CUS * CLOCK_HZ)
+    t_product = SEP_COMPLEX_MADD_FLOPS * rows * M / ((MFMA_FP64_TFLOPS if fp64 else MFMA_FP32_TFLOPS) * 1e12)
+    floor_ms = (t_sum + t_product) * 1e3
+    return {"bound": "alu", "achieved": sc.n * M / (kernel_ms * 1e-3), "peak": sc.n * M / (floor_ms * 1e-3),
+            "unit": "evals/s", "frac": floor_ms / kernel_ms, "kernel": "row_sum32_kernel + row_product_kernel",
+            "kernel_ms": kernel_ms, "rows": rows, "x_factors": sc.n * nx, "factors_floor_ms": t_sum * 1e3,
+            "product_floor_ms": t_product * 1e3, "instructions_per_factor": mix}
 
 
 def roofline(shape, N, M, kernel_ms, hg=False):
@@ -306,11 +346,12 @@ def main():
     mixed_vs_fp64 = float(np.linalg.norm(E32 - E64) / np.linalg.norm(E64))
 
     shape = plan.shape(gbd.GBD_MIXED)
-    roof = roofline(shape, N, M, kernel_ms)
+    rows = row_count(sc) if shape["variant"] == 4 else 0
+    roof = rows_roofline(sc, rows, kernel_ms) if rows else roofline(shape, N, M, kernel_ms)
     # the rest of a step: the setup kernel, its status copy and the host's
     # round trip before the evaluation, and the segment reduction
     roof["step_rest_ms"] = ms_step - kernel_ms
-    roof["traffic"] = TRAFFIC.get((args.workload, shape["rows_per_lane"], shape["waves"], shape["segments"],
+    roof["traffic"] = None if rows else TRAFFIC.get((args.workload, shape["rows_per_lane"], shape["waves"], shape["segments"],
                                    shape["variant"]))
     rec = {
         "metric": METRIC,
@@ -330,7 +371,7 @@ def main():
                    "n_beamlets": N, "n_pixels": M, "launch": shape},
         "roofline": roof,
         "eval_call_ms": eval_ms_mean,
-        "fp64": fp64_record(shape64, N, M, eval64_ms, eval_ms_mean),
+        "fp64": fp64_figures(sc, shape64, eval64_ms, eval_ms_mean),
         "err_mixed_vs_fp64_full_grid": mixed_vs_fp64,
         "wall_s_timed": wall,
         "issue_rates": rates,
@@ -382,6 +423,17 @@ def fp64_record(shape, N, M, ms, mixed_ms):
     return r
 
 
+def fp64_figures(sc, shape, ms, mixed_ms):
+    """fp64_record, with the row-factored form's roofline where it runs."""
+    r = fp64_record(shape, sc.n, sc.plane.npix, ms, mixed_ms)
+    rows = row_count(sc) if shape["variant"] == 4 else 0
+    if rows:
+        f = rows_roofline(sc, rows, ms, fp64=True)
+        r = {k: r[k] for k in ("value", "eval_ms", "launch", "speedup_mixed_over_fp64")}
+        r.update({"roofline_bound": "alu", "roofline_peak": f["peak"], "roofline_frac": f["frac"], "rows": rows})
+    return r
+
+
 def general_form(plan, N, M, out, stream, reps=20, variant=3):
     """The same workload through another form: by default the one that needs
     no separability (rotor, variant 3), what any plane with cross terms
@@ -412,8 +464,9 @@ def general_form(plan, N, M, out, stream, reps=20, variant=3):
 def aberrated(ctx, stream, reps=10, reps64=3, oracle_stride=8):
     """The aberrated, tilted-plane workload (zern128_1024: f/4, 12,892
     beamlets with seeded Zernike Z4-Z11 terms, a field angle, the plane tilted
-    10 degrees, 1024 x 1024 pixels): cross terms everywhere, so both
-    precisions take their general (rotor) forms.  Both fields' error against
+    10 degrees, 1024 x 1024 pixels): cross terms everywhere, weak ones within
+    a tile, so the mixed evaluation is the cross form on FP16 MFMA (against
+    that peak, 32 flops a pair), the FP64 one the rotor form.  Both fields' error against
     the FP64 oracle on every 8th pixel row (131,072 pixels, ~3 s on 16 host
     threads); oracle_stride 0 skips it."""
     import numpy as np
@@ -444,16 +497,15 @@ def aberrated(ctx, stream, reps=10, reps64=3, oracle_stride=8):
     E32 = out.cpu().numpy().astype(np.complex128)
     E64 = out64.cpu().numpy()
     shape, shape64 = plan.shape(gbd.GBD_MIXED), plan.shape(gbd.GBD_FP64)
-    r = roofline(shape, N, M, ms)
+    achieved = CROSS_FLOPS_PER_PAIR * N * M / (ms * 1e-3) / 1e12
+    r = {"frac": achieved / MFMA_FP16_TFLOPS, "peak": MFMA_FP16_TFLOPS}
     r64 = fp64_record(shape64, N, M, ms64, ms)
     rec = {"beamlets": N, "npix": [sc.plane.nx, sc.plane.ny], "launch": shape, "eval_ms": ms,
-           "evals_per_s": N * M / (ms * 1e-3), "roofline_frac": r["frac"], "roofline_peak": r["peak"],
+           "evals_per_s": N * M / (ms * 1e-3), "achieved_tflops": achieved, "roofline_bound": "mfma",
+           "roofline_frac": r["frac"], "roofline_peak": r["peak"],
            "fp64": {"launch": shape64, "eval_ms": ms64, "evals_per_s": N * M / (ms64 * 1e-3),
                     "roofline_frac": r64.get("roofline_frac")},
            "err_mixed_vs_fp64_full_grid": float(np.linalg.norm(E32 - E64) / np.linalg.norm(E64))}
-    if "peak_at_measured_rates" in r:
-        rec.update({"roofline_peak_at_measured_rates": r["peak_at_measured_rates"],
-                    "roofline_frac_at_measured_rates": r["frac_at_measured_rates"]})
     if oracle_stride:
         import oracle
         rows = np.arange(0, sc.plane.ny, oracle_stride)
@@ -608,7 +660,11 @@ def hermite(ctx, stream, gauss_ms, n_across=256, npix=512, reps=10):
         r = {"beamlets": sc.n, "npix": npix, "launch": shape, "eval_ms": ms,
              "evals_per_s": sc.n * npix * npix / (ms * 1e-3)}
         if shape["variant"] in (4, 5):
-            r["mfma_frac"] = roofline(shape, sc.n, npix * npix, ms)["frac"]
+            rows = row_count(sc) if shape["variant"] == 4 else 0
+            if rows:
+                r["rows"], r["roofline_frac"] = rows, rows_roofline(sc, rows, ms)["frac"]
+            else:
+                r["mfma_frac"] = roofline(shape, sc.n, npix * npix, ms)["frac"]
             r["cost_vs_fundamental"] = ms / gauss_ms
         if shape["variant"] == 4:  # the same on FP32 MFMA (variant 5) for comparison
             o5 = gbd.gbd_eval_opts(variant=5)
@@ -642,25 +698,28 @@ def hermite(ctx, stream, gauss_ms, n_across=256, npix=512, reps=10):
         shape64 = plan.shape(gbd.GBD_FP64)
         r64 = {"launch": shape64, "eval_ms": ms64, "evals_per_s": sc.n * npix * npix / (ms64 * 1e-3),
                "err_mixed_vs_fp64": float(np.linalg.norm(out.cpu().numpy() - E64) / np.linalg.norm(E64))}
-        if shape64["variant"] == 4:
+        if shape64["variant"] == 4 and row_count(sc):
+            r64["roofline_frac"] = rows_roofline(sc, row_count(sc), ms64, fp64=True)["frac"]
+        elif shape64["variant"] == 4:
             r64["fp64_mfma_frac"] = SEP64_FLOPS_PER_PAIR * sc.n * npix * npix / (ms64 * 1e-3) / 1e12 / MFMA_FP64_TFLOPS
         r["fp64"] = r64
         res[name] = r
     return res
 
 
-# Truncated-beamlet kernel (eval_cut_mixed_kernel, 2 rows x 4 wavefronts,
-# Faddeeva function with N = 16): per lane and beamlet, counted in the
-# compiled loop: 215 FP32, 19 FP64, 14 transcendental (exp2, sin, cos twice
-# and one reciprocal per pixel) and 10 other VALU instructions for 2 pixels.
-CUT_MIX = {"fp64": 19 / 2, "fp32": (215 + 10) / 2, "trans": 14 / 2}
+# Truncated-beamlet kernel (cut_column_mixed_kernel, columns of 32 rows at
+# degree 5): per lane and beamlet, counted in the compiled loop: 768 FP32, 17
+# FP64 and 12 transcendental instructions (the Faddeeva function and the
+# phasor at the anchor row once) for 32 pixels.
+CUT_MIX = {"fp64": 17 / 32, "fp32": 768 / 32, "trans": 12 / 32}
 
 
 def truncated(ctx, stream, gauss_ms, n_across=256, npix=512, reps=10):
     """The headline pupil with its rim cut: the grid extended past the rim
     and every beamlet within 1.5 w0 of it cut by the rim's tangent.  One
-    evaluation = the whole beamlets in their form (separable) + the cut ones
-    in their own kernel (complex error function) + the segment reduction.
+    evaluation = the whole beamlets in their form (separable, by rows) + the
+    cut ones in their own kernel (complex error function by columns) + the
+    segment reduction.
     Also the RMS error against the Airy pattern, plain grid vs cut rim."""
     import numpy as np
     import torch
