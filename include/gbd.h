@@ -118,7 +118,11 @@ typedef struct {
                                and FP32 MFMA products of at most N / 32 runs in the mixed
                                form, FP64 in the FP64 one.  It has no segments: a count
                                given is that of the products by beamlet, which other
-                               decompositions take */
+                               decompositions take.
+                               Truncated beamlets: a Taylor polynomial of erfc along
+                               columns of 8 to 32 pixels where the setup finds that it
+                               leaves less than 1e-7 of a term (FP64 1e-14), else and in
+                               form 1 pixel by pixel */
 } gbd_eval_opts;
 
 /* --- context ------------------------------------------------------------ */
@@ -287,7 +291,11 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
  * synchronises on its status; gbd_plan_eval runs the N x M kernels (before a
  * rotor form also a small kernel that fills the form's sigma^(k^2) tables in
  * the plan's records) and does not synchronise.  A plan's calls are ordered
- * on the context stream; calls on one plan must not overlap from two streams. */
+ * on the context stream; calls on one plan must not overlap from two streams.
+ * While the stream is captured into a graph an evaluation keeps to forms that
+ * hold for any records of the same form, since later setups may change what
+ * the graph's replays read: no sum by rows, no series of weak cross terms,
+ * truncated beamlets pixel by pixel. */
 int gbd_plan_create(gbd_ctx_t ctx, gbd_plan_t *out, int64_t capacity);
 int gbd_plan_setup(gbd_ctx_t ctx, gbd_plan_t plan, gbd_beamlets_t b, gbd_plane_t p);
 int gbd_plan_eval(gbd_ctx_t ctx, gbd_plan_t plan, int precision, void *field_out, int64_t out_bytes,
@@ -312,8 +320,8 @@ void gbd_plan_free(gbd_plan_t plan);
  * or a workload whose fewest allowed segments do not (partials take
  * 8 bytes per pixel and segment in the mixed separable form, 16 otherwise;
  * one segment without truncated beamlets takes none; the separable form by
- * rows instead takes 8 bytes, FP64 16, per pixel column and run, and where
- * those do not fit the beamlets are taken as if in no rows).  All calls on one GPU
+ * rows instead takes 8 bytes, FP64 16, per run and pixel column or row, and
+ * where those do not fit the beamlets are taken as if in no rows).  All calls on one GPU
  * share its buffer, which keeps the last call's contents (every partial is
  * written before it is read): calls that overlap in time on one GPU, from two
  * streams, threads or contexts, race; calls ordered on one stream do not. */
