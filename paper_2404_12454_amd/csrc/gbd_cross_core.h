@@ -13,7 +13,7 @@ using namespace sep;
 constexpr int kWX = 2, kWY = 4;  // wavefronts per workgroup along x and y
 constexpr int kBX = 4, kBY = 2;  // 16-pixel blocks per wavefront along x and y
 constexpr int kThreads = 64 * kWX * kWY;
-static_assert(kBX % kWY == 0 && kBY % kWX == 0, "a lane forms one U and one V factor per quad of beamlets");
+static_assert(kCrossTile == 128 && kWX * kWY == 8, "a wavefront forms the factors of two beamlets over twice 64 pixels");
 static_assert(16 * kWX * kBX == kCrossTile && 16 * kWY * kBY == kCrossTile, "cross form: host and kernel tiles");
 
 // Scales: |U| <= 2^kUExp and |V| <= 2^kVExp by the setup's bounds, up to the
@@ -29,20 +29,36 @@ template <int LEVEL>
 struct CrossCfg {
     static constexpr int NU = LEVEL == 1 ? 3 : 5, NV = 4;
 };
-constexpr int kRecWords = 28;  // the words of a Rec32 before the rotor tables
-static_assert(offsetof(Rec32, sq) == 4 * kRecWords, "Rec32 layout");
-constexpr int kWordM0 = offsetof(Rec32, m) / 4, kWordU = offsetof(Rec32, pad) / 4;
+// A Rec32 up to the rotor tables, uniform over the wavefront: scalar loads.
+typedef uint32_t u16w __attribute__((ext_vector_type(16), aligned(16)));
+typedef uint32_t u8w __attribute__((ext_vector_type(8), aligned(16)));
+typedef uint32_t u4w __attribute__((ext_vector_type(4), aligned(16)));
+struct CrossRec {
+    u16w a;
+    u8w b;
+    u4w c;
+    __device__ uint32_t word(int k) const { return k < 16 ? a[k & 15] : k < 24 ? b[k & 7] : c[k & 3]; }
+    __device__ double f64(int k) const {
+        return __builtin_bit_cast(double, (uint64_t)word(k) | ((uint64_t)word(k + 1) << 32));
+    }
+    __device__ float f32(int k) const { return __builtin_bit_cast(float, word(k)); }
+};
+__device__ inline CrossRec cross_rec(const Rec32 *__restrict__ r) {
+    CrossRec w;
+    w.a = *reinterpret_cast<const u16w *>(r);
+    w.b = *(reinterpret_cast<const u8w *>(r) + 2);
+    w.c = *(reinterpret_cast<const u4w *>(r) + 6);
+    return w;
+}
+static_assert(offsetof(Rec32, sq) == 112 && offsetof(Rec32, m) == 64 && offsetof(Rec32, pad) == 108, "Rec32 layout");
 
 template <int LEVEL>
 struct alignas(16) CrossLds {
     // [buffer][range][block][part][pixel in block][beamlet in pass, swizzled as SepHLdsT]
     uint32_t lu[2][kWX][kBX][CrossCfg<LEVEL>::NU][16][16];
     uint32_t lv[2][kWY][kBY][CrossCfg<LEVEL>::NV][16][16];
-    // [buffer][beamlet in pass][word]; the rows past 16 take the idle threads' words
-    uint32_t rs[2][(kThreads + kRecWords - 1) / kRecWords][kRecWords];
 };
 static_assert(sizeof(CrossLds<2>) <= 163840, "a workgroup's 160 KiB of LDS");
-static_assert(kThreads >= 16 * kRecWords, "one word per thread and pass");
 
 __device__ inline h8 pk_scale(h8 a, h2 s) {
     h8 r;
@@ -64,8 +80,13 @@ __device__ inline h8 rot8(h8 a) {
     return __builtin_bit_cast(h8, v);
 }
 
-// As sep_accumulate_h (passes of 16 beamlets, records staged two passes
-// ahead, factors formed one pass ahead between the products).  With (u, v)
+// As sep_accumulate_h: passes of 16 beamlets, factors formed one pass ahead
+// between the products.  A wavefront forms all factors of two beamlets, so
+// that a beamlet's record is uniform (scalar loads, half a pass ahead) and two
+// neighbouring words of a pixel leave in one LDS store; with four beamlets to
+// a wavefront, records read from LDS by every lane and single words stored,
+// LDS took half of a pass (the kernel on 12,892 beamlets and 1024 x 1024
+// pixels 580 -> 516 us in a profiled run).  With (u, v)
 // the pixel's offset from the tile's centre in half tiles and x = the
 // beamlet's cross coefficient times a half tile squared, the factors carry
 // the cross term along the centre's row and column and
@@ -79,21 +100,25 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
                                         int ty, float P, CrossLds<LEVEL> &L, f4 (&accR)[kBY][kBX],
                                         f4 (&accI)[kBY][kBX]) {
     constexpr int NU = CrossCfg<LEVEL>::NU, NV = CrossCfg<LEVEL>::NV;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wx = wv % kWX, wy = wv / kWX;
     const int X0 = tx * kCrossTile, Y0 = ty * kCrossTile;
     const int li = lane & 15, lk = lane >> 4, sw = swz(li);
     auto &lu = L.lu;
     auto &lv = L.lv;
-    auto &rs = L.rs;
-    // this wavefront forms U block wy of x range wx and V block wx of y range wy
-    const int ix = X0 + 16 * (wx * kBX + wy) + li, iy = Y0 + 16 * (wy * kBY + wx) + li;
     constexpr double half = 0.5 * kCrossTile;
     const double ac = g.a0 + (X0 + half - 0.5) * g.dx, bc = g.b0 + (Y0 + half - 0.5) * g.dy;
-    const double ax = g.a0 + ix * g.dx, by = g.b0 + iy * g.dy;
-    const float u = (float)((ix - X0 + 0.5 - half) / half), v = (float)((iy - Y0 + 0.5 - half) / half);
-    const float xs_re = (float)(0.69314718055994531 * half * half * g.dx * g.dy) * u;  // per log2 unit, times u
-    const double xs_im = 2.0 * kPi * half * half * g.dx * g.dy * (double)u;            // per turn, times u
+    // this lane's two columns and rows, as factors; their u and v
+    double ax[2], by[2];
+    float u[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        ax[h] = g.a0 + (X0 + 64 * h + lane) * g.dx;
+        by[h] = g.b0 + (Y0 + 64 * h + lane) * g.dy;
+        u[h] = (float)((64 * h + lane + 0.5 - half) / half);
+    }
+    const float xs_re = (float)(0.69314718055994531 * half * half * g.dx * g.dy);  // per log2 unit
+    const double xs_im = 2.0 * kPi * half * half * g.dx * g.dy;                    // per turn
     // the v of the rows that this lane reads as operands
     h2 vr_[kBY];
 #pragma unroll
@@ -103,92 +128,91 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
     }
     const Rec32 *__restrict__ srec = rec + jb;
     const int n = (int)(je - jb);
-    const int st = threadIdx.x, sr = st / kRecWords, sc = st - sr * kRecWords;
-    const uint32_t pad_w = sc == kWordM0 ? 0xff800000u : sc == kWordU ? kPadU : 0u;
-    auto stage_load = [&](int i0) {
-        const int i = i0 + sr;
-        const uint32_t w = reinterpret_cast<const uint32_t *>(srec + (i < n ? i : 0))[sc];
-        const uint32_t keep = 0u - (uint32_t)(i < n);
-        return (w & keep) | (pad_w & ~keep);
-    };
-    auto publish = [&](int sbuf, int buf, int qd) {
-        const uint32_t *r = rs[sbuf][4 * qd + lk];
-        uint4 w[7];
+    // beamlet `which` of this wavefront's two in the pass at i0 (past the end:
+    // the last one's record, of amplitude zero)
+    auto record = [&](int i0, int which) { return cross_rec(srec + min(i0 + 2 * wv + which, n - 1)); };
+    auto live = [&](int i0, int which) { return i0 + 2 * wv + which < n; };
+    auto form_u = [&](const CrossRec &r, bool in, uint32_t (&o)[2][NU]) {
+        const double arho = r.f64(0), dbc = bc - r.f64(2), p4 = r.f64(12);
+        const float m4 = r.f32(20), ub = r.f32(27), dbcf = (float)dbc, m0 = in ? r.f32(16) : -INFINITY;
+        const double c1 = r.f64(6) + p4 * dbc;
+        const float l1 = r.f32(17) + m4 * dbcf;
 #pragma unroll
-        for (int k = 0; k < 7; k++) w[k] = reinterpret_cast<const uint4 *>(r)[k];
-        auto f64 = [&](int k) {
-            const uint4 &q = w[k >> 2];
-            const uint32_t lo = (k & 3) == 0 ? q.x : q.z, hi = (k & 3) == 0 ? q.y : q.w;
-            return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-        };
-        auto f32 = [&](int k) {
-            const uint4 &q = w[k >> 2];
-            const uint32_t x = (k & 3) == 0 ? q.x : (k & 3) == 1 ? q.y : (k & 3) == 2 ? q.z : q.w;
-            return __builtin_bit_cast(float, x);
-        };
-        const double arho = f64(0), brho = f64(2), p4 = f64(12);
-        const float m4 = f32(20), ub = f32(27);
-        const double dac = ac - arho, dbc = bc - brho, pa = p4 * dac;
-        const float dacf = (float)dac, dbcf = (float)dbc;
-        const int col = 4 * (qd ^ sw) + lk;
-        float re, im;
-        uint32_t hi, lo;
-        // exponents near zero, so that their rounding stays below the phase's;
-        // the range's powers of two multiplied in afterwards
-        const double da = ax - arho, db = by - brho;  // (offsets rounded once, from FP64)
-        factor(da, (float)da, f64(4), f64(6) + p4 * dbc, f64(10), f32(16) - ub, f32(17) + m4 * dbcf, f32(19), re,
-               im);
-        re *= (float)(1 << kUExp);
-        im *= (float)(1 << kUExp);
-        split_halves(re, im, hi, lo);
-        lu[buf][wx][wy][0][li][col] = hi;
-        lu[buf][wx][wy][1][li][col] = lo;
-        const float xr = m4 * xs_re, xi = (float)(p4 * xs_im);
-        float r1 = xr * re - xi * im, i1 = xr * im + xi * re;
-        if constexpr (LEVEL == 1) {
-            lu[buf][wx][wy][2][li][col] = __builtin_bit_cast(uint32_t, h2{(_Float16)r1, (_Float16)i1});
-        } else {
-            split_halves(r1, i1, hi, lo);
-            lu[buf][wx][wy][2][li][col] = hi;
-            lu[buf][wx][wy][3][li][col] = lo;
-            const float r2 = 0.5f * (xr * r1 - xi * i1), i2 = 0.5f * (xr * i1 + xi * r1);
-            lu[buf][wx][wy][4][li][col] = __builtin_bit_cast(uint32_t, h2{(_Float16)r2, (_Float16)i2});
+        for (int h = 0; h < 2; h++) {
+            float re, im;
+            // exponents near zero, so that their rounding stays below the phase's;
+            // the range's powers of two multiplied in afterwards
+            const double da = ax[h] - arho;  // (offsets rounded once, from FP64)
+            factor(da, (float)da, r.f64(4), c1, r.f64(10), m0 - ub, l1, r.f32(19), re, im);
+            re *= (float)(1 << kUExp);
+            im *= (float)(1 << kUExp);
+            split_halves(re, im, o[h][0], o[h][1]);
+            const float xr = m4 * (xs_re * u[h]), xi = (float)(p4 * (xs_im * (double)u[h]));
+            const float r1 = xr * re - xi * im, i1 = xr * im + xi * re;
+            if constexpr (LEVEL == 1) {
+                o[h][2] = __builtin_bit_cast(uint32_t, h2{(_Float16)r1, (_Float16)i1});
+            } else {
+                split_halves(r1, i1, o[h][2], o[h][3]);
+                const float r2 = 0.5f * (xr * r1 - xi * i1), i2 = 0.5f * (xr * i1 + xi * r1);
+                o[h][4] = __builtin_bit_cast(uint32_t, h2{(_Float16)r2, (_Float16)i2});
+            }
         }
-        factor(db, (float)db, -pa * dbc, f64(8) + pa, f64(14), ub - P - m4 * dacf * dbcf, f32(18) + m4 * dacf,
-               f32(21), re, im);
-        re *= (float)(1 << kVExp);
-        im *= (float)(1 << kVExp);
-        split_halves_conj(re, im, hi, lo);
-        lv[buf][wy][wx][0][li][col] = hi;
-        lv[buf][wy][wx][1][li][col] = lo;
-        if constexpr (LEVEL == 1) {
-            lv[buf][wy][wx][2][li][col] = rot_halves(hi);
-            lv[buf][wy][wx][3][li][col] = rot_halves(lo);
-        } else {
-            split_halves_conj(v * re, v * im, hi, lo);
-            lv[buf][wy][wx][2][li][col] = hi;
-            lv[buf][wy][wx][3][li][col] = lo;
+    };
+    auto form_v = [&](const CrossRec &r, uint32_t (&o)[2][NV]) {
+        const double dac = ac - r.f64(0), brho = r.f64(2), dbc = bc - brho, pa = r.f64(12) * dac;
+        const float m4 = r.f32(20), dacf = (float)dac, dbcf = (float)dbc;
+        const double c0 = -pa * dbc, c1 = r.f64(8) + pa;
+        const float l0 = r.f32(27) - P - m4 * dacf * dbcf, l1 = r.f32(18) + m4 * dacf;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            float re, im;
+            const double db = by[h] - brho;
+            factor(db, (float)db, c0, c1, r.f64(14), l0, l1, r.f32(21), re, im);
+            re *= (float)(1 << kVExp);
+            im *= (float)(1 << kVExp);
+            split_halves_conj(re, im, o[h][0], o[h][1]);
+            if constexpr (LEVEL == 1) {
+                o[h][2] = rot_halves(o[h][0]);
+                o[h][3] = rot_halves(o[h][1]);
+            } else {
+                split_halves_conj(u[h] * re, u[h] * im, o[h][2], o[h][3]);
+            }
         }
+    };
+    // both beamlets' words of each pixel in one store
+    const int col = 4 * ((wv >> 1) ^ sw) + 2 * (wv & 1);
+    auto put = [](uint32_t *dst, uint32_t a, uint32_t b) { *reinterpret_cast<uint2 *>(dst) = make_uint2(a, b); };
+    auto store_u = [&](int buf, const uint32_t (&a)[2][NU], const uint32_t (&b)[2][NU]) {
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int k = 0; k < NU; k++) put(&lu[buf][h][lk][k][li][col], a[h][k], b[h][k]);
+    };
+    auto store_v = [&](int buf, const uint32_t (&a)[2][NV], const uint32_t (&b)[2][NV]) {
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int k = 0; k < NV; k++) put(&lv[buf][2 * h + (lane >> 5)][lk & 1][k][li][col], a[h][k], b[h][k]);
     };
 #pragma unroll
     for (int p = 0; p < kBY; p++)
 #pragma unroll
         for (int q = 0; q < kBX; q++) accR[p][q] = accI[p][q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    {
-        const uint32_t w0 = stage_load(0), w1 = stage_load(16);
-        rs[0][sr][sc] = w0;
-        rs[1][sr][sc] = w1;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int qd = 0; qd < 4; qd++) publish(0, 0, qd);
+    uint32_t ua[2][NU], ub[2][NU], va[2][NV], vb[2][NV];
+    CrossRec ra = record(0, 0), rb = record(0, 1);
+    form_u(ra, live(0, 0), ua);
+    form_v(ra, va);
+    form_u(rb, live(0, 1), ub);
+    form_v(rb, vb);
+    store_u(0, ua, ub);
+    store_v(0, va, vb);
+    ra = record(16, 0);
+    rb = record(16, 1);
     __syncthreads();
     const int rd = 4 * (lk ^ sw);  // this lane's operand group in a row
     int buf = 0;
     for (int i0 = 0; i0 < n; i0 += 16) {
-        const uint32_t wnext = stage_load(i0 + 32);
-        __builtin_amdgcn_sched_barrier(0);  // the load stays a pass ahead of its use
         h8 b[kBX][NU];
 #pragma unroll
         for (int q = 0; q < kBX; q++)
@@ -215,7 +239,21 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
                     w2 = pk_scale(w[2], vr_[p]);
                 }
             }
-            publish(buf ^ 1, buf ^ 1, k);
+            // the next pass's factors, a quarter to a section
+            if (k == 0) form_u(ra, live(i0 + 16, 0), ua);
+            if (k == 1) {
+                form_v(ra, va);
+                ra = record(i0 + 32, 0);
+            }
+            if (k == 2) {
+                form_u(rb, live(i0 + 16, 1), ub);
+                store_u(buf ^ 1, ua, ub);
+            }
+            if (k == 3) {
+                form_v(rb, vb);
+                store_v(buf ^ 1, va, vb);
+                rb = record(i0 + 32, 1);
+            }
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 const int m = 2 * k + i, p = m / kBX, q = m % kBX;
@@ -255,7 +293,6 @@ __device__ inline void cross_accumulate(const SepGeom &g, const Rec32 *__restric
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        rs[buf][sr][sc] = wnext;
         __syncthreads();
         buf ^= 1;
     }
