@@ -766,6 +766,15 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
             nseg_cut = gc.nseg;
         }
     }
+    if (guard) {
+        // the flags that this evaluation's route depends on
+        guard->mask = FLAG_STEEP | FLAG_CROSS | FLAG_HG;
+        if (s.form == 3 && plan->rows > 0) guard->mask |= FLAG_ROWS;
+        if (cross_applies(precision, s.form, plan->flags & ~(uint32_t)FLAG_CROSS2, n_main, M))
+            guard->mask |= FLAG_CROSS1 | FLAG_CROSS2;
+        if (plan->n_cut > 0) guard->mask |= FLAG_CUT0 | FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
+        guard->flags = plan->flags & guard->mask;
+    }
     if (by_rows) s.nseg = 1;
     if (n_main > 0) {
         g = make_geom(plan->pl, n_main, s);
@@ -1665,8 +1674,6 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
     plan->sep_scale = pscale;
     EvalGuard guard;
     guard.status = plan->status_cur;
-    guard.mask = kFormFlags;
-    guard.flags = pflags & kFormFlags;
     guard.key = pkey;
     const size_t timed_before = ctx->timed.size();
     // the setup status is posted by the separable form's kernel at its start
@@ -1675,7 +1682,7 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
     const int ahead = plan_eval_impl(ctx, plan, precision, field_out, out_bytes, opts, nullptr, 0, &guard, &post_req);
     if (post_req.post) HIP_TRY(launch_status_post(post_req, ctx->stream), "status post launch");
     rc = plan_setup_finish(ctx, plan);
-    if (!rc && ahead == GBD_OK && (plan->flags & kFormFlags) == guard.flags &&
+    if (!rc && ahead == GBD_OK && (plan->flags & guard.mask) == guard.flags &&
         (!guard.check_key || plan->sep_key == pkey))
         return GBD_OK;
     // the launch ahead wrote nothing: drop its timing pair, if any
