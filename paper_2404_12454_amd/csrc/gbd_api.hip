@@ -460,6 +460,19 @@ int64_t most_segments(int64_t n, int64_t shortest, const PlaneGeom &pl, int64_t 
     return std::max<int64_t>(1, std::max<int64_t>(n / 256, std::min<int64_t>(n / shortest, fit)));
 }
 
+// An automatic count lowered to a whole number of workgroups per CU where the
+// fullest CU then holds at least 5 % fewer beamlets: a few workgroups over a
+// multiple of the CUs cost most of another round (9 x 29 workgroups on 256
+// CUs: FP64 separable, 8,021 beamlets on 300 x 257, 354 us, in 28 segments
+// 190; FP16 halves, 6 x 43, 84, in 42 53; rotor FP64, 1,804 on 409 x 275,
+// 21 x 37 186, in 36 158; a truncated rim of 128 across on 300^2, all in all
+// 159, then 121).
+int64_t whole_rounds(int64_t seg, int64_t tiles, int64_t cus) {
+    const int64_t rounds = tiles * seg / cus;
+    const int64_t low = rounds * cus / tiles;
+    return low >= 1 && 20 * rounds * seg < 19 * (rounds + (tiles * seg % cus != 0)) * low ? low : seg;
+}
+
 // Launch shape and mixed form.  32 rows per lane is a rotor-form shape: where
 // the form resolves to direct or stepped it runs 16.
 // general: the forms that hold for any records with these form flags only (no
@@ -502,7 +515,7 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
             int64_t seg = ((int64_t)ctx->cus * per_cu + tiles - 1) / tiles;
             auto it = ctx->tuned.find(tune_key(kTuneSep, precision, n, (int64_t)pl.nx * pl.ny));
             if (it != ctx->tuned.end()) seg = std::max<int64_t>(1, seg * it->second.seg_scale_pct / 100);
-            seg = std::min<int64_t>(seg, most_segments(n, 64, pl, mixed ? 8 : 16));
+            seg = whole_rounds(std::min<int64_t>(seg, most_segments(n, 64, pl, mixed ? 8 : 16)), tiles, ctx->cus);
             s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, 1024));
         }
         // the cap wins over the 1024-segment limit (above 16.7 M beamlets)
@@ -555,7 +568,7 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
         const int64_t target_blocks = (int64_t)ctx->cus * 4 * 6 / s.waves;
         int64_t seg = (target_blocks + tiles - 1) / tiles;
         seg = std::max<int64_t>(1, seg * seg_pct / 100);
-        seg = std::min<int64_t>(seg, most_segments(n, 8, pl, 16));
+        seg = whole_rounds(std::min<int64_t>(seg, most_segments(n, 8, pl, 16)), tiles, ctx->cus);
         s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, 1024));
     }
     return s;
@@ -658,7 +671,8 @@ EvalGeom cut_geom(const gbd_ctx_s *ctx, int precision, int &level, const PlaneGe
     const int64_t ty = (pl.ny + s.waves * s.rows - 1) / (s.waves * s.rows);
     const int64_t tiles = std::max<int64_t>(1, tx * ty);
     int64_t seg = ((int64_t)ctx->cus * (level ? kCutWaves : 6) + tiles - 1) / tiles;
-    seg = std::min<int64_t>(seg, std::max<int64_t>(n_cut / 32, most_segments(n_cut, 8, pl, 16)));
+    seg = whole_rounds(std::min<int64_t>(seg, std::max<int64_t>(n_cut / 32, most_segments(n_cut, 8, pl, 16))), tiles,
+                       ctx->cus);
     if (level == 4) seg = std::max<int64_t>(seg, one);
     s.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(seg, max_seg));
     return make_geom(pl, n_cut, s);
