@@ -422,17 +422,64 @@ __global__ void __launch_bounds__(64 * rows::kRowSumWaves) batch_row_sum_kernel(
                                         B.peaks[i], B.sums + I.sum_off);
 }
 
+// The figure of merit's partial sums of one instance over the pixels a lane
+// has taken: squares and the largest deviation, then a pair for each zone.
+template <bool ZONES>
+struct MeritSums {
+    static constexpr int NQ = ZONES ? 2 + 2 * kMaxZones : 2;
+    double q[NQ];
+    __device__ MeritSums() {
+#pragma unroll
+        for (int z = 0; z < NQ; z++) q[z] = 0.0;
+    }
+    __device__ void pixel(const BatchArgs &A, const BatchEval &I, double inv0, int ix, int iy, float2 f, float ref) {
+        const double d = ((double)f.x * f.x + (double)f.y * f.y) * inv0 - (double)ref;
+        q[0] += d * d;
+        q[1] = fmax(q[1], fabs(d));
+        if constexpr (ZONES) {
+            const double a = I.a0 + ix * I.dx, b = I.b0 + iy * I.dy;
+            const double r2 = a * a + b * b;
+#pragma unroll
+            for (int z = 0; z < kMaxZones; z++)
+                if (z < A.n_zones && r2 >= A.zone_r2[z] && r2 < A.zone_r2[z + 1]) {
+                    q[2 + 2 * z] += d * d;
+                    q[3 + 2 * z] += 1.0;
+                }
+        }
+    }
+    __device__ void add(const MeritSums &o) {
+#pragma unroll
+        for (int z = 0; z < NQ; z++) q[z] = z == 1 ? fmax(q[z], o.q[z]) : q[z] + o.q[z];
+    }
+};
+
+// 1 / |E(0)|^2 of instance i, 0 for a dark one
+__device__ inline double merit_scale(const BatchArgs &A, int i) {
+    const double2 f0 = A.e0[i];
+    const double n0 = f0.x * f0.x + f0.y * f0.y;
+    return n0 > 0.0 ? 1.0 / n0 : 0.0;
+}
+
+// Tile r of XCD x: its instance and its number there
+struct ProductTile {
+    int i, t;
+    __device__ ProductTile(const BatchRows &B, int x, int r) {
+        const int e0 = B.prod_list[x];
+        const int e = e0 + list_entry(B.prod_first + e0, B.prod_list[x + 1] - e0, r);
+        i = B.prod_inst[e];
+        t = r - B.prod_first[e];
+    }
+};
+
 __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel(BatchArgs A, BatchRows B) {
-    constexpr int NQ = 2 + 2 * kMaxZones, WAVES = rows::kRowWaves;
+    constexpr int NQ = MeritSums<true>::NQ, WAVES = rows::kRowWaves;
     __shared__ float2 part[WAVES][256 * rows::kFoldBlocks<float2>];
     __shared__ double red[WAVES][NQ];
     const int x = blockIdx.x % kXcds, r = blockIdx.x / kXcds;
     if (r >= B.prod_tiles[x]) return;
-    const int e0 = B.prod_list[x];
-    const int e = e0 + list_entry(B.prod_first + e0, B.prod_list[x + 1] - e0, r);
-    const int i = B.prod_inst[e], t = r - B.prod_first[e];
-    const BatchEval &I = A.inst[i];
-    const int x0 = (t / I.tiles_y) * rows::kRowTile, y0 = (t % I.tiles_y) * rows::kRowTile;
+    const ProductTile T(B, x, r);
+    const BatchEval &I = A.inst[T.i];
+    const int x0 = (T.t / I.tiles_y) * rows::kRowTile, y0 = (T.t % I.tiles_y) * rows::kRowTile;
     // the reference at this thread's pixels, ahead of the product
     float ref[2] = {0.0f, 0.0f};
     if (A.airy)
@@ -444,50 +491,117 @@ __global__ void __launch_bounds__(64 * rows::kRowWaves) batch_row_product_kernel
     sep::f4 re[2][2], im[2][2];
     const float2 *sums = B.sums + I.sum_off;
     rows::row_product(sums, sums + (int64_t)I.rows * I.nx, I.rows, I.nx, I.ny, x0, y0, re, im);
-    const int P = (int)rows::row_exponent(B.peaks[i]);
-    double q[NQ];
-#pragma unroll
-    for (int z = 0; z < NQ; z++) q[z] = 0.0;
-    double inv0 = 0.0;
-    if (A.airy) {
-        const double2 f0 = A.e0[i];
-        const double n0 = f0.x * f0.x + f0.y * f0.y;
-        inv0 = n0 > 0.0 ? 1.0 / n0 : 0.0;
-    }
+    const int P = (int)rows::row_exponent(B.peaks[T.i]);
+    MeritSums<true> m;
+    const double inv0 = A.airy ? merit_scale(A, T.i) : 0.0;
     rows::row_fold<float2>(re, im, part, [&](int p, int c, int k, double sr, double si) {
         const int ix = x0 + 16 * c + (k & 15), iy = y0 + 16 * p + (k >> 4);
         if (ix >= I.nx || iy >= I.ny) return;
-        const int64_t px = (int64_t)iy * I.nx + ix;
         const float2 f = rows::row_value(sr, si, P);
-        if (A.fields) A.fields[I.field_off + px] = f;
-        if (A.airy) {
-            const double d = ((double)f.x * f.x + (double)f.y * f.y) * inv0 - (double)ref[p];
-            q[0] += d * d;
-            q[1] = fmax(q[1], fabs(d));
-            const double a = I.a0 + ix * I.dx, b = I.b0 + iy * I.dy;
-            const double r2 = a * a + b * b;
-#pragma unroll
-            for (int z = 0; z < kMaxZones; z++)
-                if (z < A.n_zones && r2 >= A.zone_r2[z] && r2 < A.zone_r2[z + 1]) {
-                    q[2 + 2 * z] += d * d;
-                    q[3 + 2 * z] += 1.0;
-                }
-        }
+        if (A.fields) A.fields[I.field_off + (int64_t)iy * I.nx + ix] = f;
+        if (A.airy) m.pixel(A, I, inv0, ix, iy, f, ref[p]);
     });
     if (!A.airy) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, PS = 2 + 2 * A.n_zones;
 #pragma unroll
     for (int z = 0; z < NQ; z++)
-        if (z < PS) q[z] = (z == 1) ? wave_max<64>(q[z]) : wave_sum<64>(q[z]);
+        if (z < PS) m.q[z] = (z == 1) ? wave_max<64>(m.q[z]) : wave_sum<64>(m.q[z]);
     if (lane == 0)
 #pragma unroll
-        for (int z = 0; z < NQ; z++) red[wv][z] = q[z];
+        for (int z = 0; z < NQ; z++) red[wv][z] = m.q[z];
     __syncthreads();
     if ((int)threadIdx.x < PS) {
         const int z = threadIdx.x;
         double s = red[0][z];
         for (int w = 1; w < WAVES; w++) s = (z == 1) ? fmax(s, red[w][z]) : s + red[w][z];
-        A.part[(I.item_off + t) * PS + z] = s;
+        A.part[(I.item_off + T.t) * PS + z] = s;
+    }
+}
+
+// The same, a tile to a wavefront and four consecutive tiles (of one column
+// mostly) to a workgroup: no LDS and no barriers, and the same sums in the same
+// order (a wavefront of the other kernel takes four rows of 16 pixels), so that
+// an instance's results do not depend on its company.  An instance has few
+// steps of four chunks (15 on average in the 441-instance sweep): shared out
+// they leave a wavefront one or two, and the time goes to the fold and the
+// figure of merit's sums (441 instances on 256 x 256 375 us; here 225, of which
+// the products' MFMA 90 and the fold's conversions and FP64 sums 50; 112 with
+// three zones 124, then 98).  Without zones the registers are held to four
+// wavefronts a SIMD (129 registers and three: 248).  Taken where an XCD's tiles
+// fill its CUs (kProductWaveTiles, 6 wavefronts a CU; 800 tiles in all took 16
+// us by workgroups and 26 by wavefronts, 1,600 27 and 20, or 28 and 28 with
+// more chunks, 2,450 38 and 32, 3,200 43 and 29).
+constexpr int kProductTiles = 4;
+constexpr int kProductWaveTiles = 192;
+template <bool ZONES>
+__global__ void __launch_bounds__(64 * kProductTiles, ZONES ? 2 : 4) batch_row_product_wave_kernel(BatchArgs A, BatchRows B) {
+    using Merit = MeritSums<ZONES>;
+    const int x = blockIdx.x % kXcds;
+    const int r = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / kXcds) * kProductTiles + (int)(threadIdx.x >> 6));
+    if (r >= B.prod_tiles[x]) return;
+    const ProductTile T(B, x, r);
+    const BatchEval &I = A.inst[T.i];
+    const int x0 = (T.t / I.tiles_y) * rows::kRowTile, y0 = (T.t % I.tiles_y) * rows::kRowTile;
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const float2 *sums = B.sums + I.sum_off;
+    const int P = (int)rows::row_exponent(B.peaks[T.i]);
+    const double inv0 = A.airy ? merit_scale(A, T.i) : 0.0;
+    double sr[2][2][4], si[2][2][4];
+    rows::row_product_wave(sums, sums + (int64_t)I.rows * I.nx, I.rows, I.nx, I.ny, x0, y0, sr, si);
+    float ref[2][2][4];  // the reference, all loads under way at once
+    if (A.airy)
+#pragma unroll
+        for (int p = 0; p < 2; p++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const float *row = A.airy + (int64_t)min(y0 + 16 * p + 4 * lk + e, I.ny - 1) * I.nx;
+#pragma unroll
+                for (int c = 0; c < 2; c++) ref[p][c][e] = row[min(x0 + 16 * c + li, I.nx - 1)];
+            }
+    Merit half[2];  // by column block
+    auto pixels = [&](auto whole) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            Merit pair[2];  // elements h and h + 2
+#pragma unroll
+            for (int e = h; e < 4; e += 2) {
+                Merit m[2];
+#pragma unroll
+                for (int p = 0; p < 2; p++)
+#pragma unroll
+                    for (int c = 0; c < 2; c++) {
+                        const int ix = x0 + 16 * c + li, iy = y0 + 16 * p + 4 * lk + e;
+                        if (!whole() && (ix >= I.nx || iy >= I.ny)) continue;
+                        const float2 f = rows::row_value(sr[p][c][e], si[p][c][e], P);
+                        if (A.fields) A.fields[I.field_off + (int64_t)iy * I.nx + ix] = f;
+                        if (A.airy) m[c].pixel(A, I, inv0, ix, iy, f, ref[p][c][e]);
+                    }
+#pragma unroll
+                for (int c = 0; c < 2; c++) pair[c].add(m[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < 2; c++) half[c].add(pair[c]);
+        }
+    };
+    if (x0 + rows::kRowTile <= I.nx && y0 + rows::kRowTile <= I.ny)  // uniform: no lane masks
+        pixels([] { return true; });
+    else
+        pixels([] { return false; });
+    if (!A.airy) return;
+    const int PS = 2 + 2 * A.n_zones;
+#pragma unroll
+    for (int z = 0; z < Merit::NQ; z++) {
+        double tot = 0.0;
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const double row = (z == 1) ? wave_max<16>(half[c].q[z]) : wave_sum<16>(half[c].q[z]);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const double v = __shfl(row, 16 * k);
+                tot = (z == 1) ? fmax(tot, v) : tot + v;
+            }
+        }
+        if (lane == 0 && z < PS) A.part[(I.item_off + T.t) * PS + z] = tot;
     }
 }
 
@@ -576,7 +690,13 @@ hipError_t launch_batch_rows(const BatchArgs &a, const BatchRows &r, int32_t sum
     if (e != hipSuccess) return e;
     int32_t most = 0;
     for (int x = 0; x < kXcds; x++) most = max(most, r.prod_tiles[x]);
-    batch_row_product_kernel<<<(unsigned)(kXcds * most), 64 * rows::kRowWaves, 0, s>>>(a, r);
+    const unsigned by_four = (unsigned)(kXcds * ((most + kProductTiles - 1) / kProductTiles));
+    if (most >= kProductWaveTiles && a.n_zones > 0)
+        batch_row_product_wave_kernel<true><<<by_four, 64 * kProductTiles, 0, s>>>(a, r);
+    else if (most >= kProductWaveTiles)
+        batch_row_product_wave_kernel<false><<<by_four, 64 * kProductTiles, 0, s>>>(a, r);
+    else
+        batch_row_product_kernel<<<(unsigned)(kXcds * most), 64 * rows::kRowWaves, 0, s>>>(a, r);
     return hipGetLastError();
 }
 

@@ -369,6 +369,65 @@ __device__ inline void row_fold(typename RowType<R2>::A4 (&re)[2][2], typename R
         }
 }
 
+// The whole product of a 32 x 32 tile by one wavefront, bit for bit the
+// workgroup's: each of its kRowWaves shares in FP32, in the same step order,
+// then added in FP64 in the shares' order.  Element e of block (p, q) is row
+// 4 (lane / 16) + e, column lane % 16.
+__device__ inline void row_product_wave(const float2 *__restrict__ sums, const float2 *__restrict__ vtab, int chunks,
+                                        int nx, int ny, int x0, int y0, double (&sr)[2][2][4],
+                                        double (&si)[2][2][4]) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const int xc[2] = {min(x0 + li, nx - 1), min(x0 + 16 + li, nx - 1)};
+    const int yc[2] = {min(y0 + li, ny - 1), min(y0 + 16 + li, ny - 1)};
+    const int steps = (chunks + 3) >> 2;
+    auto load = [&](int s, float2 (&f)[2], float2 (&t)[2]) {
+        const int c = 4 * s + lk, cc = min(c, chunks - 1);
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            f[q] = vtab[(int64_t)cc * ny + yc[q]];
+            t[q] = sums[(int64_t)cc * nx + xc[q]];
+            if (c >= chunks) t[q].x = t[q].y = 0.0f;
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < 2; p++)
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) sr[p][q][e] = si[p][q][e] = 0.0;
+    float2 fn[2], tn[2];
+    if (steps > 0) load(0, fn, tn);
+    for (int w = 0; w < min(kRowWaves, steps); w++) {  // a share without steps adds zero
+        f4 re[2][2], im[2][2];
+#pragma unroll
+        for (int p = 0; p < 2; p++)
+#pragma unroll
+            for (int q = 0; q < 2; q++) re[p][q] = im[p][q] = f4{0, 0, 0, 0};
+        for (int s = w; s < steps; s += kRowWaves) {
+            const float2 f[2] = {fn[0], fn[1]}, t[2] = {tn[0], tn[1]};
+            load(min(s + kRowWaves < steps ? s + kRowWaves : w + 1, steps - 1), fn, tn);
+#pragma unroll
+            for (int p = 0; p < 2; p++)
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
+                    re[p][q] = row_mfma(f[p].x, t[q].x, re[p][q]);
+                    im[p][q] = row_mfma(f[p].x, t[q].y, im[p][q]);
+                    re[p][q] = row_mfma(-f[p].y, t[q].y, re[p][q]);
+                    im[p][q] = row_mfma(f[p].y, t[q].x, im[p][q]);
+                }
+        }
+#pragma unroll
+        for (int p = 0; p < 2; p++)
+#pragma unroll
+            for (int q = 0; q < 2; q++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    sr[p][q][e] += (double)re[p][q][e];
+                    si[p][q][e] += (double)im[p][q][e];
+                }
+    }
+}
+
 // The FP32 sums' scale 2^-P undone
 __device__ inline float2 row_value(double sr, double si, int P) {
     return make_float2((float)ldexp(sr, P), (float)ldexp(si, P));

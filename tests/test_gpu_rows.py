@@ -119,3 +119,25 @@ def test_batch_mixes_rows_and_dense_instances(ctx):
         alone, _ = gbd.gbd_eval_batch(ctx, [b], [p], airy=airy, zone_edges=[0.0, 3e-5, 6e-5])
         assert np.array_equal(alone[0], metrics[k]), k
         assert rel_l2(E.numpy(), oracle.eval_field(ss[k])) <= 1e-5
+
+
+@pytest.mark.parametrize("nx,ny", [(300, 289), (288, 320), (33, 1500), (1601, 40)])
+@pytest.mark.parametrize("zones", [None, [0.0, 2e-5, 4e-5, 9e-5]])
+def test_batch_products_by_wavefronts_and_by_workgroups(ctx, nx, ny, zones):
+    """Instances of about 100 product tiles: 24 in one call are taken a tile to a wavefront, each alone a tile to a
+    workgroup.  Fields equal gbd_eval's and metrics each other's, bit for bit, with and without the other output."""
+    import torch
+    ss = [scenes.airy_scene(k, npix=nx, npix_y=ny, half_span_lamF=6.0) for k in range(9, 57, 2)]
+    bs, ps = [gbd.beamlets_from_scene(ctx, s) for s in ss], [gbd.plane_from_scene(ctx, s) for s in ss]
+    m = ss[0].meta
+    airy = gbd.gbd_airy(ctx, ps[0], m["D"], m["f"], ss[0].lam)
+    metrics, fields = gbd.gbd_eval_batch(ctx, bs, ps, airy=airy, zone_edges=zones, fields=True)
+    only, _ = gbd.gbd_eval_batch(ctx, bs, ps, airy=airy, zone_edges=zones)
+    _, bare = gbd.gbd_eval_batch(ctx, bs, ps, fields=True)
+    assert np.array_equal(only, metrics)
+    for k, (b, p) in enumerate(zip(bs, ps)):
+        E = gbd.gbd_eval(ctx, b, p, gbd.GBD_MIXED, opts=dict(segments=1, variant=4)).cpu()
+        assert torch.equal(E.view(torch.float32), fields[k].cpu().view(torch.float32)), k
+        assert torch.equal(E.view(torch.float32), bare[k].cpu().view(torch.float32)), k
+        alone, _ = gbd.gbd_eval_batch(ctx, [b], [p], airy=airy, zone_edges=zones)
+        assert np.array_equal(alone[0], metrics[k]), k
