@@ -1674,7 +1674,7 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
     // behind this setup with its flags and FP16 scale, before the host has
     // read the new status, so no host round trip separates the two kernels.
     // The reduction writes the output only if the status has no error and
-    // the same flags and key (EvalGuard); otherwise it writes nothing and,
+    // the same key and route flags (EvalGuard); otherwise it writes nothing and,
     // for a mere change of form or scale, the evaluation runs again below.
     const uint32_t pflags = plan->flags;
     const uint32_t pkey = plan->sep_key;
