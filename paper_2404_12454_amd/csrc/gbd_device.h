@@ -120,6 +120,10 @@ __device__ inline double log2_hg_envelope_max(double c1, double c2, double d0, d
     return fmax(env + pm(R), env - 64.0 + pm(T));
 }
 
+// Rec32::pad of a beamlet that contributes nothing: a V factor 2^(pad + ...) is
+// then zero as well, and m0 - pad stays -inf.
+constexpr float kDeadBound = -1e30f;
+
 // One beamlet propagated onto the plane: what a setup kernel stores of it.
 constexpr int kYKey = 11;
 template <int Q>
@@ -460,6 +464,14 @@ __device__ __forceinline__ uint32_t setup_one(const BeamletsDev &b, const PlaneG
                                         : log2_envelope_max(o32.m[2], o32.m[5], b0 - brho, pl.dy, pl.ny);
             const bool ok = isfinite(umax) && isfinite(vmax);
             o32.pad = ok ? (float)umax : 0.0f;
+            if (umax == -INFINITY || vmax == -INFINITY) {
+                // contributes nothing on the grid (no amplitude, or a zero
+                // polynomial): both FP16 factors exactly zero.  From the bound
+                // 0, V = 2^(-P) of a field below 2^-4 (dense 2^-2) leaves
+                // FP16's range, and U's zero times infinity is no number
+                o32.m[0] = -INFINITY;
+                o32.pad = kDeadBound;
+            }
             so.peak = ok ? (float)(umax + vmax) : -INFINITY;
         }
     }

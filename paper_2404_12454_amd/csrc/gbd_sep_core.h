@@ -362,8 +362,9 @@ static_assert(sizeof(Rec32) == 60 * 4 && kStageWords % 4 == 0, "staged record la
 // kStagedM0), its U bound u = -1e30 (kStagedU) and zeros in its other words:
 // its U factors 2^(m0 + 14 - u) and V factors 2^(scale - 14 + u) are both
 // exactly zero (a finite V there could leave FP16's range, and 0 x inf is NaN).
+// The setup stores the same pair for a beamlet that contributes nothing.
 constexpr int kStagedM0 = 14, kStagedU = 21;
-constexpr uint32_t kPadU = 0xf149f2cau;  // -1e30f
+constexpr uint32_t kPadU = __builtin_bit_cast(uint32_t, kDeadBound);
 static_assert(kStageSrc[kStagedM0] == offsetof(Rec32, m) / 4, "staged m0 word");
 static_assert(kStageSrc[kStagedU] == offsetof(Rec32, pad) / 4, "staged U bound word");
 // Higher-order beamlets: 12 words of each RecHG32 (the diagonal of G and the

@@ -86,3 +86,17 @@ def test_cross_form_from_call_to_call(ctx):
     for i in (0, 0, 1, 1, 2, 2, 0, 2, 1, 0, 3, 3, 0, 1, 3, 2):
         E = gbd.gbd_eval(ctx, *hs[i]).cpu()
         assert torch.equal(E.view(torch.float32), want[i].view(torch.float32)), i
+
+
+@pytest.mark.parametrize("pitch", [0.05e-6, 0.15e-6])
+@pytest.mark.parametrize("weak", [1.0, 1e-3, 1e-9])
+def test_cross_form_masked_beamlets(ctx, pitch, weak):
+    """Beamlets of zero amplitude in fields down to 1e-9, both levels: their factors are zero, not infinite."""
+    sc = scene(40, 200, 180, pitch)
+    sc.amp = weak * sc.amp
+    sc.amp[::5] = 0.0
+    sc.amp[100:300] = 0.0
+    E = plan_of(ctx, sc).eval(gbd.GBD_MIXED, opts=dict(segments=3)).cpu().numpy()
+    assert rel_l2(E, oracle.eval_field(sc)) <= 1e-6
+    assert rel_l2(gbd.gbd_eval(ctx, gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc)).cpu().numpy(),
+                  oracle.eval_field(sc)) <= 1e-6

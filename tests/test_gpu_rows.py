@@ -141,3 +141,21 @@ def test_batch_products_by_wavefronts_and_by_workgroups(ctx, nx, ny, zones):
         assert torch.equal(E.view(torch.float32), bare[k].cpu().view(torch.float32)), k
         alone, _ = gbd.gbd_eval_batch(ctx, [b], [p], airy=airy, zone_edges=zones)
         assert np.array_equal(alone[0], metrics[k]), k
+
+
+@pytest.mark.parametrize("make", [lambda: scenes.airy_scene(24, npix=97, npix_y=66, half_span_lamF=6.0),
+                                  lambda: scenes.hermite_scene(24, npix=97, npix_y=66, half_span_lamF=6.0)])
+@pytest.mark.parametrize("weak", [1.0, 1e-3, 1e-9])
+def test_masked_beamlets_in_a_weak_field(ctx, make, weak):
+    """Beamlets of zero amplitude, whole rows among them, by rows and in no order (the dense form), single and in a
+    batch: their factors are zero, not infinite."""
+    sc = make()
+    sc.amp = weak * sc.amp
+    sc.amp[::5] = 0.0
+    sc.amp[100:200] = 0.0
+    ref = oracle.eval_field(sc)
+    for s in (sc, permuted(sc, 2)):
+        assert rel_l2(field(ctx, s, gbd.GBD_MIXED), ref) <= TOL[gbd.GBD_MIXED]
+        if sc.order is None:
+            _, f = gbd.gbd_eval_batch(ctx, [gbd.beamlets_from_scene(ctx, s)], [gbd.plane_from_scene(ctx, s)], fields=True)
+            assert rel_l2(f[0].cpu().numpy(), ref) <= TOL[gbd.GBD_MIXED]
