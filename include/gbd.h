@@ -295,7 +295,8 @@ int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void
  * While the stream is captured into a graph an evaluation keeps to forms that
  * hold for any records of the same form, since later setups may change what
  * the graph's replays read: no sum by rows, no series of weak cross terms,
- * truncated beamlets pixel by pixel. */
+ * truncated beamlets pixel by pixel.  The scratch a captured evaluation writes
+ * stays allocated until the plan is freed, also once later evaluations need more. */
 int gbd_plan_create(gbd_ctx_t ctx, gbd_plan_t *out, int64_t capacity);
 int gbd_plan_setup(gbd_ctx_t ctx, gbd_plan_t plan, gbd_beamlets_t b, gbd_plane_t p);
 int gbd_plan_eval(gbd_ctx_t ctx, gbd_plan_t plan, int precision, void *field_out, int64_t out_bytes,

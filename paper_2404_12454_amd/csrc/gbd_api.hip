@@ -175,6 +175,10 @@ struct gbd_plan_s {
     uint32_t sep_key;       // the status key sep_scale came from
     void *scratch;
     size_t scratch_bytes;
+    // a captured evaluation's graph writes the scratch it was captured with at
+    // every replay: once outgrown it is kept (here) until the plan is freed
+    bool scratch_captured;
+    std::vector<void *> held;
     uint32_t *status_cur;  // the last launched setup's status pair (null: none launched)
     bool spec_ok;  // the last setup succeeded: gbd_eval may launch the next evaluation before reading the status
 };
@@ -871,12 +875,17 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         if ((by_rows || s.cross || (nseg_cut > 0 && level)) && plan != ctx->own_plan)
             need = std::max(need, general_scratch(ctx, plan, precision, opts));
         if (need > plan->scratch_bytes) {
-            if (plan->scratch) (void)hipFree(plan->scratch);
+            if (plan->scratch && plan->scratch_captured)
+                plan->held.push_back(plan->scratch);
+            else if (plan->scratch)
+                (void)hipFree(plan->scratch);
             plan->scratch = nullptr;
             plan->scratch_bytes = 0;
+            plan->scratch_captured = false;
             HIP_TRY(hipMalloc(&plan->scratch, need), "hipMalloc(segment partials)");
             plan->scratch_bytes = need;
         }
+        plan->scratch_captured |= general;
         partial = plan->scratch;
     }
     if (n_main > 0) {
@@ -1111,6 +1120,7 @@ void plan_destroy(gbd_plan_s *plan) {
     if (plan->row_start) (void)hipFree(plan->row_start);
     if (plan->status_dev) (void)hipFree(plan->status_dev);
     if (plan->scratch) (void)hipFree(plan->scratch);
+    for (void *p : plan->held) (void)hipFree(p);
     if (plan->status_post) {
         // a post still in flight writes this memory: let the device finish first
         (void)hipDeviceSynchronize();

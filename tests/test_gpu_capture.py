@@ -84,3 +84,41 @@ def test_replay_follows_the_plans_setup(kind, precision, noalloc):
             err = rel_l2(out.cpu().numpy().astype(np.complex128), refs[i])
             print(f"{kind} precision {precision} noalloc {noalloc} setup {i}: rel_l2 {err:.2e}", flush=True)
             assert err < TOL[precision]
+
+
+@pytest.mark.parametrize("precision", [gbd.GBD_FP64, gbd.GBD_MIXED])
+@pytest.mark.parametrize("kind", list(PAIRS))
+def test_a_captured_evaluations_scratch_outlives_larger_ones(kind, precision):
+    """Evaluations between the replays that need more scratch than the captured one had (other forms, more segments)
+    leave its buffer allocated: seen in the device's free memory before any replay."""
+    import torch
+    ensure_library()
+    scs = [f() for f in PAIRS[kind]]
+    refs = [oracle.eval_field(s) for s in scs]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = gbd.Context(0, stream)
+        handles = [(gbd.beamlets_from_scene(ctx, s), gbd.plane_from_scene(ctx, s)) for s in scs]
+        plan = gbd.Plan(ctx, scs[0].n).setup(*handles[1])
+        out, E = plan.eval(precision), plan.eval(precision)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            plan.eval(precision, out=out)
+        more = dict(plan.shape(precision), segments=400)
+        partials = plan.shape(precision, more)["segments"] * E.numel() * 16
+        before = torch.cuda.mem_get_info()[0]
+        plan.eval(precision, out=E, opts=more)
+        stream.synchronize()
+        kept = before - torch.cuda.mem_get_info()[0]
+        print(f"{kind} precision {precision}: partials {partials}, {kept} bytes more in use", flush=True)
+        assert kept >= partials  # less by the captured buffer if that was given back
+        for opts in (None, more):
+            for i in (0, 1):
+                plan.setup(*handles[i])
+                plan.eval(precision, out=E, opts=opts)
+                out.zero_()
+                graph.replay()
+                stream.synchronize()
+                for field in (E, out):
+                    assert rel_l2(field.cpu().numpy(), refs[i]) < TOL[precision], (opts, i)
