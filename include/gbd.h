@@ -104,10 +104,13 @@ typedef struct {
                                rotor, else direct; a request that does not apply falls
                                back to auto's choice among the others.
                                Weak cross terms: at the rotor form's 32 rows x 4 wavefronts
-                               (0 or so requested) and two or more segments, a plane whose
+                               (0 or so requested) and two or more segments of at most
+                               640 beamlets (768 of 6,144 or more; automatic counts on
+                               fewer than 128 rows 320), a plane whose
                                cross terms the setup finds weak over 128 x 128 pixel tiles
                                takes forms 0 and 3 as matrix products, e^(x u v) by its
-                               series (within 1e-7 of a term) about each tile's centre, on
+                               series (root mean square over a tile within 1e-7 of a term,
+                               in a tile's corners 6.4e-7) about each tile's centre, on
                                FP16 MFMA in halves; shape and options stay the rotor's.
                                Separable by rows: where at least 64 beamlets come in runs
                                (four or more on average) that share one ABCD and differ
@@ -322,7 +325,8 @@ void gbd_plan_free(gbd_plan_t plan);
  * 8 bytes per pixel and segment in the mixed separable form, 16 otherwise;
  * one segment without truncated beamlets takes none; the separable form by
  * rows instead takes 8 bytes, FP64 16, per run and pixel column or row, and
- * where those do not fit the beamlets are taken as if in no rows).  All calls on one GPU
+ * where those do not fit the beamlets are taken as if in no rows; weak cross
+ * terms whose sums a lowered count would make too long take the rotor form).  All calls on one GPU
  * share its buffer, which keeps the last call's contents (every partial is
  * written before it is read): calls that overlap in time on one GPU, from two
  * streams, threads or contexts, race; calls ordered on one stream do not. */

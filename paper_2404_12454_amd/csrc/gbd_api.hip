@@ -421,22 +421,39 @@ bool cross_applies(int precision, int form, uint32_t flags, int64_t n, int64_t m
            n * m >= kCrossMinPairs;
 }
 
+// Beamlets of a plain FP32 sum of the cross form at most, so that its error
+// stays below the rotor form's, which compensates its sums every 128 (the
+// rotor's 32 rows against 640, 768 and 1,024 per sum: 3,228 beamlets on 512^2
+// pixels 5.4e-7, 5.1e-7, 5.5e-7, 6.3e-7; from 8 segments on their errors
+// average out: 12,892 on 1024^2 5.5e-7, 4.5e-7, 5.1e-7, 5.9e-7, 12,720 traced on
+// 512^2 6.0e-7, 4.1e-7, 4.6e-7, 5.4e-7; 100,668 on 512^2 1.3e-6 at 3,146 and
+// 5.6e-6 at 14,381).  On planes of fewer than 128 rows the rotor form runs 16
+// rows and is nearer (1,804 on 127^2: 2.9e-7; the cross form 2.6e-7 at 320,
+// 4.2e-7 at 640); an explicit count keeps the longer sums there.
+int64_t cross_longest(int64_t n, const PlaneGeom &pl, bool given) {
+    return pl.ny < 128 && !given ? 320 : n >= 8 * 768 ? 768 : 640;
+}
+
+// Scratch that a form takes over its general form's at most: beyond it the
+// general form runs, whose scratch does not grow with the beamlets (cross
+// form: 8 bytes per pixel and `longest` beamlets).
+constexpr int64_t kFormScratch = (int64_t)4 << 30;
+
 // Its automatic segment count: one workgroup per CU at a time, each pass of 16
 // beamlets about 2.4 us and three passes' worth of start-up, 16 bytes per
-// pixel and segment through memory for the partials; segments of 64 ... 768
-// beamlets (an FP32 sum's error grows with its length: 64 across on 256^2
-// pixels 2.0e-7 at 403 per sum, 2.7e-7 at 807, 4.3e-7 at 1,614).
-int64_t cross_segments(int cus, int64_t tiles, int64_t n, int64_t m) {
-    int64_t best = 1;
+// pixel and segment through memory for the partials; segments of 64 ...
+// `longest` beamlets.  0: too long sums or too much scratch.
+int64_t cross_segments(int cus, int64_t tiles, int64_t n, int64_t m, int64_t longest) {
+    int64_t best = 0;
     double best_t = 1e300;
-    for (int64_t seg = std::max<int64_t>(2, (n + 767) / 768); seg <= std::max<int64_t>(2, n / 64); seg++) {
+    const int64_t least = std::max<int64_t>(2, (n + longest - 1) / longest), most = std::max<int64_t>(least, n / 64);
+    for (int64_t seg = least; seg <= most && seg <= 2048 && seg * m * 8 <= kFormScratch; seg++) {
         const double rounds = (double)((tiles * seg + cus - 1) / cus);
         const double t = rounds * (double)((n / seg + 15) / 16 + 3) * 2.4e-6 + (double)seg * (double)m * 16.0 / 5e12;
         if (t < best_t) {
             best_t = t;
             best = seg;
         }
-        if (seg > 1024) break;
     }
     return best;
 }
@@ -552,16 +569,20 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
     if (precision != GBD_MIXED && s.form == 2 && (flags & FLAG_HG) && s.rows > 16) s.rows = 16;
     if (cross && s.rows == 32 && s.waves == 4) {
         int64_t seg = s.nseg;
+        const int64_t longest = cross_longest(n, pl, seg > 0), M = (int64_t)pl.nx * pl.ny;
         if (seg <= 0) {
             const int64_t tiles = std::max<int64_t>(1, (int64_t)((pl.nx + kCrossTile - 1) / kCrossTile) *
                                                            ((pl.ny + kCrossTile - 1) / kCrossTile));
-            seg = cross_segments(ctx->cus, tiles, n, (int64_t)pl.nx * pl.ny) * seg_pct / 100;
-            seg = std::max<int64_t>(2, std::min<int64_t>(seg, 1024));
+            seg = cross_segments(ctx->cus, tiles, n, M, longest);
+            if (seg) seg = std::max<int64_t>(std::max<int64_t>(2, (n + longest - 1) / longest), seg * seg_pct / 100);
+        } else if (seg * longest < n) {
+            seg = 0;
         }
-        seg = std::max<int64_t>(seg, seg > 1 ? (n + kSepMaxSegLen - 1) / kSepMaxSegLen : 1);
         if (seg >= 2 && n >= 4) {
             s.cross = true;
-            s.nseg = (int)std::min<int64_t>(seg, 0x7fffffff);
+            s.nseg = (int)seg;
+        } else if (pl.ny < 128 && !(o && o->rows_per_lane)) {
+            s.rows = 16;  // the rotor form's own
         }
     }
     if (s.nseg <= 0) {
@@ -798,6 +819,22 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         g = make_geom(plan->pl, n_main, s);
         nseg_main = g.nseg;
     }
+    // Sums of the cross form too long for it once the count is lowered to what
+    // the fixed buffer holds: the rotor form's, compensated, shape and all.
+    auto rotor_instead = [&] {
+        s = choose_shape(ctx, precision, n_main, plan->pl, plan->flags, opts, true);
+        compact = false;
+        g = make_geom(plan->pl, n_main, s);
+        nseg_main = g.nseg;
+    };
+    if (fixed && s.cross && !(opts && opts->segments > 0)) {
+        const size_t per = (size_t)M * 16;
+        const int64_t room = (int64_t)(fixed_bytes / per);
+        if (nseg_main + nseg_cut > room) {
+            const int64_t left = room - std::min<int64_t>(nseg_cut, (int64_t)(fixed_bytes / 2 / per));
+            if (left < 2 || std::min<int64_t>(left, nseg_main) * cross_longest(n_main, plan->pl, false) < n_main) rotor_instead();
+        }
+    }
     if (fixed && !by_rows) {
         // partial bytes of nm main and nc truncated segments (none when one
         // segment writes the output directly)
@@ -842,12 +879,6 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                 return fail(GBD_ERANGE, "partial sums need %zu bytes; the static buffer holds %zu",
                             need_of(nseg_main, nseg_cut), fixed_bytes);
         }
-    }
-    if (s.cross && nseg_main < 2) {  // lowered to one segment: the rotor form's
-        s.cross = false;
-        compact = false;
-        g = make_geom(plan->pl, n_main, s);
-        nseg_main = g.nseg;
     }
     if (n_main > 0 && (int64_t)g.tiles_x * g.tiles_y * g.nseg > (int64_t)0x7fffffff - 8)
         return fail(GBD_ERANGE, "grid too large");

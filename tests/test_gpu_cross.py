@@ -100,3 +100,35 @@ def test_cross_form_masked_beamlets(ctx, pitch, weak):
     assert rel_l2(E, oracle.eval_field(sc)) <= 1e-6
     assert rel_l2(gbd.gbd_eval(ctx, gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc)).cpu().numpy(),
                   oracle.eval_field(sc)) <= 1e-6
+
+
+def test_cross_form_keeps_its_sums_short(ctx):
+    """100,668 beamlets: the plain FP32 sums stay short enough for the rotor form's error, whether the segment count
+    is automatic, given, or lowered to the static buffer's 4; too few segments are the rotor form's."""
+    import torch
+    sc = scene(358, 1024, 1024, 0.25e-6)
+    plan = plan_of(ctx, sc)
+    ref = plan.eval(gbd.GBD_FP64).cpu().numpy()
+    assert plan.shape(gbd.GBD_MIXED)["segments"] * 768 >= sc.n
+    fields = {k: plan.eval(gbd.GBD_MIXED, opts=dict(segments=k) if k else None).cpu() for k in (0, 4, 7, 16, 160)}
+    fields["static"] = plan.eval_noalloc(gbd.GBD_MIXED).cpu()
+    err = {k: rel_l2(E.numpy(), ref) for k, E in fields.items()}
+    print(err, flush=True)
+    assert max(err.values()) <= 1e-6
+    assert torch.equal(fields["static"].view(torch.float32), fields[4].view(torch.float32))
+
+
+def test_low_planes_keep_the_rotor_forms_rows(ctx):
+    """Fewer than 128 rows: the rotor form's 16 rows where the cross form does not run (one segment, or a static
+    buffer too small for its sums)."""
+    import torch
+    sc = scene(100, 2000, 120, 0.1e-6)
+    plan = plan_of(ctx, sc)
+    assert plan.shape(gbd.GBD_MIXED, dict(segments=1))["rows_per_lane"] == 16
+    ref = plan.eval(gbd.GBD_FP64).cpu().numpy()
+    room = (64 << 20) // (2000 * 120 * 16)
+    E = plan.eval_noalloc(gbd.GBD_MIXED).cpu()
+    assert rel_l2(E.numpy(), ref) <= 4e-7  # 16 rows; 32 rows 4.5e-7 and more
+    rotor = plan.eval(gbd.GBD_MIXED, opts=dict(rows_per_lane=16, waves=4, segments=room)).cpu()
+    assert torch.equal(E.view(torch.float32), rotor.view(torch.float32))
+    assert rel_l2(plan.eval(gbd.GBD_MIXED).cpu().numpy(), ref) <= 4e-7
