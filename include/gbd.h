@@ -347,6 +347,9 @@ int gbd_plan_shape(gbd_ctx_t ctx, gbd_plan_t plan, int precision, const gbd_eval
  * launches each, HIP events on the context stream), stores the fastest in
  * the context's cache keyed by (form family, precision, log2 N, log2 M) and
  * returns it in *best (resolved segment count) and its time in *best_ms.
+ * Beamlets taken by rows: the segment counts are timed, and kept, of the
+ * products by beamlet, *best_ms is the evaluation by rows.  Planes of weak
+ * cross terms have cache entries of their own.
  * Later calls with all-zero opts (segments 0 for the separable form) on the
  * same bucket use it.  Synchronises; overwrites no caller buffer.
  * gbd_autotune_batch: the same over rows_per_lane x waves for gbd_eval_batch

@@ -399,8 +399,11 @@ int ilog2(int64_t v) {
 }
 
 // cache kinds: single evaluations in a VALU form, batched sweeps, single
-// evaluations in the separable form (only the segment count applies)
-constexpr int kTuneEval = 0, kTuneBatch = 1, kTuneSep = 2;
+// evaluations in the separable form (only the segment count applies; the sum
+// by rows has none), single evaluations of planes that the cross form takes
+// at its shape (a kind of their own: the rotor form's best shape on strong
+// cross terms would switch it off)
+constexpr int kTuneEval = 0, kTuneBatch = 1, kTuneSep = 2, kTuneCross = 3;
 TuneKey tune_key(int kind, int precision, int64_t n, int64_t m) { return TuneKey{kind, precision, ilog2(n), ilog2(m)}; }
 
 // Fewest segments a form allows: the mixed separable form sums a segment in
@@ -551,7 +554,7 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
     int seg_pct = 100;
     const bool user = o && (o->rows_per_lane || o->waves || o->segments);
     if (!user) {
-        auto it = ctx->tuned.find(tune_key(kTuneEval, precision, n, (int64_t)pl.nx * pl.ny));
+        auto it = ctx->tuned.find(tune_key(cross ? kTuneCross : kTuneEval, precision, n, (int64_t)pl.nx * pl.ny));
         if (it != ctx->tuned.end()) {
             s.rows = it->second.rows;
             s.waves = it->second.waves;
@@ -574,7 +577,9 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
             const int64_t tiles = std::max<int64_t>(1, (int64_t)((pl.nx + kCrossTile - 1) / kCrossTile) *
                                                            ((pl.ny + kCrossTile - 1) / kCrossTile));
             seg = cross_segments(ctx->cus, tiles, n, M, longest);
-            if (seg) seg = std::max<int64_t>(std::max<int64_t>(2, (n + longest - 1) / longest), seg * seg_pct / 100);
+            if (seg)
+                seg = std::max<int64_t>(std::max<int64_t>(2, (n + longest - 1) / longest),
+                                        std::min<int64_t>(seg * seg_pct / 100, kFormScratch / (M * 8)));
         } else if (seg * longest < n) {
             seg = 0;
         }
@@ -734,9 +739,10 @@ size_t general_scratch(const gbd_ctx_s *ctx, const gbd_plan_s *plan, int precisi
 // separable form's evaluation kernel at its start, else by status_post_kernel
 // ahead of this evaluation's first kernel; post is cleared once a launch has
 // taken it (a call that launches nothing leaves it set).
+// dense: not by rows.
 int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, int64_t out_bytes,
                    const gbd_eval_opts *opts, void *fixed = nullptr, size_t fixed_bytes = 0,
-                   EvalGuard *guard = nullptr, StatusPost *post_req = nullptr) {
+                   EvalGuard *guard = nullptr, StatusPost *post_req = nullptr, bool dense = false) {
     if (!plan->ready && !guard) return fail(GBD_EINVAL, "gbd_plan_eval: plan has no valid setup");
     if (precision != GBD_FP64 && precision != GBD_MIXED) return fail(GBD_EINVAL, "precision must be GBD_FP64 or GBD_MIXED");
     const int64_t M = (int64_t)plan->pl.nx * plan->pl.ny;
@@ -787,7 +793,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     // Gauss's form is not asked for: one segment, written by the product (with
     // truncated beamlets into the first partial).  Segment counts do not apply.
     // The fixed buffer has to hold the row sums beside any partials.
-    bool by_rows = !general && s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
+    bool by_rows = !general && !dense && s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
                    (precision == GBD_FP64 || s.half);
     const size_t row_bytes = by_rows ? (size_t)plan->rows * ((size_t)plan->pl.nx + plan->pl.ny) * (size_t)elem : 0;
     auto row_offset = [&](int64_t nc) -> size_t {  // where the row sums start, with nc truncated segments
@@ -1771,13 +1777,30 @@ int gbd_autotune(gbd_ctx_t ctx, gbd_plan_t plan, int precision, int32_t reps, gb
     const int64_t n_main = plan->n - plan->n_cut;  // the beamlets choose_shape sizes the form for
     // the separable form has a fixed tile: only its segment count is tuned
     const bool sep = pick_form(precision, plan->flags, nullptr) == 3;
-    const int kind = sep ? kTuneSep : kTuneEval;
+    const int kind = sep ? kTuneSep
+                     : cross_applies(precision, pick_form(precision, plan->flags, nullptr), plan->flags, n_main, M) ? kTuneCross
+                                                                                                                  : kTuneEval;
     const int n_rows = sep ? 1
                            : precision == GBD_MIXED ? ((plan->flags & FLAG_STEEP) ? 4 : 5)
                            : (plan->flags & FLAG_STEEP) ? 3
                            : (plan->flags & FLAG_HG)    ? 4
                                                         : 5;
     const int n_waves = sep ? 1 : 3;
+    // milliseconds per evaluation (rc, he: errors)
+    auto timed = [&](bool dense) {
+        rc = plan_eval_impl(ctx, plan, precision, out, out_bytes, nullptr, nullptr, 0, nullptr, nullptr, dense);
+        float f = 0.f;  // after a warm-up / scratch growth
+        if (rc == GBD_OK) he = hipEventRecord(e0, ctx->stream);
+        for (int r = 0; r < reps && rc == GBD_OK && he == hipSuccess; r++)
+            rc = plan_eval_impl(ctx, plan, precision, out, out_bytes, nullptr, nullptr, 0, nullptr, nullptr, dense);
+        if (rc == GBD_OK && he == hipSuccess) he = hipEventRecord(e1, ctx->stream);
+        if (rc == GBD_OK && he == hipSuccess) he = hipEventSynchronize(e1);
+        if (rc == GBD_OK && he == hipSuccess) he = hipEventElapsedTime(&f, e0, e1);
+        return (double)f / reps;
+    };
+    // a plan that goes by rows has no segments: the counts are those of the
+    // product by beamlets, which captured evaluations and beamlets in no rows
+    // of the same size take
     for (int ri = 0; ri < n_rows && he == hipSuccess && rc == GBD_OK; ri++)
         for (int wi = 0; wi < n_waves && he == hipSuccess && rc == GBD_OK; wi++)
             for (int pi = 0; pi < 4 && he == hipSuccess && rc == GBD_OK; pi++) {
@@ -1786,18 +1809,7 @@ int gbd_autotune(gbd_ctx_t ctx, gbd_plan_t plan, int precision, int32_t reps, gb
                 const TuneKey key = tune_key(kind, precision, n_main, M);
                 const auto saved = ctx->tuned.find(key) != ctx->tuned.end() ? ctx->tuned[key] : TuneVal{0, 0, 0, -1};
                 ctx->tuned[key] = TuneVal{sep ? 0 : rows_c[ri], sep ? 0 : waves_c[wi], pct_c[pi], 0.0};
-                rc = plan_eval_impl(ctx, plan, precision, out, out_bytes, nullptr);  // warm-up / scratch growth
-                double ms = 0.0;
-                if (rc == GBD_OK) {
-                    he = hipEventRecord(e0, ctx->stream);
-                    for (int r = 0; r < reps && rc == GBD_OK && he == hipSuccess; r++)
-                        rc = plan_eval_impl(ctx, plan, precision, out, out_bytes, nullptr);
-                    if (he == hipSuccess) he = hipEventRecord(e1, ctx->stream);
-                    if (he == hipSuccess) he = hipEventSynchronize(e1);
-                    float f = 0.f;
-                    if (he == hipSuccess) he = hipEventElapsedTime(&f, e0, e1);
-                    ms = f / reps;
-                }
+                const double ms = timed(sep);
                 if (saved.ms < 0)
                     ctx->tuned.erase(key);
                 else
@@ -1805,6 +1817,9 @@ int gbd_autotune(gbd_ctx_t ctx, gbd_plan_t plan, int precision, int32_t reps, gb
                 if (rc == GBD_OK && he == hipSuccess && ms < bestv.ms)
                     bestv = TuneVal{sep ? 0 : rows_c[ri], sep ? 0 : waves_c[wi], pct_c[pi], ms};
             }
+    // what the plan's evaluations take
+    double ms = bestv.ms;
+    if (sep && plan->rows > 0 && rc == GBD_OK && he == hipSuccess) ms = std::min(ms, timed(false));
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(out);
@@ -1816,7 +1831,7 @@ int gbd_autotune(gbd_ctx_t ctx, gbd_plan_t plan, int precision, int32_t reps, gb
         const EvalGeom g = make_geom(plan->pl, n_main, s);
         *best = gbd_eval_opts{s.rows, s.waves, g.nseg, form_variant(precision, s.form, s.half)};
     }
-    if (best_ms) *best_ms = bestv.ms;
+    if (best_ms) *best_ms = ms;
     return GBD_OK;
 }
 
@@ -1845,7 +1860,8 @@ int gbd_autotune_load(gbd_ctx_t ctx, const char *path) {
         if (sscanf(line, "%d %d %d %d %d %d %d %lf", &k.kind, &k.precision, &k.ln, &k.lm, &v.rows, &v.waves,
                    &v.seg_scale_pct, &v.ms) == 8 &&
             (k.kind == kTuneSep ? v.rows == 0 && v.waves == 0
-                                : (k.kind == kTuneEval || k.kind == kTuneBatch) && valid_shape(v.rows, v.waves, k.precision)) &&
+                                : (k.kind == kTuneEval || k.kind == kTuneBatch || k.kind == kTuneCross) &&
+                                      valid_shape(v.rows, v.waves, k.precision)) &&
             v.seg_scale_pct > 0 && v.seg_scale_pct <= 10000) {
             ctx->tuned[k] = v;
             loaded++;

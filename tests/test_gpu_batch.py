@@ -284,3 +284,43 @@ def test_batch_with_an_empty_instance(ctx):
     A = airy.cpu().numpy().astype(np.float64)
     np.testing.assert_allclose(m3[1, 0], np.sqrt(np.mean(A * A)), rtol=1e-6)
     np.testing.assert_allclose(m3[1, 1], A.max(), rtol=1e-6)
+
+
+def test_autotuned_segments_are_the_dense_forms(ctx, tmp_path):
+    """A plan by rows: the segment count kept is timed on the products by beamlet, ten times as long at this size as
+    the sum by rows, whose time is the one returned."""
+    fresh = gbd.Context(0)
+    sc = scenes.airy_scene(128, npix=512, half_span_lamF=10.0)
+    plan = gbd.Plan(fresh, sc.n).setup(gbd.beamlets_from_scene(fresh, sc), gbd.plane_from_scene(fresh, sc))
+    _, ms = gbd.gbd_autotune(plan, gbd.GBD_FP64, reps=3)
+    path = tmp_path / "tune.txt"
+    gbd.gbd_autotune_save(fresh, str(path))
+    kept = [line.split() for line in path.read_text().splitlines() if line[0] == "2"]
+    assert len(kept) == 1 and float(kept[0][7]) > 3.0 * ms
+
+
+def test_rotor_shapes_leave_the_cross_form_alone(ctx, tmp_path):
+    """Cache entries of the rotor form (kind 0) do not decide for planes of weak cross terms of the same size, nor
+    the other way round."""
+    weak = scenes.zernike_scene(7, n_across=70, npix=130, half_span=30e-6)
+    strong = scenes.zernike_scene(7, n_across=70, npix=130, half_span=30e-6)
+    lens = np.eye(4)
+    lens[2, 1] = lens[3, 0] = 5.0
+    strong.abcd = np.ascontiguousarray((strong.abcd.reshape(-1, 4, 4) @ lens).reshape(-1, 16))
+    fresh = gbd.Context(0)
+    plans = [gbd.Plan(fresh, s.n).setup(gbd.beamlets_from_scene(fresh, s), gbd.plane_from_scene(fresh, s))
+             for s in (weak, strong)]
+    before = [p.shape(gbd.GBD_MIXED) for p in plans]
+    assert [(s["rows_per_lane"], s["waves"]) for s in before] == [(32, 4), (32, 4)]
+    ln, lm = int(np.log2(weak.n)), int(np.log2(130 * 130))
+    path = tmp_path / "tune.txt"
+    path.write_text("".join(f"0 1 {a} {b} 16 2 100 0.1\n" for a in (ln, ln + 1) for b in (lm, lm + 1)))
+    assert gbd.gbd_autotune_load(fresh, str(path)) == 4
+    assert plans[0].shape(gbd.GBD_MIXED) == before[0]
+    tuned = plans[1].shape(gbd.GBD_MIXED)
+    assert (tuned["rows_per_lane"], tuned["waves"]) == (16, 2)
+    gbd.gbd_autotune(plans[0], gbd.GBD_MIXED, reps=2)
+    assert plans[1].shape(gbd.GBD_MIXED) == tuned
+    E = plans[0].eval(gbd.GBD_MIXED).cpu().numpy().astype(np.complex128)
+    ref = oracle.eval_field(weak)
+    assert np.linalg.norm(E - ref) <= 1e-6 * np.linalg.norm(ref)
