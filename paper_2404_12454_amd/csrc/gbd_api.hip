@@ -800,6 +800,31 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         const size_t part = nc == 0 ? 0 : reduce_wide_offset(compact ? 1 : 0, M) + (size_t)(nc + (compact ? 0 : 1)) * M * 16;
         return (part + 255) & ~(size_t)255;
     };
+    // a count given by the caller is refused by its own form's limits, by rows or not
+    const bool given = opts && opts->segments > 0;
+    if (n_main > 0) {
+        g = make_geom(plan->pl, n_main, s);
+        nseg_main = g.nseg;
+    }
+    // partial bytes of nm main and nc truncated segments (none when one
+    // segment writes the output directly)
+    // (the cross form's count as the rotor form's, whose shape it reports)
+    const size_t per_cut = (size_t)M * 16;
+    auto need_of = [&](int64_t nm, int64_t nc) -> size_t {
+        if (nm + nc <= 1 && nc == 0) return 0;
+        return compact && !s.cross ? reduce_wide_offset((int32_t)nm, M) + (size_t)nc * per_cut : (size_t)(nm + nc) * per_cut;
+    };
+    auto refuse_segments = [&] {
+        return fail(GBD_ERANGE, "%d segments of %lld pixels need %zu bytes of partial sums; the static buffer holds %zu",
+                    (int)(nseg_main + nseg_cut), (long long)M, need_of(nseg_main, nseg_cut), fixed_bytes);
+    };
+    auto grid_too_large = [](const EvalGeom &q) {
+        return (int64_t)q.tiles_x * q.tiles_y * q.nseg > (int64_t)0x7fffffff - 8;
+    };
+    if (by_rows && given) {
+        if (grid_too_large(g)) return fail(GBD_ERANGE, "grid too large");
+        if (fixed && need_of(nseg_main, nseg_cut) > fixed_bytes) return refuse_segments();
+    }
     if (fixed && by_rows) {
         while (nseg_cut > 1 && row_offset(nseg_cut) + row_bytes > fixed_bytes) {
             gc = cut_geom(ctx, precision, level, plan->pl, plan->n_cut, nseg_cut - 1);
@@ -820,8 +845,8 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         if (plan->n_cut > 0) guard->mask |= FLAG_CUT0 | FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
         guard->flags = plan->flags & guard->mask;
     }
-    if (by_rows) s.nseg = 1;
-    if (n_main > 0) {
+    if (by_rows) {
+        s.nseg = 1;
         g = make_geom(plan->pl, n_main, s);
         nseg_main = g.nseg;
     }
@@ -833,7 +858,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         g = make_geom(plan->pl, n_main, s);
         nseg_main = g.nseg;
     };
-    if (fixed && s.cross && !(opts && opts->segments > 0)) {
+    if (fixed && s.cross && !given) {
         const size_t per = (size_t)M * 16;
         const int64_t room = (int64_t)(fixed_bytes / per);
         if (nseg_main + nseg_cut > room) {
@@ -842,20 +867,10 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         }
     }
     if (fixed && !by_rows) {
-        // partial bytes of nm main and nc truncated segments (none when one
-        // segment writes the output directly)
-        // (the cross form's count as the rotor form's, whose shape it reports)
         const bool small = compact && !s.cross;
-        const size_t per_main = (size_t)M * (small ? 8 : 16), per_cut = (size_t)M * 16;
-        auto need_of = [&](int64_t nm, int64_t nc) -> size_t {
-            if (nm + nc <= 1 && nc == 0) return 0;
-            return small ? reduce_wide_offset((int32_t)nm, M) + (size_t)nc * per_cut : (size_t)(nm + nc) * per_cut;
-        };
+        const size_t per_main = (size_t)M * (small ? 8 : 16);
         if (need_of(nseg_main, nseg_cut) > fixed_bytes) {
-            if (opts && opts->segments > 0)
-                return fail(GBD_ERANGE, "%d segments of %lld pixels need %zu bytes of partial sums; the static buffer "
-                            "holds %zu", (int)(nseg_main + nseg_cut), (long long)M, need_of(nseg_main, nseg_cut),
-                            fixed_bytes);
+            if (given) return refuse_segments();
             if (nseg_cut > 0) {  // truncated beamlets: at most half the buffer
                 const int64_t max_cut = (int64_t)((fixed_bytes / 2) / per_cut);
                 if (max_cut < 1)
@@ -886,9 +901,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
                             need_of(nseg_main, nseg_cut), fixed_bytes);
         }
     }
-    if (n_main > 0 && (int64_t)g.tiles_x * g.tiles_y * g.nseg > (int64_t)0x7fffffff - 8)
-        return fail(GBD_ERANGE, "grid too large");
-    if (nseg_cut > 0 && (int64_t)gc.tiles_x * gc.tiles_y * gc.nseg > (int64_t)0x7fffffff - 8)
+    if ((n_main > 0 && grid_too_large(g)) || (nseg_cut > 0 && grid_too_large(gc)))
         return fail(GBD_ERANGE, "grid too large");
     const int32_t total = nseg_main + nseg_cut;
     const bool reduce = total > 1 || nseg_cut > 0;

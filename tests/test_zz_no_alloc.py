@@ -135,3 +135,22 @@ def test_noalloc_empty_plan_clears_the_output(ctx):
         plan.eval_noalloc(prec, out=out)
         torch.cuda.synchronize()
         assert not bool(out.abs().sum())
+
+
+@pytest.mark.parametrize("precision,segments", [(gbd.GBD_MIXED, 20), (gbd.GBD_FP64, 10)])
+def test_noalloc_refuses_explicit_segments_of_beamlets_in_rows(ctx, precision, segments):
+    """Taken by rows no segment partials are written, but a count beyond the buffer stays refused, output untouched."""
+    import torch
+    sc = scenes.airy_scene(40, npix=700, npix_y=660, half_span_lamF=10.0)
+    M = 700 * 660
+    plan = plan_of(ctx, sc)
+    most = LIMIT // (M * (8 if precision == gbd.GBD_MIXED else 16))
+    assert segments > most
+    out = torch.full((660, 700), 3.0 + 1.0j, dtype=plan.eval(precision).dtype, device="cuda")
+    with pytest.raises(gbd.GbdError) as e:
+        plan.eval_noalloc(precision, out=out, opts=dict(segments=segments))
+    assert e.value.code == -7 and "static buffer" in str(e.value)
+    torch.cuda.synchronize()
+    assert bool((out == (3.0 + 1.0j)).all())
+    got = plan.eval_noalloc(precision, opts=dict(segments=most - 1)).cpu()
+    assert torch.equal(bits(got), bits(plan.eval(precision, opts=dict(segments=most - 1)).cpu()))
