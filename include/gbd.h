@@ -116,7 +116,9 @@ typedef struct {
                                (four or more on average) that share one ABCD and differ
                                along x only, as on a pupil grid stored row by row, and the
                                setup finds each run's y factors V equal, forms 0 and 4 (not
-                               5) sum each run's U first, E = sum_runs V(y) sum_j U_j(x):
+                               5) sum each run's U first where that is shorter (not on
+                               short runs over small planes) and takes 4 GiB of scratch
+                               at most, E = sum_runs V(y) sum_j U_j(x):
                                factors and terms as above, FP32 sums of at most 1,024 U
                                and FP32 MFMA products of at most N / 32 runs in the mixed
                                form, FP64 in the FP64 one.  It has no segments: a count

@@ -461,6 +461,33 @@ int64_t cross_segments(int cus, int64_t tiles, int64_t n, int64_t m, int64_t lon
     return best;
 }
 
+// Bytes of the row sums and y factors of an evaluation by rows.
+size_t row_scratch(int64_t rows, const PlaneGeom &pl, int precision) {
+    return (size_t)rows * ((size_t)pl.nx + (size_t)pl.ny) * (precision == GBD_FP64 ? 16 : 8);
+}
+
+// Whether the sum by rows of n beamlets in `rows` chunks takes less time than
+// the products by beamlet.  Its product has a workgroup per 32 x 32 pixels,
+// each through all chunks (0.030 us a chunk, FP64 0.046, up to a round of
+// workgroups over the CUs), the other splits the beamlets over the chip
+// whatever the plane: short runs on small planes are better off there.
+// Microseconds, mixed, by rows / by beamlet, of runs of 4 and of 16: 10,000
+// on 64^2 79 / 39, 31 / 39; 100,000 on 64^2 642 / 114, 183 / 115; 1,000 on 64^2
+// 23 / 32, 18 / 32; 100,000 on 300^2 700 / 442, 205 / 440; 10,000 on 1024^2 236 /
+// 256, 79 / 254.  FP64, whose products by beamlet are slower: 10,000 on 64^2
+// 123 / 73, 43 / 75, but 144 / 248 on 300^2 at runs of 4.
+bool rows_pay(int precision, int cus, int64_t n, int64_t rows, const PlaneGeom &pl) {
+    if (rows <= 0 || row_scratch(rows, pl, precision) > (size_t)kFormScratch) return false;
+    const bool mixed = precision == GBD_MIXED;
+    auto tiles = [&](int64_t wx, int64_t wy) { return ((pl.nx + wx - 1) / wx) * ((pl.ny + wy - 1) / wy); };
+    const double rounds = (double)tiles(kRowTilePx, kRowTilePx) / cus;
+    const double product = (double)rows * std::max(mixed ? 0.030 : 0.046, (mixed ? 0.0225 : 0.037) * rounds);
+    const double sums = (double)n * pl.nx / (mixed ? 1.05e6 : 5.3e5);
+    const double by_beamlet = mixed ? (double)n * (256 * 128 * tiles(256, 128)) / 4.9e7 + 14.0
+                                    : (double)n * (128 * 128 * tiles(128, 128)) / 6.9e6 + 44.0;
+    return product + sums <= by_beamlet;
+}
+
 // Workgroup tile of a separable shape in pixels.
 void sep_wg_tile(const Shape &s, int &px, int &py) {
     if (s.half) {
@@ -789,13 +816,14 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         nseg_cut = gc.nseg;
     }
     // The separable form by rows wherever the beamlets come in row chunks
-    // (row_chunks; the setup found their y factors equal) and FP32 MFMA in
+    // (row_chunks; the setup found their y factors equal) that pay and FP32 MFMA in
     // Gauss's form is not asked for: one segment, written by the product (with
     // truncated beamlets into the first partial).  Segment counts do not apply.
     // The fixed buffer has to hold the row sums beside any partials.
-    bool by_rows = !general && !dense && s.form == 3 && n_main > 0 && plan->rows > 0 && !(plan->flags & FLAG_ROWS) &&
-                   (precision == GBD_FP64 || s.half);
-    const size_t row_bytes = by_rows ? (size_t)plan->rows * ((size_t)plan->pl.nx + plan->pl.ny) * (size_t)elem : 0;
+    const bool rows_route = !general && !dense && s.form == 3 && n_main > 0 && (precision == GBD_FP64 || s.half) &&
+                            rows_pay(precision, ctx->cus, n_main, plan->rows, plan->pl);
+    bool by_rows = rows_route && !(plan->flags & FLAG_ROWS);
+    const size_t row_bytes = by_rows ? row_scratch(plan->rows, plan->pl, precision) : 0;
     auto row_offset = [&](int64_t nc) -> size_t {  // where the row sums start, with nc truncated segments
         const size_t part = nc == 0 ? 0 : reduce_wide_offset(compact ? 1 : 0, M) + (size_t)(nc + (compact ? 0 : 1)) * M * 16;
         return (part + 255) & ~(size_t)255;
@@ -839,7 +867,7 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
     if (guard) {
         // the flags that this evaluation's route depends on
         guard->mask = FLAG_STEEP | FLAG_CROSS | FLAG_HG;
-        if (s.form == 3 && plan->rows > 0) guard->mask |= FLAG_ROWS;
+        if (rows_route) guard->mask |= FLAG_ROWS;
         if (cross_applies(precision, s.form, plan->flags & ~(uint32_t)FLAG_CROSS2, n_main, M))
             guard->mask |= FLAG_CROSS1 | FLAG_CROSS2;
         if (plan->n_cut > 0) guard->mask |= FLAG_CUT0 | FLAG_CUT1 | FLAG_CUT2 | FLAG_CUT3;
@@ -2017,7 +2045,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     const size_t t2_items = al(n_inst * sizeof(BatchEval));
     const size_t t2_e0map = t2_items + al((size_t)std::max<int64_t>(2 * n_items, 2) * sizeof(int32_t));
     const size_t t2_rows = t2_e0map + al((size_t)max_chunks * sizeof(int32_t));
-    const size_t t2_bytes = t2_rows + al((4 * (size_t)n_inst + 1) * sizeof(int32_t));
+    const size_t t2_bytes = t2_rows + al(4 * (size_t)n_inst * sizeof(int32_t));
     if ((rc = grow(w.rec, (size_t)std::max<int64_t>(total, 1) * sizeof(Rec32), "batch records")) ||
         (rc = grow(w.l5, (size_t)std::max<int64_t>(total, 1) * sizeof(double), "batch records")) ||
         (airy && (rc = grow(w.e0t, (size_t)std::max<int64_t>(total, 1) * sizeof(double2), "batch normalisation"))) ||
@@ -2102,10 +2130,17 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     int32_t *e0map = reinterpret_cast<int32_t *>(h2 + t2_e0map);  // normalisation chunk -> instance
     // each instance whose beamlets come in row chunks goes by rows, as a single evaluation of it does
     int32_t *sum_inst = reinterpret_cast<int32_t *>(h2 + t2_rows), *sum_first = sum_inst + n_inst,
-            *prod_inst = sum_first + n_inst + 1, *prod_first = prod_inst + n_inst;
-    BatchRows br{};
-    int32_t sum_blocks = 0;
-    int64_t sum_off = 0;
+            *prod_inst = sum_first + n_inst, *prod_first = prod_inst + n_inst;
+    // in groups, one after the other, whose sums share one buffer of kFormScratch at most
+    struct RowGroup {
+        BatchRows br{};
+        int32_t begin, end;  // instances
+        int32_t list = 0;    // its first entry of the lists
+        int32_t sum_blocks = 0;
+    };
+    std::vector<RowGroup> groups;
+    int64_t sum_off = 0, sum_most = 0;
+    int32_t n_rows = 0;
     int64_t foff = 0;
     int32_t n_chunks = 0;
     for (int32_t i = 0; i < n_inst; i++) {
@@ -2117,15 +2152,24 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         e.nx = g.nx;
         e.ny = g.ny;
         const BeamletsDev &b = bs[i]->dev;
-        if (half && b.rows > 0 && !rowbad[i] && (int64_t)g.nx * g.ny > 0) {
+        if (half && !rowbad[i] && (int64_t)g.nx * g.ny > 0 && rows_pay(GBD_MIXED, ctx->cus, b.n, b.rows, g)) {
+            const int64_t elems = (int64_t)b.rows * (g.nx + g.ny);
+            if (groups.empty() || (sum_off + elems) * (int64_t)sizeof(float2) > kFormScratch) {
+                groups.push_back(RowGroup{BatchRows{}, i, i, n_rows, 0});
+                sum_off = 0;
+            }
+            RowGroup &G = groups.back();
             e.rows = b.rows;
             e.row_start = b.row_start;
             e.sum_off = sum_off;
-            sum_off += (int64_t)b.rows * (g.nx + g.ny);
-            sum_inst[br.n] = i;
-            sum_first[br.n++] = sum_blocks;
+            sum_off += elems;
+            sum_most = std::max(sum_most, sum_off);
+            sum_inst[n_rows] = i;
+            sum_first[n_rows++] = G.sum_blocks;
             const int cols = g.nx > 64 ? 128 : 64;
-            sum_blocks += b.rows * ((g.nx + cols - 1) / cols);
+            G.sum_blocks += b.rows * ((g.nx + cols - 1) / cols);
+            G.br.n++;
+            G.end = i + 1;
             e.tiles_x = (g.nx + kRowTilePx - 1) / kRowTilePx;
             e.tiles_y = (g.ny + kRowTilePx - 1) / kRowTilePx;
         } else if (form == 3) {  // separable form: the single evaluation's workgroup tiles
@@ -2153,18 +2197,18 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         e.e0_chunks = (int32_t)((e.n + kE0Chunk - 1) / kE0Chunk);
         for (int32_t c = 0; c < e.e0_chunks; c++) e0map[n_chunks++] = i;
     }
-    sum_first[br.n] = sum_blocks;
     std::vector<int32_t> order(n_inst);
     for (int32_t i = 0; i < n_inst; i++) order[i] = i;
     // an instance's cost: its pairs, by rows its (chunk, pixel) products
     auto cost = [&](int32_t i) { return (ev[i].rows ? ev[i].rows : ev[i].n) * ((int64_t)ev[i].nx * ev[i].ny); };
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost(x) > cost(y); });
     // by rows: the k-th largest to XCD 0 ... 7, 7 ... 0, 0 ...
-    {
+    for (RowGroup &G : groups) {
+        BatchRows &br = G.br;
         std::vector<int32_t> list[kXcds];
         int32_t k = 0;
         for (int32_t i : order)
-            if (ev[i].rows) {
+            if (ev[i].rows && i >= G.begin && i < G.end) {
                 const int32_t r = k++ % (2 * kXcds);
                 list[r < kXcds ? r : 2 * kXcds - 1 - r].push_back(i);
             }
@@ -2172,8 +2216,8 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
         for (int x = 0; x < kXcds; x++) {
             br.prod_list[x] = at;
             for (int32_t i : list[x]) {
-                prod_inst[at] = i;
-                prod_first[at++] = br.prod_tiles[x];
+                prod_inst[G.list + at] = i;
+                prod_first[G.list + at++] = br.prod_tiles[x];
                 br.prod_tiles[x] += ev[i].tiles_x * ev[i].tiles_y;
             }
         }
@@ -2198,9 +2242,9 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
             ev[i].item_off = n_part;
             n_part += (int64_t)ev[i].tiles_x * ev[i].tiles_y;
         }
-    if ((rc = grow(w.row_sums, (size_t)std::max<int64_t>(sum_off, 1) * sizeof(float2), "batch row sums"))) return rc;
+    if ((rc = grow(w.row_sums, (size_t)std::max<int64_t>(sum_most, 1) * sizeof(float2), "batch row sums"))) return rc;
     // the tables up to the last part in use (the work list is empty when every instance goes by rows)
-    const size_t t2_used = br.n ? t2_bytes : t2_e0map + (size_t)n_chunks * sizeof(int32_t);
+    const size_t t2_used = n_rows ? t2_bytes : t2_e0map + (size_t)n_chunks * sizeof(int32_t);
     HIP_TRY(hipMemcpyAsync(d2, h2, t2_used, hipMemcpyHostToDevice, st), "table upload");
     HIP_TRY(hipEventRecord(w.stage_ev, st), "hipEventRecord");
     w.stage_pending = true;
@@ -2224,15 +2268,15 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
                                 static_cast<const double2 *>(w.e0t.p), static_cast<double2 *>(w.e0part.p),
                                 static_cast<double2 *>(w.e0.p), st),
                 "normalisation launch");
-    if (br.n > 0) {
-        const int32_t *lists = reinterpret_cast<const int32_t *>(d2 + t2_rows);
-        br.sum_inst = lists;
-        br.sum_first = lists + n_inst;
-        br.prod_inst = lists + 2 * n_inst + 1;
-        br.prod_first = lists + 3 * n_inst + 1;
-        br.peaks = flags + 4;
-        br.sums = static_cast<float2 *>(w.row_sums.p);
-        HIP_TRY(launch_batch_rows(a, br, sum_blocks, st), "batch row launch");
+    for (RowGroup &G : groups) {
+        const int32_t *lists = reinterpret_cast<const int32_t *>(d2 + t2_rows) + G.list;
+        G.br.sum_inst = lists;
+        G.br.sum_first = lists + n_inst;
+        G.br.prod_inst = lists + 2 * n_inst;
+        G.br.prod_first = lists + 3 * n_inst;
+        G.br.peaks = flags + 4;
+        G.br.sums = static_cast<float2 *>(w.row_sums.p);
+        HIP_TRY(launch_batch_rows(a, G.br, G.sum_blocks, st), "batch row launch");
     }
     HIP_TRY(launch_batch_eval(rows, waves, form, half, ctx->cus, a, st), "batch eval launch");
     if (airy) {

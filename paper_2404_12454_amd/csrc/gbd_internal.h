@@ -253,15 +253,15 @@ struct BatchArgs {
     double zone_r2[kMaxZones + 1];  // squared radii bounding the annular zones
 };
 
-// The instances of a batch taken by rows.  Row sums: list position k's
-// workgroups are [sum_first[k], sum_first[k + 1]).  Products: workgroup b
+// Instances of a batch taken by rows.  Row sums: list position k's
+// workgroups start at sum_first[k].  Products: workgroup b
 // runs on XCD b % 8, which takes the instances prod_inst[prod_list[x] ...
 // prod_list[x + 1] - 1] whole, one after the other (their row sums stay in
 // that XCD's L2); prod_first[e] tiles of its precede list entry e.
 constexpr int kXcds = 8;
 struct BatchRows {
     int32_t n;               // instances taken by rows
-    const int32_t *sum_inst, *sum_first;    // [n], [n + 1]
+    const int32_t *sum_inst, *sum_first;    // [n], [n]
     const int32_t *prod_inst, *prod_first;  // [n], [n]
     int32_t prod_list[kXcds + 1], prod_tiles[kXcds];
     const uint32_t *peaks;   // per instance, the setup's key

@@ -159,3 +159,67 @@ def test_masked_beamlets_in_a_weak_field(ctx, make, weak):
         if sc.order is None:
             _, f = gbd.gbd_eval_batch(ctx, [gbd.beamlets_from_scene(ctx, s)], [gbd.plane_from_scene(ctx, s)], fields=True)
             assert rel_l2(f[0].cpu().numpy(), ref) <= TOL[gbd.GBD_MIXED]
+
+
+def runs(length, rows, nx, ny, seed=4):
+    """`rows` rows of `length` beamlets each."""
+    a = scenes.airy_scene(12, npix=nx, npix_y=ny, half_span_lamF=5.0)
+    x, y = np.linspace(-4e-3, 4e-3, length), np.linspace(-4e-3, 4e-3, rows)
+    r1 = np.stack([np.tile(x, rows), np.repeat(y, length)], axis=1)
+    n = len(r1)
+    amp = np.random.default_rng(seed).normal(size=(n, 2))
+    return scenes.Scene(a.lam, a.l0, r1, np.zeros((n, 2)), np.full(n, 3e-4), amp, np.zeros(n), a.abcd, a.plane)
+
+
+@pytest.mark.parametrize("precision,length,rows,nx,ny,by_rows", [
+    (gbd.GBD_MIXED, 4, 2500, 64, 64, False), (gbd.GBD_MIXED, 16, 2500, 64, 64, False),
+    (gbd.GBD_MIXED, 64, 100, 64, 64, True), (gbd.GBD_MIXED, 4, 500, 300, 130, True),
+    (gbd.GBD_FP64, 4, 2500, 64, 64, False), (gbd.GBD_FP64, 4, 250, 64, 64, True)])
+def test_short_runs_on_small_planes_go_by_beamlet(ctx, precision, length, rows, nx, ny, by_rows):
+    """The sum by rows only where it is the faster one: it has no segments, so a count changes no bit of it."""
+    import torch
+    sc = runs(length, rows, nx, ny)
+    b, p = gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc)
+    plan = gbd.Plan(ctx, sc.n).setup(b, p)
+    E = [torch.view_as_real(plan.eval(precision, opts=dict(segments=k)).cpu()) for k in (2, 5)]
+    assert torch.equal(*E) == by_rows
+    assert rel_l2(field(ctx, sc, precision), oracle.eval_field(sc)) <= TOL[precision]
+    if precision == gbd.GBD_MIXED and sc.n <= 16384:  # the batch goes the same way (more: its rotor form)
+        one = plan.eval(precision, opts=dict(segments=1, variant=4)).cpu()
+        _, f = gbd.gbd_eval_batch(ctx, [b], [p], fields=True)
+        assert torch.equal(torch.view_as_real(one), torch.view_as_real(f[0].cpu()))
+
+
+def test_row_scratch_is_bounded():
+    """560,000 beamlets in runs of 4 on 1024 x 1024 pixels, FP64: 4.6 GB of row sums, so by beamlet."""
+    import torch
+    ensure_library()
+    ctx = gbd.Context(0)
+    sc = runs(4, 140000, 1024, 1024)
+    plan = gbd.Plan(ctx, sc.n).setup(gbd.beamlets_from_scene(ctx, sc), gbd.plane_from_scene(ctx, sc))
+    out = torch.empty((1024, 1024), dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan.eval(gbd.GBD_FP64, out=out)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] < 1 << 30
+    assert rel_l2(plan.eval(gbd.GBD_MIXED).cpu().numpy(), out.cpu().numpy()) <= TOL[gbd.GBD_MIXED]
+
+
+def test_batch_row_scratch_is_bounded():
+    """300 instances of 250 runs on 8192 x 1 pixels: 4.9 GB of row sums, taken in two groups that share a buffer."""
+    import torch
+    ensure_library()
+    ctx = gbd.Context(0)
+    ss = [runs(4, 250, 8192, 1, seed) for seed in range(300)]
+    bs, ps = [gbd.beamlets_from_scene(ctx, s) for s in ss], [gbd.plane_from_scene(ctx, s) for s in ss]
+    want = {k: gbd.gbd_eval(ctx, bs[k], ps[k], gbd.GBD_MIXED, opts=dict(segments=1, variant=4)).cpu()
+            for k in (0, 1, 130, 261, 262, 299)}
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    _, f = gbd.gbd_eval_batch(ctx, bs, ps, fields=True)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] < 4.4 * 2**30
+    for k, E in want.items():
+        assert torch.equal(torch.view_as_real(E), torch.view_as_real(f[k].cpu())), k
+    assert rel_l2(f[299].cpu().numpy(), oracle.eval_field(ss[299])) <= TOL[gbd.GBD_MIXED]
