@@ -430,6 +430,15 @@ int gbd_airy(gbd_ctx_t ctx, gbd_plane_t p, double D, double f, double lambda, fl
 int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *beamlets, const gbd_plane_t *planes,
                    const float *airy, int64_t airy_bytes, const double *zone_edges, int32_t n_zones,
                    double *metrics_out, void *fields_out, int64_t fields_bytes, const gbd_eval_opts *opts);
+/* The same in two calls: _start returns once everything is launched (it still
+ * waits for the setup status), _finish waits for the metrics of the context's
+ * last started batch (count = n_inst * (2 + n_zones); GBD_EINVAL if it had no
+ * airy or was collected, GBD_ERANGE for another count).  airy and fields_out
+ * stay in use until then. */
+int gbd_eval_batch_start(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *beamlets, const gbd_plane_t *planes,
+                         const float *airy, int64_t airy_bytes, const double *zone_edges, int32_t n_zones,
+                         void *fields_out, int64_t fields_bytes, const gbd_eval_opts *opts);
+int gbd_eval_batch_finish(gbd_ctx_t ctx, double *metrics_out, int64_t count);
 
 /* --- surrogate network ------------------------------------------------------
  * A multilayer perceptron n_in -> width (SiLU) x depth -> 1 trained with AdamW

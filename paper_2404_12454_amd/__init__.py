@@ -106,6 +106,8 @@ def load_library():
         "gbd_autotune_save": (ctypes.c_int, [P, ctypes.c_char_p]),
         "gbd_autotune_load": (ctypes.c_int, [P, ctypes.c_char_p]),
         "gbd_eval_batch": (ctypes.c_int, [P, I32, P, P, P, I64, P, I32, P, P, I64, P]),
+        "gbd_eval_batch_start": (ctypes.c_int, [P, I32, P, P, P, I64, P, I32, P, I64, P]),
+        "gbd_eval_batch_finish": (ctypes.c_int, [P, P, I64]),
         "gbd_issue_probe": (ctypes.c_int, [P, I32, I32, P, P]),
     }
     for name, (res, args) in sig.items():
@@ -446,25 +448,30 @@ def gbd_eval_batch(ctx: Context, beamlets, planes, airy=None, zone_edges=None, f
     metrics = np.zeros((n, 2 + nz)) if airy is not None else None
     fbuf = None
     if fields:
-        total = sum(p.nx * p.ny for p in planes)
+        sizes = {(p.nx, p.ny) for p in planes}
+        nx, ny = sizes.pop() if len(sizes) == 1 else (0, 0)  # of planes all alike
+        total = n * nx * ny or sum(p.nx * p.ny for p in planes)
         fbuf = torch.empty(max(total, 1), dtype=torch.complex64, device=f"cuda:{ctx.device}")
     o = _opts(opts)
-    _check(load_library().gbd_eval_batch(
+    _check(load_library().gbd_eval_batch_start(
         ctx.handle, n, _p(hb), _p(hp), None if airy is None else ctypes.c_void_p(airy.data_ptr()),
-        0 if airy is None else airy.numel() * 4, _p(ze), nz, _p(metrics),
+        0 if airy is None else airy.numel() * 4, _p(ze), nz,
         None if fbuf is None else ctypes.c_void_p(fbuf.data_ptr()), 0 if fbuf is None else fbuf.numel() * 8,
         None if o is None else ctypes.byref(o)))
     out_fields = None
     if fbuf is not None:
-        nx, ny = (planes[0].nx, planes[0].ny) if n else (0, 0)
-        if n and nx * ny > 0 and all(p.nx == nx and p.ny == ny for p in planes):
-            out_fields = list(fbuf.view(n, ny, nx).unbind(0))
+        if nx * ny > 0:
+            # one view each, by index: unbind's are refused in-place changes that record gradients
+            planes_of = fbuf.view(n, ny, nx)
+            out_fields = [planes_of[i] for i in range(n)]
         else:
             out_fields, off = [], 0
             for p in planes:
                 m = p.nx * p.ny
                 out_fields.append(fbuf[off:off + m].view(p.ny, p.nx))
                 off += m
+    if metrics is not None and n:  # the views were made while the kernels run
+        _check(load_library().gbd_eval_batch_finish(ctx.handle, _p(metrics), metrics.size))
     return metrics, out_fields
 
 

@@ -46,6 +46,8 @@ struct BatchWork {
     size_t stage_bytes = 0;
     hipEvent_t stage_ev = nullptr;   // after the last copy from stage
     bool stage_pending = false;      // stage_ev recorded and not yet waited for
+    const double *host_metrics = nullptr;  // in stage: where the metrics of a started batch arrive
+    int64_t n_metrics = 0;                 // how many (0: none to collect)
 };
 
 // autotuner cache key: (kind, precision, log2 N bucket, log2 M bucket)
@@ -1958,10 +1960,10 @@ int gbd_airy(gbd_ctx_t ctx, gbd_plane_t p, double D, double f, double lambda, fl
     return GBD_OK;
 }
 
-int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, const gbd_plane_t *ps, const float *airy,
-                   int64_t airy_bytes, const double *zone_edges, int32_t n_zones, double *metrics_out,
-                   void *fields_out, int64_t fields_bytes, const gbd_eval_opts *opts) {
+int gbd_eval_batch_start(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, const gbd_plane_t *ps, const float *airy,
+                   int64_t airy_bytes, const double *zone_edges, int32_t n_zones, void *fields_out, int64_t fields_bytes, const gbd_eval_opts *opts) {
     if (!ctx) return fail(GBD_EINVAL, "ctx is NULL");
+    ctx->batch.n_metrics = 0;
     if (n_inst < 0) return fail(GBD_EINVAL, "n_inst < 0");
     if (n_inst == 0) return GBD_OK;
     if (!bs || !ps) return fail(GBD_EINVAL, "beamlets/planes arrays are NULL");
@@ -1972,8 +1974,6 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
             if (!(zone_edges[z] >= 0.0) || !std::isfinite(zone_edges[z]) || (z > 0 && zone_edges[z] < zone_edges[z - 1]))
                 return fail(GBD_EINVAL, "zone_edges must be finite, >= 0 and non-decreasing");
     }
-    if (metrics_out && !airy) return fail(GBD_EINVAL, "metrics need the reference irradiance");
-    if (airy && !metrics_out) return fail(GBD_EINVAL, "metrics_out is NULL");
     if (opts && (opts->variant < 0 || opts->variant > 5)) return fail(GBD_EINVAL, "variant must be 0 ... 5");
     int rows = 32, waves = 4;  // 32 rows: rotor form; 16 where the form resolves otherwise
     int64_t pairs = 0, n_max = 0;
@@ -2030,6 +2030,7 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     //   [BatchInst x n | offs x (n + 1) | blks x (n + 1)]   uploaded before the setup (tab1)
     //   [status x 4 | peaks x n | row flags x n]            read back after it
     //   [BatchEval x n | items | e0map | row lists]         uploaded before the evaluation (tab2)
+    //   [metrics]                                           read back after it
     // each table part in one copy to a device buffer of the same layout.  The
     // host rewrites the buffer only once the stream has passed the previous
     // call's copies from it (stage_ev).
@@ -2061,7 +2062,8 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming), "hipEventCreate");
     if (w.stage_pending) HIP_TRY(hipEventSynchronize(w.stage_ev), "hipEventSynchronize");
     w.stage_pending = false;
-    const size_t stage_bytes = t1_bytes + rb_bytes + t2_bytes;
+    const int64_t n_metrics = airy ? (int64_t)n_inst * (2 + n_zones) : 0;
+    const size_t stage_bytes = t1_bytes + rb_bytes + t2_bytes + (size_t)n_metrics * sizeof(double);
     if (stage_bytes > w.stage_bytes) {
         if (w.stage) (void)hipHostFree(w.stage);
         w.stage = nullptr;
@@ -2282,13 +2284,42 @@ int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, cons
     if (airy) {
         HIP_TRY(launch_batch_finalize(a.inst, n_inst, a.part, n_zones, static_cast<double *>(w.metrics.p), st),
                 "finalize launch");
-        HIP_TRY(hipMemcpyAsync(metrics_out, w.metrics.p, (size_t)n_inst * (2 + n_zones) * sizeof(double),
-                               hipMemcpyDeviceToHost, st),
+        double *host = reinterpret_cast<double *>(h2 + t2_bytes);
+        HIP_TRY(hipMemcpyAsync(host, w.metrics.p, (size_t)n_metrics * sizeof(double), hipMemcpyDeviceToHost, st),
                 "metrics copy");
-        HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-        w.stage_pending = false;
+        HIP_TRY(hipEventRecord(w.stage_ev, st), "hipEventRecord");
+        w.host_metrics = host;
+        w.n_metrics = n_metrics;
     }
     return GBD_OK;
+}
+
+int gbd_eval_batch_finish(gbd_ctx_t ctx, double *metrics_out, int64_t count) {
+    if (!ctx || !metrics_out) return fail(GBD_EINVAL, "NULL argument");
+    BatchWork &w = ctx->batch;
+    if (w.n_metrics == 0) return fail(GBD_EINVAL, "no batch was started with a reference irradiance");
+    if (count != w.n_metrics)
+        return fail(GBD_ERANGE, "metrics_out holds %lld values, the batch has %lld", (long long)count, (long long)w.n_metrics);
+    const int rc = ensure_device(ctx);
+    if (rc) return rc;
+    HIP_TRY(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");  // a stream left since has been drained
+    w.stage_pending = false;
+    memcpy(metrics_out, w.host_metrics, (size_t)count * sizeof(double));
+    w.n_metrics = 0;
+    return GBD_OK;
+}
+
+int gbd_eval_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, const gbd_plane_t *ps, const float *airy,
+                   int64_t airy_bytes, const double *zone_edges, int32_t n_zones, double *metrics_out,
+                   void *fields_out, int64_t fields_bytes, const gbd_eval_opts *opts) {
+    if (ctx && n_inst > 0) {
+        if (metrics_out && !airy) return fail(GBD_EINVAL, "metrics need the reference irradiance");
+        if (airy && !metrics_out) return fail(GBD_EINVAL, "metrics_out is NULL");
+    }
+    const int rc = gbd_eval_batch_start(ctx, n_inst, bs, ps, airy, airy_bytes, zone_edges, n_zones, fields_out,
+                                        fields_bytes, opts);
+    if (rc || n_inst == 0 || !airy) return rc;
+    return gbd_eval_batch_finish(ctx, metrics_out, (int64_t)n_inst * (2 + n_zones));
 }
 
 int gbd_autotune_batch(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs, const gbd_plane_t *ps,

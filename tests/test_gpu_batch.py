@@ -324,3 +324,58 @@ def test_rotor_shapes_leave_the_cross_form_alone(ctx, tmp_path):
     E = plans[0].eval(gbd.GBD_MIXED).cpu().numpy().astype(np.complex128)
     ref = oracle.eval_field(weak)
     assert np.linalg.norm(E - ref) <= 1e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("sizes", [[(40, 30)] * 3, [(40, 30), (31, 17)]])
+def test_batch_fields_take_in_place_changes_with_gradients(ctx, sizes):
+    """Fields are ordinary views of one allocation, of equal planes too."""
+    import torch
+    ss = [scenes.airy_scene(12, npix=nx, npix_y=ny) for nx, ny in sizes]
+    bs, ps = [gbd.beamlets_from_scene(ctx, s) for s in ss], [gbd.plane_from_scene(ctx, s) for s in ss]
+    _, fields = gbd.gbd_eval_batch(ctx, bs, ps, fields=True)
+    base, off = fields[0]._base, 0
+    for f, (nx, ny) in zip(fields, sizes):
+        assert f._base is base and f.shape == (ny, nx) and f.stride() == (nx, 1) and f.storage_offset() == off
+        off += nx * ny
+    phase = torch.ones(fields[1].shape, dtype=torch.complex64, device="cuda", requires_grad=True)
+    want = fields[1].clone()
+    fields[1].mul_(phase)
+    fields[1].abs().square().sum().backward()
+    assert torch.allclose(phase.grad, 2.0 * want.abs().square().to(torch.complex64))
+
+
+def test_batch_in_two_calls(ctx):
+    """start and finish give gbd_eval_batch's metrics; finish once, with the right count, after a start with a
+    reference only, and a later start replaces an uncollected one."""
+    import ctypes
+    lib = gbd.load_library()
+    ss = [scenes.airy_scene(k, npix=60, half_span_lamF=6.0) for k in (10, 14, 12)]
+    bs, ps = [gbd.beamlets_from_scene(ctx, s) for s in ss], [gbd.plane_from_scene(ctx, s) for s in ss]
+    m = ss[0].meta
+    airy = gbd.gbd_airy(ctx, ps[0], m["D"], m["f"], ss[0].lam)
+
+    def arrays(k):
+        return np.array([b.hv for b in bs[:k]], np.uintp), np.array([p.hv for p in ps[:k]], np.uintp)
+
+    def start(k, ref=True):
+        hb, hp = arrays(k)
+        fields = start.fields = airy.new_empty(2 * k * 3600)
+        return lib.gbd_eval_batch_start(ctx.handle, k, hb.ctypes.data, hp.ctypes.data, airy.data_ptr() if ref else None,
+                                        airy.numel() * 4, None, 0, fields.data_ptr(), fields.numel() * 4, None)
+
+    def finish(k):
+        out = np.zeros((k, 2))
+        return lib.gbd_eval_batch_finish(ctx.handle, out.ctypes.data, out.size), out
+
+    hb, hp = arrays(3)
+    want = np.zeros((3, 2))
+    assert lib.gbd_eval_batch(ctx.handle, 3, hb.ctypes.data, hp.ctypes.data, airy.data_ptr(), airy.numel() * 4, None, 0,
+                              want.ctypes.data, None, 0, None) == 0
+    assert finish(3)[0] == -1
+    assert start(2) == 0 and start(3) == 0 and finish(2)[0] == -7
+    rc, got = finish(3)
+    assert rc == 0 and np.array_equal(got, want) and finish(3)[0] == -1
+    assert start(3, False) == 0 and finish(3)[0] == -1
+    assert start(2) == 0 and np.array_equal(finish(2)[1], want[:2])
+    assert lib.gbd_eval_batch_start(ctx.handle, -1, None, None, None, 0, None, 0, None, 0, None) == -1 and finish(2)[0] == -1
+    assert np.array_equal(gbd.gbd_eval_batch(ctx, bs, ps, airy=airy)[0], want)
