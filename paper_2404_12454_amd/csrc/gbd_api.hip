@@ -15,6 +15,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 using namespace gbd;
@@ -306,29 +307,42 @@ std::vector<int32_t> row_chunks(int64_t n, std::vector<int64_t> &perm, const dou
                                 const double *w0, int64_t n_w0, const int32_t *order) {
     std::vector<int32_t> start;
     if (n < kRowMinBeamlets || n > 0x7fffffff) return start;
-    auto same = [&](int64_t a, int64_t b) {
-        return r1[2 * a + 1] == r1[2 * b + 1] && (!th1 || th1[2 * a + 1] == th1[2 * b + 1]) &&
-               (n_w0 == 1 || w0[a] == w0[b]);
-    };
     const size_t most = (size_t)(n / kRowGain);
-    for (int64_t i = 0; i < n;) {
-        int64_t e = i + 1;
-        while (e < n && same(perm[e - 1], perm[e])) e++;
-        if (order) {  // a counting sort by the y order
-            int64_t at[4] = {0, 0, 0, 0};
-            for (int64_t k = i; k < e; k++) at[order[2 * perm[k] + 1] + 1]++;
-            for (int o = 1; o < 4; o++) at[o] += at[o - 1];
-            const std::vector<int64_t> run(perm.begin() + i, perm.begin() + e);
-            for (int64_t j : run) perm[i + at[order[2 * j + 1]]++] = j;
+    start.reserve(std::min<size_t>(most, 1024) + 1);
+    auto cut = [&](int64_t i, int64_t e) {  // beamlets [i, e) into chunks; false: too many
+        for (; i < e; i += kRowLen) {
+            if (start.size() >= most) return false;
+            start.push_back((int32_t)i);
         }
-        int64_t first = i;
-        for (int64_t k = i; k < e; k++)
-            if (k == i || k - first == kRowLen || (order && order[2 * perm[k] + 1] != order[2 * perm[k - 1] + 1])) {
-                if (start.size() >= most) return std::vector<int32_t>();
-                start.push_back((int32_t)k);
-                first = k;
-            }
-        i = e;
+        return true;
+    };
+    int64_t j = perm[0];  // the run's first beamlet
+    for (int64_t i = 0, e; i < n; i = e) {
+        const double y = r1[2 * j + 1], th = th1 ? th1[2 * j + 1] : 0.0, w = n_w0 == 1 ? 0.0 : w0[j];
+        for (e = i + 1; e < n; e++) {
+            j = perm[e];
+            if (r1[2 * j + 1] != y || (th1 && th1[2 * j + 1] != th) || (n_w0 != 1 && w0[j] != w)) break;
+        }
+        if (!order) {
+            if (!cut(i, e)) return std::vector<int32_t>();
+            continue;
+        }
+        // by the y order, stable (beamlets with orders have no edges: perm is the identity)
+        int64_t n1 = 0, n2 = 0;
+        for (int64_t k = i; k < e; k++) {
+            n1 += order[2 * k + 1] == 1;
+            n2 += order[2 * k + 1] == 2;
+        }
+        const int64_t b2 = e - n2, b1 = b2 - n1;
+        int64_t at0 = i, at1 = b1, at2 = b2;  // no array: a counter stored and read back would be a chain
+        for (int64_t k = i; k < e; k++) {
+            const int32_t o = order[2 * k + 1];
+            perm[o == 0 ? at0 : o == 1 ? at1 : at2] = k;
+            at0 += o == 0;
+            at1 += o == 1;
+            at2 += o == 2;
+        }
+        if (!cut(i, b1) || !cut(b1, b2) || !cut(b2, e)) return std::vector<int32_t>();
     }
     start.push_back((int32_t)n);
     return start;
@@ -1435,55 +1449,42 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
     double *host = static_cast<double *>(ctx->up_stage);
     bool in_order = n > 0;  // stored as the caller has them: whole arrays are copied
     for (int64_t i = 0; i < n; i++) in_order &= perm[i] == i;
-    if (!in_order) memset(host, 0, bytes);
-    auto put_rows = [&](size_t at, size_t width, const double *src) {
-        if (src)
-            memcpy(&host[at], src, (size_t)n * width * sizeof(double));
+    // the n rows of one array, in stored order (no source: zeros)
+    auto put_rows = [&](auto *dst, auto width, const auto *src) {
+        constexpr int W = decltype(width)::value;
+        if (!src)
+            memset(dst, 0, (size_t)n * W * sizeof *dst);
+        else if (in_order)
+            memcpy(dst, src, (size_t)n * W * sizeof *dst);
         else
-            memset(&host[at], 0, (size_t)n * width * sizeof(double));
+            for (int64_t i = 0; i < n; i++) memcpy(dst + W * i, src + W * perm[i], W * sizeof *dst);
     };
-    if (in_order) {
-        put_rows(off_r1, 2, r1);
-        put_rows(off_th1, 2, th1);
+    using std::integral_constant;
+    if (n > 0) {
+        put_rows(&host[off_r1], integral_constant<int, 2>(), r1);
+        put_rows(&host[off_th1], integral_constant<int, 2>(), th1);
         if (amp)
-            put_rows(off_amp, 2, amp);
+            put_rows(&host[off_amp], integral_constant<int, 2>(), amp);
         else
             for (int64_t i = 0; i < n; i++) {
                 host[off_amp + 2 * i] = 1.0;
                 host[off_amp + 2 * i + 1] = 0.0;
             }
-        memcpy(&host[off_w0], w0, (size_t)n_w0 * sizeof(double));
-        put_rows(off_path, 1, path);
-        memcpy(&host[off_abcd], abcd, 16 * (size_t)n_abcd * sizeof(double));
-        if (base) put_rows(off_base, 5, base);
-        if (edge) put_rows(off_edge, 3, edge);
-        if (order) memcpy(&host[off_order], order, 2 * (size_t)n * sizeof(int32_t));
+        if (n_w0 == 1 || order)  // orders reorder beamlets of one waist only (row_chunks)
+            memcpy(&host[off_w0], w0, (size_t)n_w0 * sizeof(double));
+        else
+            put_rows(&host[off_w0], integral_constant<int, 1>(), w0);
+        put_rows(&host[off_path], integral_constant<int, 1>(), path);
+        if (n_abcd == 1)
+            memcpy(&host[off_abcd], abcd, 16 * sizeof(double));
+        else
+            put_rows(&host[off_abcd], integral_constant<int, 16>(), abcd);
+        if (base) put_rows(&host[off_base], integral_constant<int, 5>(), base);
+        if (edge) put_rows(&host[off_edge], integral_constant<int, 3>(), edge);
+        if (order) put_rows(reinterpret_cast<int32_t *>(&host[off_order]), integral_constant<int, 2>(), order);
         memset(&host[off_rows], 0, (total - off_rows) * sizeof(double));
-    } else if (n > 0) {
-        int32_t *ord = reinterpret_cast<int32_t *>(&host[off_order]);
-        if (n_w0 == 1) host[off_w0] = w0[0];
-        if (n_abcd == 1) memcpy(&host[off_abcd], abcd, 16 * sizeof(double));
-        for (int64_t i = 0; i < n; i++) {
-            const int64_t j = perm[i];
-            host[off_r1 + 2 * i] = r1[2 * j];
-            host[off_r1 + 2 * i + 1] = r1[2 * j + 1];
-            if (th1) {
-                host[off_th1 + 2 * i] = th1[2 * j];
-                host[off_th1 + 2 * i + 1] = th1[2 * j + 1];
-            }
-            host[off_amp + 2 * i] = amp ? amp[2 * j] : 1.0;
-            host[off_amp + 2 * i + 1] = amp ? amp[2 * j + 1] : 0.0;
-            if (n_w0 == n) host[off_w0 + i] = w0[j];
-            if (path) host[off_path + i] = path[j];
-            if (n_abcd == n) memcpy(&host[off_abcd + 16 * i], abcd + 16 * j, 16 * sizeof(double));
-            if (base) memcpy(&host[off_base + 5 * i], base + 5 * j, 5 * sizeof(double));
-            if (edge) memcpy(&host[off_edge + 3 * i], edge + 3 * j, 3 * sizeof(double));
-            if (order) {
-                ord[2 * i] = order[2 * j];
-                ord[2 * i + 1] = order[2 * j + 1];
-            }
-        }
     } else {
+        memset(host, 0, bytes);
         host[off_w0] = 1.0;
         for (int i = 0; i < 4; i++) host[off_abcd + 5 * i] = 1.0;
     }
@@ -1532,8 +1533,9 @@ static int beamlets_impl(gbd_ctx_t ctx, gbd_beamlets_t *out, int64_t n, double l
     b->dev.row_bits = n_rows ? reinterpret_cast<const uint32_t *>(d + off_bits) : nullptr;
     b->dev.rows = (int32_t)n_rows;
     b->higher_order = higher;
-    b->one_matrix = n > 0 && n_abcd == 1 && !base;
-    for (int64_t i = 1; i < n_w0; i++) b->one_matrix &= w0[i] == w0[0];
+    bool one = n > 0 && n_abcd == 1 && !base;
+    for (int64_t i = 1; i < n_w0 && one; i++) one = w0[i] == w0[0];
+    b->one_matrix = one;
     if (b->one_matrix) {
         memcpy(b->abcd0, abcd, sizeof b->abcd0);
         b->w00 = w0[0];

@@ -223,3 +223,18 @@ def test_batch_row_scratch_is_bounded():
     for k, E in want.items():
         assert torch.equal(torch.view_as_real(E), torch.view_as_real(f[k].cpu())), k
     assert rel_l2(f[299].cpu().numpy(), oracle.eval_field(ss[299])) <= TOL[gbd.GBD_MIXED]
+
+
+@pytest.mark.parametrize("precision", BOTH)
+def test_rows_of_higher_orders_keep_each_beamlets_own_inputs(ctx, precision):
+    """Orders reorder beamlets within a row: waists that change from row to row and, in some rows, along them, and
+    amplitudes, slopes and paths of each beamlet's own stay with their beamlets."""
+    sc = scenes.hermite_scene(22, npix=97, npix_y=60, half_span_lamF=8.0, z0=40e-6)
+    rng = np.random.default_rng(8)
+    row = np.unique(sc.r1[:, 1], return_inverse=True)[1]
+    sc.w0 = sc.w0 * rng.choice([0.9, 1.0, 1.1], row.max() + 1)[row]
+    sc.w0[row == 11] *= rng.choice([0.95, 1.0], int((row == 11).sum()))
+    sc.amp = rng.normal(size=sc.amp.shape)
+    sc.path = rng.uniform(0.0, 1e-6, sc.n)
+    sc.th1 = np.stack([rng.uniform(-1e-6, 1e-6, sc.n), 1e-6 * np.cos(row)], axis=1)
+    assert rel_l2(field(ctx, sc, precision), oracle.eval_field(sc)) <= TOL[precision]
