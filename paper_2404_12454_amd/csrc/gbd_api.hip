@@ -41,14 +41,15 @@ struct DevBuf {
 };
 
 struct BatchWork {
-    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, metrics, flags, point, row_sums, terms;
+    DevBuf rec, l5, e0t, tab1, tab2, e0, e0part, part, flags, point, row_sums, terms;
     uint32_t *host_flags = nullptr;  // pinned: the point evaluation's status
     void *stage = nullptr;           // pinned staging of the batch tables
     size_t stage_bytes = 0;
     hipEvent_t stage_ev = nullptr;   // after the last copy from stage
     bool stage_pending = false;      // stage_ev recorded and not yet waited for
-    const double *host_metrics = nullptr;  // in stage: where the metrics of a started batch arrive
-    int64_t n_metrics = 0;                 // how many (0: none to collect)
+    double *metrics = nullptr;       // pinned: the finalising kernel writes the metrics here
+    int64_t metrics_cap = 0;
+    int64_t n_metrics = 0;           // of a started batch (0: none to collect)
 };
 
 // autotuner cache key: (kind, precision, log2 N bucket, log2 M bucket)
@@ -1257,7 +1258,7 @@ int grow(DevBuf &b, size_t bytes, const char *what) {
 
 void batch_free(BatchWork &w) {
     DevBuf *all[] = {&w.rec,    &w.l5,   &w.e0t,     &w.tab1,  &w.tab2, &w.e0,
-                     &w.e0part, &w.part, &w.metrics, &w.flags, &w.point, &w.row_sums, &w.terms};
+                     &w.e0part, &w.part, &w.flags, &w.point, &w.row_sums, &w.terms};
     if (w.stage_ev) {
         (void)hipEventSynchronize(w.stage_ev);
         (void)hipEventDestroy(w.stage_ev);
@@ -1266,6 +1267,11 @@ void batch_free(BatchWork &w) {
         if (b->p) (void)hipFree(b->p);
     if (w.host_flags) (void)hipHostFree(w.host_flags);
     if (w.stage) (void)hipHostFree(w.stage);
+    if (w.metrics) {
+        // a batch not collected may still write them: let the device finish first
+        (void)hipDeviceSynchronize();
+        (void)hipHostFree(w.metrics);
+    }
     w = BatchWork();
 }
 
@@ -2032,7 +2038,6 @@ int gbd_eval_batch_start(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs
     //   [BatchInst x n | offs x (n + 1) | blks x (n + 1)]   uploaded before the setup (tab1)
     //   [status x 4 | peaks x n | row flags x n]            read back after it
     //   [BatchEval x n | items | e0map | row lists]         uploaded before the evaluation (tab2)
-    //   [metrics]                                           read back after it
     // each table part in one copy to a device buffer of the same layout.  The
     // host rewrites the buffer only once the stream has passed the previous
     // call's copies from it (stage_ev).
@@ -2057,15 +2062,22 @@ int gbd_eval_batch_start(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs
         (rc = grow(w.e0, n_inst * sizeof(double2), "batch normalisation")) ||
         (rc = grow(w.terms, n_inst * sizeof(MatrixTerms), "batch matrix terms")) ||
         (rc = grow(w.part, (size_t)std::max<int64_t>(n_items + row_tiles, 1) * PS * sizeof(double), "batch partials")) ||
-        (rc = grow(w.metrics, (size_t)n_inst * (2 + n_zones) * sizeof(double), "batch metrics")) ||
         (rc = grow(w.flags, rb_bytes, "batch flags")))
         return rc;
     hipStream_t st = ctx->stream;
     if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming), "hipEventCreate");
     if (w.stage_pending) HIP_TRY(hipEventSynchronize(w.stage_ev), "hipEventSynchronize");
     w.stage_pending = false;
-    const int64_t n_metrics = airy ? (int64_t)n_inst * (2 + n_zones) : 0;
-    const size_t stage_bytes = t1_bytes + rb_bytes + t2_bytes + (size_t)n_metrics * sizeof(double);
+    if (airy && (int64_t)n_inst * (2 + n_zones) > w.metrics_cap) {
+        HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");  // a batch not collected may still write them
+        if (w.metrics) (void)hipHostFree(w.metrics);
+        w.metrics = nullptr;
+        w.metrics_cap = 0;
+        const int64_t cap = std::max<int64_t>((int64_t)n_inst * (2 + n_zones), 1024);
+        HIP_TRY(hipHostMalloc(&w.metrics, (size_t)cap * sizeof(double), hipHostMallocDefault), "hipHostMalloc(metrics)");
+        w.metrics_cap = cap;
+    }
+    const size_t stage_bytes = t1_bytes + rb_bytes + t2_bytes;
     if (stage_bytes > w.stage_bytes) {
         if (w.stage) (void)hipHostFree(w.stage);
         w.stage = nullptr;
@@ -2284,14 +2296,9 @@ int gbd_eval_batch_start(gbd_ctx_t ctx, int32_t n_inst, const gbd_beamlets_t *bs
     }
     HIP_TRY(launch_batch_eval(rows, waves, form, half, ctx->cus, a, st), "batch eval launch");
     if (airy) {
-        HIP_TRY(launch_batch_finalize(a.inst, n_inst, a.part, n_zones, static_cast<double *>(w.metrics.p), st),
+        HIP_TRY(launch_batch_finalize(a.inst, n_inst, a.part, n_zones, w.metrics, st),
                 "finalize launch");
-        double *host = reinterpret_cast<double *>(h2 + t2_bytes);
-        HIP_TRY(hipMemcpyAsync(host, w.metrics.p, (size_t)n_metrics * sizeof(double), hipMemcpyDeviceToHost, st),
-                "metrics copy");
-        HIP_TRY(hipEventRecord(w.stage_ev, st), "hipEventRecord");
-        w.host_metrics = host;
-        w.n_metrics = n_metrics;
+        w.n_metrics = (int64_t)n_inst * (2 + n_zones);
     }
     return GBD_OK;
 }
@@ -2304,9 +2311,9 @@ int gbd_eval_batch_finish(gbd_ctx_t ctx, double *metrics_out, int64_t count) {
         return fail(GBD_ERANGE, "metrics_out holds %lld values, the batch has %lld", (long long)count, (long long)w.n_metrics);
     const int rc = ensure_device(ctx);
     if (rc) return rc;
-    HIP_TRY(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");  // a stream left since has been drained
+    HIP_TRY(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");  // (a stream left since has been drained)
     w.stage_pending = false;
-    memcpy(metrics_out, w.host_metrics, (size_t)count * sizeof(double));
+    memcpy(metrics_out, w.metrics, (size_t)count * sizeof(double));
     w.n_metrics = 0;
     return GBD_OK;
 }
