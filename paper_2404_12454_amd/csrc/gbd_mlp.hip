@@ -147,13 +147,24 @@ __global__ void __launch_bounds__(kSumCols * kSumRows) colsum_kernel(const float
     column_sums(dZ, nullptr, B, W, false, (int)blockIdx.x, [&](int i, float s) { db[i] = s; });
 }
 
-__global__ void __launch_bounds__(256) adamw_kernel(MlpNet net, const float *__restrict__ g,
+__global__ void __launch_bounds__(256) adamw_kernel(float *__restrict__ p, const float *__restrict__ g,
                                                     float *__restrict__ m, float *__restrict__ v, int64_t n, float lr,
                                                     float b1, float b2, float eps, float wd, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) adamw_step(p[i], g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
+}
+
+// the same with the packed weights
+__global__ void __launch_bounds__(256) adamw_pack_kernel(MlpNet net, const float *__restrict__ g,
+                                                         float *__restrict__ m, float *__restrict__ v, int64_t n,
+                                                         float lr, float b1, float b2, float eps, float wd, float c1,
+                                                         float c2) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    adamw_step(net.params[i], g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
-    if (net.wf) pack_param(net, i, net.params[i]);
+    float p = net.params[i];
+    adamw_step(p, g[i], m[i], v[i], lr, b1, b2, eps, wd, c1, c2);
+    net.params[i] = p;
+    pack_param(net, i, p);
 }
 
 __global__ void __launch_bounds__(256) pack_kernel(MlpNet net, int64_t n) {
@@ -216,7 +227,10 @@ hipError_t launch_mlp_colsum(const float *dZ, int B, int W, float *db, hipStream
 hipError_t launch_mlp_adamw(const MlpNet &n, const float *g, float *m, float *v, int64_t count, float lr, float b1,
                             float b2, float eps, float wd, float c1, float c2, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    adamw_kernel<<<blocks_for(count, 256), 256, 0, s>>>(n, g, m, v, count, lr, b1, b2, eps, wd, c1, c2);
+    if (n.wf)
+        adamw_pack_kernel<<<blocks_for(count, 256), 256, 0, s>>>(n, g, m, v, count, lr, b1, b2, eps, wd, c1, c2);
+    else
+        adamw_kernel<<<blocks_for(count, 256), 256, 0, s>>>(n.params, g, m, v, count, lr, b1, b2, eps, wd, c1, c2);
     return hipGetLastError();
 }
 

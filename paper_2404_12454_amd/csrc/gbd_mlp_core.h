@@ -5,6 +5,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace gbd {
 namespace mlp {
 
@@ -61,8 +63,24 @@ __device__ inline void column_sums(const float *__restrict__ X, const float *__r
     const int i = block * kSumCols + c;
     float acc = 0.0f;
     if (i < W) {
-#pragma unroll 16
-        for (int b = r; b < B; b += kSumRows) acc = fmaf(wgt ? wgt[b] : 1.0f, X[(int64_t)b * W + i], acc);
+        // 16 rows' loads under way at once, then 4 (100 rows: 12.5 a thread)
+        int b = r;
+        auto rows = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            for (; b + (N - 1) * kSumRows < B; b += N * kSumRows) {
+                float x[N], w[N];
+#pragma unroll
+                for (int k = 0; k < N; k++) {
+                    x[k] = X[(int64_t)(b + k * kSumRows) * W + i];
+                    w[k] = wgt ? wgt[b + k * kSumRows] : 1.0f;
+                }
+#pragma unroll
+                for (int k = 0; k < N; k++) acc = fmaf(w[k], x[k], acc);
+            }
+        };
+        rows(std::integral_constant<int, 16>());
+        rows(std::integral_constant<int, 4>());
+        rows(std::integral_constant<int, 1>());
     } else if (bias_col && i == W) {
         for (int b = r; b < B; b += kSumRows) acc += wgt ? wgt[b] : 1.0f;
     }
