@@ -105,8 +105,8 @@ typedef struct {
                                back to auto's choice among the others.
                                Weak cross terms: at the rotor form's 32 rows x 4 wavefronts
                                (0 or so requested) and two or more segments of at most
-                               640 beamlets (768 of 6,144 or more; automatic counts on
-                               fewer than 128 rows 320), a plane whose
+                               656 beamlets (automatic counts 320 ... 656 by the
+                               plane), a plane whose
                                cross terms the setup finds weak over 128 x 128 pixel tiles
                                takes forms 0 and 3 as matrix products, e^(x u v) by its
                                series (root mean square over a tile within 1e-7 of a term,

@@ -442,16 +442,21 @@ bool cross_applies(int precision, int form, uint32_t flags, int64_t n, int64_t m
 }
 
 // Beamlets of a plain FP32 sum of the cross form at most, so that its error
-// stays below the rotor form's, which compensates its sums every 128 (the
-// rotor's 32 rows against 640, 768 and 1,024 per sum: 3,228 beamlets on 512^2
-// pixels 5.4e-7, 5.1e-7, 5.5e-7, 6.3e-7; from 8 segments on their errors
-// average out: 12,892 on 1024^2 5.5e-7, 4.5e-7, 5.1e-7, 5.9e-7, 12,720 traced on
-// 512^2 6.0e-7, 4.1e-7, 4.6e-7, 5.4e-7; 100,668 on 512^2 1.3e-6 at 3,146 and
-// 5.6e-6 at 14,381).  On planes of fewer than 128 rows the rotor form runs 16
-// rows and is nearer (1,804 on 127^2: 2.9e-7; the cross form 2.6e-7 at 320,
-// 4.2e-7 at 640); an explicit count keeps the longer sums there.
-int64_t cross_longest(int64_t n, const PlaneGeom &pl, bool given) {
-    return pl.ny < 128 && !given ? 320 : n >= 8 * 768 ? 768 : 640;
+// stays below the rotor form's, which compensates its sums every 128 (12,892
+// beamlets on 1024^2 pixels, rotor 5.5e-7: 4.5e-7 at 640, 5.1e-7 at 768, 5.9e-7 at
+// 1,024; 15,856 on 323 x 433, 5.4e-7: 5.0e-7 at 566, 6.2e-7 at 755; 100,668 on 512^2
+// 1.3e-6 at 3,146 and 5.6e-6 at 14,381).  Over 90 drawn planes the errors meet
+// between 500 and 760 beamlets, so automatic counts cut the sums short where
+// that costs little, the partials growing with the plane; with these limits none
+// of 230 drawn planes of up to 128 across on 1024^2 was further off, of 200
+// larger ones 6, by 2 to 16 %, at 600 to 645.  On fewer than 128 rows the rotor form runs 16 rows and is nearer
+// (1,804 on 127^2: 2.9e-7; the cross form 2.6e-7 at 320, 4.2e-7 at 640).
+// kCrossSegLen: what a count of the caller's own may leave, and one lowered to
+// a fixed buffer, which is held to the field of the same count given.
+constexpr int64_t kCrossSegLen = 656, kCrossSegLenLow = 320;
+int64_t cross_longest(int64_t n, const PlaneGeom &pl) {
+    const int64_t m = (int64_t)pl.nx * pl.ny;
+    return pl.ny < 128 ? kCrossSegLenLow : m < 100000 ? 384 : m < 500000 ? 512 : n < 6144 ? 576 : kCrossSegLen;
 }
 
 // Scratch that a form takes over its general form's at most: beyond it the
@@ -616,7 +621,8 @@ Shape choose_shape(const gbd_ctx_s *ctx, int precision, int64_t n, const PlaneGe
     if (precision != GBD_MIXED && s.form == 2 && (flags & FLAG_HG) && s.rows > 16) s.rows = 16;
     if (cross && s.rows == 32 && s.waves == 4) {
         int64_t seg = s.nseg;
-        const int64_t longest = cross_longest(n, pl, seg > 0), M = (int64_t)pl.nx * pl.ny;
+        const int64_t longest = seg > 0 ? kCrossSegLen : cross_longest(n, pl);
+        const int64_t M = (int64_t)pl.nx * pl.ny;
         if (seg <= 0) {
             const int64_t tiles = std::max<int64_t>(1, (int64_t)((pl.nx + kCrossTile - 1) / kCrossTile) *
                                                            ((pl.ny + kCrossTile - 1) / kCrossTile));
@@ -908,7 +914,8 @@ int plan_eval_impl(gbd_ctx_s *ctx, gbd_plan_s *plan, int precision, void *out, i
         const int64_t room = (int64_t)(fixed_bytes / per);
         if (nseg_main + nseg_cut > room) {
             const int64_t left = room - std::min<int64_t>(nseg_cut, (int64_t)(fixed_bytes / 2 / per));
-            if (left < 2 || std::min<int64_t>(left, nseg_main) * cross_longest(n_main, plan->pl, false) < n_main) rotor_instead();
+            if (left < 2 || std::min<int64_t>(left, nseg_main) * (plan->pl.ny < 128 ? kCrossSegLenLow : kCrossSegLen) < n_main)
+                rotor_instead();
         }
     }
     if (fixed && !by_rows) {
