@@ -283,9 +283,10 @@ void gbd_plane_free(gbd_plane_t p);
  * new status (no host round trip between the kernels): the final reduction
  * writes field_out only if that status has no error and selects the same
  * form and scale; otherwise nothing is written, and on a change of form or
- * scale the evaluation runs again.  Evaluations that write field_out
- * without a reduction (a single segment, no beamlets) are launched after
- * the status is read. */
+ * scale the evaluation runs again.  The sum by rows writes
+ * field_out without a reduction; its product is guarded by the same
+ * condition.  Other evaluations without one (a single segment, no beamlets)
+ * are launched after the status is read. */
 int gbd_eval(gbd_ctx_t ctx, gbd_beamlets_t b, gbd_plane_t p, int precision, void *field_out,
              int64_t out_bytes, const gbd_eval_opts *opts);
 

@@ -188,7 +188,7 @@ struct gbd_plan_s {
 };
 
 // plan_eval_impl under a guard: the configuration writes the output without
-// the guarded reduction (no partials), so it cannot run before the status
+// the guarded reduction (no partials) or product by rows, so it cannot run before the status
 constexpr int kNoSpeculation = 1;
 
 // the setup flags that select how an evaluation runs
@@ -782,7 +782,7 @@ size_t general_scratch(const gbd_ctx_s *ctx, const gbd_plan_s *plan, int precisi
 // buffer of gbd_plan_eval_noalloc), used instead of the plan's grow-only one;
 // then nothing is allocated and an automatic segment count is lowered to fit.
 // guard (gbd_eval's launch ahead of the setup status): the output is
-// written only by the guarded reduction, or nothing is launched and the call
+// written only by the guarded reduction or product by rows, or nothing is launched and the call
 // returns kNoSpeculation; guard->check_key is set when the form's FP16 scale
 // depends on the key.
 // post_req (with post set): a setup status still to be posted, by the

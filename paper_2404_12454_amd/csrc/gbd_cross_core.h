@@ -18,7 +18,7 @@ static_assert(16 * kWX * kBX == kCrossTile && 16 * kWY * kBY == kCrossTile, "cro
 
 // Scales: |U| <= 2^kUExp and |V| <= 2^kVExp by the setup's bounds, up to the
 // factor 2 (U) and 4 (V) that the cross term's share in them can add
-// (kCrossShift); FP16 holds 65504.
+// (FLAG_CROSS2 bounds it); FP16 holds 65504.
 constexpr int kUExp = 13, kVExp = 12;
 
 // Words of a U and a V factor in LDS:

@@ -177,7 +177,9 @@ enum : uint32_t {
     FLAG_CUT3 = 4096u,
     // the same as FLAG_CUT1 for a column of twice the rows
     FLAG_CUT0 = 8192u,
+    FLAG_LAST = FLAG_CUT0,
 };
+static_assert(FLAG_LAST <= 0xffffu, "the posted status word holds 16 bits of flags");
 // largest t = |k zb dy| (2 |zeta| + sqrt(2 p)) over the rows k of a column
 // of the truncated beamlets' column form (gbd_cut.hip): (e t / p)^p is 2^-26
 // at t = 0.115 for p = 6 and 2^-50 for p = 10, 2^-25 at t = 0.67 for p = 10
@@ -415,7 +417,7 @@ hipError_t launch_mlp_adamw(const MlpNet &n, const float *g, float *m, float *v,
 // as ceil(log2) + 2048 (0: none; the FP16 separable form's range); and
 // status_next: the next setup's two words, set to zero (the host alternates
 // the pairs, so no separate clear is needed).
-// A finished setup's status[0] (flags, < 4096) and status[1] (key, < 4096)
+// A finished setup's status[0] (flags, < 65536) and status[1] (key, < 4096)
 // posted to the host: (seq << 32) | flags | key << 16 in one system-scope
 // store into *post (coherent host memory), which the host polls for seq (an
 // event after a copy would end with a system-scope release that stalls the
@@ -569,9 +571,9 @@ struct RowGeom {
 };
 // Row chunks of beamlets [0, start[chunks]) from the records: sums is scratch
 // for the sums [chunks][nx] and behind them the y factors [chunks][ny].  Mixed: status[1] is the setup's key
-// (the largest term's log2, the FP32 sums' common scale).  Writes out, or
-// partial when out is null (complex64 / complex128), unless the guard's
-// condition fails.  t0 / t1 time the two kernels from the first one's start
+// (the largest term's log2, the FP32 sums' common scale).  Writes out (complex64
+// / complex128, the field or a first partial) unless the guard's condition
+// fails.  t0 / t1 time the two kernels from the first one's start
 // to the second one's end; sp: a setup status to post at the start.
 hipError_t launch_rows32(const RowGeom &g, const int32_t *start, const Rec32 *rec, const RecHG32 *hg,
                          const uint32_t *status, float2 *sums, float2 *out, const EvalGuard &guard,
