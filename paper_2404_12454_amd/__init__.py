@@ -461,9 +461,9 @@ def gbd_eval_batch(ctx: Context, beamlets, planes, airy=None, zone_edges=None, f
     out_fields = None
     if fbuf is not None:
         if nx * ny > 0:
-            # one view each, by index: unbind's are refused in-place changes that record gradients
-            planes_of = fbuf.view(n, ny, nx)
-            out_fields = [planes_of[i] for i in range(n)]
+            # one view each: unbind's are refused in-place changes that record gradients
+            view, shape, stride = fbuf.as_strided, (ny, nx), (nx, 1)
+            out_fields = [view(shape, stride, i) for i in range(0, total, ny * nx)]
         else:
             out_fields, off = [], 0
             for p in planes:
