@@ -456,7 +456,7 @@ bool cross_applies(int precision, int form, uint32_t flags, int64_t n, int64_t m
 constexpr int64_t kCrossSegLen = 656, kCrossSegLenLow = 320;
 int64_t cross_longest(int64_t n, const PlaneGeom &pl) {
     const int64_t m = (int64_t)pl.nx * pl.ny;
-    return pl.ny < 128 ? kCrossSegLenLow : m < 100000 ? 384 : m < 500000 ? 512 : n < 6144 ? 576 : kCrossSegLen;
+    return pl.ny < 128 ? kCrossSegLenLow : m < 100000 ? 480 : m < 500000 ? 496 : n < 6144 ? 576 : kCrossSegLen;
 }
 
 // Scratch that a form takes over its general form's at most: beyond it the
