@@ -175,7 +175,8 @@ CROSS_FLOPS_PER_PAIR = 8 * 16384 / (16 * 256)
 def row_count(sc):
     """Row chunks of a scene that the separable form takes by rows (beamlets
     of equal y, higher orders of equal y order too, at least 4 to a chunk on
-    average, one matrix for all), else 0."""
+    average, one matrix for all; at this program's sizes the sum by rows is
+    always the shorter way), else 0."""
     import numpy as np
     order = getattr(sc, "order", None)
     if sc.n < 64 or sc.abcd.size != 16 or getattr(sc, "base", None) is not None:

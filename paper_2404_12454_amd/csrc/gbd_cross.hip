@@ -19,7 +19,7 @@
 //
 // 12,892 beamlets on 1024 x 1024 pixels: a gbd_eval call 2,678 us (rotor) ->
 // 487 us, error against FP64 5.0e-7 -> 4.6e-7; 12,720 traced ones on 512 x
-// 512: the kernel 775 -> 131 us.  (Records read from LDS by every lane: 535
+// 512: the kernel 775 -> 127 us.  (Records read from LDS by every lane: 535
 // and 146 us; with the factors ahead of the products as the scheduler chose
 // besides: 570 and 160.)
 // Bound by MFMA and the factors' VALU, which overlap little at two

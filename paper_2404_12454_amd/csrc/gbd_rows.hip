@@ -25,7 +25,8 @@
 // -> 45 us (row sums 25, product 10, setup 10) with an error against FP64 of
 // 2e-7 instead of 9e-7, FP64 1,954 -> 73 us (50, 16, 10); the y factors formed
 // by the product's tiles instead, nx / 32 times each: 46.5 and 79 us, of higher
-// order 78 instead of 71.  441 instances of the parameter sweep 3.50 -> 1.27 ms.
+// order 78 instead of 71.  441 instances of the parameter sweep 3.50 -> 1.27 ms
+// (0.94 with the products by wavefronts and the host's share hidden).
 #include "gbd_row_core.h"
 
 namespace gbd {
